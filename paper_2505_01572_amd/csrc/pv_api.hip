@@ -8,6 +8,7 @@
 #include <new>
 #include <mutex>
 #include "pv_kernels_common.h"
+#include "pv_prefill.h"
 
 static thread_local char g_err[512] = "";
 
@@ -297,7 +298,7 @@ extern "C" int pv_cache_bytes(const pv_model *m, int32_t max_tokens, size_t *pag
     const pv_model_config &c = m->cfg;
     const int n_pages = (max_tokens + c.page_tokens - 1) / c.page_tokens;
     *page_pool_bytes = align_up((size_t)c.n_layers * n_pages * c.n_kv_heads * 2 * c.page_tokens * c.head_dim * m->elt, 256);
-    *workspace_bytes = layout_ws(m, rows_cap_of(m), units_cap_of(m), n_pages, nullptr, nullptr);
+    *workspace_bytes = layout_ws(m, rows_cap_of(m), units_cap_of(m), n_pages, nullptr, nullptr) + pv_pre_bytes(m, max_tokens);
     return PV_OK;
 }
 
@@ -312,13 +313,14 @@ extern "C" int pv_cache_create(const pv_model *m, void *d_page_pool, size_t page
     if (page_pool_bytes < need_p || workspace_bytes < need_w) { pv_set_error("pool %zu < %zu or workspace %zu < %zu", page_pool_bytes, need_p, workspace_bytes, need_w); return PV_ENOMEM; }
     if (m->path >= PV_PATH_MATRIX && (rc = pv_mat_attention_init(m->cfg.head_dim)) != PV_OK) return rc;
     if (m->path >= PV_PATH_MATRIX && m->wbits == 4 && (rc = pv_mat_gemm_init()) != PV_OK) return rc;
+    if (pv_pre_rows(m, max_tokens) && (rc = pv_pre_init(m->cfg.head_dim)) != PV_OK) return rc;
     pv_cache *c = new (std::nothrow) pv_cache();
     if (!c) return PV_ENOMEM;
     c->m = m; c->d_pool = (char *)d_page_pool; c->pool_bytes = page_pool_bytes;
     c->d_ws = (char *)d_workspace; c->ws_bytes = workspace_bytes;
     c->max_tokens = max_tokens; c->n_pages = (max_tokens + m->cfg.page_tokens - 1) / m->cfg.page_tokens;
     c->rows_cap = rows_cap_of(m); c->units_cap = units_cap_of(m);
-    layout_ws(m, c->rows_cap, c->units_cap, c->n_pages, &c->ws, c->d_ws);
+    c->pre_base = c->d_ws + layout_ws(m, c->rows_cap, c->units_cap, c->n_pages, &c->ws, c->d_ws); c->pre_rows = pv_pre_rows(m, max_tokens);
     c->len = 0; c->pending = -1; c->last_rows = 0; c->blk_start = 0; c->blk_rows = 0; c->blk_units = 0; c->blk_seq_rows = 0; c->attn_keys = 0; c->in_flight = false; c->flight_stream = nullptr; c->io = nullptr;
     c->prof_kind = PV_PROF_NONE; c->prof_pending = 0; c->prof_ev = nullptr; c->prof_ms = 0; c->prof_launches = 0;
     c->use_graphs = true; c->cap_stream = nullptr;
@@ -582,7 +584,25 @@ extern "C" int pv_prefill(pv_cache *c, const int32_t *tokens, int32_t n, void *h
         if (tokens[j] < 0 || tokens[j] >= c->m->cfg.vocab) { pv_set_error("token id %d at position %d outside [0, %d)", tokens[j], j, c->m->cfg.vocab); return PV_ERANGE; }
     hipStream_t s = (hipStream_t)hip_stream;
     const int chunk = prefill_rows_of(c->m);
-    for (int off = 0; off < n; off += chunk) {
+    int off = 0;
+    // a long prompt goes in with as few passes over the weights as the cache's buffers allow; its last rows (as many as the
+    // last block would have if all were blocks of `chunk` rows) end up as the running block, with logits and a prediction
+    while (c->pre_rows && n - off > PV_PRE_MIN) {
+        const int rows = n - off < c->pre_rows ? n - off : c->pre_rows;
+        const int keep = off + rows == n ? (rows - 1) % chunk + 1 : 0;
+        memcpy(c->io->prompt, tokens + off, sizeof(int32_t) * rows);
+        c->io->hdr[2] = keep; c->io->hdr[3] = keep ? PV_MODE_PREFILL_LAST : PV_MODE_PREFILL_MID;
+        rc = pv_mat_run_prompt(c, rows, keep, s);
+        if (rc != PV_OK) return rc;
+        PV_HIP(hipStreamSynchronize(s));
+        c->len += rows - keep;
+        if (rows > keep) c->pending = -1;
+        c->last_rows = keep;
+        c->blk_start = keep ? c->len : c->len - chunk; c->blk_rows = keep ? keep : chunk;
+        if (keep) { if ((rc = absorb_result(c)) != PV_OK) return rc; } else prof_collect(c);
+        off += rows;
+    }
+    for (; off < n; off += chunk) {
         const int rows = n - off < chunk ? n - off : chunk;
         const bool last = off + rows >= n;
         rc = enqueue_block(c, tokens + off, rows, last ? PV_MODE_PREFILL_LAST : PV_MODE_PREFILL_MID, s);

@@ -49,11 +49,7 @@ __device__ inline void split8(const float v[8], uint4 &hi, uint4 &lo)
 {
     uint32_t h[4], l[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint16_t h0 = pv_f32_to_bf16(v[2 * i]), h1 = pv_f32_to_bf16(v[2 * i + 1]);
-        const uint16_t l0 = pv_f32_to_bf16(v[2 * i] - pv_bf16_to_f32(h0)), l1 = pv_f32_to_bf16(v[2 * i + 1] - pv_bf16_to_f32(h1));
-        h[i] = h0 | ((uint32_t)h1 << 16); l[i] = l0 | ((uint32_t)l1 << 16);
-    }
+    for (int i = 0; i < 4; ++i) split2(v[2 * i], v[2 * i + 1], h[i], l[i]);
     hi = make_uint4(h[0], h[1], h[2], h[3]); lo = make_uint4(l[0], l[1], l[2], l[3]);
 }
 

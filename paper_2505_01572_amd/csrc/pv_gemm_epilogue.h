@@ -201,16 +201,16 @@ __device__ inline void epi_apply(const gemm_args &a, int strip, int lane, f32x4 
             if (live) {
                 if (strip < a.q_strips) {
                     // queries leave as bf16 hi + lo pairs, the form attention feeds to the matrix cores
-                    uint16_t qh[4], ql[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) { qh[r] = bf16_rne(o[r]); ql[r] = bf16_rne(o[r] - pv_bf16_to_f32(qh[r])); }
+                    uint2 qh, ql;
+                    split2(o[0], o[1], qh.x, ql.x);
+                    split2(o[2], o[3], qh.y, ql.y);
                     const size_t qo = ((size_t)j * a.n_q_heads + h) * hd + e + side * half;
-                    *(uint2 *)(a.q_hi + qo) = make_uint2(qh[0] | ((uint32_t)qh[1] << 16), qh[2] | ((uint32_t)qh[3] << 16));
-                    *(uint2 *)(a.q_lo + qo) = make_uint2(ql[0] | ((uint32_t)ql[1] << 16), ql[2] | ((uint32_t)ql[3] << 16));
+                    *(uint2 *)(a.q_hi + qo) = qh;
+                    *(uint2 *)(a.q_lo + qo) = ql;
                 } else {
                     const int kvh = h - a.n_q_heads;
                     uint16_t *kp = pool + pv_kv_block(gm, a.layer, phys, kvh, 0) + pv_k_off(gm, tok, e + side * half);
-                    *(uint2 *)kp = make_uint2(bf16_rne(o[0]) | ((uint32_t)bf16_rne(o[1]) << 16), bf16_rne(o[2]) | ((uint32_t)bf16_rne(o[3]) << 16));
+                    *(uint2 *)kp = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
                 }
             }
         } else if (live) {

@@ -6,6 +6,7 @@
 #include "pipeverify.h"
 
 #define PV_MAX_ROWS 64          // hard cap on rows per block (max_gamma)
+#define PV_PRE_ROWS 2048        // most rows of one long-prompt pass (its buffers are part of a cache's workspace: 88 KiB a row for an 8B shape)
 #define PV_KEY_BUCKETS 24       // attention grids of recorded steps are sized for the next power of two of (length + rows)
 #define PV_ROW_PAD 16           // activation buffers are padded to a multiple of this many rows
 
@@ -62,6 +63,7 @@ struct pv_host_io {
     int32_t result[2 * PV_MAX_SEQ + 2];   // written by the step's last kernel: (accepted, next_token) per sequence, then the error flag
     pv_block_desc single;       // the one-sequence description of this cache (constant)
     pv_block_desc batch;        // staging of a batched step's description
+    int32_t prompt[PV_PRE_ROWS];   // token ids of one pass of a long prompt
 };
 #define PV_RESULT_ERR (2 * PV_MAX_SEQ)
 
@@ -103,6 +105,7 @@ struct pv_cache {
     int32_t max_tokens, n_pages, rows_cap;
     int32_t units_cap;          // attention row-group units the workspace's partial arrays hold
     pv_ws ws;
+    char *pre_base; int32_t pre_rows;  // long-prompt buffers behind the step's workspace, and the rows they hold (0: none)
     pv_host_io *io;             // pinned host memory, mapped into the device's address space
     pv_host_io *d_io;           // the same mailbox as the kernels address it
     int32_t len, pending, last_rows;
@@ -161,6 +164,7 @@ __host__ __device__ static inline size_t pv_v_off(const pv_kv_geom &g, int t, in
 // ---- kernel-family entry points (host functions that enqueue on `s`) ----
 int pv_vec_run_block(pv_cache *c, hipStream_t s);        // pv_kernels_vector.hip
 int pv_mat_run_block(pv_cache *c, hipStream_t s);        // pv_kernels_matrix.hip
+int pv_mat_run_prompt(pv_cache *c, int rows, int keep, hipStream_t s);   // a long-prompt pass (pv_prefill.h); keep > 0: with head and result for its last `keep` rows
 int pv_mat_repack(const pv_model *m, const pv_tensor_ref &t, int kind, int64_t row_begin, int64_t row_count, hipStream_t s);
 int pv_mat_repack_q4(const pv_model *m, const pv_tensor_ref &t, int kind, int64_t row_begin, int64_t row_count, size_t scales_off, hipStream_t s);
 

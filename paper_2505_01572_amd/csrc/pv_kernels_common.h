@@ -4,12 +4,7 @@
 
 // storage-type access: float, or bfloat16 kept as raw uint16_t bit patterns
 __device__ inline float pv_bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-__device__ inline uint16_t pv_f32_to_bf16(float f)      // round to nearest, ties to even
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+__device__ inline uint16_t pv_f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }     // round to nearest, ties to even (v_cvt_pk_bf16_f32)
 __device__ inline float pv_ld(const float *p, size_t i) { return p[i]; }
 __device__ inline float pv_ld(const uint16_t *p, size_t i) { return pv_bf16_to_f32(p[i]); }
 __device__ inline void pv_st(float *p, size_t i, float v) { p[i] = v; }

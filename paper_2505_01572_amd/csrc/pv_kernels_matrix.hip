@@ -27,6 +27,7 @@
 #include <stdlib.h>
 #include <type_traits>
 #include "pv_gemm_epilogue.h"
+#include "pv_prefill.h"
 
 
 
@@ -1115,4 +1116,26 @@ int pv_mat_run_block(pv_cache *c, hipStream_t s)
     if (rows <= 16) return run_block<2, 1>(c, s);
     if (rows <= 32) return run_block<2, 2>(c, s);
     return run_block<2, 4>(c, s);
+}
+
+int pv_mat_run_prompt(pv_cache *c, int rows, int keep, hipStream_t s)
+{
+    const pv_model *m = c->m;
+    const pv_model_config &f = m->cfg;
+    mat_ws mw;
+    mat_ws_layout(m, c->rows_cap, c->units_cap, c->n_pages * f.page_tokens, c->ws.part, &mw);
+    pv_pre_out out;
+    int rc = pv_pre_block(c, c->pre_base, c->d_io->prompt, rows, keep, mw.tile_part, tile_part_floats(col_tiles(c->rows_cap)), &out, s);
+    if (rc != PV_OK || keep == 0) return rc;
+    // the head of the kept rows (whatever their number, as column tiles of 16 rows: the layout of the prompt's operand)
+    gemm_args g = {};
+    g.st = c->ws.state; g.lo_off = 8; g.inv_d = 1.0f / (float)f.d_model; g.eps = (float)f.rms_eps; g.ssq_parts = f.d_model / 16;
+    g.logits = c->ws.logits; g.pmax_val = mw.pmax_val; g.pmax_idx = mw.pmax_idx; g.vocab = f.vocab; g.tile_part = mw.tile_part;
+    g.W = (const uint4 *)(m->d_weights + m->global[PV_T_LM_HEAD].off); g.xop = (const uint4 *)out.xop; g.ktiles = f.d_model / 32; g.ssq = out.ssq;
+    if ((rc = pv_prof_mark(c, PV_PROF_LMHEAD, 0, 0, s)) != PV_OK) return rc;
+    const int ct = col_tiles(keep);
+    rc = ct == 1 ? launch_gemm<2, 1, EPI_LMHEAD>(m, g, f.vocab / 16, s) : ct == 2 ? launch_gemm<2, 2, EPI_LMHEAD>(m, g, f.vocab / 16, s) : launch_gemm<2, 4, EPI_LMHEAD>(m, g, f.vocab / 16, s);
+    if (rc != PV_OK) return rc;
+    if ((rc = pv_prof_mark(c, PV_PROF_LMHEAD, 0, 1, s)) != PV_OK) return rc;
+    return pv_k_finish(c, keep, mw.pmax_val, mw.pmax_idx, f.vocab / 16, s);
 }

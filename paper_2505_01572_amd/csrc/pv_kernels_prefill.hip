@@ -1,0 +1,651 @@
+// Long prompts on the matrix path: up to PV_PRE_ROWS rows in one pass over the weights.
+//
+// The kernels for blocks of up to 64 rows stream every weight once per block, so a prompt in
+// 64-row blocks is bound by the weight stream (8B-shaped layer: 0.16 ms per 64 rows, 180
+// TFLOP/s).  Here a block has up to 2048 rows and the matrix cores are the bound: the operands
+// of a GEMM are as before (16-bit weights in MFMA tile order, activations as bf16 hi + lo pairs,
+// fp32 accumulators), but a workgroup owns a rectangle of 128 rows x 128 to 256 features, and both operands
+// pass through LDS, loaded by direct global -> LDS copies.  2048 tokens through four 8B-shaped layers:
+// 20.7 -> 6.6 ms; the gate/up GEMM then takes 0.70 ms, 1370 TFLOP/s of MFMAs (hi and lo counted).
+#include "pv_gemm_epilogue.h"
+#include "pv_prefill.h"
+#include <algorithm>
+
+// One 1 KiB operand tile (64 lanes x 16 bytes) from global memory straight into LDS.  Written in assembly (there is
+// no output register) because the compiler otherwise waits for every copy in flight before any LDS read; the
+// kernels wait for the copies by count (pre_wait).  src is uniform, voff the lane's byte offset behind it.
+__device__ inline void dma_tile(uint32_t lds, const void *src, uint32_t voff)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(src) : "memory");
+}
+
+__device__ inline uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }
+
+// all but the newest N copies of this wave have landed, its LDS reads are done, and so it is for every wave of the workgroup
+template <int N> __device__ inline void pre_wait()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+template <typename T> __device__ inline const T *uniform_ptr(const T *p)
+{
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));   // (the builtin returns a signed int)
+    return (const T *)((uint64_t)hi << 32 | lo);
+}
+
+// workgroup number -> position in the work list: the 8 XCDs take workgroups in turn, so each gets a contiguous run of the list (its
+// workgroups then share operand tiles in that XCD's L2)
+__device__ inline int xcd_order(int bid, int total)
+{
+    const int q = total >> 3, r = total & 7, x = bid & 7;
+    return x * q + min(x, r) + (bid >> 3);
+}
+
+// tiles of a stage: activations (hi, lo), weights, rounded up so that every wave copies the same number (what is beyond is a strip more, not used)
+constexpr int pre_stage_tiles(int br, int bf) { return (2 * br + bf + 7) / 8 * 8; }
+
+// K-tiles added up in one accumulator before it is added to the total: an accumulator that ran over the whole K would carry
+// a rounding error of the size of the operands' own (measured on K and V of a first layer, d = 8192: 40 % more bf16 values
+// off the 64-bit result than with blocks of 64 rows, whose K is cut over workgroups or waves; runs of 16: 15 % fewer)
+#define PRE_RUN 16
+
+struct pre_gemm_args {
+    const float *rscale;        // RMSNorm scale of each row (QKV, SWIGLU)
+    float4 *part;               // K-slice partial sums [slice][strip][row tile][64], or null: one slice
+    int mtiles;                 // 16-row tiles of the block
+    int rb, fb;                 // rectangles along the rows and the features
+    int kps;                    // K-tiles per slice
+    int rows, len;              // rows of the block, and the position of the first
+};
+
+// What the epilogue of a strip needs from memory.  Rows, length and the row's page are known here (epi_prefetch reads them
+// from the step's state in memory, which the stores of the previous strip might have changed, for all the compiler knows).
+template <int EPI>
+__device__ inline void pre_fetch(const gemm_args &a, const pre_gemm_args &p, int strip, int lane, int ct, int phys, float rj, epi_pre &e)
+{
+    const int j = ct * 16 + (lane & 15), g = lane >> 4, jr = min(j, p.rows - 1);
+    e.rows = p.rows; e.rj = rj; e.pos = p.len + j; e.phys = phys;
+    if (EPI == EPI_RESID) {
+        const int n = strip * 16 + 4 * g;
+        e.xo = *(const float4 *)(a.x + (size_t)jr * a.d + n);
+        e.gn = *(const uint2 *)(a.gain_next + n);
+    }
+    if (EPI == EPI_QKV) {
+        const int tt = strip % (a.geom.head_dim >> 4), i = tt * 8 + 4 * (g >> 1);
+        const float4 *q = (const float4 *)(a.rope + (size_t)jr * (a.geom.head_dim >> 1) + i);     // (used by q and k strips only)
+        const float4 c0 = q[0], c1 = q[1];
+        e.cs[0] = make_float2(c0.x, c0.y); e.cs[1] = make_float2(c0.z, c0.w); e.cs[2] = make_float2(c1.x, c1.y); e.cs[3] = make_float2(c1.z, c1.w);
+    }
+}
+
+template <int EPI>
+__device__ inline int pre_page(const gemm_args &a, const pre_gemm_args &p, int lane, int ct)
+{
+    return EPI == EPI_QKV ? a.page_table[(p.len + min(ct * 16 + (lane & 15), p.rows - 1)) >> a.geom.page_shift] : 0;
+}
+
+// SwiGLU of two neighbouring strips at once: the lanes of a pair (16 apart) hold the gate and the up features of both, so
+// one takes the first strip and the other the second, instead of both computing the same (expf and the
+// division are most of this epilogue).
+__device__ inline void pre_swiglu2(const gemm_args &a, const pre_gemm_args &p, int strip, int lane, int ct, float rj, f32x4 v0, f32x4 v1)
+{
+    const int j = ct * 16 + (lane & 15), g = lane >> 4;
+    const bool odd = g & 1;
+    float act[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float mine = (odd ? v1[r] : v0[r]) * rj, other = __shfl_xor((odd ? v0[r] : v1[r]) * rj, 16, 64);
+        const float gate = odd ? other : mine, up = odd ? mine : other;
+        act[r] = gate / (1.0f + expf(-gate)) * up;
+    }
+    if (j < p.rows) store_operand4<2>(a.xop_act, a.F, j, (strip + odd) * 8 + 4 * (g >> 1), act, 8);
+}
+
+// ------------------------------------------------------------------------------------------
+// The GEMM.  WR x WF waves of a workgroup, each RT row tiles x FT strips: per K-tile a wave
+// reads 2 RT + FT operand tiles from LDS for 2 RT FT MFMAs, a workgroup copies 2 WR RT + WF FT
+// tiles into it.  NST stages of one K-tile each; the barrier of stage k + 1 sits in front of the last
+// row tile's MFMAs of stage k, whose operands are in registers, so the matrix cores have work while
+// the next stage's first operands come out of LDS.  One barrier per K-tile.
+// 256 x 256 rectangles (half the operand traffic) were 4 % faster where they fill the CUs, but leave no registers
+// for the second level of accumulators (PRE_RUN).
+// ------------------------------------------------------------------------------------------
+template <int WR, int WF, int RT, int FT, int NST, int EPI>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_pre_gemm(const gemm_args a, const pre_gemm_args p)
+{
+    static_assert(WR * WF == 8 && RT % 2 == 0, "8 waves; row tiles alternate between two operand buffers");
+    constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
+    constexpr int BR = WR * RT, BF = WF * FT, TPS = pre_stage_tiles(BR, BF), NLD = TPS / 8;
+    static_assert((2 * BR) % 8 == 0, "a wave's i-th tile is an activation tile in every wave or in none");
+    extern __shared__ uint4 pre_lds[];                 // [NST][TPS][64]
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wr = wave / WF, wf = wave % WF;
+    const int L = xcd_order(blockIdx.x, gridDim.x), per = p.rb * p.fb, slice = L / per, rest = L - slice * per;
+    const int ct0 = (rest % p.rb) * BR, fs0 = (rest / p.rb) * BF;           // rows vary fastest
+    const int KT = a.ktiles, kt0 = slice * p.kps, n = min(KT - kt0, p.kps); // this slice's K-tiles (not empty: the launch sees to it)
+    const size_t arr = (size_t)KT * 64;
+    // the tiles this wave copies: activation tiles (row tile, hi | lo) first, then weight tiles; past the end of either the last one again
+    const uint4 *src[NLD];
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+        const int t = wave + 8 * i;
+        const uint4 *q = i < 2 * BR / 8 ? a.xop + (size_t)(2 * min(ct0 + (t >> 1), p.mtiles - 1) + (t & 1)) * arr
+                                        : a.W + (size_t)min(fs0 + t - 2 * BR, a.nstrips - 1) * arr;
+        src[i] = uniform_ptr(q + (size_t)kt0 * 64);
+    }
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(pre_lds)) + wave * 1024;
+    // tiles [i0, i1) of this wave's share of stage s (K-tile kt0 + s; past the end the last one again: the counts of copies in flight stay constant) into buffer buf
+    auto copy = [&](int s, int buf, int i0, int i1) {
+        const uint32_t vo = (uint32_t)lane * 16 + (uint32_t)min(s, n - 1) * 1024;
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) if (i >= i0 && i < i1) dma_tile(lds0 + (uint32_t)(buf * TPS + 8 * i) * 1024, src[i], vo);
+    };
+    f32x4 acc[RT][FT], tot[RT][FT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int f = 0; f < FT; ++f) acc[r][f] = tot[r][f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    uint4 wa[FT], wb[FT], xh[2], xl[2];
+    const uint4 *Lx = pre_lds + (wr * RT * 2) * 64 + lane, *Lw = pre_lds + (2 * BR + wf * FT) * 64 + lane;
+    auto read_w = [&](uint4 (&w)[FT], int buf) {
+#pragma unroll
+        for (int f = 0; f < FT; ++f) w[f] = Lw[buf * TPS * 64 + f * 64];
+    };
+    auto read_x = [&](int r, int buf) { xh[r & 1] = Lx[buf * TPS * 64 + 2 * r * 64]; xl[r & 1] = Lx[buf * TPS * 64 + (2 * r + 1) * 64]; };
+    int buf = 0, fill = NST - 1;                       // buffers of the stage in use and of the one being copied
+    auto step = [&](int s, const uint4 (&w)[FT], uint4 (&wn)[FT]) {      // on entry: w and row tile 0 of stage s are in registers (or on their way)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            if (r + 1 < RT) read_x(r + 1, buf);
+            else {
+                pre_wait<(NST - 2) * NLD>();           // stage s + 1 is there
+                fill = buf;
+                buf = buf + 1 == NST ? 0 : buf + 1;
+                read_w(wn, buf);
+                read_x(0, buf);
+            }
+            // The copies of stage s + NST - 1 go out a few at a time among the MFMAs: issued together behind the barrier they
+            // hold up the waves (the address path takes 16 cycles for each of the workgroup's copies).
+            constexpr int PER = (NLD + RT - 2) / (RT - 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = 0; f < FT; ++f) acc[r][f] = mfma16(w[f], xh[r & 1], acc[r][f]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (r + 1 < RT) copy(s + NST - 1, fill, r * PER, r * PER + (PER + 1) / 2);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = 0; f < FT; ++f) acc[r][f] = mfma16(w[f], xl[r & 1], acc[r][f]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (r + 1 < RT) copy(s + NST - 1, fill, r * PER + (PER + 1) / 2, (r + 1) * PER);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s) copy(s, s, 0, NLD);
+    pre_wait<(NST - 2) * NLD>();
+    read_w(wa, 0);
+    read_x(0, 0);
+    for (int s = 0; s < n;) {
+        const int e = min(s + PRE_RUN, n);
+        for (; s + 2 <= e; s += 2) { step(s, wa, wb); step(s + 1, wb, wa); }
+        if (s < e) { step(s, wa, wb); ++s; }
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int f = 0; f < FT; ++f) { tot[r][f] += acc[r][f]; acc[r][f] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+    }
+
+    // Epilogue, one row tile after the other: its accumulators go through the wave's own piece of LDS, so that the loop over
+    // the strips need not be unrolled (unrolled, the rotary epilogue of 32 accumulator tiles does not fit the registers).
+    pre_wait<0>();                                     // every wave is done with the stages, and no copy is on its way
+    f32x4 *mine = (f32x4 *)pre_lds + wave * FT * 64 + lane;
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const int ct = ct0 + wr * RT + r, strip0 = fs0 + wf * FT;
+        if (ct >= p.mtiles) break;
+#pragma unroll
+        for (int f = 0; f < FT; ++f) mine[f * 64] = tot[r][f];
+        const int nf = min(FT, a.nstrips - strip0);
+        if (p.part != nullptr) {
+            for (int f = 0; f < nf; ++f) ((f32x4 *)p.part)[(((size_t)slice * a.nstrips + strip0 + f) * p.mtiles + ct) * 64 + lane] = mine[f * 64];
+            continue;
+        }
+        const float rj = NORM ? p.rscale[min(ct * 16 + (lane & 15), p.rows - 1)] : 1.f;
+        const int phys = pre_page<EPI>(a, p, lane, ct);
+        if constexpr (EPI == EPI_SWIGLU) {
+            int f = 0;
+            for (; f + 2 <= nf; f += 2) pre_swiglu2(a, p, strip0 + f, lane, ct, rj, mine[f * 64], mine[(f + 1) * 64]);
+            if (f < nf) { epi_pre e; pre_fetch<EPI>(a, p, strip0 + f, lane, ct, phys, rj, e); epi_apply<2, EPI>(a, strip0 + f, lane, mine[f * 64], e, ct); }
+        } else {
+            constexpr int G = EPI == EPI_RESID ? FT : FT < 4 ? FT : 4;          // the loads of G strips go out together
+            for (int f = 0; f < nf; f += G) {
+                epi_pre e[G];
+#pragma unroll
+                for (int u = 0; u < G; ++u) pre_fetch<EPI>(a, p, min(strip0 + f + u, a.nstrips - 1), lane, ct, phys, rj, e[u]);
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+                    if (f + u < nf) epi_apply<2, EPI>(a, strip0 + f + u, lane, mine[(f + u) * 64], e[u], ct);
+            }
+        }
+    }
+}
+
+// Adds the K-slices' partial sums in slice order and runs the epilogue: one wave per (strip, row tile).
+template <int EPI>
+__global__ void __launch_bounds__(256)
+k_pre_sum(const gemm_args a, const pre_gemm_args p, int slices)
+{
+    constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
+    const int lane = threadIdx.x & 63, strip = blockIdx.x * 4 + (threadIdx.x >> 6), ct = blockIdx.y;
+    if (strip >= a.nstrips) return;
+    const float4 *q = p.part + ((size_t)strip * p.mtiles + ct) * 64 + lane;
+    const size_t step = (size_t)a.nstrips * p.mtiles * 64;
+    epi_pre pre;
+    pre_fetch<EPI>(a, p, strip, lane, ct, pre_page<EPI>(a, p, lane, ct), NORM ? p.rscale[min(ct * 16 + (lane & 15), p.rows - 1)] : 1.f, pre);
+    float4 v = q[0];
+    for (int y = 1; y < slices; ++y) { const float4 u = q[y * step]; v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w; }
+    epi_apply<2, EPI>(a, strip, lane, (f32x4){v.x, v.y, v.z, v.w}, pre, ct);
+}
+
+// ------------------------------------------------------------------------------------------
+// Block set-up.  The token ids come from pinned host memory in one read.  The cache's state only changes when the block is
+// committed; until then rows and length are kernel arguments (the launches are not recorded).
+// ------------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(1024)
+k_pre_tokens(const int32_t *host_tokens, int32_t *tokens, int rows)
+{
+    for (int i = threadIdx.x; i < rows; i += 1024) tokens[i] = host_tokens[i];
+}
+
+__global__ void __launch_bounds__(64)
+k_pre_embed(int rows, int len, const int32_t *tokens, const uint16_t *embed, const uint16_t *gain, const double *inv_freq,
+            float *x, float *ssq, uint16_t *xop, float2 *rope, int d, int half)
+{
+    const int lane = threadIdx.x, ct = blockIdx.y, j = ct * 16 + (lane & 15), g = lane >> 4, strip = blockIdx.x;
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (j < rows) {
+        const uint16_t *e = embed + (size_t)tokens[j] * d + strip * 16 + 4 * g;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = pv_bf16_to_f32(e[r]);
+    }
+    emit_x<2>(lane, rows, strip, d, v, *(const uint2 *)(gain + strip * 16 + 4 * g), x, ssq, xop, ct, 8);
+    // rotary table: every workgroup takes its share
+    for (int idx = (ct * gridDim.x + strip) * 64 + lane; idx < rows * half; idx += gridDim.x * gridDim.y * 64) {
+        const int jj = idx / half, i = idx - jj * half;
+        double sn, cs;
+        sincos((double)(len + jj) * inv_freq[i], &sn, &cs);
+        rope[idx] = make_float2((float)cs, (float)sn);
+    }
+}
+
+// RMSNorm scales of the block's rows from the per-strip sums of squares ([row tile][strips][16]): once per row instead
+// of once per workgroup of the GEMM that follows.  One workgroup per row tile: thread t adds the strips t / 16, t / 16 + 16, ... of row t % 16.
+__global__ void __launch_bounds__(256)
+k_pre_rscale(const float *ssq, float *rscale, int strips, float inv_d, float eps)
+{
+    __shared__ float s[256];
+    const float *q = ssq + (size_t)blockIdx.x * strips * 16 + threadIdx.x;
+    float v = 0.f;
+    for (int i = threadIdx.x >> 4; i < strips; i += 16, q += 256) v += *q;
+    s[threadIdx.x] = v;
+    __syncthreads();
+    if (threadIdx.x < 16) {
+        for (int i = 1; i < 16; ++i) v += s[i * 16 + threadIdx.x];
+        rscale[blockIdx.x * 16 + threadIdx.x] = 1.0f / sqrtf(v * inv_d + eps);
+    }
+}
+
+// The block's rows are part of the cache, but for its last `keep` rows, which become the cache's running block: the
+// head and k_finish commit those as they do for a block of at most 64 rows.
+__global__ void k_pre_commit(pv_dev_state *st, int rows, int keep)
+{
+    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    st->len += rows - keep;
+    if (rows > keep) st->pending = -1;
+    if (keep) { st->gamma = keep; st->mode = PV_MODE_PREFILL_LAST; st->blk.seq[0].gamma = keep; }
+}
+
+// ------------------------------------------------------------------------------------------
+// Causal attention of the whole block.  A workgroup of 4 waves owns 128 query rows of one kv
+// head (row m = token * group + head in group, so a workgroup's tokens are neighbours), a wave
+// two 16-row tiles; Q (hi + lo) and the running output stay in registers while the keys go by 64
+// at a time through LDS (two buffers, copied a step ahead).  Products, operand orders and splits are those
+// of attn_chunk (pv_attention_body.h); the softmax is kept running (maximum and sum per row).
+// Every query row reads K and V once per workgroup from L2 instead of once per 32 rows as partial
+// results: at 2048 keys the chunked kernel with its merge took 26 us per 64 rows of an 8B-shaped layer.
+// ------------------------------------------------------------------------------------------
+struct pre_attn_args {
+    int rows, len;
+    const int32_t *page_table;
+    const uint16_t *q_hi, *q_lo;
+    const uint16_t *pool;
+    pv_kv_geom geom;
+    int layer, n_q_heads, group, qtiles, paired;
+    float scale2;               // log2(e) / sqrt(head_dim)
+    uint16_t *xop_o;
+};
+
+template <int HD>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_pre_attn(const pre_attn_args a)
+{
+    constexpr int KS = HD / 32, ET = HD / 16, RT = 2, TB = 2 * KS;          // TB: KiB of one 16-key group (K and V)
+    extern __shared__ uint4 pre_lds[];                                       // [2][4 groups][K | V][KS][64]
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, jl = lane & 15, g = lane >> 4;
+    // The longest first.  Two workgroups fit on a CU: where all of them start at once, the second half comes
+    // shortest first, so that a CU's two add up to about the same everywhere.
+    const int kvh = blockIdx.x % a.geom.n_kv_heads, o = blockIdx.x / a.geom.n_kv_heads, half = (a.qtiles + 1) >> 1;
+    const int qt = (a.paired && o >= half) ? o - half : a.qtiles - 1 - o;
+    const int len = a.len, nrows = a.rows * a.group;
+    const int m0 = qt * 128;
+    const int jmin = m0 / a.group, jmax = min(m0 + 127, nrows - 1) / a.group;
+    const int nkeys = len + jmax + 1, nsteps = (nkeys + 63) >> 6;
+    const int sub_shift = a.geom.page_shift - 4, sub_mask = (1 << sub_shift) - 1;
+    const int last_grp = (nkeys - 1) >> 4;
+    // group 4 s + wave of step s: copied by this wave.  Page table entries are fetched one step ahead.
+    const __attribute__((address_space(4))) int32_t *pt = (const __attribute__((address_space(4))) int32_t *)(uintptr_t)uniform_ptr(a.page_table);
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(pre_lds)) + wave * TB * 1024;
+    auto page_of = [&](int s) { return pt[min(4 * s + wave, last_grp) >> sub_shift]; };
+    auto copy = [&](int s, int phys, int buf) {
+        const int grp = min(4 * s + wave, last_grp);
+        const char *kb = (const char *)(a.pool + pv_kv_block(a.geom, a.layer, phys, kvh, 0) + (size_t)(grp & sub_mask) * 16 * HD);
+        const char *vb = (const char *)(a.pool + pv_kv_block(a.geom, a.layer, phys, kvh, 1) + (size_t)(grp & sub_mask) * 16 * HD);
+        kb = uniform_ptr(kb); vb = uniform_ptr(vb);
+#pragma unroll
+        for (int i = 0; i < KS; ++i) dma_tile(lds0 + (uint32_t)(buf * 4 * TB + i) * 1024, kb + i * 1024, lane * 16);
+#pragma unroll
+        for (int i = 0; i < KS; ++i) dma_tile(lds0 + (uint32_t)(buf * 4 * TB + KS + i) * 1024, vb + i * 1024, lane * 16);
+    };
+    copy(0, page_of(0), 0);
+    int ph_next = page_of(1);
+
+    // this lane's query rows (a row past the end reads the last one and is not stored)
+    int j[RT], al[RT];
+    uint4 qh[RT][KS], ql[RT][KS];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        const int m = min(m0 + wave * 32 + t * 16 + jl, nrows - 1);
+        j[t] = m / a.group; al[t] = m - j[t] * a.group;
+        const size_t qo = ((size_t)j[t] * a.n_q_heads + kvh * a.group + al[t]) * HD + g * 8;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) { qh[t][ks] = *(const uint4 *)(a.q_hi + qo + ks * 32); ql[t][ks] = *(const uint4 *)(a.q_lo + qo + ks * 32); }
+    }
+    // Q is here before the loop starts: a wait for it inside would also wait for the copies of the next step
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+    f32x4 O[RT][ET];
+    float mx[RT], sum[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        mx[t] = -INFINITY; sum[t] = 0.f;
+#pragma unroll
+        for (int e = 0; e < ET; ++e) O[t][e] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    for (int s = 0; s < nsteps; ++s) {
+        const int buf = s & 1;
+        pre_wait<0>();                                 // step s has landed for every wave, and every wave is done with the other buffer
+        if (s + 1 < nsteps) { copy(s + 1, ph_next, buf ^ 1); ph_next = page_of(s + 2); }
+        const uint4 *Lk = pre_lds + (size_t)buf * 4 * TB * 64 + lane;
+        const char *Lv = (const char *)(pre_lds + (size_t)buf * 4 * TB * 64) + KS * 1024 + jl * 32 + g * 8;
+        f32x4 S[RT][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t) S[t][q] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const uint4 k = Lk[(q * TB + ks) * 64];
+#pragma unroll
+                for (int t = 0; t < RT; ++t) { S[t][q] = mfma16(k, qh[t][ks], S[t][q]); S[t][q] = mfma16(k, ql[t][ks], S[t][q]); }
+            }
+        }
+        const bool edge = s * 64 + 63 > len + jmin;    // some row of the workgroup may not see some key of the step
+        uint32_t P[RT][4][4];                          // per group: keys 4 g .. + 3 as hi (2 dwords), lo (2 dwords)
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            if (edge) {
+                const int lim = len + j[t] - s * 64 - 4 * g;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) if (16 * q + r > lim) S[t][q][r] = -INFINITY;
+            }
+            float m = mx[t];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) m = fmaxf(fmaxf(m, fmaxf(S[t][q][0], S[t][q][1])), fmaxf(S[t][q][2], S[t][q][3]));
+            m = fmaxf(m, __shfl_xor(m, 16, 64));
+            m = fmaxf(m, __shfl_xor(m, 32, 64));
+            if (__any(m > mx[t])) {                    // (key 0 is visible to every row: the maximum is finite from the first step on)
+                const float f = __builtin_amdgcn_exp2f((mx[t] - m) * a.scale2);
+                sum[t] *= f;
+#pragma unroll
+                for (int e = 0; e < ET; ++e) { O[t][e][0] *= f; O[t][e][1] *= f; O[t][e][2] *= f; O[t][e][3] *= f; }
+                mx[t] = m;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float p[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) { p[r] = __builtin_amdgcn_exp2f((S[t][q][r] - m) * a.scale2); sum[t] += p[r]; }
+                split2(p[0], p[1], P[t][q][0], P[t][q][2]);
+                split2(p[2], p[3], P[t][q][1], P[t][q][3]);
+            }
+        }
+#pragma unroll
+        for (int hq = 0; hq < 2; ++hq)
+#pragma unroll
+            for (int e = 0; e < ET; ++e) {
+                const uint2 v0 = *(const uint2 *)(Lv + (2 * hq) * TB * 1024 + e * 512), v1 = *(const uint2 *)(Lv + (2 * hq + 1) * TB * 1024 + e * 512);
+                const uint4 v = make_uint4(v0.x, v0.y, v1.x, v1.y);
+#pragma unroll
+                for (int t = 0; t < RT; ++t) {
+                    const uint4 ph = make_uint4(P[t][2 * hq][0], P[t][2 * hq][1], P[t][2 * hq + 1][0], P[t][2 * hq + 1][1]);
+                    const uint4 pl = make_uint4(P[t][2 * hq][2], P[t][2 * hq][3], P[t][2 * hq + 1][2], P[t][2 * hq + 1][3]);
+                    O[t][e] = mfma16(v, ph, O[t][e]);
+                    O[t][e] = mfma16(v, pl, O[t][e]);
+                }
+            }
+    }
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        float l = sum[t];
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        const float inv = 1.0f / l;
+        if (m0 + wave * 32 + t * 16 + jl < nrows) {
+#pragma unroll
+            for (int e = 0; e < ET; ++e) {
+                const float y[4] = {O[t][e][0] * inv, O[t][e][1] * inv, O[t][e][2] * inv, O[t][e][3] * inv};
+                store_operand4<2>(a.xop_o, a.n_q_heads * HD, j[t], (kvh * a.group + al[t]) * HD + e * 16 + 4 * g, y, 8);
+            }
+        }
+    }
+}
+
+// ------------------------------- host side ----------------------------------------
+
+int pv_pre_rows(const pv_model *m, int max_tokens)
+{
+    if (m->path < PV_PATH_MATRIX || m->wbits == 4) return 0;
+    const int rows = std::min(PV_PRE_ROWS, (max_tokens + 63) / 64 * 64);
+    return rows > PV_PRE_MIN ? rows : 0;
+}
+
+struct pre_ws {
+    int32_t *tokens;
+    float2 *rope;
+    float *x, *ssq, *rscale;
+    uint16_t *xop;              // QKV and gate/up input (K = d)
+    uint16_t *xop_d;            // down input (K = F); before that the queries and the O input (K = qd)
+    uint16_t *q_hi, *q_lo, *xop_o;
+};
+
+static size_t pre_layout(const pv_model *m, int rows, char *base, pre_ws *w)
+{
+    const pv_model_config &f = m->cfg;
+    const size_t R = rows, d = f.d_model, qd = (size_t)f.n_q_heads * f.head_dim;
+    size_t off = 0;
+    auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) / 256 * 256; return base ? base + o : (char *)nullptr; };
+    char *p;
+    p = take(4 * R); if (w) w->tokens = (int32_t *)p;
+    p = take(sizeof(float2) * R * (f.head_dim / 2)); if (w) w->rope = (float2 *)p;
+    p = take(4 * R * d); if (w) w->x = (float *)p;
+    p = take(4 * R * (d / 16)); if (w) w->ssq = (float *)p;
+    p = take(4 * R); if (w) w->rscale = (float *)p;
+    p = take(4 * R * d); if (w) w->xop = (uint16_t *)p;
+    p = take(std::max((size_t)4 * R * f.ffn_dim, 8 * R * qd));
+    if (w) { w->xop_d = (uint16_t *)p; w->q_hi = w->xop_d; w->q_lo = w->q_hi + R * qd; w->xop_o = w->q_lo + R * qd; }
+    return off;
+}
+
+size_t pv_pre_bytes(const pv_model *m, int max_tokens)
+{
+    const int rows = pv_pre_rows(m, max_tokens);
+    return rows ? pre_layout(m, rows, nullptr, nullptr) : 0;
+}
+
+template <int WR, int WF, int RT, int FT, int NST>
+struct pre_shape {
+    static constexpr int BR = WR * RT, BF = WF * FT;
+    static constexpr int lds = NST * pre_stage_tiles(BR, BF) * 1024;
+    template <int EPI> static int allow()
+    {
+        PV_HIP(hipFuncSetAttribute((const void *)k_pre_gemm<WR, WF, RT, FT, NST, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        return PV_OK;
+    }
+    static int allow_all()
+    {
+        int rc;
+        if ((rc = allow<EPI_QKV>()) != PV_OK || (rc = allow<EPI_RESID>()) != PV_OK) return rc;
+        return allow<EPI_SWIGLU>();
+    }
+    template <int EPI> static int run(const gemm_args &ga, pre_gemm_args pa, int slices, hipStream_t s)
+    {
+        pa.rb = (pa.mtiles + BR - 1) / BR; pa.fb = (ga.nstrips + BF - 1) / BF;
+        pa.kps = (ga.ktiles + slices - 1) / slices;
+        slices = (ga.ktiles + pa.kps - 1) / pa.kps;
+        if (slices == 1) pa.part = nullptr;
+        k_pre_gemm<WR, WF, RT, FT, NST, EPI><<<pa.rb * pa.fb * slices, 512, lds, s>>>(ga, pa);
+        PV_HIP(hipGetLastError());
+        if (slices > 1) { k_pre_sum<EPI><<<dim3((ga.nstrips + 3) / 4, pa.mtiles), 256, 0, s>>>(ga, pa, slices); PV_HIP(hipGetLastError()); }
+        return PV_OK;
+    }
+};
+using pre_wide = pre_shape<2, 4, 4, 4, 4>;     // 128 rows x 256 features
+using pre_mid = pre_shape<2, 4, 4, 3, 5>;      // 128 x 192
+using pre_small = pre_shape<2, 4, 4, 2, 6>;    // 128 x 128
+
+int pv_pre_init(int head_dim)
+{
+    int rc;
+    if ((rc = pre_mid::allow_all()) != PV_OK || (rc = pre_wide::allow_all()) != PV_OK || (rc = pre_small::allow_all()) != PV_OK) return rc;
+    return PV_OK;
+}
+
+template <int EPI>
+static int pre_gemm(const pv_model *m, const gemm_args &g, int strips, const float *rscale, int rows, int len, size_t part_floats, hipStream_t s)
+{
+    const int mtiles = (rows + 15) / 16;
+    gemm_args ga = g;
+    ga.nstrips = strips;
+    pre_gemm_args pa = {};
+    pa.rscale = rscale; pa.part = (float4 *)g.tile_part; pa.mtiles = mtiles; pa.rows = rows; pa.len = len;
+    // The rectangle and the number of K-slices with the smallest estimated time.  Unit: one MFMA pair's share of a 256 x 256 rectangle
+    // (3.85 ns per 16 x 16 outputs and K-tile of a workgroup).  Measured (4096 x 4096 and 4096 x 14336 weights, few workgroups): per
+    // K-tile 0.99, 0.77, 0.53 and 0.30 us, on top of 20, 16, 14 and 9 us for the start, the epilogue and the end; partial
+    // sums: 3 us and 0.2 ns for each 16 x 16 of them.  Where more workgroups than CUs come out, they run in rounds.
+    static const struct { int br, bf; double cost; } R[3] = {{8, 16, 1.07}, {8, 12, 1.12}, {8, 8, 1.22}};
+    double best = 1e30; int shape = 0, cut = 1;
+    for (int i = 0; i < 3; ++i) {
+        const int blocks = ((mtiles + R[i].br - 1) / R[i].br) * ((strips + R[i].bf - 1) / R[i].bf);
+        for (int sl = 1; sl <= 16; ++sl) {
+            if (sl > 1 && (g.ktiles / sl < 8 || (size_t)sl * strips * mtiles * 256 > part_floats || g.tile_part == nullptr)) break;
+            const int rounds = (blocks * sl + m->n_cus - 1) / m->n_cus;
+            const double t = rounds * ((g.ktiles + sl - 1) / sl * R[i].br * R[i].bf * R[i].cost + 1500.0 + 15.0 * R[i].br * R[i].bf)
+                           + (sl > 1 ? 800.0 + 0.05 * sl * strips * mtiles : 0.0);
+            if (t < best) { best = t; shape = i; cut = sl; }
+        }
+    }
+    if (shape == 0) return pre_wide::run<EPI>(ga, pa, cut, s);
+    if (shape == 1) return pre_mid::run<EPI>(ga, pa, cut, s);
+    return pre_small::run<EPI>(ga, pa, cut, s);
+}
+
+template <int HD>
+static int pre_attention(const pre_attn_args &a, int kv_heads, hipStream_t s)
+{
+    k_pre_attn<HD><<<a.qtiles * kv_heads, 256, 2 * 4 * 2 * (HD / 32) * 1024, s>>>(a);
+    PV_HIP(hipGetLastError());
+    return PV_OK;
+}
+
+int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows, int keep, float *tile_part, size_t part_floats, pv_pre_out *out, hipStream_t s)
+{
+    const pv_model *m = c->m;
+    const pv_model_config &f = m->cfg;
+    const int d = f.d_model, hd = f.head_dim, qd = f.n_q_heads * hd, kvd = f.n_kv_heads * hd, F = f.ffn_dim, mtiles = (rows + 15) / 16, len = c->len;
+    const char *Wb = m->d_weights;
+    auto gainp = [&](int kind, int l) { return (const uint16_t *)(Wb + pv_tref(m, kind, l).off); };
+    pre_ws w;
+    pre_layout(m, pv_pre_rows(m, c->max_tokens), base, &w);
+
+    k_pre_tokens<<<1, 1024, 0, s>>>(d_host_tokens, w.tokens, rows);
+    PV_HIP(hipGetLastError());
+    k_pre_embed<<<dim3(d / 16, mtiles), 64, 0, s>>>(rows, len, w.tokens, (const uint16_t *)(Wb + m->global[PV_T_EMBED].off), gainp(PV_T_ATTN_NORM, 0),
+                                                    (const double *)(Wb + m->inv_freq_off), w.x, w.ssq, w.xop, w.rope, d, hd / 2);
+    PV_HIP(hipGetLastError());
+
+    gemm_args g = {};
+    g.st = c->ws.state; g.lo_off = 8; g.inv_d = 1.0f / (float)d; g.eps = (float)f.rms_eps; g.ssq_parts = d / 16;
+    g.q_hi = w.q_hi; g.q_lo = w.q_lo; g.pool = (uint16_t *)c->d_pool; g.page_table = c->ws.page_table; g.rope = w.rope; g.geom = pv_geom(c);
+    g.n_q_heads = f.n_q_heads; g.q_strips = qd / 16; g.k_strips = kvd / 16;
+    g.x = w.x; g.d = d; g.xop_act = w.xop_d; g.F = F; g.tile_part = tile_part; g.ssq = w.ssq; g.ssq_out = w.ssq; g.xop_out = w.xop;
+
+    pre_attn_args at = {};
+    at.rows = rows; at.len = len; at.page_table = c->ws.page_table; at.q_hi = w.q_hi; at.q_lo = w.q_lo; at.pool = (const uint16_t *)c->d_pool; at.geom = g.geom;
+    at.n_q_heads = f.n_q_heads; at.group = f.n_q_heads / f.n_kv_heads; at.qtiles = (rows * at.group + 127) / 128;
+    at.paired = at.qtiles * f.n_kv_heads <= 2 * m->n_cus;
+    at.scale2 = 1.44269504088896340736f / sqrtf((float)hd); at.xop_o = w.xop_o;
+
+    int rc;
+    for (int l = 0; l < f.n_layers; ++l) {
+        k_pre_rscale<<<mtiles, 256, 0, s>>>(w.ssq, w.rscale, d / 16, g.inv_d, g.eps);
+        PV_HIP(hipGetLastError());
+        g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WQ, l).off); g.xop = (const uint4 *)w.xop; g.ktiles = d / 32; g.layer = l;
+        if ((rc = pv_prof_mark(c, PV_PROF_QKV, l, 0, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_QKV>(m, g, (qd + 2 * kvd) / 16, w.rscale, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pv_prof_mark(c, PV_PROF_QKV, l, 1, s)) != PV_OK) return rc;
+        at.layer = l;
+        if ((rc = pv_prof_mark(c, PV_PROF_ATTENTION, l, 0, s)) != PV_OK) return rc;
+        rc = hd == 128 ? pre_attention<128>(at, f.n_kv_heads, s) : hd == 64 ? pre_attention<64>(at, f.n_kv_heads, s) : pre_attention<32>(at, f.n_kv_heads, s);
+        if (rc != PV_OK) return rc;
+        if ((rc = pv_prof_mark(c, PV_PROF_ATTENTION, l, 1, s)) != PV_OK) return rc;
+        g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WO, l).off); g.xop = (const uint4 *)w.xop_o; g.ktiles = qd / 32; g.gain_next = gainp(PV_T_FFN_NORM, l);
+        if ((rc = pv_prof_mark(c, PV_PROF_OPROJ, l, 0, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pv_prof_mark(c, PV_PROF_OPROJ, l, 1, s)) != PV_OK) return rc;
+        k_pre_rscale<<<mtiles, 256, 0, s>>>(w.ssq, w.rscale, d / 16, g.inv_d, g.eps);
+        PV_HIP(hipGetLastError());
+        g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WG, l).off); g.xop = (const uint4 *)w.xop; g.ktiles = d / 32;
+        if ((rc = pv_prof_mark(c, PV_PROF_GATEUP, l, 0, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_SWIGLU>(m, g, F / 8, w.rscale, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pv_prof_mark(c, PV_PROF_GATEUP, l, 1, s)) != PV_OK) return rc;
+        g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WD, l).off); g.xop = (const uint4 *)w.xop_d; g.ktiles = F / 32;
+        g.gain_next = (l + 1 < f.n_layers) ? gainp(PV_T_ATTN_NORM, l + 1) : (const uint16_t *)(Wb + m->global[PV_T_FINAL_NORM].off);
+        if ((rc = pv_prof_mark(c, PV_PROF_DOWN, l, 0, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pv_prof_mark(c, PV_PROF_DOWN, l, 1, s)) != PV_OK) return rc;
+    }
+    k_pre_commit<<<1, 64, 0, s>>>(c->ws.state, rows, keep);
+    PV_HIP(hipGetLastError());
+    const int ct = (rows - keep) / 16;                  // (the kept rows start on a row tile)
+    out->xop = w.xop + (size_t)ct * 2 * (d / 32) * 512;
+    out->ssq = w.ssq + (size_t)ct * d;
+    return PV_OK;
+}

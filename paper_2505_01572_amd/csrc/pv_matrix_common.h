@@ -37,6 +37,16 @@ __device__ inline uint2 load_once(const uint2 *p)
 // ------------------------------------------------------------------------------------------
 __device__ inline uint16_t bf16_rne(float f) { return pv_f32_to_bf16(f); }
 
+// two numbers as bf16 hi parts, and what is left of them as bf16 lo parts: one conversion instruction per pair
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+__device__ inline uint32_t pack_bf16(float a, float b) { const f32x2 v = {a, b}; return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2)); }
+__device__ inline void split2(float a, float b, uint32_t &hi, uint32_t &lo)
+{
+    hi = pack_bf16(a, b);
+    lo = pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
+}
+
 // four consecutive k (k0 % 4 == 0) of row j
 // lo column offset of a packed-row block of `rows` rows
 __host__ __device__ inline int pv_lo_off(int rows) { return rows <= 4 ? 4 : 8; }
@@ -44,12 +54,10 @@ __host__ __device__ inline int pv_lo_off(int rows) { return rows <= 4 ? 4 : 8; }
 template <int NB>
 __device__ inline void store_operand4(uint16_t *xop, int K, int j, int k0, const float y[4], int lo_off)
 {
-    uint16_t hi[4], lo[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) { hi[r] = bf16_rne(y[r]); lo[r] = bf16_rne(y[r] - pv_bf16_to_f32(hi[r])); }
     const size_t tile = (size_t)(k0 >> 5) * 512, in = (size_t)(((k0 & 31) >> 3) * 16) * 8 + (k0 & 7);
-    const uint2 vh = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
-    const uint2 vl = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+    uint2 vh, vl;
+    split2(y[0], y[1], vh.x, vl.x);
+    split2(y[2], y[3], vh.y, vl.y);
     if (NB == 1) {
         *(uint2 *)(xop + tile + in + (size_t)j * 8) = vh;
         *(uint2 *)(xop + tile + in + (size_t)(j + lo_off) * 8) = vl;

@@ -1,0 +1,101 @@
+"""Long prompts (more than 64 tokens in one prefill call) against the CPU oracle and against the same prompt put in as
+64-token pieces: lengths at the edges of the row rectangles (16, 64, 128, 256) and of a pass (2048), head dimensions and
+group sizes, a prefix already in the cache, shuffled pages, ragged strip counts, K cut into slices."""
+import numpy as np
+import pytest
+
+import pv_inputs
+from helpers import ref_model
+from oracle import ref
+
+pytestmark = pytest.mark.gpu
+
+S = pv_inputs.ModelShape
+SHAPES = {
+    "gqa64": S("pr_gqa64", 2, 512, 8, 2, 64, 1408, 1008, rope_base=500000.0, seed=7101),          # 88 gate/up strips x 2, ragged rectangles
+    "mha128": S("pr_mha128", 2, 256, 3, 3, 128, 736, 512, seed=7102),                             # no sharing of K/V heads, K of 8, 12 and 23 tiles
+    "odd32": S("pr_odd32", 2, 160, 15, 5, 32, 96, 512, seed=7103),                                # three heads to a kv head; K of 5, 15 and 3 tiles
+    "deep": S("pr_deep", 1, 1024, 8, 1, 128, 8448, 2000, rope_base=500000.0, seed=7104),          # long K: cut into slices; eight heads to a kv head
+    "q4": S("pr_q4", 2, 512, 8, 2, 64, 1408, 1008, rope_base=500000.0, seed=7105, weight_bits=4),
+    "q4_deep": S("pr_q4_deep", 1, 1024, 8, 2, 128, 8448, 2000, rope_base=500000.0, seed=7106, weight_bits=4),
+}
+CASES = [("gqa64", 0, 65, 64), ("gqa64", 3, 80, 16), ("deep", 0, 128, 16), ("gqa64", 0, 129, 64), ("gqa64", 0, 257, 16), ("gqa64", 37, 300, 16), ("gqa64", 128, 192, 64), ("mha128", 5, 400, 16), ("mha128", 0, 145, 16),
+         ("odd32", 0, 520, 16), ("odd32", 70, 131, 32), ("deep", 0, 260, 16), ("deep", 3, 600, 128), ("gqa64", 0, 2048 + 70, 16), ("gqa64", 9, 2048 + 200, 16),
+         ("q4", 0, 129, 16), ("q4", 37, 300, 16), ("q4_deep", 0, 260, 16), ("q4_deep", 3, 600, 16)]
+
+
+@pytest.mark.parametrize("name,before,n,page", CASES)
+def test_long_prompt(name, before, n, page):
+    import paper_2505_01572_amd as pv
+    from gpu_helpers import gpu_model, logit_scale
+    shape = SHAPES[name].replace(page_tokens=page)
+    gm = gpu_model(shape, gains="perturbed")
+    toks = pv_inputs.uniform_tokens(71, before + n, shape.vocab)
+    room = before + n + 24
+    pages = -(-room // page)
+    a, b = pv.Cache(gm, room), pv.Cache(gm, room)
+    a.set_page_table(np.random.default_rng(3).permutation(pages))
+    if before:
+        a.prefill(toks[:before])
+    a.prefill(toks[before:])
+    if before:
+        b.prefill(toks[:before])
+    for i in range(before, before + n, 64):
+        b.prefill(toks[i:min(i + 64, before + n)])
+    lg, lb = a.debug_logits(), b.debug_logits()
+    # rows, logits and prediction of the last block of 64, whatever the prompt went in as
+    assert lg.shape == lb.shape == ((n - 1) % 64 + 1, shape.vocab)
+    scale = logit_scale(lb)
+    assert (np.abs(lg - lb) / scale).max() < 2e-3
+    margin = np.sort(lb, axis=1)
+    safe = margin[:, -1] - margin[:, -2] > 4 * np.abs(lg - lb).max()
+    assert np.array_equal(a.debug_pred()[safe], b.debug_pred()[safe])
+    assert len(a) == len(b) == before + n
+    if safe[-1]:
+        assert a.state() == b.state()
+    ka, kb = (pv_inputs.bf16_bits_to_f32(c.export()).astype(np.float64) for c in (a, b))
+    assert np.mean(ka != kb) < 0.02 and np.abs(ka - kb).max() <= 2.0 ** -7 * np.abs(kb).max()     # one bf16 step at rounding boundaries
+    d = pv_inputs.uniform_tokens(72, 8, shape.vocab)
+    d[0] = a.pending
+    a.verify(before + n, d)
+    lv = a.debug_logits()
+    if before + n <= 620:
+        rm = ref_model(shape, gains="perturbed")
+        rc = ref.RefCache(rm, room, ref.KV_BF16)
+        last = rc.prefill(toks)
+        assert (np.abs(lg[-1] - last) / logit_scale(last)).max() < 2e-3
+        _, _, _, want = rc.verify(before + n, d, want_logits=True)
+        assert (np.abs(lv - want) / logit_scale(want)).max() < 2e-3
+    else:
+        b.set_pending(int(d[0]))
+        b.verify(before + n, d)
+        assert (np.abs(lv - b.debug_logits()) / logit_scale(lv)).max() < 2e-3
+
+
+def test_non_finite_prompt_commits_all_but_the_last_block():
+    """Weights that make every logit NaN: the last 64-token block is not committed, as with short prompts."""
+    import paper_2505_01572_amd as pv
+    shape = SHAPES["gqa64"]
+    from gpu_helpers import gpu_model
+    gm = gpu_model(shape)
+    bad = np.full((1, shape.d_model), 0x7FC0, dtype=np.uint16)
+    gm.load_weights("final_norm", 0, 0, bad)
+    c = pv.Cache(gm, 400)
+    with pytest.raises(pv.PVError) as e:
+        c.prefill(pv_inputs.uniform_tokens(5, 300, shape.vocab))
+    assert e.value.status == -6
+    assert c.state() == (256, -1)
+
+
+def test_rollback_and_readmit_after_a_long_prompt():
+    import paper_2505_01572_amd as pv
+    from gpu_helpers import gpu_model
+    shape = SHAPES["gqa64"]
+    gm = gpu_model(shape, gains="perturbed")
+    toks = pv_inputs.uniform_tokens(73, 400, shape.vocab)
+    a, b = pv.Cache(gm, 480), pv.Cache(gm, 480)
+    a.prefill(toks[:300])
+    a.rollback(150)
+    a.prefill(toks[150:])
+    b.prefill(toks[:150]); b.prefill(toks[150:])
+    assert a.state() == b.state() and np.array_equal(a.export(), b.export())

@@ -10,7 +10,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.parametrize("src", ["pv_kernels_matrix.hip", "pv_kernels_attention.hip", "pv_kernels_common.hip", "pv_kernels_vector.hip"])
+@pytest.mark.parametrize("src", ["pv_kernels_matrix.hip", "pv_kernels_attention.hip", "pv_kernels_common.hip", "pv_kernels_vector.hip", "pv_kernels_prefill.hip"])
 def test_kernels_use_no_scratch(tmp_path, src):
     from paper_2505_01572_amd import build
     out = str(tmp_path / "k.s")

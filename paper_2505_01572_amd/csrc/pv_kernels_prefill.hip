@@ -10,6 +10,7 @@
 #include "pv_gemm_epilogue.h"
 #include "pv_prefill.h"
 #include <algorithm>
+#include <type_traits>
 
 // One 1 KiB operand tile (64 lanes x 16 bytes) from global memory straight into LDS.  Written in assembly (there is
 // no output register) because the compiler otherwise waits for every copy in flight before any LDS read; the
@@ -59,6 +60,7 @@ struct pre_gemm_args {
     int rb, fb;                 // rectangles along the rows and the features
     int kps;                    // K-tiles per slice
     int rows, len;              // rows of the block, and the position of the first
+    const float *rowsum; int rsum_rows;   // 4-bit weights: -24 x the operand's row sums, [K-tile][rsum_rows]
 };
 
 // What the epilogue of a strip needs from memory.  Rows, length and the row's page are known here (epi_prefetch reads them
@@ -104,6 +106,35 @@ __device__ inline void pre_swiglu2(const gemm_args &a, const pre_gemm_args &p, i
     if (j < p.rows) store_operand4<2>(a.xop_act, a.F, j, (strip + odd) * 8 + 4 * (g >> 1), act, 8);
 }
 
+// Epilogue of one row tile of a wave, whose nf accumulators (strip0 ...) lie in the wave's own piece of LDS (`mine`, at this lane): the loop
+// over the strips need not be unrolled then (unrolled, the rotary epilogue of 16 accumulator tiles does not fit the registers).
+template <int EPI, int FT>
+__device__ inline void pre_epilogue(const gemm_args &a, const pre_gemm_args &p, int slice, int ct, int strip0, int nf, int lane, const f32x4 *mine)
+{
+    constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
+    if (p.part != nullptr) {
+        for (int f = 0; f < nf; ++f) ((f32x4 *)p.part)[(((size_t)slice * a.nstrips + strip0 + f) * p.mtiles + ct) * 64 + lane] = mine[f * 64];
+        return;
+    }
+    const float rj = NORM ? p.rscale[min(ct * 16 + (lane & 15), p.rows - 1)] : 1.f;
+    const int phys = pre_page<EPI>(a, p, lane, ct);
+    if constexpr (EPI == EPI_SWIGLU) {
+        int f = 0;
+        for (; f + 2 <= nf; f += 2) pre_swiglu2(a, p, strip0 + f, lane, ct, rj, mine[f * 64], mine[(f + 1) * 64]);
+        if (f < nf) { epi_pre e; pre_fetch<EPI>(a, p, strip0 + f, lane, ct, phys, rj, e); epi_apply<2, EPI>(a, strip0 + f, lane, mine[f * 64], e, ct); }
+    } else {
+        constexpr int G = EPI == EPI_RESID ? FT : FT < 4 ? FT : 4;          // the loads of G strips go out together
+        for (int f = 0; f < nf; f += G) {
+            epi_pre e[G];
+#pragma unroll
+            for (int u = 0; u < G; ++u) pre_fetch<EPI>(a, p, min(strip0 + f + u, a.nstrips - 1), lane, ct, phys, rj, e[u]);
+#pragma unroll
+            for (int u = 0; u < G; ++u)
+                if (f + u < nf) epi_apply<2, EPI>(a, strip0 + f + u, lane, mine[(f + u) * 64], e[u], ct);
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // The GEMM.  WR x WF waves of a workgroup, each RT row tiles x FT strips: per K-tile a wave
 // reads 2 RT + FT operand tiles from LDS for 2 RT FT MFMAs, a workgroup copies 2 WR RT + WF FT
@@ -118,7 +149,6 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 k_pre_gemm(const gemm_args a, const pre_gemm_args p)
 {
     static_assert(WR * WF == 8 && RT % 2 == 0, "8 waves; row tiles alternate between two operand buffers");
-    constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
     constexpr int BR = WR * RT, BF = WF * FT, TPS = pre_stage_tiles(BR, BF), NLD = TPS / 8;
     static_assert((2 * BR) % 8 == 0, "a wave's i-th tile is an activation tile in every wave or in none");
     extern __shared__ uint4 pre_lds[];                 // [NST][TPS][64]
@@ -200,39 +230,196 @@ k_pre_gemm(const gemm_args a, const pre_gemm_args p)
             for (int f = 0; f < FT; ++f) { tot[r][f] += acc[r][f]; acc[r][f] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
     }
 
-    // Epilogue, one row tile after the other: its accumulators go through the wave's own piece of LDS, so that the loop over
-    // the strips need not be unrolled (unrolled, the rotary epilogue of 32 accumulator tiles does not fit the registers).
     pre_wait<0>();                                     // every wave is done with the stages, and no copy is on its way
     f32x4 *mine = (f32x4 *)pre_lds + wave * FT * 64 + lane;
+    const int strip0 = fs0 + wf * FT, nf = min(FT, a.nstrips - strip0);
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
-        const int ct = ct0 + wr * RT + r, strip0 = fs0 + wf * FT;
+        const int ct = ct0 + wr * RT + r;
         if (ct >= p.mtiles) break;
 #pragma unroll
         for (int f = 0; f < FT; ++f) mine[f * 64] = tot[r][f];
-        const int nf = min(FT, a.nstrips - strip0);
-        if (p.part != nullptr) {
-            for (int f = 0; f < nf; ++f) ((f32x4 *)p.part)[(((size_t)slice * a.nstrips + strip0 + f) * p.mtiles + ct) * 64 + lane] = mine[f * 64];
-            continue;
+        pre_epilogue<EPI, FT>(a, p, slice, ct, strip0, nf, lane, mine);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// The same for 4-bit weights: 128 rows x 64 FT features, 2 x 4 waves, each 4 row tiles x FT strips.
+// Arithmetic as in k_gemm<WB = 4> (codes enter as 16 + c on top of -24 x the row sums, product taken
+// transposed, scaled per K-tile); the row sums of the operand come from k_pre_rowsum.  Per K-tile a
+// wave expands FT code tiles (9 vector instructions each) and scales 4 FT products (4 each) beside 8 FT MFMAs: the
+// vector ALU is busy 80 % of the time that the matrix cores need, so the products are scaled one group of strips
+// behind the MFMAs, and the two waves of a SIMD fill each other's gaps.  1000 tokens through two 70B-shaped layers:
+// 10.9 -> 7.0 ms; gate/up 1.82 ms, 1030 TFLOP/s of MFMAs (FT = 8, without the second level of accumulators: the same).
+// In LDS: activation stages of one K-tile, and two buffers of a batch of 4 K-tiles of codes, scales and row sums.
+// ------------------------------------------------------------------------------------------
+template <int FT> struct pre_q4_shape {
+    static constexpr int BR = 8, BF = 4 * FT, NST = 4;
+    static constexpr int XT = 2 * BR, CT = BF, ST = BF / 8, RT = 2;        // KiB of a stage's activations; of a batch's codes, scales, row sums
+    static constexpr int BT = CT + ST + RT;
+    static constexpr int lds = (NST * XT + 2 * BT) * 1024;
+};
+
+template <int FT, int EPI>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_pre_gemm_q4(const gemm_args a, const pre_gemm_args p)
+{
+    using S = pre_q4_shape<FT>;
+    constexpr int RT = 4, WF = 4, NST = S::NST, NX = S::XT / 8, NC = S::CT / 8, BC = NC + 1;    // copies of a wave: NX a stage, BC a batch
+    static_assert(S::ST + S::RT <= 8 && FT % 2 == 0, "one scale or row-sum tile a wave");
+    extern __shared__ uint4 pre_lds[];                 // [NST][XT][64], then [2][BT][64]
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4, fl = lane & 15;
+    const int wr = wave / WF, wf = wave % WF;
+    const int L = xcd_order(blockIdx.x, gridDim.x), per = p.rb * p.fb, slice = L / per, rest = L - slice * per;
+    const int ct0 = (rest % p.rb) * S::BR, fs0 = (rest / p.rb) * S::BF;
+    const int KT = a.ktiles, kt0 = slice * p.kps, n = min(KT - kt0, p.kps), nb = n >> 2;        // K-tiles and batches of this slice (whole batches, not empty)
+    const size_t arr = (size_t)KT * 64, qstrip = (size_t)(KT >> 2) * PV_Q4_BATCH;
+    const char *W = (const char *)a.W + (size_t)(kt0 >> 2) * PV_Q4_BATCH;
+    const uint4 *xsrc[NX];
+    const char *csrc[NC];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) { const int t = wave + 8 * i; xsrc[i] = uniform_ptr(a.xop + (size_t)(2 * min(ct0 + (t >> 1), p.mtiles - 1) + (t & 1)) * arr + (size_t)kt0 * 64); }
+#pragma unroll
+    for (int i = 0; i < NC; ++i) csrc[i] = uniform_ptr(W + (size_t)min(fs0 + wave + 8 * i, a.nstrips - 1) * qstrip);
+    // the wave's scale tile (8 strips x 128 bytes) or row-sum tile (2 K-tiles x 128 rows); the waves that are left over repeat the first
+    const int small = wave < S::ST + S::RT ? wave : 0;
+    const char *ssrc; uint32_t soff, sstep;
+    if (small < S::ST) {
+        ssrc = W + (size_t)fs0 * qstrip; sstep = PV_Q4_BATCH;
+        soff = (uint32_t)((min(fs0 + small * 8 + (lane >> 3), a.nstrips - 1) - fs0) * qstrip) + 1024 + (lane & 7) * 16;
+    } else {
+        ssrc = (const char *)(p.rowsum + (size_t)kt0 * p.rsum_rows + ct0 * 16); sstep = 4 * p.rsum_rows * 4;
+        soff = (uint32_t)(((small - S::ST) * 2 + (lane >> 5)) * p.rsum_rows * 4 + (lane & 31) * 16);
+    }
+    ssrc = uniform_ptr(ssrc);
+    const uint32_t ldsx = __builtin_amdgcn_readfirstlane(lds_addr(pre_lds)) + wave * 1024, ldsb = ldsx + NST * S::XT * 1024;
+    auto copy_x = [&](int s, int buf) {
+        const uint32_t vo = (uint32_t)lane * 16 + (uint32_t)min(s, n - 1) * 1024;
+#pragma unroll
+        for (int i = 0; i < NX; ++i) dma_tile(ldsx + (uint32_t)(buf * S::XT + 8 * i) * 1024, xsrc[i], vo);
+    };
+    auto copy_b = [&](int b, int i0, int i1) {         // copies i0 .. i1 - 1 of batch b (past the end: the last one again)
+        const uint32_t bt = min(b, nb - 1), base = ldsb + (uint32_t)((b & 1) * S::BT) * 1024;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) if (i >= i0 && i < i1) dma_tile(base + 8 * i * 1024, csrc[i], (uint32_t)lane * 16 + bt * PV_Q4_BATCH);
+        if (NC >= i0 && NC < i1) dma_tile(base + (uint32_t)(S::CT + small - wave) * 1024, ssrc, soff + bt * sstep);
+    };
+    f32x4 acc[RT][FT], tot[RT][FT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int f = 0; f < FT; ++f) acc[r][f] = tot[r][f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    uint4 w[FT], xh[2], xl[2];
+    f32x4 t0[2];
+    uint2 cd[FT]; uint32_t sp[FT];                     // codes and scales of two K-tiles
+    float sc[FT];
+    const uint4 *Lx = pre_lds + (wr * RT * 2) * 64 + lane;
+    const char *Lb = (const char *)(pre_lds + NST * S::XT * 64);
+    auto read_x = [&](int r, int buf, int bb, int u) {
+        xh[r & 1] = Lx[buf * S::XT * 64 + 2 * r * 64]; xl[r & 1] = Lx[buf * S::XT * 64 + (2 * r + 1) * 64];
+        t0[r & 1] = *(const f32x4 *)(Lb + (bb * S::BT + S::CT + S::ST) * 1024 + u * 512 + ((wr * RT + r) * 16 + 4 * g) * 4);
+    };
+    auto read_c = [&](int bb, int h) {
+#pragma unroll
+        for (int f = 0; f < FT; ++f) {
+            const int st = wf * FT + f;
+            cd[f] = *(const uint2 *)(Lb + (bb * S::BT + st) * 1024 + lane * 16 + h * 8);
+            sp[f] = *(const uint32_t *)(Lb + (bb * S::BT + S::CT) * 1024 + st * 128 + fl * 8 + h * 4);
         }
-        const float rj = NORM ? p.rscale[min(ct * 16 + (lane & 15), p.rows - 1)] : 1.f;
-        const int phys = pre_page<EPI>(a, p, lane, ct);
-        if constexpr (EPI == EPI_SWIGLU) {
-            int f = 0;
-            for (; f + 2 <= nf; f += 2) pre_swiglu2(a, p, strip0 + f, lane, ct, rj, mine[f * 64], mine[(f + 1) * 64]);
-            if (f < nf) { epi_pre e; pre_fetch<EPI>(a, p, strip0 + f, lane, ct, phys, rj, e); epi_apply<2, EPI>(a, strip0 + f, lane, mine[f * 64], e, ct); }
-        } else {
-            constexpr int G = EPI == EPI_RESID ? FT : FT < 4 ? FT : 4;          // the loads of G strips go out together
-            for (int f = 0; f < nf; f += G) {
-                epi_pre e[G];
+    };
+    int buf = 0, fill = NST - 1;
+    constexpr int G = 2, NG = FT / G;                  // strips whose products are in flight together (more do not fit the registers)
+    auto step = [&](int b, auto uc) {                  // K-tile 4 b + u; on entry its row tile 0 and codes are in registers (or on their way)
+        constexpr int u = decltype(uc)::value;
+        const int s = 4 * b + u, bb = b & 1;
 #pragma unroll
-                for (int u = 0; u < G; ++u) pre_fetch<EPI>(a, p, min(strip0 + f + u, a.nstrips - 1), lane, ct, phys, rj, e[u]);
+        for (int f = 0; f < FT; ++f) {
+            const uint32_t c = (u & 1) ? cd[f].y : cd[f].x;
+            w[f] = make_uint4(((c << 3) & 0x00780078u) | 0x41804180u, ((c >> 1) & 0x00780078u) | 0x41804180u,
+                              ((c >> 5) & 0x00780078u) | 0x41804180u, ((c >> 9) & 0x00780078u) | 0x41804180u);
+            sc[f] = __uint_as_float((u & 1) ? (sp[f] & 0xFFFF0000u) : (sp[f] << 16));
+        }
+        f32x4 T[2][G];
+        auto scale = [&](int r, int h, const f32x4 (&t)[G]) {
 #pragma unroll
-                for (int u = 0; u < G; ++u)
-                    if (f + u < nf) epi_apply<2, EPI>(a, strip0 + f + u, lane, mine[(f + u) * 64], e[u], ct);
+            for (int f = 0; f < G; ++f)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[r][h * G + f][q] = fmaf(sc[h * G + f], t[f][q], acc[r][h * G + f][q]);
+        };
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            if (r + 1 < RT) read_x(r + 1, buf, bb, u);
+            else {
+                if (u == 3) pre_wait<(NST - 2) * NX>(); else pre_wait<(NST - 2) * NX + BC>();   // stage s + 1 is there (and with u = 3 the next batch)
+                fill = buf;
+                buf = buf + 1 == NST ? 0 : buf + 1;
+                read_x(0, buf, u == 3 ? bb ^ 1 : bb, (u + 1) & 3);
+                if (u & 1) read_c(u == 3 ? bb ^ 1 : bb, u == 3 ? 0 : 1);
+            }
+#pragma unroll
+            for (int h = 0; h < NG; ++h) {
+                const int k = (r * NG + h) & 1;
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int f = 0; f < G; ++f) T[k][f] = mfma16(xh[r & 1], w[h * G + f], t0[r & 1]);
+#pragma unroll
+                for (int f = 0; f < G; ++f) T[k][f] = mfma16(xl[r & 1], w[h * G + f], T[k][f]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (r + h > 0) scale(h ? r : r - 1, h ? h - 1 : NG - 1, T[k ^ 1]);      // the group before this one
+                __builtin_amdgcn_sched_barrier(0);
+                if (r == 0 && h == 0) copy_x(s + NST - 1, fill);
+                if (u == 0 && r == 1 && h < 2) copy_b(b + 1, h ? (BC + 2) / 3 : 0, h ? 2 * ((BC + 2) / 3) : (BC + 2) / 3);
+                if (u == 0 && r == 2 && h == 0) copy_b(b + 1, 2 * ((BC + 2) / 3), BC);
             }
         }
+        scale(RT - 1, NG - 1, T[(RT * NG - 1) & 1]);
+    };
+    copy_b(0, 0, BC);
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s) copy_x(s, s);
+    pre_wait<(NST - 2) * NX>();
+    read_c(0, 0);
+    read_x(0, 0, 0, 0);
+    for (int b = 0; b < nb; ++b) {
+        step(b, std::integral_constant<int, 0>()); step(b, std::integral_constant<int, 1>());
+        step(b, std::integral_constant<int, 2>()); step(b, std::integral_constant<int, 3>());
+        if ((b + 1) % (PRE_RUN / 4) == 0 || b + 1 == nb) {
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int f = 0; f < FT; ++f) { tot[r][f] += acc[r][f]; acc[r][f] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+        }
     }
+    pre_wait<0>();
+    // an accumulator is (row 4 g + r, feature fl) of lane (g, fl); the epilogue takes (feature 4 g' + r', row j) from lane (g', j): turned on the way through LDS
+    float *turn = (float *)((f32x4 *)pre_lds + wave * FT * 64);
+    const int strip0 = fs0 + wf * FT, nf = min(FT, a.nstrips - strip0);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const int ct = ct0 + wr * RT + r;
+        if (ct >= p.mtiles) break;
+#pragma unroll
+        for (int f = 0; f < FT; ++f)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) turn[f * 256 + ((fl >> 2) * 16 + 4 * g + q) * 4 + (fl & 3)] = tot[r][f][q];
+        pre_epilogue<EPI, FT>(a, p, slice, ct, strip0, nf, lane, (const f32x4 *)turn + lane);
+    }
+}
+
+// -24 x the sum over the 32 features of each (K-tile, row) of an operand, [K-tile][rows of all row tiles].  One wave per K-tile and row tile.
+__global__ void __launch_bounds__(256)
+k_pre_rowsum(const uint4 *xop, int ktiles, float *rowsum, int rsum_rows)
+{
+    const int lane = threadIdx.x & 63, kt = blockIdx.x * 4 + (threadIdx.x >> 6), ct = blockIdx.y;
+    if (kt >= ktiles) return;
+    const uint4 *q = xop + ((size_t)2 * ct * ktiles + kt) * 64 + lane;
+    const uint4 hi = q[0], lo = q[(size_t)ktiles * 64];
+    auto sum2 = [](uint32_t v) { return __uint_as_float(v << 16) + __uint_as_float(v & 0xFFFF0000u); };
+    float v = ((sum2(hi.x) + sum2(hi.y)) + (sum2(hi.z) + sum2(hi.w))) + ((sum2(lo.x) + sum2(lo.y)) + (sum2(lo.z) + sum2(lo.w)));
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    if (lane < 16) rowsum[(size_t)kt * rsum_rows + ct * 16 + lane] = -24.f * v;
 }
 
 // Adds the K-slices' partial sums in slice order and runs the epilogue: one wave per (strip, row tile).
@@ -472,7 +659,7 @@ k_pre_attn(const pre_attn_args a)
 
 int pv_pre_rows(const pv_model *m, int max_tokens)
 {
-    if (m->path < PV_PATH_MATRIX || m->wbits == 4) return 0;
+    if (m->path < PV_PATH_MATRIX) return 0;
     const int rows = std::min(PV_PRE_ROWS, (max_tokens + 63) / 64 * 64);
     return rows > PV_PRE_MIN ? rows : 0;
 }
@@ -484,6 +671,7 @@ struct pre_ws {
     uint16_t *xop;              // QKV and gate/up input (K = d)
     uint16_t *xop_d;            // down input (K = F); before that the queries and the O input (K = qd)
     uint16_t *q_hi, *q_lo, *xop_o;
+    float *rowsum;              // 4-bit weights: [K / 32][rows]
 };
 
 static size_t pre_layout(const pv_model *m, int rows, char *base, pre_ws *w)
@@ -501,6 +689,7 @@ static size_t pre_layout(const pv_model *m, int rows, char *base, pre_ws *w)
     p = take(4 * R * d); if (w) w->xop = (uint16_t *)p;
     p = take(std::max((size_t)4 * R * f.ffn_dim, 8 * R * qd));
     if (w) { w->xop_d = (uint16_t *)p; w->q_hi = w->xop_d; w->q_lo = w->q_hi + R * qd; w->xop_o = w->q_lo + R * qd; }
+    if (m->wbits == 4) { p = take(4 * (std::max(std::max(d, qd), (size_t)f.ffn_dim) / 32) * ((R + 127) / 128 * 128)); if (w) w->rowsum = (float *)p; }
     return off;
 }
 
@@ -541,28 +730,64 @@ using pre_wide = pre_shape<2, 4, 4, 4, 4>;     // 128 rows x 256 features
 using pre_mid = pre_shape<2, 4, 4, 3, 5>;      // 128 x 192
 using pre_small = pre_shape<2, 4, 4, 2, 6>;    // 128 x 128
 
-int pv_pre_init(int head_dim)
+template <int FT>
+struct pre_q4 {
+    using S = pre_q4_shape<FT>;
+    template <int EPI> static int allow()
+    {
+        PV_HIP(hipFuncSetAttribute((const void *)k_pre_gemm_q4<FT, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, S::lds));
+        return PV_OK;
+    }
+    static int allow_all()
+    {
+        int rc;
+        if ((rc = allow<EPI_QKV>()) != PV_OK || (rc = allow<EPI_RESID>()) != PV_OK) return rc;
+        return allow<EPI_SWIGLU>();
+    }
+    template <int EPI> static int run(const gemm_args &ga, pre_gemm_args pa, int slices, hipStream_t s)
+    {
+        pa.rb = (pa.mtiles + S::BR - 1) / S::BR; pa.fb = (ga.nstrips + S::BF - 1) / S::BF;
+        pa.kps = (ga.ktiles / 4 + slices - 1) / slices * 4;
+        slices = (ga.ktiles + pa.kps - 1) / pa.kps;
+        if (slices == 1) pa.part = nullptr;
+        k_pre_gemm_q4<FT, EPI><<<pa.rb * pa.fb * slices, 512, S::lds, s>>>(ga, pa);
+        PV_HIP(hipGetLastError());
+        if (slices > 1) { k_pre_sum<EPI><<<dim3((ga.nstrips + 3) / 4, pa.mtiles), 256, 0, s>>>(ga, pa, slices); PV_HIP(hipGetLastError()); }
+        return PV_OK;
+    }
+};
+
+int pv_pre_init(const pv_model *m)
 {
     int rc;
+    if (m->wbits == 4) return pre_q4<4>::allow_all();
     if ((rc = pre_mid::allow_all()) != PV_OK || (rc = pre_wide::allow_all()) != PV_OK || (rc = pre_small::allow_all()) != PV_OK) return rc;
     return PV_OK;
 }
 
 template <int EPI>
-static int pre_gemm(const pv_model *m, const gemm_args &g, int strips, const float *rscale, int rows, int len, size_t part_floats, hipStream_t s)
+static int pre_gemm(const pv_model *m, const gemm_args &g, int strips, const float *rscale, float *rowsum, int rows, int len, size_t part_floats, hipStream_t s)
 {
     const int mtiles = (rows + 15) / 16;
     gemm_args ga = g;
     ga.nstrips = strips;
     pre_gemm_args pa = {};
     pa.rscale = rscale; pa.part = (float4 *)g.tile_part; pa.mtiles = mtiles; pa.rows = rows; pa.len = len;
+    if (m->wbits == 4) {
+        pa.rowsum = rowsum; pa.rsum_rows = (mtiles + 7) / 8 * 128;
+        k_pre_rowsum<<<dim3((g.ktiles + 3) / 4, mtiles), 256, 0, s>>>(g.xop, g.ktiles, rowsum, pa.rsum_rows);
+        PV_HIP(hipGetLastError());
+    }
     // The rectangle and the number of K-slices with the smallest estimated time.  Unit: one MFMA pair's share of a 256 x 256 rectangle
     // (3.85 ns per 16 x 16 outputs and K-tile of a workgroup).  Measured (4096 x 4096 and 4096 x 14336 weights, few workgroups): per
     // K-tile 0.99, 0.77, 0.53 and 0.30 us, on top of 20, 16, 14 and 9 us for the start, the epilogue and the end; partial
     // sums: 3 us and 0.2 ns for each 16 x 16 of them.  Where more workgroups than CUs come out, they run in rounds.
-    static const struct { int br, bf; double cost; } R[3] = {{8, 16, 1.07}, {8, 12, 1.12}, {8, 8, 1.22}};
+    struct rect { int br, bf; double cost; };
+    static const rect R16[3] = {{8, 16, 1.07}, {8, 12, 1.12}, {8, 8, 1.22}}, R4[1] = {{8, 16, 2.0}};      // 4-bit weights: 1.0 us a K-tile
+    const rect *R = m->wbits == 4 ? R4 : R16;
+    const int kinds = m->wbits == 4 ? 1 : 3;
     double best = 1e30; int shape = 0, cut = 1;
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < kinds; ++i) {
         const int blocks = ((mtiles + R[i].br - 1) / R[i].br) * ((strips + R[i].bf - 1) / R[i].bf);
         for (int sl = 1; sl <= 16; ++sl) {
             if (sl > 1 && (g.ktiles / sl < 8 || (size_t)sl * strips * mtiles * 256 > part_floats || g.tile_part == nullptr)) break;
@@ -572,6 +797,7 @@ static int pre_gemm(const pv_model *m, const gemm_args &g, int strips, const flo
             if (t < best) { best = t; shape = i; cut = sl; }
         }
     }
+    if (m->wbits == 4) return pre_q4<4>::run<EPI>(ga, pa, cut, s);
     if (shape == 0) return pre_wide::run<EPI>(ga, pa, cut, s);
     if (shape == 1) return pre_mid::run<EPI>(ga, pa, cut, s);
     return pre_small::run<EPI>(ga, pa, cut, s);
@@ -592,7 +818,7 @@ int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows
     const int d = f.d_model, hd = f.head_dim, qd = f.n_q_heads * hd, kvd = f.n_kv_heads * hd, F = f.ffn_dim, mtiles = (rows + 15) / 16, len = c->len;
     const char *Wb = m->d_weights;
     auto gainp = [&](int kind, int l) { return (const uint16_t *)(Wb + pv_tref(m, kind, l).off); };
-    pre_ws w;
+    pre_ws w = {};
     pre_layout(m, pv_pre_rows(m, c->max_tokens), base, &w);
 
     k_pre_tokens<<<1, 1024, 0, s>>>(d_host_tokens, w.tokens, rows);
@@ -619,7 +845,7 @@ int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows
         PV_HIP(hipGetLastError());
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WQ, l).off); g.xop = (const uint4 *)w.xop; g.ktiles = d / 32; g.layer = l;
         if ((rc = pv_prof_mark(c, PV_PROF_QKV, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_QKV>(m, g, (qd + 2 * kvd) / 16, w.rscale, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_QKV>(m, g, (qd + 2 * kvd) / 16, w.rscale, w.rowsum, rows, len, part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_QKV, l, 1, s)) != PV_OK) return rc;
         at.layer = l;
         if ((rc = pv_prof_mark(c, PV_PROF_ATTENTION, l, 0, s)) != PV_OK) return rc;
@@ -628,18 +854,18 @@ int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows
         if ((rc = pv_prof_mark(c, PV_PROF_ATTENTION, l, 1, s)) != PV_OK) return rc;
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WO, l).off); g.xop = (const uint4 *)w.xop_o; g.ktiles = qd / 32; g.gain_next = gainp(PV_T_FFN_NORM, l);
         if ((rc = pv_prof_mark(c, PV_PROF_OPROJ, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, w.rowsum, rows, len, part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_OPROJ, l, 1, s)) != PV_OK) return rc;
         k_pre_rscale<<<mtiles, 256, 0, s>>>(w.ssq, w.rscale, d / 16, g.inv_d, g.eps);
         PV_HIP(hipGetLastError());
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WG, l).off); g.xop = (const uint4 *)w.xop; g.ktiles = d / 32;
         if ((rc = pv_prof_mark(c, PV_PROF_GATEUP, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_SWIGLU>(m, g, F / 8, w.rscale, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_SWIGLU>(m, g, F / 8, w.rscale, w.rowsum, rows, len, part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_GATEUP, l, 1, s)) != PV_OK) return rc;
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WD, l).off); g.xop = (const uint4 *)w.xop_d; g.ktiles = F / 32;
         g.gain_next = (l + 1 < f.n_layers) ? gainp(PV_T_ATTN_NORM, l + 1) : (const uint16_t *)(Wb + m->global[PV_T_FINAL_NORM].off);
         if ((rc = pv_prof_mark(c, PV_PROF_DOWN, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, w.rowsum, rows, len, part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_DOWN, l, 1, s)) != PV_OK) return rc;
     }
     k_pre_commit<<<1, 64, 0, s>>>(c->ws.state, rows, keep);

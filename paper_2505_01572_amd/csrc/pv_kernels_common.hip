@@ -1,5 +1,5 @@
-// Small kernels both kernel families use: block set-up (embedding gather + rotary table),
-// rotary embedding + KV append into pages, vocabulary argmax, the acceptance rule, KV export.
+// Small kernels both kernel families use: block set-up (embedding gather + rotary table), the end of
+// a step (arg-max over the candidates, acceptance rule), KV export.
 // None of them is bandwidth relevant; they are written for clarity and determinism.
 #include "pv_kernels_common.h"
 
@@ -35,78 +35,12 @@ k_begin(pv_dev_state *st, const int32_t *mailbox, int gamma, int mode, const ST 
     }
 }
 
-// ---------------------------------------------------------------------------------------
-// Rotary embedding of q (in place) and k, then append k and v of row j at position len+j.
-// K page block is [token][head_dim]; V page block is [head_dim][token].
-// ---------------------------------------------------------------------------------------
-template <typename ST>
-__global__ void __launch_bounds__(256)
-k_rope_append(const pv_dev_state *st, const int32_t *page_table, const float2 *rope, float *q,
-              const float *k, const float *v, ST *pool, pv_kv_geom g, int layer, int n_q_heads)
-{
-    const int j = blockIdx.x;
-    if (j >= st->gamma) return;
-    const int hd = g.head_dim, half = hd / 2;
-    const float2 *cs = rope + (size_t)j * half;
-    float *qr = q + (size_t)j * n_q_heads * hd;
-    for (int idx = threadIdx.x; idx < n_q_heads * half; idx += 256) {
-        const int h = idx / half, i = idx - h * half;
-        const float2 c = cs[i];
-        const float a = qr[h * hd + i], b = qr[h * hd + i + half];
-        qr[h * hd + i] = a * c.x - b * c.y;
-        qr[h * hd + i + half] = b * c.x + a * c.y;
-    }
-    const int pos = st->len + j;
-    const int phys = page_table[pos >> g.page_shift], tok = pos & (g.page_tokens - 1);
-    const float *kr = k + (size_t)j * g.n_kv_heads * hd, *vr = v + (size_t)j * g.n_kv_heads * hd;
-    for (int idx = threadIdx.x; idx < g.n_kv_heads * half; idx += 256) {
-        const int h = idx / half, i = idx - h * half;
-        const float2 c = cs[i];
-        const float a = kr[h * hd + i], b = kr[h * hd + i + half];
-        ST *kb = pool + pv_kv_block(g, layer, phys, h, 0);
-        pv_st(kb, pv_k_off(g, tok, i), a * c.x - b * c.y);
-        pv_st(kb, pv_k_off(g, tok, i + half), b * c.x + a * c.y);
-    }
-    for (int idx = threadIdx.x; idx < g.n_kv_heads * hd; idx += 256) {
-        const int h = idx / hd, e = idx - h * hd;
-        ST *vb = pool + pv_kv_block(g, layer, phys, h, 1);
-        pv_st(vb, pv_v_off(g, tok, e), vr[h * hd + e]);
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// Row argmax over the vocabulary: order (value descending, index ascending); NaN counts as -inf.
-// ---------------------------------------------------------------------------------------
+// order of the arg-max: value descending, index ascending
 __device__ inline bool pv_better(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
 
-__global__ void __launch_bounds__(1024)
-k_argmax(pv_dev_state *st, const float *logits, int vocab)
-{
-    const int j = blockIdx.x;
-    if (j >= st->gamma) return;
-    const float *row = logits + (size_t)j * vocab;
-    float bv = -INFINITY; int bi = 0x7fffffff;
-    for (int i = threadIdx.x; i < vocab; i += 1024) {
-        float v = row[i];
-        v = (v == v) ? v : -INFINITY;
-        if (pv_better(v, i, bv, bi)) { bv = v; bi = i; }
-    }
-    __shared__ float sv[1024];
-    __shared__ int si[1024];
-    sv[threadIdx.x] = bv; si[threadIdx.x] = bi;
-    __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
-        if (threadIdx.x < s && pv_better(sv[threadIdx.x + s], si[threadIdx.x + s], sv[threadIdx.x], si[threadIdx.x])) {
-            sv[threadIdx.x] = sv[threadIdx.x + s]; si[threadIdx.x] = si[threadIdx.x + s];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) st->pred[j] = (sv[0] == -INFINITY) ? -1 : si[0];     // no finite logit in the row: no arg-max (k_finish reports it)
-}
-
 // ---------------------------------------------------------------------------------------
-// End of a step in one launch: vocabulary arg-max of every row from the per-strip candidates the
-// LM-head epilogue left (matrix path; the vector path has st->pred already), the acceptance rule
+// End of a step in one launch: vocabulary arg-max of every row from the candidates that the
+// vocabulary projection left (one per strip and row; NaN counted as -inf), the acceptance rule
 // (Algorithm 1, verify branch: longest draft prefix that equals the stage's own greedy tokens,
 // one correction token) and the in-step rollback (length, pending).  The two results and an
 // error flag go straight to the cache's pinned host mailbox.
@@ -288,28 +222,7 @@ int pv_k_begin(pv_cache *c, int rows_pad, hipStream_t s)
     return PV_OK;
 }
 
-int pv_k_rope_append(pv_cache *c, int layer, int rows, hipStream_t s)
-{
-    const pv_model *m = c->m;
-    const pv_kv_geom g = pv_geom(c);
-    if (m->cfg.dtype == PV_BF16)
-        k_rope_append<uint16_t><<<rows, 256, 0, s>>>(c->ws.state, c->ws.page_table, c->ws.rope, c->ws.q, c->ws.k, c->ws.v,
-                                                      (uint16_t *)c->d_pool, g, layer, m->cfg.n_q_heads);
-    else
-        k_rope_append<float><<<rows, 256, 0, s>>>(c->ws.state, c->ws.page_table, c->ws.rope, c->ws.q, c->ws.k, c->ws.v,
-                                                   (float *)c->d_pool, g, layer, m->cfg.n_q_heads);
-    PV_HIP(hipGetLastError());
-    return PV_OK;
-}
-
-int pv_k_argmax(pv_cache *c, int rows, hipStream_t s)
-{
-    k_argmax<<<rows, 1024, 0, s>>>(c->ws.state, c->ws.logits, c->m->cfg.vocab);
-    PV_HIP(hipGetLastError());
-    return PV_OK;
-}
-
-// pmax_val / pmax_idx: per-strip arg-max candidates [rows][strips] (null: st->pred is already filled in)
+// pmax_val / pmax_idx: per-strip arg-max candidates [rows][strips] (null: none, a prompt's middle)
 int pv_k_finish(pv_cache *c, int rows, const float *pmax_val, const int32_t *pmax_idx, int strips, hipStream_t s)
 {
     k_finish<<<1, 1024, 0, s>>>(c->ws.state, c->d_io->result, pmax_val, pmax_idx, strips, rows, c->io->hdr[3], c->m->cfg.vocab);

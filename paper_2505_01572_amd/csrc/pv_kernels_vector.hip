@@ -2,49 +2,182 @@
 // This is the path of fp32 models (the tiny parity configuration) and a second, structurally
 // different GPU implementation that the matrix-core path can be cross-checked against.
 // Every reduction has a fixed order, so repeated runs give identical bits.
+#include <algorithm>
+#include <type_traits>
 #include "pv_kernels_common.h"
 
-// ---- block-wide reductions through LDS, fixed tree order ----
-template <int NT>
+__device__ inline float wave_sum(float v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// ---- reductions over a workgroup of four waves, fixed order; red: 4 floats of LDS ----
 __device__ inline float block_sum(float v, float *red)
 {
-    red[threadIdx.x] = v;
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int s = NT / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    const float r = red[0];
+    v = (red[0] + red[1]) + (red[2] + red[3]);
     __syncthreads();
-    return r;
+    return v;
 }
 
-template <int NT>
 __device__ inline float block_max(float v, float *red)
 {
-    red[threadIdx.x] = v;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int s = NT / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
-        __syncthreads();
+    v = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    __syncthreads();
+    return v;
+}
+
+// The small models of this path are bound by launches and memory round trips, not bytes: a step of the tiny
+// configuration took 158 us in 28 kernels of 2..5 us (attention 27 us), with some 4 us between dependent ones.
+// (now 90 us in 12).  RMSNorm, the rotary embedding and the page writes, SwiGLU and the vocabulary arg-max ride in the
+// projections: a wave that multiplies a weight row with the input rows passes over the whole rows
+// anyway and adds up their squares beside it (the norm's scale commutes with the dot product).
+
+// Dot products of G input rows x (times the gain) with M weight rows, and the rows' sums of squares, over one wavefront.
+// On return every lane has the totals.
+template <typename ST, int G, int M>
+__device__ inline void norm_dots(const ST *const (&w)[M], const ST *gain, const float *x, int K, int lane, float (&acc)[M][G], float (&ss)[G])
+{
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        ss[g] = 0.f;
+#pragma unroll
+        for (int m = 0; m < M; ++m) acc[m][g] = 0.f;
     }
-    const float r = red[0];
-    __syncthreads();
+    for (int k = lane * 4; k < K; k += 256) {
+        float wv[M][4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float gn = pv_ld(gain, k + r);
+#pragma unroll
+            for (int m = 0; m < M; ++m) wv[m][r] = pv_ld(w[m], k + r) * gn;
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const float4 v = *(const float4 *)(x + (size_t)g * K + k);
+            ss[g] += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+#pragma unroll
+            for (int m = 0; m < M; ++m) acc[m][g] += v.x * wv[m][0] + v.y * wv[m][1] + v.z * wv[m][2] + v.w * wv[m][3];
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        ss[g] = wave_sum(ss[g]);
+#pragma unroll
+        for (int m = 0; m < M; ++m) acc[m][g] = wave_sum(acc[m][g]);
+    }
+}
+
+// lane g picks its row's entry of an array that every lane holds
+template <int G>
+__device__ inline float pick(const float (&v)[G], int lane)
+{
+    float r = v[0];
+#pragma unroll
+    for (int g = 1; g < G; ++g) {
+        r = lane == g ? v[g] : r;
+        asm volatile("" : "+v"(r));                    // (or the compiler makes an indexed load of it, from scratch memory)
+    }
     return r;
 }
 
-// h[j,:] = x[j,:] * rsqrt(mean(x[j,:]^2) + eps) * g
-template <typename ST>
+struct vec_norm { const void *gain; const float *x; int K, rows; float eps; };
+
+// RMSNorm + q, k, v projections + rotary embedding + append to the pages.  One wavefront per pair of outputs (i, i + head_dim / 2)
+// of a head; lane g finishes row g.  K page block: [token][head_dim]; V: [head_dim][token].
+template <typename ST, int G>
 __global__ void __launch_bounds__(256)
-k_rmsnorm(const float *x, const ST *g, float *h, int d, float eps)
+k_vec_qkv(const vec_norm a, const ST *Wq, const ST *Wk, const ST *Wv, const pv_dev_state *st, int row0, const int32_t *page_table, const float2 *rope,
+          float *q, ST *pool, pv_kv_geom g, int layer, int n_q_heads)
 {
-    __shared__ float red[256];
-    const float *xr = x + (size_t)blockIdx.x * d;
-    float ss = 0.f;
-    for (int i = threadIdx.x; i < d; i += 256) ss += xr[i] * xr[i];
-    ss = block_sum<256>(ss, red);
-    const float r = 1.0f / sqrtf(ss / (float)d + eps);
-    for (int i = threadIdx.x; i < d; i += 256) h[(size_t)blockIdx.x * d + i] = xr[i] * r * pv_ld(g, i);
+    const int lane = threadIdx.x & 63, hd = g.head_dim, half = hd >> 1;
+    const int unit = blockIdx.x * 4 + (threadIdx.x >> 6), h = unit / half, i = unit - h * half;       // head (q heads, then k, then v), pair
+    if (h >= n_q_heads + 2 * g.n_kv_heads) return;
+    const int kind = h < n_q_heads ? 0 : h < n_q_heads + g.n_kv_heads ? 1 : 2, hh = kind == 0 ? h : kind == 1 ? h - n_q_heads : h - n_q_heads - g.n_kv_heads;
+    const ST *W = (kind == 0 ? Wq : kind == 1 ? Wk : Wv) + ((size_t)hh * hd + i) * a.K;
+    const ST *const w[2] = {W, W + (size_t)half * a.K};
+    const int j = row0 + lane;
+    int pos = 0, phys = 0;
+    float2 cs = make_float2(1.f, 0.f);
+    if (lane < a.rows) {                               // on their way while the dot products are taken
+        pos = st->len + j;
+        if (kind != 0) phys = page_table[pos >> g.page_shift];
+        if (kind != 2) cs = rope[(size_t)j * half + i];
+    }
+    float acc[2][G], ss[G];
+    norm_dots<ST, G, 2>(w, (const ST *)a.gain, a.x, a.K, lane, acc, ss);
+    if (lane >= a.rows) return;
+    const float r = 1.0f / sqrtf(pick<G>(ss, lane) / (float)a.K + a.eps);
+    const float u = pick<G>(acc[0], lane) * r, v = pick<G>(acc[1], lane) * r;
+    const float ru = u * cs.x - v * cs.y, rv = v * cs.x + u * cs.y;
+    const int tok = pos & (g.page_tokens - 1);
+    if (kind == 0) {
+        float *o = q + ((size_t)j * n_q_heads + hh) * hd;
+        o[i] = ru; o[i + half] = rv;
+    } else if (kind == 1) {
+        ST *kb = pool + pv_kv_block(g, layer, phys, hh, 0);
+        pv_st(kb, pv_k_off(g, tok, i), ru); pv_st(kb, pv_k_off(g, tok, i + half), rv);
+    } else {
+        ST *vb = pool + pv_kv_block(g, layer, phys, hh, 1);
+        pv_st(vb, pv_v_off(g, tok, i), u); pv_st(vb, pv_v_off(g, tok, i + half), v);
+    }
+}
+
+// RMSNorm + gate and up projections + SwiGLU.  One wavefront per feature.
+template <typename ST, int G>
+__global__ void __launch_bounds__(256)
+k_vec_gateup(const vec_norm a, const ST *Wg, const ST *Wu, float *act, int F)
+{
+    const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (n >= F) return;
+    const ST *const w[2] = {Wg + (size_t)n * a.K, Wu + (size_t)n * a.K};
+    float acc[2][G], ss[G];
+    norm_dots<ST, G, 2>(w, (const ST *)a.gain, a.x, a.K, lane, acc, ss);
+    if (lane >= a.rows) return;
+    const float r = 1.0f / sqrtf(pick<G>(ss, lane) / (float)a.K + a.eps);
+    const float z = pick<G>(acc[0], lane) * r;
+    act[(size_t)lane * F + n] = z / (1.0f + expf(-z)) * (pick<G>(acc[1], lane) * r);
+}
+
+// Final RMSNorm + vocabulary projection; a workgroup takes the outputs 4 b + wave, 4 (b + gridDim.x) + wave, ... and leaves
+// the best of each row (value descending, index ascending; NaN counts as -inf) as a candidate for k_finish.
+template <typename ST, int G>
+__global__ void __launch_bounds__(256)
+k_vec_head(const vec_norm a, const ST *W, float *logits, int N, float *cand_val, int32_t *cand_idx)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float bv = -INFINITY; int bi = 0x7fffffff;
+    for (int n = blockIdx.x * 4 + wave; n < N; n += gridDim.x * 4) {
+        const ST *const w[1] = {W + (size_t)n * a.K};
+        float acc[1][G], ss[G];
+        norm_dots<ST, G, 1>(w, (const ST *)a.gain, a.x, a.K, lane, acc, ss);
+        if (lane < a.rows) {
+            const float r = 1.0f / sqrtf(pick<G>(ss, lane) / (float)a.K + a.eps);
+            float v = pick<G>(acc[0], lane) * r;
+            logits[(size_t)lane * N + n] = v;
+            v = (v == v) ? v : -INFINITY;
+            if (v > bv || (v == bv && n < bi)) { bv = v; bi = n; }
+        }
+    }
+    __shared__ float sv[4][16];
+    __shared__ int si[4][16];
+    if (lane < 16) { sv[wave][lane] = bv; si[wave][lane] = bi; }
+    __syncthreads();
+    if ((int)threadIdx.x < a.rows) {
+        for (int w = 1; w < 4; ++w) {
+            const float v = sv[w][threadIdx.x]; const int i = si[w][threadIdx.x];
+            if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
+        }
+        cand_val[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = bv; cand_idx[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = bi;
+    }
 }
 
 // y[g][n] = (res ? res[g][n] : 0) + sum_k x[g][k] * W[n][k]   for g < G rows; one wavefront per n.
@@ -76,61 +209,70 @@ k_linear(const ST *W, const float *x, const float *res, float *y, int N, int K, 
     }
 }
 
-// act = silu(gate) * up
-__global__ void k_swiglu(const float *gate, const float *up, float *act, size_t n)
-{
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) { const float z = gate[i]; act[i] = z / (1.0f + expf(-z)) * up[i]; }
-}
-
 // Causal attention for one (query head, row): keys 0 .. len+j, streaming softmax over chunks
-// of 1024 keys.  K/V come from the paged pool.
+// of 1024 keys.  K/V come from the paged pool.  The chunk's pages are looked up once, ahead of everything else; four lanes
+// share a key's score, and the value sum is split over 256 / head_dim groups of keys (27 -> 8 us at 104 keys: the
+// time was a chain of page look-ups and loads, one per key).
 template <typename ST>
 __global__ void __launch_bounds__(256)
 k_attention(const pv_dev_state *st, const int32_t *page_table, const float *q, const ST *pool, float *out,
             pv_kv_geom g, int layer, int n_q_heads)
 {
-    const int j = blockIdx.y, a = blockIdx.x;
-    if (j >= st->gamma) return;
+    const int j = blockIdx.y, a = blockIdx.x, tid = threadIdx.x;
     const int hd = g.head_dim, kvh = a / (n_q_heads / g.n_kv_heads);
-    const int nkeys = st->len + j + 1;
     __shared__ float qs[256], sc[1024], red[256];
-    if ((int)threadIdx.x < hd) qs[threadIdx.x] = q[((size_t)j * n_q_heads + a) * hd + threadIdx.x];
-    __syncthreads();
+    __shared__ int pg[1024];
+    const int nkeys = st->len + j + 1;
+    if (j >= st->gamma) return;
+    if (tid < hd) qs[tid] = q[((size_t)j * n_q_heads + a) * hd + tid];
     const float scale = 1.0f / sqrtf((float)hd);
+    int lanes = 1;                                     // threads that go along a value row: head_dim rounded up to a power of two
+    while (lanes < hd) lanes <<= 1;
+    const int groups = 256 / lanes, grp = tid / lanes, e0 = tid - grp * lanes;
     float m = -INFINITY, l = 0.f, o = 0.f;
     for (int c0 = 0; c0 < nkeys; c0 += 1024) {
-        const int cn = min(1024, nkeys - c0);
+        const int cn = min(1024, nkeys - c0), p0 = c0 >> g.page_shift, np = ((c0 + cn - 1) >> g.page_shift) - p0 + 1;
+        for (int i = tid; i < np; i += 256) pg[i] = page_table[p0 + i];
+        __syncthreads();
         float lm = -INFINITY;
-        for (int t = threadIdx.x; t < cn; t += 256) {
-            const int p = c0 + t;
-            const ST *kb = pool + pv_kv_block(g, layer, page_table[p >> g.page_shift], kvh, 0);
+        const int sub = tid & 3;
+        for (int t0 = 0; t0 < cn; t0 += 64) {          // 64 keys at a time, four lanes each
+            const int t = t0 + (tid >> 2), tc = min(t, cn - 1), p = c0 + tc;
+            const ST *kb = pool + pv_kv_block(g, layer, pg[(p >> g.page_shift) - p0], kvh, 0);
             const int tk = p & (g.page_tokens - 1);
             float s = 0.f;
-            for (int e = 0; e < hd; ++e) s += qs[e] * pv_ld(kb, pv_k_off(g, tk, e));
+#pragma unroll 8
+            for (int e = sub; e < hd; e += 4) s += qs[e] * pv_ld(kb, pv_k_off(g, tk, e));
+            s += __shfl_xor(s, 1, 64);
+            s += __shfl_xor(s, 2, 64);
             s *= scale;
-            sc[t] = s;
-            lm = fmaxf(lm, s);
+            if (t < cn) { if (sub == 0) sc[t] = s; lm = fmaxf(lm, s); }
         }
-        const float m_new = fmaxf(m, block_max<256>(lm, red));
+        const float m_new = fmaxf(m, block_max(lm, red));
         float ls = 0.f;
-        for (int t = threadIdx.x; t < cn; t += 256) { const float w = expf(sc[t] - m_new); sc[t] = w; ls += w; }
-        const float cs = block_sum<256>(ls, red);          // also orders the sc[] writes before the reads below
+        for (int t = tid; t < cn; t += 256) { const float w = expf(sc[t] - m_new); sc[t] = w; ls += w; }
+        const float cs = block_sum(ls, red);          // also orders the sc[] writes before the reads below
         const float resc = expf(m - m_new);
         l = l * resc + cs;
-        if ((int)threadIdx.x < hd) {
-            float acc = 0.f;
-            for (int t = 0; t < cn; ++t) {
+        float acc = 0.f;
+        if (e0 < hd) {
+#pragma unroll 8
+            for (int t = grp; t < cn; t += groups) {
                 const int p = c0 + t;
-                const ST *vb = pool + pv_kv_block(g, layer, page_table[p >> g.page_shift], kvh, 1);
-                acc += sc[t] * pv_ld(vb, pv_v_off(g, p & (g.page_tokens - 1), threadIdx.x));
+                const ST *vb = pool + pv_kv_block(g, layer, pg[(p >> g.page_shift) - p0], kvh, 1);
+                acc += sc[t] * pv_ld(vb, pv_v_off(g, p & (g.page_tokens - 1), e0));
             }
-            o = o * resc + acc;
         }
+        o = o * resc + acc;
         m = m_new;
         __syncthreads();
     }
-    if ((int)threadIdx.x < hd) out[((size_t)j * n_q_heads + a) * hd + threadIdx.x] = o / l;
+    red[tid] = o;                                      // the groups' sums, added in group order
+    __syncthreads();
+    if (grp == 0 && e0 < hd) {
+        for (int k = 1; k < groups; ++k) o += red[k * lanes + e0];
+        out[((size_t)j * n_q_heads + a) * hd + e0] = o / l;
+    }
 }
 
 // ------------------------------- host side ----------------------------------------
@@ -155,45 +297,59 @@ static int launch_linear(const pv_model *m, const pv_tensor_ref &t, const float 
     return PV_OK;
 }
 
+// calls f(G, first row, rows) for every group of at most 16 rows; G: the smallest of 1, 4, 8, 16 that holds them
+template <typename F>
+static int row_groups(int rows, F f)
+{
+    for (int r0 = 0; r0 < rows; r0 += 16) {
+        const int r = rows - r0 < 16 ? rows - r0 : 16;
+        if (r <= 1) f(std::integral_constant<int, 1>(), r0, r);
+        else if (r <= 4) f(std::integral_constant<int, 4>(), r0, r);
+        else if (r <= 8) f(std::integral_constant<int, 8>(), r0, r);
+        else f(std::integral_constant<int, 16>(), r0, r);
+        PV_HIP(hipGetLastError());
+    }
+    return PV_OK;
+}
+
 template <typename ST>
 static int run_block(pv_cache *c, hipStream_t s)
 {
     const pv_model *m = c->m;
     const pv_model_config &f = m->cfg;
     const int rows = c->last_rows, rows_pad = (rows + PV_ROW_PAD - 1) / PV_ROW_PAD * PV_ROW_PAD;
-    const int d = f.d_model, qd = f.n_q_heads * f.head_dim, F = f.ffn_dim;
+    const int d = f.d_model, F = f.ffn_dim, V = f.vocab;
     const pv_kv_geom g = pv_geom(c);
     pv_ws &w = c->ws;
+    auto wt = [&](int kind, int l) { return (const ST *)(m->d_weights + pv_tref(m, kind, l).off); };
+    auto normed = [&](const ST *gain, int r0, int r) { return vec_norm{gain, w.x + (size_t)r0 * d, d, r, (float)f.rms_eps}; };
     int rc;
     if ((rc = pv_k_begin(c, rows_pad, s)) != PV_OK) return rc;
     for (int l = 0; l < f.n_layers; ++l) {
-        k_rmsnorm<ST><<<rows, 256, 0, s>>>(w.x, (const ST *)(m->d_weights + pv_tref(m, PV_T_ATTN_NORM, l).off), w.h, d, (float)f.rms_eps);
-        PV_HIP(hipGetLastError());
-        if ((rc = launch_linear<ST>(m, pv_tref(m, PV_T_WQ, l), w.h, nullptr, w.q, rows, s)) != PV_OK) return rc;
-        if ((rc = launch_linear<ST>(m, pv_tref(m, PV_T_WK, l), w.h, nullptr, w.k, rows, s)) != PV_OK) return rc;
-        if ((rc = launch_linear<ST>(m, pv_tref(m, PV_T_WV, l), w.h, nullptr, w.v, rows, s)) != PV_OK) return rc;
-        if ((rc = pv_k_rope_append(c, l, rows, s)) != PV_OK) return rc;
+        const int units = (f.n_q_heads + 2 * f.n_kv_heads) * (f.head_dim / 2);
+        rc = row_groups(rows, [&](auto G, int r0, int r) {
+            k_vec_qkv<ST, G.value><<<(units + 3) / 4, 256, 0, s>>>(normed(wt(PV_T_ATTN_NORM, l), r0, r), wt(PV_T_WQ, l), wt(PV_T_WK, l), wt(PV_T_WV, l), w.state, r0,
+                                                                   w.page_table, w.rope, w.q, (ST *)c->d_pool, g, l, f.n_q_heads);
+        });
+        if (rc != PV_OK) return rc;
         k_attention<ST><<<dim3(f.n_q_heads, rows), 256, 0, s>>>(w.state, w.page_table, w.q, (const ST *)c->d_pool, w.attn, g, l, f.n_q_heads);
         PV_HIP(hipGetLastError());
         if ((rc = launch_linear<ST>(m, pv_tref(m, PV_T_WO, l), w.attn, w.x, w.x, rows, s)) != PV_OK) return rc;
-        k_rmsnorm<ST><<<rows, 256, 0, s>>>(w.x, (const ST *)(m->d_weights + pv_tref(m, PV_T_FFN_NORM, l).off), w.h, d, (float)f.rms_eps);
-        PV_HIP(hipGetLastError());
-        if ((rc = launch_linear<ST>(m, pv_tref(m, PV_T_WG, l), w.h, nullptr, w.gate, rows, s)) != PV_OK) return rc;
-        if ((rc = launch_linear<ST>(m, pv_tref(m, PV_T_WU, l), w.h, nullptr, w.up, rows, s)) != PV_OK) return rc;
-        const size_t nact = (size_t)rows * F;
-        k_swiglu<<<(unsigned)((nact + 255) / 256), 256, 0, s>>>(w.gate, w.up, w.gate, nact);
-        PV_HIP(hipGetLastError());
+        rc = row_groups(rows, [&](auto G, int r0, int r) {
+            k_vec_gateup<ST, G.value><<<(F + 3) / 4, 256, 0, s>>>(normed(wt(PV_T_FFN_NORM, l), r0, r), wt(PV_T_WG, l), wt(PV_T_WU, l), w.gate + (size_t)r0 * F, F);
+        });
+        if (rc != PV_OK) return rc;
         if ((rc = launch_linear<ST>(m, pv_tref(m, PV_T_WD, l), w.gate, w.x, w.x, rows, s)) != PV_OK) return rc;
     }
-    const bool head = c->io->hdr[3] != PV_MODE_PREFILL_MID;
-    if (head) {
-        k_rmsnorm<ST><<<rows, 256, 0, s>>>(w.x, (const ST *)(m->d_weights + m->global[PV_T_FINAL_NORM].off), w.h, d, (float)f.rms_eps);
-        PV_HIP(hipGetLastError());
-        if ((rc = launch_linear<ST>(m, m->global[PV_T_LM_HEAD], w.h, nullptr, w.logits, rows, s)) != PV_OK) return rc;
-    }
-    (void)qd;
-    if (head && (rc = pv_k_argmax(c, rows, s)) != PV_OK) return rc;
-    return pv_k_finish(c, rows, nullptr, nullptr, 0, s);
+    if (c->io->hdr[3] == PV_MODE_PREFILL_MID) return pv_k_finish(c, rows, nullptr, nullptr, 0, s);
+    // the candidates ([row][strips]) go where gate and up were
+    const int strips = std::min((V + 3) / 4, F);
+    rc = row_groups(rows, [&](auto G, int r0, int r) {
+        k_vec_head<ST, G.value><<<strips, 256, 0, s>>>(normed((const ST *)(m->d_weights + m->global[PV_T_FINAL_NORM].off), r0, r), (const ST *)(m->d_weights + m->global[PV_T_LM_HEAD].off),
+                                                       w.logits + (size_t)r0 * V, V, w.gate + (size_t)r0 * strips, (int32_t *)w.up + (size_t)r0 * strips);
+    });
+    if (rc != PV_OK) return rc;
+    return pv_k_finish(c, rows, w.gate, (const int32_t *)w.up, strips, s);
 }
 
 int pv_vec_run_block(pv_cache *c, hipStream_t s)

@@ -696,7 +696,7 @@ k_gemm_tile(const gemm_args a, int tps, float4 *part)
 // K-slice's partial sums for k_tile_finish).
 // ------------------------------------------------------------------------------------------
 template <int CT, int EPI>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CT <= 2 ? 4 : 2)))
 k_gemm_tile_q4(const gemm_args a, int bps, float4 *part)
 {
     constexpr int NW = 8, S = 2, U = 4, P = U * CT, TPS = P * 2;            // P (K-tile, column tile) pairs = TPS activation tiles per step
@@ -948,8 +948,8 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
             // 4-bit weights, 9..64 rows: activation tiles shared through LDS, two strips per wave, one workgroup per CU
             // (256 registers a lane); few strips: cut along K so that about 256 workgroups run, as for 16-bit weights
             const int nbat = g.ktiles / 4, ngroups = (strips + 15) / 16;
-            int slices = (ngroups >= 192 || g.tile_part == nullptr) ? 1 : min(TILE_MAX_SLICES, (256 + ngroups - 1) / ngroups);
-            int bps = max(4, (nbat + slices - 1) / slices);
+            int slices = g.tile_part == nullptr ? 1 : max(1, min(TILE_MAX_SLICES, (CT <= 2 ? 512 : 256) / ngroups));
+            int bps = max(CT <= 2 ? 2 : 4, (nbat + slices - 1) / slices);
             slices = (nbat + bps - 1) / bps;
             while (slices > 1 && (size_t)slices * strips * CT * 256 > tile_part_floats(CT)) { bps += 1; slices = (nbat + bps - 1) / bps; }
             float4 *part = slices > 1 ? (float4 *)g.tile_part : nullptr;

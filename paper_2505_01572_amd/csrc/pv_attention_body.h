@@ -56,22 +56,97 @@ __device__ inline void split8(const float v[8], uint4 &hi, uint4 &lo)
 template <int HD>
 __host__ __device__ constexpr int attn_smem_floats() { return 8 * 16 * (HD + 4) + 2 * 8 * 16; }
 
+// A wave's running result for its 16 query rows: lane (g, jl) has row jl's maximum and sum and its features 16 e + 4 g .. + 3.
+template <int HD> struct attn_acc { f32x4 O[HD / 16]; float m, l; };
+
+// 32 keys (two groups of 16, from p0 on) of one wave.  Called with Q on its way, so that Q, K and V are one memory round trip.  MORE:
+// the accumulator holds earlier keys.
+template <int HD, bool MORE, typename VIS>
+__device__ inline void attn_keys(const attn_args &a, const pv_kv_geom &gm, const uint16_t *pool, int kvh, int p0, int nkeys, int ph0, int ph1g,
+                                 const uint4 (&qh)[HD / 32], const uint4 (&ql)[HD / 32], VIS visible, attn_acc<HD> &A)
+{
+    constexpr int KS = HD / 32, ET = HD / 16;
+    const int lane = threadIdx.x & 63, jl = lane & 15, g = lane >> 4;
+    const int sub_mask = (1 << (gm.page_shift - 4)) - 1;
+    uint4 kt[2][KS];
+    uint2 vt[2][ET];
+    // a second group past the end re-reads the first one (it is masked)
+    const bool two = p0 + 16 < nkeys;
+    const int g0 = p0 >> 4, g1 = two ? g0 + 1 : g0;
+    const int ph1 = two ? ph1g : ph0;
+    const uint16_t *kb0 = pool + pv_kv_block(gm, a.layer, ph0, kvh, 0) + (size_t)(g0 & sub_mask) * 16 * HD;
+    const uint16_t *kb1 = pool + pv_kv_block(gm, a.layer, ph1, kvh, 0) + (size_t)(g1 & sub_mask) * 16 * HD;
+    const uint16_t *vb0 = pool + pv_kv_block(gm, a.layer, ph0, kvh, 1) + (size_t)(g0 & sub_mask) * 16 * HD;
+    const uint16_t *vb1 = pool + pv_kv_block(gm, a.layer, ph1, kvh, 1) + (size_t)(g1 & sub_mask) * 16 * HD;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) { kt[0][ks] = ((const uint4 *)kb0)[ks * 64 + lane]; kt[1][ks] = ((const uint4 *)kb1)[ks * 64 + lane]; }
+#pragma unroll
+    for (int et = 0; et < ET; ++et) {
+        vt[0][et] = *(const uint2 *)(vb0 + (size_t)(et * 16 + jl) * 16 + 4 * g);
+        vt[1][et] = *(const uint2 *)(vb1 + (size_t)(et * 16 + jl) * 16 + 4 * g);
+    }
+    // every load above is in flight before the first use: one memory round trip, not one per operand
+    asm volatile("" ::: "memory");
+
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        s0 = mfma16(kt[0][ks], qh[ks], s0); s1 = mfma16(kt[1][ks], qh[ks], s1);
+        s0 = mfma16(kt[0][ks], ql[ks], s0); s1 = mfma16(kt[1][ks], ql[ks], s1);
+    }
+    float sv[8];
+    float mx = MORE ? A.m : -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int pa = p0 + 4 * g + r, pb = pa + 16;
+        sv[r] = visible(pa) ? s0[r] * a.scale : -INFINITY;
+        sv[4 + r] = visible(pb) ? s1[r] * a.scale : -INFINITY;
+        mx = fmaxf(mx, fmaxf(sv[r], sv[4 + r]));
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const bool none = mx == -INFINITY;                 // no visible key for this row so far
+    const float keep = MORE ? (A.m == -INFINITY ? 0.f : __expf(A.m - mx)) : 0.f;
+    float pr[8], ps = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { pr[i] = none ? 0.f : __expf(sv[i] - mx); ps += pr[i]; }
+    ps += __shfl_xor(ps, 16, 64);
+    ps += __shfl_xor(ps, 32, 64);
+    A.l = MORE ? A.l * keep + ps : ps;
+    A.m = mx;
+    uint4 ph, pl;
+    split8(pr, ph, pl);
+#pragma unroll
+    for (int et = 0; et < ET; ++et) {
+        const uint4 va = make_uint4(vt[0][et].x, vt[0][et].y, vt[1][et].x, vt[1][et].y);
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        if (MORE) { const f32x4 b = A.O[et]; o = (f32x4){b[0] * keep, b[1] * keep, b[2] * keep, b[3] * keep}; }
+        o = mfma16(va, ph, o);
+        o = mfma16(va, pl, o);
+        A.O[et] = o;
+    }
+}
+
 // One (kv head, chunk, 32-row group) unit, executed by the 8 wavefronts of the workgroup (all
 // 512 threads must call).  TILES as above; chunk c covers keys c * (256 / TILES) ... .
+// NB = 0: the chunk's partial result is left for the merge kernel.  NB = 1, 2: the workgroup goes through all the chunks
+// one after the other and writes the output projection's operand (of that layout) itself.
 // smem: attn_smem_floats<HD>() floats of LDS (more than 64 KiB for HD = 128: dynamic).
-template <int HD, int TILES>
+template <int HD, int TILES, int NB>
 __device__ inline void attn_chunk(const attn_args &a, int c, int kvh, int z, int n_units, float *smem)
 {
     constexpr int KS = HD / 32, ET = HD / 16, OS = HD + 4, NWM = 8 / TILES, CK = 256 / TILES;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, jl = lane & 15, g = lane >> 4;
     const int rt = wave / NWM, kq = wave % NWM;
     pv_kv_geom gm = a.geom;
-    const int sub_shift = gm.page_shift - 4, sub_mask = (1 << sub_shift) - 1;
+    const int sub_shift = gm.page_shift - 4;
     // this wave's 32 keys: two groups of 16.  Which pages they sit in does not depend on the cache
     // length, so the page-table entries are fetched beside the length, not behind it (an entry past
     // the table's end is clamped; such keys are past the length as well and never used).
-    const int p0 = c * CK + kq * 32;
-    int ph0 = a.page_table[min((p0 >> 4) >> sub_shift, a.n_pages - 1)], ph1g = a.page_table[min(((p0 >> 4) + 1) >> sub_shift, a.n_pages - 1)];
+    int p0 = c * CK + kq * 32;
+    const int32_t *pt = a.page_table;
+    int npages = a.n_pages;
+    int ph0 = pt[min((p0 >> 4) >> sub_shift, npages - 1)], ph1 = pt[min(((p0 >> 4) + 1) >> sub_shift, npages - 1)];
     const int nseq = a.st->blk.n_seq;
     int len = a.st->len, gamma = a.st->gamma, row0 = 0, mp = z;
     const uint16_t *pool = a.pool;
@@ -82,13 +157,13 @@ __device__ inline void attn_chunk(const attn_args &a, int c, int kvh, int z, int
         const pv_seq_ref &sq = a.st->blk.seq[sidx];
         len = sq.st->len; gamma = sq.gamma; row0 = sq.row0; mp = z - sq.unit0;
         pool = (const uint16_t *)sq.pool; gm.n_pages = sq.n_pages;
-        ph0 = sq.page_table[min((p0 >> 4) >> sub_shift, sq.n_pages - 1)]; ph1g = sq.page_table[min(((p0 >> 4) + 1) >> sub_shift, sq.n_pages - 1)];
+        pt = sq.page_table; npages = sq.n_pages;
+        ph0 = pt[min((p0 >> 4) >> sub_shift, npages - 1)]; ph1 = pt[min(((p0 >> 4) + 1) >> sub_shift, npages - 1)];
     }
     const int nkeys = len + gamma;
     if (c * CK >= nkeys) return;
     const int nrows = a.group * gamma;
     if (mp * 32 >= nrows) return;                      // (a unit beyond the sequence's rows: the grid is sized for the largest)
-    const bool has_keys = p0 < nkeys;
     // this lane's query row: row lane%16 of the wave's 16-row tile
     const int m = mp * 32 + rt * 16 + jl;
     const bool live = m < nrows;
@@ -97,74 +172,25 @@ __device__ inline void attn_chunk(const attn_args &a, int c, int kvh, int z, int
     // mask names (a chain: up to its own; a draft tree: its ancestors and itself); a dead lane sees nothing
     const uint64_t vmask = live ? a.st->rowmask[row0 + j] : 0ull;
     auto visible = [&](int p) { const int q = p - len; return live && (q < 0 || (q < 64 && ((vmask >> q) & 1ull))); };
-    uint4 kt[2][KS], qh[KS], ql[KS];
-    uint2 vt[2][ET];
-    if (has_keys) {
-        // a second group past the end re-reads the first one (it is masked)
-        const bool two = p0 + 16 < nkeys;
-        const int g0 = p0 >> 4, g1 = two ? g0 + 1 : g0;
-        const int ph1 = two ? ph1g : ph0;
-        // a dead lane reads row 0 of the first head: its scores are masked below
+    attn_acc<HD> A;
+    A.m = -INFINITY; A.l = 0.f;
+#pragma unroll
+    for (int et = 0; et < ET; ++et) A.O[et] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if (p0 < nkeys) {
+        // a dead lane reads row 0 of the first head: its scores are masked
         const size_t qoff = ((size_t)(row0 + j) * a.n_q_heads + kvh * a.group + al) * HD + g * 8;
+        uint4 qh[KS], ql[KS];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             qh[ks] = *(const uint4 *)(a.q_hi + qoff + ks * 32);
             ql[ks] = *(const uint4 *)(a.q_lo + qoff + ks * 32);
         }
-        const uint16_t *kb0 = pool + pv_kv_block(gm, a.layer, ph0, kvh, 0) + (size_t)(g0 & sub_mask) * 16 * HD;
-        const uint16_t *kb1 = pool + pv_kv_block(gm, a.layer, ph1, kvh, 0) + (size_t)(g1 & sub_mask) * 16 * HD;
-        const uint16_t *vb0 = pool + pv_kv_block(gm, a.layer, ph0, kvh, 1) + (size_t)(g0 & sub_mask) * 16 * HD;
-        const uint16_t *vb1 = pool + pv_kv_block(gm, a.layer, ph1, kvh, 1) + (size_t)(g1 & sub_mask) * 16 * HD;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) { kt[0][ks] = ((const uint4 *)kb0)[ks * 64 + lane]; kt[1][ks] = ((const uint4 *)kb1)[ks * 64 + lane]; }
-#pragma unroll
-        for (int et = 0; et < ET; ++et) {
-            vt[0][et] = *(const uint2 *)(vb0 + (size_t)(et * 16 + jl) * 16 + 4 * g);
-            vt[1][et] = *(const uint2 *)(vb1 + (size_t)(et * 16 + jl) * 16 + 4 * g);
-        }
-    }
-    // every load above is in flight before the first use: one memory round trip, not one per operand
-    asm volatile("" ::: "memory");
-
-    f32x4 O[ET];
-    float mrow = -INFINITY, lrow = 0.f;
-#pragma unroll
-    for (int et = 0; et < ET; ++et) O[et] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
-    if (has_keys) {
-        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            s0 = mfma16(kt[0][ks], qh[ks], s0); s1 = mfma16(kt[1][ks], qh[ks], s1);
-            s0 = mfma16(kt[0][ks], ql[ks], s0); s1 = mfma16(kt[1][ks], ql[ks], s1);
-        }
-        float sv[8];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int pa = p0 + 4 * g + r, pb = pa + 16;
-            sv[r] = visible(pa) ? s0[r] * a.scale : -INFINITY;
-            sv[4 + r] = visible(pb) ? s1[r] * a.scale : -INFINITY;
-            mx = fmaxf(mx, fmaxf(sv[r], sv[4 + r]));
-        }
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const bool none = mx == -INFINITY;                 // no visible key for this row here
-        float pr[8], ps = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) { pr[i] = none ? 0.f : __expf(sv[i] - mx); ps += pr[i]; }
-        ps += __shfl_xor(ps, 16, 64);
-        ps += __shfl_xor(ps, 32, 64);
-        lrow = ps; mrow = mx;
-        uint4 ph, pl;
-        split8(pr, ph, pl);
-#pragma unroll
-        for (int et = 0; et < ET; ++et) {
-            const uint4 va = make_uint4(vt[0][et].x, vt[0][et].y, vt[1][et].x, vt[1][et].y);
-            f32x4 o = {0.f, 0.f, 0.f, 0.f};
-            o = mfma16(va, ph, o);
-            o = mfma16(va, pl, o);
-            O[et] = o;
+        attn_keys<HD, false>(a, gm, pool, kvh, p0, nkeys, ph0, ph1, qh, ql, visible, A);
+        if (NB != 0) {
+            for (p0 += CK; p0 < nkeys; p0 += CK) {
+                ph0 = pt[(p0 >> 4) >> sub_shift]; ph1 = pt[min(((p0 >> 4) + 1) >> sub_shift, npages - 1)];
+                attn_keys<HD, true>(a, gm, pool, kvh, p0, nkeys, ph0, ph1, qh, ql, visible, A);
+            }
         }
     }
 
@@ -173,16 +199,16 @@ __device__ inline void attn_chunk(const attn_args &a, int c, int kvh, int z, int
     float (*sh_m)[16] = (float (*)[16])smem;                                  // [8][16]
     float (*sh_l)[16] = (float (*)[16])(smem + 8 * 16);                       // [8][16]
     float (*sh_o)[16][OS] = (float (*)[16][OS])(smem + 2 * 8 * 16);           // [8][16][OS]
-    if (g == 0) sh_m[wave][jl] = mrow;
+    if (g == 0) sh_m[wave][jl] = A.m;
     __syncthreads();
     float M = sh_m[rt * NWM][jl];
 #pragma unroll
     for (int w = 1; w < NWM; ++w) M = fmaxf(M, sh_m[rt * NWM + w][jl]);
-    const float f = (mrow == -INFINITY) ? 0.f : __expf(mrow - M);
+    const float f = (A.m == -INFINITY) ? 0.f : __expf(A.m - M);
 #pragma unroll
     for (int et = 0; et < ET; ++et)
-        *(float4 *)&sh_o[wave][jl][et * 16 + 4 * g] = make_float4(O[et][0] * f, O[et][1] * f, O[et][2] * f, O[et][3] * f);
-    if (g == 0) sh_l[wave][jl] = lrow * f;
+        *(float4 *)&sh_o[wave][jl][et * 16 + 4 * g] = make_float4(A.O[et][0] * f, A.O[et][1] * f, A.O[et][2] * f, A.O[et][3] * f);
+    if (g == 0) sh_l[wave][jl] = A.l * f;
     __syncthreads();
     const size_t unit = ((size_t)kvh * n_units + z) * a.max_chunks + c;
     float *po = a.part_o + unit * 32 * HD;
@@ -194,9 +220,19 @@ __device__ inline void attn_chunk(const attn_args &a, int c, int kvh, int z, int
             const float4 v = *(const float4 *)&sh_o[t * NWM + w][r][4 * c4];
             acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
         }
-        *(float4 *)(po + (size_t)row * HD + 4 * c4) = acc;
+        if constexpr (NB == 0) *(float4 *)(po + (size_t)row * HD + 4 * c4) = acc;
+        else {
+            const int mr = mp * 32 + row;
+            if (mr >= nrows) continue;
+            float L = sh_l[t * NWM][r];
+#pragma unroll
+            for (int w = 1; w < NWM; ++w) L += sh_l[t * NWM + w][r];
+            const float inv = 1.0f / L, y[4] = {acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv};
+            const int alr = mr / gamma, jr = mr - alr * gamma;
+            store_operand4<(NB == 1 ? 1 : 2)>(a.xop_o, a.n_q_heads * HD, row0 + jr, (kvh * a.group + alr) * HD + 4 * c4, y, a.lo_off);
+        }
     }
-    if (threadIdx.x < TILES * 16) {
+    if (NB == 0 && threadIdx.x < TILES * 16) {
         const int t = threadIdx.x >> 4, r = threadIdx.x & 15;
         float Mr = sh_m[t * NWM][r], L = sh_l[t * NWM][r];
 #pragma unroll

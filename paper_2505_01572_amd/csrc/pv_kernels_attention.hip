@@ -1,12 +1,13 @@
 // Kernel wrappers of the attention units (pv_attention_body.h) for the per-kernel step sequence.
 #include "pv_attention_body.h"
 
-template <int HD, int TILES>
-__global__ void __launch_bounds__(512)
+// NB = 0: one chunk a workgroup, partial results (k_attn_merge follows); NB = 1, 2: all chunks, the operand itself
+template <int HD, int TILES, int NB>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4)))
 k_attn(const attn_args a)
 {
     extern __shared__ float4 smem4[];               // attn_smem_floats<HD>() floats: above the static limit for HD = 128
-    attn_chunk<HD, TILES>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, (float *)smem4);
+    attn_chunk<HD, TILES, NB>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, (float *)smem4);
 }
 
 template <int NB, int HD>
@@ -46,12 +47,21 @@ static int launch(pv_cache *c, attn_args &a, int rows, hipStream_t s)
     constexpr size_t lds = attn_smem_floats<HD>() * sizeof(float);
     // chunks to launch: enough for the keys this step can reach (the host's bound), not for the whole cache
     const int keys = c->attn_keys > 0 && c->attn_keys < c->max_tokens ? c->attn_keys : c->max_tokens;
+    // Up to two chunks: one workgroup per kv head and row group goes through them and there is nothing to merge.  Measured per layer
+    // against chunks and merge (8B and 1B shapes): one chunk -3.5 us, two -2 us, four +3 us, eight +10 us (a chunk costs its
+    // workgroup 2 us, mostly latency; loading the next keys ahead did not help).
+    if (keys <= (nrows <= 16 ? 512 : 256)) {
+        if (nrows <= 16) k_attn<HD, 1, NB><<<dim3(1, f.n_kv_heads, units), 512, lds, s>>>(a);
+        else k_attn<HD, 2, NB><<<dim3(1, f.n_kv_heads, units), 512, lds, s>>>(a);
+        PV_HIP(hipGetLastError());
+        return PV_OK;
+    }
     if (nrows <= 16) {
         a.chunk_shift = 8; a.max_chunks = (c->max_tokens + 255) / 256;
-        k_attn<HD, 1><<<dim3((keys + 255) / 256, f.n_kv_heads, units), 512, lds, s>>>(a);
+        k_attn<HD, 1, 0><<<dim3((keys + 255) / 256, f.n_kv_heads, units), 512, lds, s>>>(a);
     } else {
         a.chunk_shift = 7; a.max_chunks = (c->max_tokens + 127) / 128;
-        k_attn<HD, 2><<<dim3((keys + 127) / 128, f.n_kv_heads, units), 512, lds, s>>>(a);
+        k_attn<HD, 2, 0><<<dim3((keys + 127) / 128, f.n_kv_heads, units), 512, lds, s>>>(a);
     }
     PV_HIP(hipGetLastError());
     k_attn_merge<NB, HD><<<dim3(rows, f.n_q_heads), 256, 0, s>>>(a, units);
@@ -63,8 +73,9 @@ template <int HD>
 static int allow_lds()
 {
     constexpr int lds = attn_smem_floats<HD>() * (int)sizeof(float);
-    PV_HIP(hipFuncSetAttribute((const void *)k_attn<HD, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-    PV_HIP(hipFuncSetAttribute((const void *)k_attn<HD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    auto allow = [&](const void *k) { return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
+    PV_HIP(allow((const void *)k_attn<HD, 1, 0>)); PV_HIP(allow((const void *)k_attn<HD, 1, 1>)); PV_HIP(allow((const void *)k_attn<HD, 1, 2>));
+    PV_HIP(allow((const void *)k_attn<HD, 2, 0>)); PV_HIP(allow((const void *)k_attn<HD, 2, 1>)); PV_HIP(allow((const void *)k_attn<HD, 2, 2>));
     return PV_OK;
 }
 

@@ -121,6 +121,7 @@ static size_t layout_arena(const pv_model_config *c, pv_model *m)
     place(PV_T_LM_HEAD, -1);
     if (m) m->inv_freq_off = off;
     off = align_up(off + (size_t)(c->head_dim / 2) * sizeof(double), 256);
+    if (c->weight_bits == 4) { if (m) m->q4_flag_off = off; off += 256; }
     return off;
 }
 
@@ -164,6 +165,7 @@ extern "C" int pv_model_create(const pv_model_config *cfg, void *d_weights, size
     for (int i = 0; i < half; ++i) inv[i] = pow(cfg->rope_base, -2.0 * (double)i / (double)cfg->head_dim);
     hipError_t e = hipMemcpy(m->d_weights + m->inv_freq_off, inv, sizeof(double) * half, hipMemcpyHostToDevice);
     free(inv);
+    if (e == hipSuccess && m->wbits == 4) e = hipMemset(m->d_weights + m->q4_flag_off, 0, sizeof(uint32_t));
     if (e != hipSuccess) { pv_set_error("upload of rotary table failed: %s", hipGetErrorString(e)); free(m->layer); delete m; return PV_EHIP; }
     *out = m;
     return PV_OK;
@@ -234,8 +236,10 @@ extern "C" int pv_load_weights_q4(pv_model *m, int32_t kind, int32_t layer, int6
     hipStream_t s = (hipStream_t)hip_stream;
     PV_HIP(hipMemcpyAsync(m->d_staging, host_codes, cbytes, hipMemcpyHostToDevice, s));
     PV_HIP(hipMemcpyAsync(m->d_staging + soff, host_scales, sbytes, hipMemcpyHostToDevice, s));
-    int rc = pv_mat_repack_q4(m, t, kind, row_begin, row_count, soff, s);
+    uint32_t *wide = (uint32_t *)(m->d_weights + m->q4_flag_off);
+    int rc = pv_mat_repack_q4(m, t, kind, row_begin, row_count, soff, wide, s);
     if (rc != PV_OK) return rc;
+    PV_HIP(hipMemcpyAsync(&m->q4_wide, wide, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     PV_HIP(hipStreamSynchronize(s));
     t.loaded_rows = row_begin + row_count;
     return PV_OK;

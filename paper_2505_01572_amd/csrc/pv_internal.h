@@ -87,6 +87,8 @@ struct pv_model {
     pv_tensor_ref global[PV_T_NKINDS];
     size_t inv_freq_off;        // double[head_dim/2]
     int n_cus;
+    size_t q4_flag_off;         // 4-bit models: a word of the arena, not 0 once a scale was loaded that the f16 form of the weights does not hold ...
+    uint32_t q4_wide;           // ... and its copy, read after every load
 };
 
 struct pv_ws {                  // pointers into the caller's workspace
@@ -166,7 +168,7 @@ int pv_vec_run_block(pv_cache *c, hipStream_t s);        // pv_kernels_vector.hi
 int pv_mat_run_block(pv_cache *c, hipStream_t s);        // pv_kernels_matrix.hip
 int pv_mat_run_prompt(pv_cache *c, int rows, int keep, hipStream_t s);   // a long-prompt pass (pv_prefill.h); keep > 0: with head and result for its last `keep` rows
 int pv_mat_repack(const pv_model *m, const pv_tensor_ref &t, int kind, int64_t row_begin, int64_t row_count, hipStream_t s);
-int pv_mat_repack_q4(const pv_model *m, const pv_tensor_ref &t, int kind, int64_t row_begin, int64_t row_count, size_t scales_off, hipStream_t s);
+int pv_mat_repack_q4(const pv_model *m, const pv_tensor_ref &t, int kind, int64_t row_begin, int64_t row_count, size_t scales_off, uint32_t *wide, hipStream_t s);
 
 // 4-bit matrices: a strip (16 output features) is a run of cols/128 batches of PV_Q4_BATCH bytes:
 // 4 K-tiles of codes, [lane 0..63][tile 0..3] dwords (a dword = the lane's 8 consecutive k of its

@@ -118,7 +118,7 @@ int pv_mat_repack(const pv_model *m, const pv_tensor_ref &t, int kind, int64_t r
 // k, low nibble first; scales: K/32 bf16 per row), into the batched strip layout (pv_internal.h).
 // One thread moves one dword of codes; the thread of a tile's first dword also moves its scale.
 __global__ void k_repack_q4(const uint32_t *codes, const uint16_t *scales, char *dst, int64_t row_begin, int64_t row_count,
-                            int K, int perm, int head_dim, int strip_mul, int strip_add)
+                            int K, int perm, int head_dim, int strip_mul, int strip_add, uint32_t *wide)
 {
     const int kd = K / 8, nb4 = K / 128;
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -146,17 +146,23 @@ __global__ void k_repack_q4(const uint32_t *codes, const uint16_t *scales, char 
 #pragma unroll
     for (int t = 0; t < 4; ++t) { even |= ((src >> (8 * t)) & 0xFu) << (4 * t); odd |= ((src >> (8 * t + 4)) & 0xFu) << (4 * t); }
     ((uint32_t *)batch)[(i + 16 * q) * 4 + u] = even | (odd << 16);
-    if (q == 0) ((uint16_t *)(batch + 1024))[i * 4 + u] = scales[nl * (K / 32) + kt];
+    if (q == 0) {
+        const uint16_t sc = scales[nl * (K / 32) + kt];
+        ((uint16_t *)(batch + 1024))[i * 4 + u] = sc;
+        // (c - 8) x scale and scale / 16 are exact in f16 for scales of 0 and of 2^-13 .. 2^12
+        const int e = (sc >> 7) & 0xFF;
+        if ((sc & 0x7FFF) != 0 && (e < 114 || e > 138)) *wide = 1;
+    }
 }
 
-int pv_mat_repack_q4(const pv_model *m, const pv_tensor_ref &t, int kind, int64_t row_begin, int64_t row_count, size_t scales_off, hipStream_t s)
+int pv_mat_repack_q4(const pv_model *m, const pv_tensor_ref &t, int kind, int64_t row_begin, int64_t row_count, size_t scales_off, uint32_t *wide, hipStream_t s)
 {
     int perm = PERM_NONE, mul = 1, add = 0;
     if (kind == PV_T_WQ || kind == PV_T_WK) perm = PERM_ROPE;
     else if (kind == PV_T_WG || kind == PV_T_WU) { perm = PERM_GATEUP; add = t.strip_add; }
     const int64_t n = row_count * (t.cols / 8);
     k_repack_q4<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((const uint32_t *)m->d_staging, (const uint16_t *)(m->d_staging + scales_off),
-                                                            m->d_weights + t.off, row_begin, row_count, (int)t.cols, perm, m->cfg.head_dim, mul, add);
+                                                            m->d_weights + t.off, row_begin, row_count, (int)t.cols, perm, m->cfg.head_dim, mul, add, wide);
     PV_HIP(hipGetLastError());
     return PV_OK;
 }
@@ -1125,7 +1131,7 @@ int pv_mat_run_prompt(pv_cache *c, int rows, int keep, hipStream_t s)
     mat_ws mw;
     mat_ws_layout(m, c->rows_cap, c->units_cap, c->n_pages * f.page_tokens, c->ws.part, &mw);
     pv_pre_out out;
-    int rc = pv_pre_block(c, c->pre_base, c->d_io->prompt, rows, keep, mw.tile_part, tile_part_floats(col_tiles(c->rows_cap)), &out, s);
+    int rc = pv_pre_block(c, c->pre_base, c->d_io->prompt, rows, keep, &out, s);
     if (rc != PV_OK || keep == 0) return rc;
     // the head of the kept rows (whatever their number, as column tiles of 16 rows: the layout of the prompt's operand)
     gemm_args g = {};

@@ -17,7 +17,7 @@
 // kernels wait for the copies by count (pre_wait).  src is uniform, voff the lane's byte offset behind it.
 __device__ inline void dma_tile(uint32_t lds, const void *src, uint32_t voff)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(src) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(src) : "memory");
 }
 
 __device__ inline uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }
@@ -61,6 +61,7 @@ struct pre_gemm_args {
     int kps;                    // K-tiles per slice
     int rows, len;              // rows of the block, and the position of the first
     const float *rowsum; int rsum_rows;   // 4-bit weights: -24 x the operand's row sums, [K-tile][rsum_rows]
+    const float *rinv;          // 16-bit float operand: what its rows' sums have to be multiplied with (null: nothing)
 };
 
 // What the epilogue of a strip needs from memory.  Rows, length and the row's page are known here (epi_prefetch reads them
@@ -106,17 +107,26 @@ __device__ inline void pre_swiglu2(const gemm_args &a, const pre_gemm_args &p, i
     if (j < p.rows) store_operand4<2>(a.xop_act, a.F, j, (strip + odd) * 8 + 4 * (g >> 1), act, 8);
 }
 
+// factor of this lane's row: its RMSNorm scale, and what takes the scaling of a 16-bit float operand back
+template <int EPI>
+__device__ inline float pre_rowfactor(const pre_gemm_args &p, int lane, int ct)
+{
+    const int j = min(ct * 16 + (lane & 15), p.rows - 1);
+    float v = (EPI == EPI_QKV || EPI == EPI_SWIGLU) ? p.rscale[j] : 1.f;
+    if (p.rinv != nullptr) v *= p.rinv[j];
+    return v;
+}
+
 // Epilogue of one row tile of a wave, whose nf accumulators (strip0 ...) lie in the wave's own piece of LDS (`mine`, at this lane): the loop
 // over the strips need not be unrolled then (unrolled, the rotary epilogue of 16 accumulator tiles does not fit the registers).
 template <int EPI, int FT>
 __device__ inline void pre_epilogue(const gemm_args &a, const pre_gemm_args &p, int slice, int ct, int strip0, int nf, int lane, const f32x4 *mine)
 {
-    constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
     if (p.part != nullptr) {
         for (int f = 0; f < nf; ++f) ((f32x4 *)p.part)[(((size_t)slice * a.nstrips + strip0 + f) * p.mtiles + ct) * 64 + lane] = mine[f * 64];
         return;
     }
-    const float rj = NORM ? p.rscale[min(ct * 16 + (lane & 15), p.rows - 1)] : 1.f;
+    const float rj = pre_rowfactor<EPI>(p, lane, ct);
     const int phys = pre_page<EPI>(a, p, lane, ct);
     if constexpr (EPI == EPI_SWIGLU) {
         int f = 0;
@@ -130,7 +140,7 @@ __device__ inline void pre_epilogue(const gemm_args &a, const pre_gemm_args &p, 
             for (int u = 0; u < G; ++u) pre_fetch<EPI>(a, p, min(strip0 + f + u, a.nstrips - 1), lane, ct, phys, rj, e[u]);
 #pragma unroll
             for (int u = 0; u < G; ++u)
-                if (f + u < nf) epi_apply<2, EPI>(a, strip0 + f + u, lane, mine[(f + u) * 64], e[u], ct);
+                if (f + u < nf) epi_apply<2, EPI>(a, strip0 + f + u, lane, EPI == EPI_RESID ? mine[(f + u) * 64] * rj : mine[(f + u) * 64], e[u], ct);
         }
     }
 }
@@ -422,21 +432,219 @@ k_pre_rowsum(const uint4 *xop, int ktiles, float *rowsum, int rsum_rows)
     if (lane < 16) rowsum[(size_t)kt * rsum_rows + ct * 16 + lane] = -24.f * v;
 }
 
+// ------------------------------------------------------------------------------------------
+// 4-bit weights as 16-bit floats.  (c - 8) x scale has at most 11 significant bits (3 of the code, 8 of the bf16
+// scale), which is what f16 holds, so for scales inside f16's range the weight itself enters the matrix core, exactly,
+// and nothing is left to do per product: the vector ALU, which bounds k_pre_gemm_q4 (scaling every product), only
+// expands the codes.  The activations become f16 hi + lo pairs (22 bits; the bf16 pairs have 16) of rows that are
+// scaled by a power of two so that a row's largest value lies in [2^14, 2^15); the rows' sums are scaled back in the epilogue.  128
+// rows x 64 FT features, 2 x 4 waves of 4 row tiles x FT strips; the codes of K-tile k + 1 are expanded, one strip per row tile,
+// among the MFMAs of K-tile k.  70B-shaped gate/up, 1000 rows: 1.82 -> 1.71 ms (16-bit weights: 1.45), and fewer K/V
+// values off by a rounding step against 64 bits (1.43 % for 1.66 %, 1.62 % in blocks of 64 rows).
+// ------------------------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
+typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+
+__device__ inline f32x4 mfma16h(uint4 a, uint4 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+
+template <int FT> struct pre_h4_shape {
+    static constexpr int BR = 8, BF = 4 * FT, NST = 4;
+    static constexpr int XT = 2 * BR, CT = 16, ST = 2, BT = CT + ST;           // KiB of a stage's activations; of a batch's codes and scales (of 16 strips, also where fewer are used)
+    static constexpr int lds = (NST * XT + 2 * BT) * 1024;
+};
+
+template <int FT, int EPI>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_pre_gemm_h4(const gemm_args a, const pre_gemm_args p)
+{
+    using S = pre_h4_shape<FT>;
+    constexpr int RT = 4, WF = 4, NST = S::NST, NX = S::XT / 8, NC = S::CT / 8, BC = NC + 1;    // copies of a wave: NX a stage, BC a batch
+    static_assert(FT <= RT && S::BF <= S::CT, "a strip is expanded beside each row tile");
+    extern __shared__ uint4 pre_lds[];                 // [NST][XT][64], then [2][BT][64]
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, fl = lane & 15;
+    const int wr = wave / WF, wf = wave % WF;
+    const int L = xcd_order(blockIdx.x, gridDim.x), per = p.rb * p.fb, slice = L / per, rest = L - slice * per;
+    const int ct0 = (rest % p.rb) * S::BR, fs0 = (rest / p.rb) * S::BF;
+    const int KT = a.ktiles, kt0 = slice * p.kps, n = min(KT - kt0, p.kps), nb = n >> 2;        // K-tiles and batches of this slice (whole batches, not empty)
+    const size_t arr = (size_t)KT * 64, qstrip = (size_t)(KT >> 2) * PV_Q4_BATCH;
+    const char *W = (const char *)a.W + (size_t)(kt0 >> 2) * PV_Q4_BATCH;
+    const uint4 *xsrc[NX];
+    const char *csrc[NC];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) { const int t = wave + 8 * i; xsrc[i] = uniform_ptr(a.xop + (size_t)(2 * min(ct0 + (t >> 1), p.mtiles - 1) + (t & 1)) * arr + (size_t)kt0 * 64); }
+#pragma unroll
+    for (int i = 0; i < NC; ++i) csrc[i] = uniform_ptr(W + (size_t)min(fs0 + wave + 8 * i, a.nstrips - 1) * qstrip);
+    const int small = wave < S::ST ? wave : 0;         // the wave's scale tile (8 strips x 128 bytes); the waves that are left over repeat the first
+    const char *ssrc = uniform_ptr(W + (size_t)fs0 * qstrip);
+    const uint32_t soff = (uint32_t)((min(fs0 + small * 8 + (lane >> 3), a.nstrips - 1) - fs0) * qstrip) + 1024 + (lane & 7) * 16;
+    const uint32_t ldsx = __builtin_amdgcn_readfirstlane(lds_addr(pre_lds)) + wave * 1024, ldsb = ldsx + NST * S::XT * 1024;
+    auto copy_x = [&](int s, int buf) {
+        const uint32_t vo = (uint32_t)lane * 16 + (uint32_t)min(s, n - 1) * 1024;
+#pragma unroll
+        for (int i = 0; i < NX; ++i) dma_tile(ldsx + (uint32_t)(buf * S::XT + 8 * i) * 1024, xsrc[i], vo);
+    };
+    auto copy_b = [&](int b, int i0, int i1) {         // copies i0 .. i1 - 1 of batch b (past the end: the last one again)
+        const uint32_t bt = min(b, nb - 1), base = ldsb + (uint32_t)((b & 1) * S::BT) * 1024;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) if (i >= i0 && i < i1) dma_tile(base + 8 * i * 1024, csrc[i], (uint32_t)lane * 16 + bt * PV_Q4_BATCH);
+        if (NC >= i0 && NC < i1) dma_tile(base + (uint32_t)(S::CT + small - wave) * 1024, ssrc, soff + bt * PV_Q4_BATCH);
+    };
+    f32x4 acc[RT][FT], tot[RT][FT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int f = 0; f < FT; ++f) acc[r][f] = tot[r][f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    uint4 wa[FT], wb[FT], xh[2], xl[2];
+    uint2 cd[FT]; uint32_t sp[FT];                     // codes and scales of two K-tiles
+    const uint4 *Lx = pre_lds + (wr * RT * 2) * 64 + lane;
+    const char *Lb = (const char *)(pre_lds + NST * S::XT * 64);
+    auto read_x = [&](int r, int buf) { xh[r & 1] = Lx[buf * S::XT * 64 + 2 * r * 64]; xl[r & 1] = Lx[buf * S::XT * 64 + (2 * r + 1) * 64]; };
+    auto read_c = [&](int bb, int h) {
+#pragma unroll
+        for (int f = 0; f < FT; ++f) {
+            const int st = wf * FT + f;
+            cd[f] = *(const uint2 *)(Lb + (bb * S::BT + st) * 1024 + lane * 16 + h * 8);
+            sp[f] = *(const uint32_t *)(Lb + (bb * S::BT + S::CT) * 1024 + st * 128 + fl * 8 + h * 4);
+        }
+    };
+    // the codes of one strip and K-tile (the odd or the even one of the pair) as weights.  A nibble OR-ed into 1024.0 (0x6400) counts ones in the lowest
+    // mantissa bits and sixteens in the next: 1024 + c and 1024 + 16 c; less 1032 or 1152 that is c - 8 or 16 (c - 8), exactly
+    auto expand = [&](int f, bool odd) {
+        const uint32_t c = odd ? cd[f].y : cd[f].x, c8 = c >> 8;
+        const float sc = __uint_as_float(odd ? (sp[f] & 0xFFFF0000u) : (sp[f] << 16));
+        const f16x2 s1 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(sc, sc)), s16 = s1 * (f16x2){(_Float16)0.0625f, (_Float16)0.0625f};
+        const f16x2 one = {(_Float16)-1032.f, (_Float16)-1032.f}, sixteen = {(_Float16)-1152.f, (_Float16)-1152.f};
+        auto low = [&](uint32_t v) { return __builtin_bit_cast(uint32_t, (__builtin_bit_cast(f16x2, (v & 0x000F000Fu) | 0x64006400u) + one) * s1); };
+        auto high = [&](uint32_t v) { return __builtin_bit_cast(uint32_t, (__builtin_bit_cast(f16x2, (v & 0x00F000F0u) | 0x64006400u) + sixteen) * s16); };
+        return make_uint4(low(c), high(c), low(c8), high(c8));
+    };
+    int buf = 0, fill = NST - 1;
+    auto step = [&](int b, auto uc, const uint4 (&w)[FT], uint4 (&wn)[FT]) {   // K-tile 4 b + u; on entry its weights are expanded and row tile 0 is in registers (or on its way)
+        constexpr int u = decltype(uc)::value;
+        const int s = 4 * b + u, bb = b & 1;
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            if (r + 1 < RT) read_x(r + 1, buf);
+            else {
+                if (u >= 2) pre_wait<(NST - 2) * NX>(); else pre_wait<(NST - 2) * NX + BC>();   // stage s + 1 is there; from u = 2 on the next batch is, too
+                fill = buf;
+                buf = buf + 1 == NST ? 0 : buf + 1;
+                read_x(0, buf);
+            }
+            if (r == 0 && (u & 1)) read_c(u == 3 ? bb ^ 1 : bb, u == 3 ? 0 : 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = 0; f < FT; ++f) acc[r][f] = mfma16h(w[f], xh[r & 1], acc[r][f]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (r == 0) copy_x(s + NST - 1, fill);
+            if (u == 0 && r == 1) copy_b(b + 1, 0, 1);
+            if (u == 0 && r == 2) copy_b(b + 1, 1, BC);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = 0; f < FT; ++f) acc[r][f] = mfma16h(w[f], xl[r & 1], acc[r][f]);
+            if (r < FT) wn[r] = expand(r, !(u & 1));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    copy_b(0, 0, BC);
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s) copy_x(s, s);
+    pre_wait<(NST - 2) * NX>();
+    read_c(0, 0);
+    read_x(0, 0);
+#pragma unroll
+    for (int f = 0; f < FT; ++f) wa[f] = expand(f, false);
+    for (int b = 0; b < nb; ++b) {
+        step(b, std::integral_constant<int, 0>(), wa, wb); step(b, std::integral_constant<int, 1>(), wb, wa);
+        step(b, std::integral_constant<int, 2>(), wa, wb); step(b, std::integral_constant<int, 3>(), wb, wa);
+        if ((b + 1) % (PRE_RUN / 4) == 0 || b + 1 == nb) {
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int f = 0; f < FT; ++f) { tot[r][f] += acc[r][f]; acc[r][f] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+        }
+    }
+    pre_wait<0>();
+    f32x4 *mine = (f32x4 *)pre_lds + wave * FT * 64 + lane;
+    const int strip0 = fs0 + wf * FT, nf = min(FT, a.nstrips - strip0);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const int ct = ct0 + wr * RT + r;
+        if (ct >= p.mtiles) break;
+#pragma unroll
+        for (int f = 0; f < FT; ++f) mine[f * 64] = tot[r][f];
+        pre_epilogue<EPI, FT>(a, p, slice, ct, strip0, nf, lane, mine);
+    }
+}
+
+// An operand's rows as scaled f16 pairs, in place.  First the largest |hi| of each row, PRE_MAX_PARTS pieces of K side by side; then the conversion.
+#define PRE_MAX_PARTS 16
+__global__ void __launch_bounds__(256)
+k_pre_rowmax(const uint4 *xop, int ktiles, float *part, int part_rows)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ct = blockIdx.y;
+    const int per = (ktiles + PRE_MAX_PARTS - 1) / PRE_MAX_PARTS, t0 = blockIdx.x * per, t1 = min(ktiles, t0 + per);
+    const uint4 *q = xop + (size_t)2 * ct * ktiles * 64 + lane;
+    uint32_t m = 0;                                    // as the bits of |hi| (NaN and infinity largest)
+    auto take = [&](uint32_t v) { m = max(m, max(v & 0x7FFFu, (v >> 16) & 0x7FFFu)); };
+#pragma unroll 4
+    for (int t = t0 + wave; t < t1; t += 4) { const uint4 v = q[(size_t)t * 64]; take(v.x); take(v.y); take(v.z); take(v.w); }
+    m = max(m, (uint32_t)__shfl_xor((int)m, 16, 64));
+    m = max(m, (uint32_t)__shfl_xor((int)m, 32, 64));
+    __shared__ uint32_t s[4][16];
+    if (lane < 16) s[wave][lane] = m;
+    __syncthreads();
+    if (threadIdx.x < 16) part[(size_t)blockIdx.x * part_rows + ct * 16 + threadIdx.x] = __uint_as_float(max(max(s[0][threadIdx.x], s[1][threadIdx.x]), max(s[2][threadIdx.x], s[3][threadIdx.x])) << 16);
+}
+
+__global__ void __launch_bounds__(256)
+k_pre_to_f16(uint4 *xop, int ktiles, const float *part, int part_rows, float *rinv)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ct = blockIdx.y, row = ct * 16 + (lane & 15);
+    uint32_t m = 0;
+#pragma unroll
+    for (int i = 0; i < PRE_MAX_PARTS; ++i) m = max(m, __float_as_uint(part[(size_t)i * part_rows + row]));
+    // 2^e <= the row's largest value < 2^(e + 1); a row of zeros or with something not finite stays as it is
+    const int e = (int)(m >> 23) - 127, up = m == 0 || e == 128 ? 0 : 14 - max(e, -100);
+    const float f = __uint_as_float((uint32_t)(127 + up) << 23), inv = __uint_as_float((uint32_t)(127 - up) << 23);
+    if (blockIdx.x == 0 && threadIdx.x < 16) rinv[row] = inv;
+    const int t = blockIdx.x * 4 + wave;
+    if (t >= ktiles) return;
+    uint4 *q = xop + ((size_t)2 * ct * ktiles + t) * 64 + lane;
+    uint4 *ql = q + (size_t)ktiles * 64;
+    const uint4 hi = *q, lo = *ql;
+    uint4 oh, ol;
+    auto conv = [&](uint32_t h, uint32_t l, uint32_t &rh, uint32_t &rl) {
+        const float x0 = (__uint_as_float(h << 16) + __uint_as_float(l << 16)) * f, x1 = (__uint_as_float(h & 0xFFFF0000u) + __uint_as_float(l & 0xFFFF0000u)) * f;
+        const f16x2 a = {(_Float16)x0, (_Float16)x1};
+        const f16x2 b = {(_Float16)(x0 - (float)a.x), (_Float16)(x1 - (float)a.y)};
+        rh = __builtin_bit_cast(uint32_t, a); rl = __builtin_bit_cast(uint32_t, b);
+    };
+    conv(hi.x, lo.x, oh.x, ol.x); conv(hi.y, lo.y, oh.y, ol.y); conv(hi.z, lo.z, oh.z, ol.z); conv(hi.w, lo.w, oh.w, ol.w);
+    *q = oh; *ql = ol;
+}
+
 // Adds the K-slices' partial sums in slice order and runs the epilogue: one wave per (strip, row tile).
 template <int EPI>
 __global__ void __launch_bounds__(256)
 k_pre_sum(const gemm_args a, const pre_gemm_args p, int slices)
 {
-    constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
     const int lane = threadIdx.x & 63, strip = blockIdx.x * 4 + (threadIdx.x >> 6), ct = blockIdx.y;
     if (strip >= a.nstrips) return;
     const float4 *q = p.part + ((size_t)strip * p.mtiles + ct) * 64 + lane;
     const size_t step = (size_t)a.nstrips * p.mtiles * 64;
     epi_pre pre;
-    pre_fetch<EPI>(a, p, strip, lane, ct, pre_page<EPI>(a, p, lane, ct), NORM ? p.rscale[min(ct * 16 + (lane & 15), p.rows - 1)] : 1.f, pre);
+    const float rj = pre_rowfactor<EPI>(p, lane, ct);
+    pre_fetch<EPI>(a, p, strip, lane, ct, pre_page<EPI>(a, p, lane, ct), rj, pre);
     float4 v = q[0];
     for (int y = 1; y < slices; ++y) { const float4 u = q[y * step]; v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w; }
-    epi_apply<2, EPI>(a, strip, lane, (f32x4){v.x, v.y, v.z, v.w}, pre, ct);
+    f32x4 sum = {v.x, v.y, v.z, v.w};
+    if (EPI == EPI_RESID) sum *= rj;
+    epi_apply<2, EPI>(a, strip, lane, sum, pre, ct);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -671,7 +879,8 @@ struct pre_ws {
     uint16_t *xop;              // QKV and gate/up input (K = d)
     uint16_t *xop_d;            // down input (K = F); before that the queries and the O input (K = qd)
     uint16_t *q_hi, *q_lo, *xop_o;
-    float *rowsum;              // 4-bit weights: [K / 32][rows]
+    float *rowsum;              // 4-bit weights: see pre_layout
+    float *part; size_t part_floats;   // K-slices' partial sums
 };
 
 static size_t pre_layout(const pv_model *m, int rows, char *base, pre_ws *w)
@@ -689,7 +898,11 @@ static size_t pre_layout(const pv_model *m, int rows, char *base, pre_ws *w)
     p = take(4 * R * d); if (w) w->xop = (uint16_t *)p;
     p = take(std::max((size_t)4 * R * f.ffn_dim, 8 * R * qd));
     if (w) { w->xop_d = (uint16_t *)p; w->q_hi = w->xop_d; w->q_lo = w->q_hi + R * qd; w->xop_o = w->q_lo + R * qd; }
-    if (m->wbits == 4) { p = take(4 * (std::max(std::max(d, qd), (size_t)f.ffn_dim) / 32) * ((R + 127) / 128 * 128)); if (w) w->rowsum = (float *)p; }
+    // row sums [K / 32][rows], or the rows' factors and PRE_MAX_PARTS maxima of each
+    if (m->wbits == 4) { p = take(4 * std::max(std::max(std::max(d, qd), (size_t)f.ffn_dim) / 32, (size_t)PRE_MAX_PARTS + 1) * ((R + 127) / 128 * 128)); if (w) w->rowsum = (float *)p; }
+    // a GEMM is cut along K only where it has fewer rectangles than the chip has CUs: 256 x 128 KiB
+    const size_t pf = std::min((size_t)8 << 20, 8 * R * d);
+    p = take(4 * pf); if (w) { w->part = (float *)p; w->part_floats = pf; }
     return off;
 }
 
@@ -757,10 +970,37 @@ struct pre_q4 {
     }
 };
 
+template <int FT>
+struct pre_h4 {
+    using S = pre_h4_shape<FT>;
+    template <int EPI> static int allow()
+    {
+        PV_HIP(hipFuncSetAttribute((const void *)k_pre_gemm_h4<FT, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, S::lds));
+        return PV_OK;
+    }
+    static int allow_all()
+    {
+        int rc;
+        if ((rc = allow<EPI_QKV>()) != PV_OK || (rc = allow<EPI_RESID>()) != PV_OK) return rc;
+        return allow<EPI_SWIGLU>();
+    }
+    template <int EPI> static int run(const gemm_args &ga, pre_gemm_args pa, int slices, hipStream_t s)
+    {
+        pa.rb = (pa.mtiles + S::BR - 1) / S::BR; pa.fb = (ga.nstrips + S::BF - 1) / S::BF;
+        pa.kps = (ga.ktiles / 4 + slices - 1) / slices * 4;
+        slices = (ga.ktiles + pa.kps - 1) / pa.kps;
+        if (slices == 1) pa.part = nullptr;
+        k_pre_gemm_h4<FT, EPI><<<pa.rb * pa.fb * slices, 512, S::lds, s>>>(ga, pa);
+        PV_HIP(hipGetLastError());
+        if (slices > 1) { k_pre_sum<EPI><<<dim3((ga.nstrips + 3) / 4, pa.mtiles), 256, 0, s>>>(ga, pa, slices); PV_HIP(hipGetLastError()); }
+        return PV_OK;
+    }
+};
+
 int pv_pre_init(const pv_model *m)
 {
     int rc;
-    if (m->wbits == 4) return pre_q4<4>::allow_all();
+    if (m->wbits == 4) { if ((rc = pre_q4<4>::allow_all()) != PV_OK) return rc; if ((rc = pre_h4<4>::allow_all()) != PV_OK) return rc; return pre_h4<3>::allow_all(); }
     if ((rc = pre_mid::allow_all()) != PV_OK || (rc = pre_wide::allow_all()) != PV_OK || (rc = pre_small::allow_all()) != PV_OK) return rc;
     return PV_OK;
 }
@@ -773,7 +1013,15 @@ static int pre_gemm(const pv_model *m, const gemm_args &g, int strips, const flo
     ga.nstrips = strips;
     pre_gemm_args pa = {};
     pa.rscale = rscale; pa.part = (float4 *)g.tile_part; pa.mtiles = mtiles; pa.rows = rows; pa.len = len;
-    if (m->wbits == 4) {
+    const bool h4 = m->wbits == 4 && !m->q4_wide;      // every scale of the model fits the f16 form of its weights
+    if (h4) {
+        float *rinv = rowsum, *part = rowsum + (mtiles + 7) / 8 * 128;       // (in the place of the row sums)
+        pa.rinv = rinv;
+        k_pre_rowmax<<<dim3(PRE_MAX_PARTS, mtiles), 256, 0, s>>>(g.xop, g.ktiles, part, mtiles * 16);
+        PV_HIP(hipGetLastError());
+        k_pre_to_f16<<<dim3((g.ktiles + 3) / 4, mtiles), 256, 0, s>>>((uint4 *)g.xop, g.ktiles, part, mtiles * 16, rinv);
+        PV_HIP(hipGetLastError());
+    } else if (m->wbits == 4) {
         pa.rowsum = rowsum; pa.rsum_rows = (mtiles + 7) / 8 * 128;
         k_pre_rowsum<<<dim3((g.ktiles + 3) / 4, mtiles), 256, 0, s>>>(g.xop, g.ktiles, rowsum, pa.rsum_rows);
         PV_HIP(hipGetLastError());
@@ -783,9 +1031,9 @@ static int pre_gemm(const pv_model *m, const gemm_args &g, int strips, const flo
     // K-tile 0.99, 0.77, 0.53 and 0.30 us, on top of 20, 16, 14 and 9 us for the start, the epilogue and the end; partial
     // sums: 3 us and 0.2 ns for each 16 x 16 of them.  Where more workgroups than CUs come out, they run in rounds.
     struct rect { int br, bf; double cost; };
-    static const rect R16[3] = {{8, 16, 1.07}, {8, 12, 1.12}, {8, 8, 1.22}}, R4[1] = {{8, 16, 2.0}};      // 4-bit weights: 1.0 us a K-tile
+    static const rect R16[3] = {{8, 16, 1.07}, {8, 12, 1.12}, {8, 8, 1.22}}, R4[2] = {{8, 16, 1.6}, {8, 12, 1.65}};      // 4-bit weights: 0.81 us a K-tile
     const rect *R = m->wbits == 4 ? R4 : R16;
-    const int kinds = m->wbits == 4 ? 1 : 3;
+    const int kinds = h4 ? 2 : m->wbits == 4 ? 1 : 3;
     double best = 1e30; int shape = 0, cut = 1;
     for (int i = 0; i < kinds; ++i) {
         const int blocks = ((mtiles + R[i].br - 1) / R[i].br) * ((strips + R[i].bf - 1) / R[i].bf);
@@ -797,6 +1045,7 @@ static int pre_gemm(const pv_model *m, const gemm_args &g, int strips, const flo
             if (t < best) { best = t; shape = i; cut = sl; }
         }
     }
+    if (h4) return shape == 0 ? pre_h4<4>::run<EPI>(ga, pa, cut, s) : pre_h4<3>::run<EPI>(ga, pa, cut, s);
     if (m->wbits == 4) return pre_q4<4>::run<EPI>(ga, pa, cut, s);
     if (shape == 0) return pre_wide::run<EPI>(ga, pa, cut, s);
     if (shape == 1) return pre_mid::run<EPI>(ga, pa, cut, s);
@@ -811,7 +1060,7 @@ static int pre_attention(const pre_attn_args &a, int kv_heads, hipStream_t s)
     return PV_OK;
 }
 
-int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows, int keep, float *tile_part, size_t part_floats, pv_pre_out *out, hipStream_t s)
+int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows, int keep, pv_pre_out *out, hipStream_t s)
 {
     const pv_model *m = c->m;
     const pv_model_config &f = m->cfg;
@@ -831,7 +1080,7 @@ int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows
     g.st = c->ws.state; g.lo_off = 8; g.inv_d = 1.0f / (float)d; g.eps = (float)f.rms_eps; g.ssq_parts = d / 16;
     g.q_hi = w.q_hi; g.q_lo = w.q_lo; g.pool = (uint16_t *)c->d_pool; g.page_table = c->ws.page_table; g.rope = w.rope; g.geom = pv_geom(c);
     g.n_q_heads = f.n_q_heads; g.q_strips = qd / 16; g.k_strips = kvd / 16;
-    g.x = w.x; g.d = d; g.xop_act = w.xop_d; g.F = F; g.tile_part = tile_part; g.ssq = w.ssq; g.ssq_out = w.ssq; g.xop_out = w.xop;
+    g.x = w.x; g.d = d; g.xop_act = w.xop_d; g.F = F; g.tile_part = w.part; g.ssq = w.ssq; g.ssq_out = w.ssq; g.xop_out = w.xop;
 
     pre_attn_args at = {};
     at.rows = rows; at.len = len; at.page_table = c->ws.page_table; at.q_hi = w.q_hi; at.q_lo = w.q_lo; at.pool = (const uint16_t *)c->d_pool; at.geom = g.geom;
@@ -845,7 +1094,7 @@ int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows
         PV_HIP(hipGetLastError());
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WQ, l).off); g.xop = (const uint4 *)w.xop; g.ktiles = d / 32; g.layer = l;
         if ((rc = pv_prof_mark(c, PV_PROF_QKV, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_QKV>(m, g, (qd + 2 * kvd) / 16, w.rscale, w.rowsum, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_QKV>(m, g, (qd + 2 * kvd) / 16, w.rscale, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_QKV, l, 1, s)) != PV_OK) return rc;
         at.layer = l;
         if ((rc = pv_prof_mark(c, PV_PROF_ATTENTION, l, 0, s)) != PV_OK) return rc;
@@ -854,18 +1103,18 @@ int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows
         if ((rc = pv_prof_mark(c, PV_PROF_ATTENTION, l, 1, s)) != PV_OK) return rc;
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WO, l).off); g.xop = (const uint4 *)w.xop_o; g.ktiles = qd / 32; g.gain_next = gainp(PV_T_FFN_NORM, l);
         if ((rc = pv_prof_mark(c, PV_PROF_OPROJ, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, w.rowsum, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_OPROJ, l, 1, s)) != PV_OK) return rc;
         k_pre_rscale<<<mtiles, 256, 0, s>>>(w.ssq, w.rscale, d / 16, g.inv_d, g.eps);
         PV_HIP(hipGetLastError());
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WG, l).off); g.xop = (const uint4 *)w.xop; g.ktiles = d / 32;
         if ((rc = pv_prof_mark(c, PV_PROF_GATEUP, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_SWIGLU>(m, g, F / 8, w.rscale, w.rowsum, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_SWIGLU>(m, g, F / 8, w.rscale, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_GATEUP, l, 1, s)) != PV_OK) return rc;
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WD, l).off); g.xop = (const uint4 *)w.xop_d; g.ktiles = F / 32;
         g.gain_next = (l + 1 < f.n_layers) ? gainp(PV_T_ATTN_NORM, l + 1) : (const uint16_t *)(Wb + m->global[PV_T_FINAL_NORM].off);
         if ((rc = pv_prof_mark(c, PV_PROF_DOWN, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, w.rowsum, rows, len, part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_DOWN, l, 1, s)) != PV_OK) return rc;
     }
     k_pre_commit<<<1, 64, 0, s>>>(c->ws.state, rows, keep);

@@ -11,4 +11,4 @@ size_t pv_pre_bytes(const pv_model *m, int max_tokens);
 int pv_pre_init(const pv_model *m);
 // rows tokens through all layers; the first rows - keep are committed, the last `keep` (a multiple of 16 rows behind the
 // start) are left as the cache's running block
-int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows, int keep, float *tile_part, size_t part_floats, pv_pre_out *out, hipStream_t s);
+int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows, int keep, pv_pre_out *out, hipStream_t s);

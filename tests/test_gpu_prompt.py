@@ -99,3 +99,41 @@ def test_rollback_and_readmit_after_a_long_prompt():
     a.prefill(toks[150:])
     b.prefill(toks[:150]); b.prefill(toks[150:])
     assert a.state() == b.state() and np.array_equal(a.export(), b.export())
+
+
+@pytest.mark.parametrize("bits", [0x3580, 0x4600, 0x8000, 0xBC00], ids=["small", "large", "minus_zero", "negative"])
+def test_scales_at_the_ends(bits):
+    """4-bit weights go into long prompts as 16-bit floats unless some scale of the model does not fit that form
+    (0x3580 = 2^-20, 0x4600 = 2^13; -0 and negative scales fit): either way as with the blocks of 64 tokens, which use the bf16 scales as they are."""
+    import paper_2505_01572_amd as pv
+    from gpu_helpers import logit_scale, paired_models
+    shape = SHAPES["q4"]
+    gm, _ = paired_models(shape)
+    arr = pv_inputs.fill_tensor(shape, "wo", 0).reshape(pv_inputs.tensor_shape(shape, "wo"))
+    codes, scales = pv_inputs.quantize_q4(arr)
+    scales[5, 3] = bits
+    gm.load_weights_q4("wo", 0, 0, codes, scales)
+    toks = pv_inputs.uniform_tokens(74, 200, shape.vocab)
+    a, b = pv.Cache(gm, 256), pv.Cache(gm, 256)
+    a.prefill(toks)
+    for i in range(0, 200, 64):
+        b.prefill(toks[i:i + 64])
+    la, lb = a.debug_logits(), b.debug_logits()
+    assert np.isfinite(la).all() and (np.abs(la - lb) / logit_scale(lb)).max() < 2e-3
+
+
+def test_large_activations_of_a_4bit_model():
+    """An FFN gain of 2^20: operands of 2^20 and (SwiGLU) some 2^38, whose rows are scaled before they become 16-bit floats.  (Larger
+    gains would overflow the sums of squares in fp32 on any path.)"""
+    import paper_2505_01572_amd as pv
+    from gpu_helpers import logit_scale, paired_models
+    shape = SHAPES["q4"]
+    gm, _ = paired_models(shape)
+    gm.load_weights("ffn_norm", 0, 0, np.full((1, shape.d_model), 0x4980, dtype=np.uint16))
+    toks = pv_inputs.uniform_tokens(75, 200, shape.vocab)
+    a, b = pv.Cache(gm, 256), pv.Cache(gm, 256)
+    a.prefill(toks)
+    for i in range(0, 200, 64):
+        b.prefill(toks[i:i + 64])
+    la, lb = a.debug_logits(), b.debug_logits()
+    assert np.isfinite(lb).all() and np.abs(lb).max() > 0 and (np.abs(la - lb) / logit_scale(lb)).max() < 2e-3

@@ -37,7 +37,7 @@ __device__ inline float block_max(float v, float *red)
 
 // The small models of this path are bound by launches and memory round trips, not bytes: a step of the tiny
 // configuration took 158 us in 28 kernels of 2..5 us (attention 27 us), with some 4 us between dependent ones.
-// (now 90 us in 12).  RMSNorm, the rotary embedding and the page writes, SwiGLU and the vocabulary arg-max ride in the
+// (now 92 us in 13).  RMSNorm, the rotary embedding and the page writes, SwiGLU and the vocabulary arg-max ride in the
 // projections: a wave that multiplies a weight row with the input rows passes over the whole rows
 // anyway and adds up their squares beside it (the norm's scale commutes with the dot product).
 

@@ -14,7 +14,7 @@ prefix 2048, gamma 8): `value` = verified draft positions per second (gamma * st
 `roofline` = the dominant kernel (the gate/up projection stream), timed with HIP events on the
 step's stream in a second, instrumented pass over the same steps; `stream_ceiling` = what a plain
 read-only stream of the step's byte count reaches on this device in this run; `prefill_tokens_per_s` =
-the prompt's rate when it was fed in (once, 64-row chunks, outside the timed region); `cpu_baseline` =
+the prompt's rate when it was fed in (once, outside the timed region); `cpu_baseline` =
 the CPU oracle timed on a bounded slice of the same workload.  With no --workload / --gamma
 given, `also` carries the other points of the metric measured the same way in the same run:
 the 8B shape at gamma 1, 4, 16, batched verification of 4 sequences x gamma 8 on the 8B shape, and the
@@ -187,7 +187,7 @@ class Workload:
              "verified_tokens_per_s": gamma * K / elapsed, "committed_tokens_per_s": accepted / elapsed,
              "mean_accepted_len": accepted / K, "step_bytes": step_bytes,
              "step_hbm_gbps": step_bytes / (elapsed / K) / 1e9, "step_hbm_frac": step_bytes / (elapsed / K) / 1e9 / HBM_PEAK_GBPS,
-             "prefill_tokens_per_s": self.T0 / self.prefill_s}     # the prompt, once, in 64-row chunks (untimed region; wall clock with its launch)
+             "prefill_tokens_per_s": self.T0 / self.prefill_s}     # the prompt, once (untimed region; wall clock with its launch)
         if prof_kernel:
             c.rollback(T)
             c.set_pending(int(self.G[T - self.T0]))

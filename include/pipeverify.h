@@ -102,7 +102,7 @@ typedef struct pv_cache pv_cache;   /* one sequence of one stage             */
 int pv_model_bytes(const pv_model_config *cfg, size_t *weight_bytes, size_t *staging_bytes);
 
 /* page_pool_bytes: KV pages for max_tokens tokens.  workspace_bytes: activations, partial
- * results, logits of one step. */
+ * results, logits of one step, and (matrix path) the buffers of a prompt's chunks. */
 int pv_cache_bytes(const pv_model *m, int32_t max_tokens, size_t *page_pool_bytes, size_t *workspace_bytes);
 
 /* ---- objects ---- */
@@ -149,8 +149,10 @@ int pv_cache_set_page_table(pv_cache *c, const int32_t *phys_pages, int32_t n_pa
 
 /*
  * The prefill phase of Sec. 2.1 (the prompt is processed in parallel before decoding starts):
- * append n prompt tokens (host array), all accepted, in chunks of at most max_gamma rows
- * (matrix path: of up to 64 rows, whatever max_gamma is).
+ * append n prompt tokens (host array), all accepted, in chunks of at most max_gamma rows (matrix
+ * path, whatever max_gamma is: of up to 64 rows, or of up to 2048 where more than 64 are left).
+ * What a call leaves behind (pv_debug_logits, pv_debug_pred, pv_cache_readmit, and what is not committed when a
+ * row has no finite logit) is that of the last max_gamma (matrix path: 64) rows, as if all chunks had that size.
  * Afterwards length += n and pending = the stage's greedy token after the prompt.
  * Synchronises hip_stream before returning.
  */

@@ -5,7 +5,7 @@
 // densely (row m = head_in_group * gamma + j).  Two shapes of the unit:
 //   TILES = 1: up to 16 rows, 256 keys; every wave takes 32 keys of the one 16-row tile;
 //   TILES = 2: 17..32 rows, 128 keys; wave w takes row tile w / 4 and 32 keys (w % 4).
-// Either way a wave makes one pass.  The waves of a row tile are merged through LDS (every
+// A wave makes one pass (in a short context the workgroup goes through all chunks, one pass each).  The waves of a row tile are merged through LDS (every
 // wave writes its rescaled partial, then all threads add them in wave order) into one partial
 // (max, sum, output) per chunk; a small merge kernel combines the chunks and writes the
 // attention output directly as the output projection's split-bf16 operand.

@@ -6,7 +6,7 @@
 #include "pipeverify.h"
 
 #define PV_MAX_ROWS 64          // hard cap on rows per block (max_gamma)
-#define PV_PRE_ROWS 2048        // most rows of one long-prompt pass (its buffers are part of a cache's workspace: 88 KiB a row for an 8B shape)
+#define PV_PRE_ROWS 2048        // most rows of one long-prompt pass (its buffers are part of a cache's workspace: 88 KiB a row for an 8B shape, and 32 MiB)
 #define PV_KEY_BUCKETS 24       // attention grids of recorded steps are sized for the next power of two of (length + rows)
 #define PV_ROW_PAD 16           // activation buffers are padded to a multiple of this many rows
 

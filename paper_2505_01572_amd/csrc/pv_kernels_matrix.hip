@@ -951,8 +951,9 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
             else if (g.ktiles >= 64) k_gemm<1, 1, 1, EPI, 16, 4><<<strips, 1024, 0, s>>>(ga);
             else k_gemm<1, 1, 1, EPI, 8, 4><<<strips, 512, 0, s>>>(ga);
         } else {
-            // 4-bit weights, 9..64 rows: activation tiles shared through LDS, two strips per wave, one workgroup per CU
-            // (256 registers a lane); few strips: cut along K so that about 256 workgroups run, as for 16-bit weights
+            // 4-bit weights, 9..64 rows: activation tiles shared through LDS, two strips per wave.  Few strips: cut along K.  Up to 32 rows two
+            // workgroups fit on a CU (120 registers): at most 512 of them in one round (8B shape, 4 layers: 13 rows 396 -> 356 us a
+            // step against 256 and one per CU, 24 rows 483 -> 442); more rows: one per CU, at most 256
             const int nbat = g.ktiles / 4, ngroups = (strips + 15) / 16;
             int slices = g.tile_part == nullptr ? 1 : max(1, min(TILE_MAX_SLICES, (CT <= 2 ? 512 : 256) / ngroups));
             int bps = max(CT <= 2 ? 2 : 4, (nbat + slices - 1) / slices);

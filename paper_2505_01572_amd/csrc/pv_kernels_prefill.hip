@@ -254,13 +254,14 @@ k_pre_gemm(const gemm_args a, const pre_gemm_args p)
 }
 
 // ------------------------------------------------------------------------------------------
-// The same for 4-bit weights: 128 rows x 64 FT features, 2 x 4 waves, each 4 row tiles x FT strips.
+// The same for 4-bit weights (of models with scales that k_pre_gemm_h4 below does not hold): 128 rows x 64 FT features, 2 x 4 waves, each 4
+// row tiles x FT strips.
 // Arithmetic as in k_gemm<WB = 4> (codes enter as 16 + c on top of -24 x the row sums, product taken
 // transposed, scaled per K-tile); the row sums of the operand come from k_pre_rowsum.  Per K-tile a
 // wave expands FT code tiles (9 vector instructions each) and scales 4 FT products (4 each) beside 8 FT MFMAs: the
 // vector ALU is busy 80 % of the time that the matrix cores need, so the products are scaled one group of strips
 // behind the MFMAs, and the two waves of a SIMD fill each other's gaps.  1000 tokens through two 70B-shaped layers:
-// 10.9 -> 7.0 ms; gate/up 1.82 ms, 1030 TFLOP/s of MFMAs (FT = 8, without the second level of accumulators: the same).
+// 11.5 ms in blocks of 64 rows, 7.0 here; gate/up 1.82 ms, 1030 TFLOP/s of MFMAs (FT = 8, without the second level of accumulators: the same).
 // In LDS: activation stages of one K-tile, and two buffers of a batch of 4 K-tiles of codes, scales and row sums.
 // ------------------------------------------------------------------------------------------
 template <int FT> struct pre_q4_shape {

@@ -41,9 +41,9 @@ struct mat_ws {                 // carved out of pv_ws::part
 
 static inline size_t xop_elems(int K) { return (size_t)2 * (K / 32) * 512; }   // hi and lo arrays of one 16-row column tile
 static inline int col_tiles(int rows) { return rows <= 16 ? 1 : rows <= 32 ? 2 : 4; }
-// K-slice partial sums of the shared-tile GEMMs: slices x strips x column tiles KiB.  The launches cut a GEMM of fewer than
-// 192 workgroups into at most 16 slices and about 256 workgroups in all, which bounds slices x strips by 16 x 256 + 16 x 191
-// (16 strips per workgroup; fewer with 8), i.e. under 2 Mi floats per column tile; 24 MiB in all, which the launches stay under.
+// K-slice partial sums of the shared-tile GEMMs: slices x strips x column tiles KiB.  The launches cut a GEMM into at most 16
+// slices and 256 workgroups in all (512 for 4-bit weights and up to 32 rows), which bounds slices x strips by 16 x 512 (16 strips per
+// workgroup; fewer with 8), i.e. 2 Mi floats per column tile; 24 MiB in all, which the launches stay under.
 static const size_t TILE_PART_FLOATS = (size_t)6 << 20;
 static inline size_t tile_part_floats(int col_tiles) { return std::min(TILE_PART_FLOATS, (size_t)col_tiles << 21); }
 // blocks that use those kernels: more than 16 rows, or any block of more than 8 rows with 4-bit weights
@@ -595,11 +595,19 @@ k_gemm_tile(const gemm_args a, int tps, float4 *part)
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) ssq_issue(a.ssq + (size_t)ct * a.ssq_parts * 16, a.ssq_parts, threadIdx.x, NW * 64, sl[ct]);
     }
-    f32x4 acc[S][CT];
+    f32x4 acc[S][CT], tot[S][CT];
 #pragma unroll
     for (int si = 0; si < S; ++si)
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) acc[si][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int ct = 0; ct < CT; ++ct) acc[si][ct] = tot[si][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    // An accumulator takes 16 K-tiles, then it is added to the total: over a whole slice of up to 448 it would carry a rounding error
+    // of the size of the operands' own
+    auto add_up = [&]() {
+#pragma unroll
+        for (int si = 0; si < S; ++si)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) { tot[si][ct] += acc[si][ct]; acc[si][ct] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+    };
 
     struct slot { uint4 x0, x1, w[S][U]; };           // one step in flight: the wave's one or two activation tiles, its weight tiles
     auto first_tile = [&](int step) { int k = step + rot; if (k >= nsteps) k -= nsteps; return t0 + k * U; };
@@ -655,17 +663,19 @@ k_gemm_tile(const gemm_args a, int tps, float4 *part)
         use(q1, 1, s0 + 1); issue(q1, min(s0 + 5, nsteps - 1));
         use(q2, 0, s0 + 2); issue(q2, min(s0 + 6, nsteps - 1));
         use(q3, 1, s0 + 3); issue(q3, min(s0 + 7, nsteps - 1));
+        if (s0 & D) add_up();
     }
     if (s0 < nsteps) use(q0, 0, s0);
     if (s0 + 1 < nsteps) use(q1, 1, s0 + 1);
     if (s0 + 2 < nsteps) use(q2, 0, s0 + 2);
+    add_up();
 
     if (part != nullptr) {
 #pragma unroll
         for (int si = 0; si < S; ++si)
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
-                if (sw + si < a.nstrips) part[(((size_t)blockIdx.y * a.nstrips + sw + si) * CT + ct) * 64 + lane] = make_float4(acc[si][ct][0], acc[si][ct][1], acc[si][ct][2], acc[si][ct][3]);
+                if (sw + si < a.nstrips) part[(((size_t)blockIdx.y * a.nstrips + sw + si) * CT + ct) * 64 + lane] = make_float4(tot[si][ct][0], tot[si][ct][1], tot[si][ct][2], tot[si][ct][3]);
         return;
     }
     __syncthreads();                                  // (ssq_s of every wave; also covers a slice of a single step)
@@ -683,7 +693,7 @@ k_gemm_tile(const gemm_args a, int tps, float4 *part)
                 for (int w = 1; w < NW; ++w) tot += ssq_s[w][ct][lane & 15];
                 pre.rj = 1.0f / sqrtf(tot * a.inv_d + a.eps);
             }
-            epi_apply<2, EPI>(a, strip, lane, acc[si][ct], pre, ct);
+            epi_apply<2, EPI>(a, strip, lane, tot[si][ct], pre, ct);
         }
     }
 }
@@ -971,10 +981,12 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         // strips keeps one strip per workgroup and more waves instead.
         constexpr int S = CT == 1 ? 2 : 4, NW = CT == 1 ? 8 : 4;
         if constexpr (CT >= 2) {
-            // activation tiles shared through LDS; few strips: cut along K so that about 256 workgroups run
+            // Activation tiles shared through LDS; few strips: cut along K, into at most 256 workgroups, one a CU: with a few more (288 for the
+            // 8B-shaped QKV projection, 344 for the 7B-shaped gate/up) some CUs have two and the others wait for them (4 layers, us a step: 8B 32
+            // rows 542 -> 528, 48 rows 632 -> 614; 7B 24 rows 552 -> 492; up to 512 workgroups: 570, 663, 567)
             if (g.ktiles >= 16) {
                 const int ngroups = (strips + 7) / 8;
-                int slices = (ngroups >= 192 || g.tile_part == nullptr) ? 1 : min(TILE_MAX_SLICES, (256 + ngroups - 1) / ngroups);
+                int slices = g.tile_part == nullptr ? 1 : max(1, min(TILE_MAX_SLICES, 256 / ngroups));
                 int tps = (g.ktiles + slices - 1) / slices;
                 tps = max(8, (tps + 1) & ~1);                        // whole steps, at least four per slice
                 slices = (g.ktiles + tps - 1) / tps;

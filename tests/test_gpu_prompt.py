@@ -137,3 +137,33 @@ def test_large_activations_of_a_4bit_model():
         b.prefill(toks[i:i + 64])
     la, lb = a.debug_logits(), b.debug_logits()
     assert np.isfinite(lb).all() and np.abs(lb).max() > 0 and (np.abs(la - lb) / logit_scale(lb)).max() < 2e-3
+
+
+@pytest.mark.parametrize("name,before,n,page", [("gqa64", 1000, 5000, 16), ("mha128", 700, 4400, 64), ("q4", 300, 4500, 16)])
+def test_several_passes(name, before, n, page):
+    test_long_prompt(name, before, n, page)
+
+
+@pytest.mark.parametrize("heads,kv_heads,head_dim", [(2, 2, 128), (8, 2, 64), (4, 1, 128)])
+def test_attention_error_does_not_grow_with_the_context(heads, kv_heads, head_dim):
+    """A prompt of one repeated token: all values are equal, so attention's exact output, and with one layer every row's
+    logits, are those of the single token whatever the length.  What 12000 keys add in rounding errors stays within 1.4 times what
+    300 add (rms over 40 or more rows; one accumulator over all keys: 1.5 to 2.2 times)."""
+    import paper_2505_01572_amd as pv
+    from gpu_helpers import gpu_model, logit_scale
+    shape = S("pr_same", 1, 256, heads, kv_heads, head_dim, 352, 512, rope_base=500000.0, seed=7401, page_tokens=64)
+    wo = pv_inputs.fill_tensor(shape, "wo", 0).reshape(pv_inputs.tensor_shape(shape, "wo"))
+    large = {("wo", 0): (wo + np.uint16(4 << 7)).astype(np.uint16)}                # times 16: attention's output dominates the residual
+    gm = gpu_model(shape, gains="perturbed", overrides=large)
+    want = ref.RefCache(ref_model(shape, gains="perturbed", overrides=large), 8, ref.KV_BF16).prefill(np.array([7], dtype=np.int32))
+    one = pv.Cache(gm, 8)
+    one.prefill([7])
+    base = one.debug_logits()
+    rms = {}
+    for n in (300, 12000):
+        c = pv.Cache(gm, n)
+        c.prefill(np.full(n, 7, dtype=np.int32))
+        lg = c.debug_logits()
+        assert len(lg) >= 32 and np.sqrt((((lg - want) / logit_scale(want)) ** 2).mean()) < 4e-6
+        rms[n] = np.sqrt((((lg - base) / logit_scale(want)) ** 2).mean())
+    assert rms[12000] < 1.4 * rms[300], rms

@@ -48,10 +48,13 @@ __device__ inline int xcd_order(int bid, int total)
 // tiles of a stage: activations (hi, lo), weights, rounded up so that every wave copies the same number (what is beyond is a strip more, not used)
 constexpr int pre_stage_tiles(int br, int bf) { return (2 * br + bf + 7) / 8 * 8; }
 
-// K-tiles added up in one accumulator before it is added to the total: an accumulator that ran over the whole K would carry
-// a rounding error of the size of the operands' own (measured on K and V of a first layer, d = 8192: 40 % more bf16 values
-// off the 64-bit result than with blocks of 64 rows, whose K is cut over workgroups or waves; runs of 16: 15 % fewer)
-#define PRE_RUN 16
+// K-tiles added up in one accumulator before it is added to the total.  An accumulator that ran over the whole K would carry
+// a rounding error of the size of the operands' own.  Blocks of 64 rows cut K over workgroups, into runs of at least 8 (K of 2048) to 16 (4096)
+// tiles for the projections with few strips; a prompt's values must not be further off.  Keys and values of a first layer that are not the rounded
+// 64-bit result, 1000 tokens, runs of 16 / runs of 8 / blocks of 64 rows: K = 2048 2.16 / 1.76 / 1.76e-4, K = 2080 2.19 / 1.82 /
+// 1.85e-4, K = 4096 2.41 / 1.97 / 2.22e-4 (one accumulator for each slice of K, as those blocks had: 2.68e-4), K = 8192 2.62 / 2.05 / 2.53e-4
+// (4.34e-4).  Runs of 8 take 2 % more time (8B shape, 2048 tokens: 6.60 -> 6.73 ms), hence only where they are needed.
+static inline int pre_run(int ktiles) { return ktiles < 128 ? 8 : 16; }
 
 struct pre_gemm_args {
     const float *rscale;        // RMSNorm scale of each row (QKV, SWIGLU)
@@ -59,6 +62,7 @@ struct pre_gemm_args {
     int mtiles;                 // 16-row tiles of the block
     int rb, fb;                 // rectangles along the rows and the features
     int kps;                    // K-tiles per slice
+    int run;                    // K-tiles per accumulator (pre_run): a multiple of 4
     int rows, len;              // rows of the block, and the position of the first
     const float *rowsum; int rsum_rows;   // 4-bit weights: -24 x the operand's row sums, [K-tile][rsum_rows]
     const float *rinv;          // 16-bit float operand: what its rows' sums have to be multiplied with (null: nothing)
@@ -152,7 +156,7 @@ __device__ inline void pre_epilogue(const gemm_args &a, const pre_gemm_args &p, 
 // row tile's MFMAs of stage k, whose operands are in registers, so the matrix cores have work while
 // the next stage's first operands come out of LDS.  One barrier per K-tile.
 // 256 x 256 rectangles (half the operand traffic) were 4 % faster where they fill the CUs, but leave no registers
-// for the second level of accumulators (PRE_RUN).
+// for the second level of accumulators (pre_run).
 // ------------------------------------------------------------------------------------------
 template <int WR, int WF, int RT, int FT, int NST, int EPI>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -231,7 +235,7 @@ k_pre_gemm(const gemm_args a, const pre_gemm_args p)
     read_w(wa, 0);
     read_x(0, 0);
     for (int s = 0; s < n;) {
-        const int e = min(s + PRE_RUN, n);
+        const int e = min(s + p.run, n);
         for (; s + 2 <= e; s += 2) { step(s, wa, wb); step(s + 1, wb, wa); }
         if (s < e) { step(s, wa, wb); ++s; }
 #pragma unroll
@@ -392,10 +396,11 @@ k_pre_gemm_q4(const gemm_args a, const pre_gemm_args p)
     pre_wait<(NST - 2) * NX>();
     read_c(0, 0);
     read_x(0, 0, 0, 0);
-    for (int b = 0; b < nb; ++b) {
+    for (int b = 0, left = p.run >> 2; b < nb; ++b) {
         step(b, std::integral_constant<int, 0>()); step(b, std::integral_constant<int, 1>());
         step(b, std::integral_constant<int, 2>()); step(b, std::integral_constant<int, 3>());
-        if ((b + 1) % (PRE_RUN / 4) == 0 || b + 1 == nb) {
+        if (--left == 0 || b + 1 == nb) {
+            left = p.run >> 2;
 #pragma unroll
             for (int r = 0; r < RT; ++r)
 #pragma unroll
@@ -559,10 +564,11 @@ k_pre_gemm_h4(const gemm_args a, const pre_gemm_args p)
     read_x(0, 0);
 #pragma unroll
     for (int f = 0; f < FT; ++f) wa[f] = expand(f, false);
-    for (int b = 0; b < nb; ++b) {
+    for (int b = 0, left = p.run >> 2; b < nb; ++b) {
         step(b, std::integral_constant<int, 0>(), wa, wb); step(b, std::integral_constant<int, 1>(), wb, wa);
         step(b, std::integral_constant<int, 2>(), wa, wb); step(b, std::integral_constant<int, 3>(), wb, wa);
-        if ((b + 1) % (PRE_RUN / 4) == 0 || b + 1 == nb) {
+        if (--left == 0 || b + 1 == nb) {
+            left = p.run >> 2;
 #pragma unroll
             for (int r = 0; r < RT; ++r)
 #pragma unroll
@@ -1023,7 +1029,7 @@ static int pre_gemm(const pv_model *m, const gemm_args &g, int strips, const flo
     gemm_args ga = g;
     ga.nstrips = strips;
     pre_gemm_args pa = {};
-    pa.rscale = rscale; pa.part = (float4 *)g.tile_part; pa.mtiles = mtiles; pa.rows = rows; pa.len = len;
+    pa.rscale = rscale; pa.part = (float4 *)g.tile_part; pa.mtiles = mtiles; pa.run = pre_run(g.ktiles); pa.rows = rows; pa.len = len;
     const bool h4 = m->wbits == 4 && !m->q4_wide;      // every scale of the model fits the f16 form of its weights
     if (h4) {
         float *rinv = rowsum, *part = rowsum + (mtiles + 7) / 8 * 128;       // (in the place of the row sums)

@@ -719,9 +719,11 @@ __global__ void k_pre_commit(pv_dev_state *st, int rows, int keep)
 // at a time through LDS (two buffers, copied a step ahead).  Products, operand orders and splits are those
 // of attn_chunk (pv_attention_body.h); the softmax is kept running (maximum and sum per row).
 // The matrix cores add up the 64 keys of a step only: the step's P x V and its sum of weights are added to the running totals on the
-// vector ALU (by the multiply-add that also rescales them).  In one accumulator over all keys the rounding errors grew with the
-// context: a prompt of one repeated token, whose exact output is the same at any length, was off by 1.1 - 1.3e-6 of the logits' rms at 300
-// keys and 1.8 - 2.5e-6 at 12000; now 1.2 - 1.4e-6 at 12000, at the same speed (2048 tokens, 8B shape, 4 layers: 6.68 ms either way).
+// vector ALU (by the multiply-add that also rescales them), one feature tile behind the matrix cores.  In one accumulator over all
+// keys the rounding errors grew with the context: a prompt of one repeated token, whose exact output is the same at any length, was
+// off by 1.1 - 1.3e-6 of the logits' rms at 300 keys and 1.8 - 2.5e-6 at 12000; now 1.2 - 1.4e-6 at 12000.  The additions cost 1 - 4 %
+// (8B shape, passes of 12000 tokens: 443 -> 447 us a layer; 2048 tokens, 7B shape: 115 -> 119 us), 5 - 8 % without the lag and
+// with the exponent's difference and product as two instructions.
 // Every query row reads K and V once per workgroup from L2 instead of once per 32 rows as partial
 // results: at 2048 keys the chunked kernel with its merge took 26 us per 64 rows of an 8B-shaped layer.
 // ------------------------------------------------------------------------------------------
@@ -786,10 +788,10 @@ k_pre_attn(const pre_attn_args a)
     __builtin_amdgcn_s_waitcnt(0);
     asm volatile("" ::: "memory");
     f32x4 O[RT][ET];
-    float mx[RT], sum[RT];
+    float mx[RT], mxs[RT], sum[RT];                    // maximum (as it is, and times scale2), sum
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-        mx[t] = -INFINITY; sum[t] = 0.f;
+        mx[t] = mxs[t] = -INFINITY; sum[t] = 0.f;
 #pragma unroll
         for (int e = 0; e < ET; ++e) O[t][e] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
@@ -828,24 +830,32 @@ k_pre_attn(const pre_attn_args a)
             for (int q = 0; q < 4; ++q) m = fmaxf(fmaxf(m, fmaxf(S[t][q][0], S[t][q][1])), fmaxf(S[t][q][2], S[t][q][3]));
             m = fmaxf(m, __shfl_xor(m, 16, 64));
             m = fmaxf(m, __shfl_xor(m, 32, 64));
-            f[t] = __builtin_amdgcn_exp2f((mx[t] - m) * a.scale2);     // (key 0 is visible to every row: the maximum is finite from the first step on)
-            mx[t] = m;
+            const float ms = m * a.scale2;             // (key 0 is visible to every row: the maximum is finite from the first step on)
+            f[t] = __builtin_amdgcn_exp2f(mxs[t] - ms);
+            mx[t] = m; mxs[t] = ms;
             float ps = 0.f;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 float p[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) { p[r] = __builtin_amdgcn_exp2f((S[t][q][r] - m) * a.scale2); ps += p[r]; }
+                for (int r = 0; r < 4; ++r) { p[r] = __builtin_amdgcn_exp2f(fmaf(S[t][q][r], a.scale2, -ms)); ps += p[r]; }
                 split2(p[0], p[1], P[t][q][0], P[t][q][2]);
                 split2(p[2], p[3], P[t][q][1], P[t][q][3]);
             }
             sum[t] = fmaf(sum[t], f[t], ps);
         }
+        f32x4 T[2][RT];                                // (added to the totals one feature tile behind the matrix cores)
+        auto add = [&](int e) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) O[t][e][r] = fmaf(O[t][e][r], f[t], T[e & 1][t][r]);
+        };
 #pragma unroll
         for (int e = 0; e < ET; ++e) {
-            f32x4 T[RT];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int t = 0; t < RT; ++t) T[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            for (int t = 0; t < RT; ++t) T[e & 1][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int hq = 0; hq < 2; ++hq) {
                 const uint2 v0 = *(const uint2 *)(Lv + (2 * hq) * TB * 1024 + e * 512), v1 = *(const uint2 *)(Lv + (2 * hq + 1) * TB * 1024 + e * 512);
@@ -854,15 +864,13 @@ k_pre_attn(const pre_attn_args a)
                 for (int t = 0; t < RT; ++t) {
                     const uint4 ph = make_uint4(P[t][2 * hq][0], P[t][2 * hq][1], P[t][2 * hq + 1][0], P[t][2 * hq + 1][1]);
                     const uint4 pl = make_uint4(P[t][2 * hq][2], P[t][2 * hq][3], P[t][2 * hq + 1][2], P[t][2 * hq + 1][3]);
-                    T[t] = mfma16(v, ph, T[t]);
-                    T[t] = mfma16(v, pl, T[t]);
+                    T[e & 1][t] = mfma16(v, ph, T[e & 1][t]);
+                    T[e & 1][t] = mfma16(v, pl, T[e & 1][t]);
                 }
             }
-#pragma unroll
-            for (int t = 0; t < RT; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) O[t][e][r] = fmaf(O[t][e][r], f[t], T[t][r]);
+            if (e > 0) add(e - 1);
         }
+        add(ET - 1);
     }
 #pragma unroll
     for (int t = 0; t < RT; ++t) {

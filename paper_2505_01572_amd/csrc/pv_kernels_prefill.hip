@@ -13,11 +13,16 @@
 #include <type_traits>
 
 // One 1 KiB operand tile (64 lanes x 16 bytes) from global memory straight into LDS.  Written in assembly (there is
-// no output register) because the compiler otherwise waits for every copy in flight before any LDS read; the
-// kernels wait for the copies by count (pre_wait).  src is uniform, voff the lane's byte offset behind it.
+// no vector output register) because the compiler otherwise waits for every copy in flight before any LDS read; the
+// kernels wait for the copies by count (pre_wait).  src is uniform, voff the lane's byte offset behind it.  m0 is put back:
+// the compiler may hold a value of its own in it, and a clobber list does not tell it otherwise (m0 is a reserved register there: it
+// warns, and reuses the value all the same).  0.3 % of a prompt's time (8B shape, 2048 tokens: 6.68 -> 6.70 ms); 0.9 % with an s_nop behind
+// it, which only an instruction that reads m0 next would need: tests/test_lds_copies.py sees to it that there is none.
 __device__ inline void dma_tile(uint32_t lds, const void *src, uint32_t voff)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(src) : "memory");
+    uint32_t m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0) : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(src) : "memory");
 }
 
 __device__ inline uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }

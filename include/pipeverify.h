@@ -89,7 +89,7 @@ typedef struct {
 
 #define PV_Q4_GROUP 32      /* input features per scale of a 4-bit matrix */
 
-typedef struct pv_model pv_model;   /* immutable once all weights are loaded */
+typedef struct pv_model pv_model;   /* immutable once all weights are loaded (but for the prompts' buffers, see pv_prompt_bytes) */
 typedef struct pv_cache pv_cache;   /* one sequence of one stage             */
 
 /* ---- sizes: the caller allocates all device memory ----
@@ -97,17 +97,25 @@ typedef struct pv_cache pv_cache;   /* one sequence of one stage             */
  * loading and cache management: everything from here to pv_cache_set_page_table is this library's
  * own design around the public LLaMA decoder definition.) */
 
-/* weight_bytes: device arena for all weights (+ small tables).  staging_bytes: device scratch
+/* weight_bytes: device arena for all weights (+ small tables) and, behind them, the activations of long prompts
+ * (pv_prompt_bytes for 2048 rows).  staging_bytes: device scratch
  * used only while pv_load_weights runs (may be freed after the last load has completed). */
 int pv_model_bytes(const pv_model_config *cfg, size_t *weight_bytes, size_t *staging_bytes);
 
+/* The part of weight_bytes that is for prompts put in `rows` (0 .. 2048, rounded up to a multiple of 64) tokens a pass:
+ * about 8.3 * d_model + max(4 * ffn_dim, 8 * n_q_heads * head_dim) bytes a row and at most 32 MiB of partial sums, for
+ * 2048 rows 211 MiB (8B shape), 389 MiB (70B) or 130 MiB (1B), up to 2 % more with 4-bit weights; none on the vector path.  It is optional: pv_model_create
+ * takes any arena from weight_bytes less the bytes of 2048 rows upwards and puts in as many tokens a pass as fit (none: blocks of
+ * 64, as prompts of up to 64 tokens go in).  One part serves all caches of the model: their prompts take turns, pass by pass. */
+int pv_prompt_bytes(const pv_model_config *cfg, int32_t rows, size_t *bytes);
+
 /* page_pool_bytes: KV pages for max_tokens tokens.  workspace_bytes: activations, partial
- * results, logits of one step, and (matrix path) the buffers of a prompt's chunks. */
+ * results, logits of one step. */
 int pv_cache_bytes(const pv_model *m, int32_t max_tokens, size_t *page_pool_bytes, size_t *workspace_bytes);
 
 /* ---- objects ---- */
 
-/* d_weights / d_staging: device, 256-byte aligned, at least the sizes reported above. */
+/* d_weights / d_staging: device, 256-byte aligned, at least the sizes reported above (d_weights: see pv_prompt_bytes). */
 int pv_model_create(const pv_model_config *cfg, void *d_weights, size_t weight_bytes,
                     void *d_staging, size_t staging_bytes, pv_model **out);
 void pv_model_destroy(pv_model *m);
@@ -150,7 +158,7 @@ int pv_cache_set_page_table(pv_cache *c, const int32_t *phys_pages, int32_t n_pa
 /*
  * The prefill phase of Sec. 2.1 (the prompt is processed in parallel before decoding starts):
  * append n prompt tokens (host array), all accepted, in chunks of at most max_gamma rows (matrix
- * path, whatever max_gamma is: of up to 64 rows, or of up to 2048 where more than 64 are left).
+ * path, whatever max_gamma is: of up to 64 rows, or of as many as pv_prompt_bytes provides for where more than 64 are left).
  * What a call leaves behind (pv_debug_logits, pv_debug_pred, pv_cache_readmit, and what is not committed when a
  * row has no finite logit) is that of the last max_gamma (matrix path: 64) rows, as if all chunks had that size.
  * Afterwards length += n and pending = the stage's greedy token after the prompt.

@@ -30,7 +30,7 @@ class pv_model_config(ctypes.Structure):
 
 
 EXPORTS = [
-    "pv_model_bytes", "pv_cache_bytes", "pv_model_create", "pv_model_destroy", "pv_load_weights",
+    "pv_model_bytes", "pv_prompt_bytes", "pv_cache_bytes", "pv_model_create", "pv_model_destroy", "pv_load_weights",
     "pv_cache_create", "pv_cache_destroy", "pv_cache_set_page_table", "pv_prefill", "pv_verify",
     "pv_verify_async", "pv_verify_wait", "pv_rollback", "pv_cache_len", "pv_cache_set_pending",
     "pv_debug_logits", "pv_debug_pred", "pv_cache_export", "pv_step_bytes", "pv_strerror", "pv_last_error",
@@ -51,6 +51,7 @@ def lib():
         P = ctypes.POINTER
         cfgp = P(pv_model_config)
         L.pv_model_bytes.argtypes = [cfgp, P(sz), P(sz)]
+        L.pv_prompt_bytes.argtypes = [cfgp, i32, P(sz)]
         L.pv_cache_bytes.argtypes = [vp, i32, P(sz), P(sz)]
         L.pv_model_create.argtypes = [cfgp, vp, sz, vp, sz, P(vp)]
         L.pv_model_destroy.argtypes = [vp]; L.pv_model_destroy.restype = None
@@ -140,9 +141,10 @@ def verify_batch(caches, drafts, stream=None):
 class Model:
     """pv_model plus the torch-owned device arena behind it."""
 
-    def __init__(self, shape, max_gamma=16, kernel_path=PATH_AUTO, device="cuda:0"):
+    def __init__(self, shape, max_gamma=16, kernel_path=PATH_AUTO, device="cuda:0", prompt_rows=2048):
         """shape: object with n_layers, d_model, n_q_heads, n_kv_heads, head_dim, ffn_dim, vocab,
-        rms_eps, rope_base, dtype ("f32"|"bf16"), page_tokens and optionally weight_bits (16 | 4)."""
+        rms_eps, rope_base, dtype ("f32"|"bf16"), page_tokens and optionally weight_bits (16 | 4).
+        prompt_rows: tokens a pass of a long prompt (0: blocks of 64, no memory for them)."""
         self.L, self.shape, self.device = lib(), shape, torch.device(device)
         self.cfg = pv_model_config(shape.n_layers, shape.d_model, shape.n_q_heads, shape.n_kv_heads,
                                    shape.head_dim, shape.ffn_dim, shape.vocab, shape.rms_eps, shape.rope_base,
@@ -151,14 +153,18 @@ class Model:
         self.weight_bits = self.cfg.weight_bits
         wb, sb = ctypes.c_size_t(), ctypes.c_size_t()
         _check(self.L.pv_model_bytes(ctypes.byref(self.cfg), ctypes.byref(wb), ctypes.byref(sb)), "pv_model_bytes")
+        most, part = ctypes.c_size_t(), ctypes.c_size_t()
+        _check(self.L.pv_prompt_bytes(ctypes.byref(self.cfg), 2048, ctypes.byref(most)), "pv_prompt_bytes")
+        _check(self.L.pv_prompt_bytes(ctypes.byref(self.cfg), prompt_rows, ctypes.byref(part)), "pv_prompt_bytes")
+        weights = wb.value - most.value
         with torch.cuda.device(self.device):
-            self.arena = _dev_bytes(wb.value, self.device)
+            self.arena = _dev_bytes(weights + part.value, self.device)
             self.staging = _dev_bytes(sb.value, self.device)
             self.h = ctypes.c_void_p()
             _check(self.L.pv_model_create(ctypes.byref(self.cfg), self.arena.data_ptr(), self.arena.numel(),
                                           self.staging.data_ptr(), self.staging.numel(), ctypes.byref(self.h)),
                    "pv_model_create")
-        self.weight_bytes, self.staging_bytes = wb.value, sb.value
+        self.weight_bytes, self.staging_bytes = weights, sb.value
         self.np_dtype = np.uint16 if shape.dtype == "bf16" else np.float32
 
     def load_weights(self, kind, layer, row_begin, rows, stream=None):

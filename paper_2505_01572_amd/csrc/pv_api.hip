@@ -125,12 +125,30 @@ static size_t layout_arena(const pv_model_config *c, pv_model *m)
     return off;
 }
 
+// buffers of long-prompt passes of up to `rows` rows: behind the weights in the arena
+static size_t prompt_bytes(const pv_model_config *c, int rows)
+{
+    pv_model m = {};
+    m.cfg = *c; m.path = resolve_path(c); m.wbits = c->weight_bits == 4 ? 4 : 16;
+    return align_up(pv_pre_bytes(&m, rows), 256);
+}
+
+extern "C" int pv_prompt_bytes(const pv_model_config *cfg, int32_t rows, size_t *bytes)
+{
+    int rc = check_config(cfg);
+    if (rc != PV_OK) return rc;
+    if (!bytes) { pv_set_error("null output pointer"); return PV_EINVAL; }
+    if (rows < 0 || rows > PV_PRE_ROWS) { pv_set_error("rows %d outside [0, %d]", rows, PV_PRE_ROWS); return PV_ERANGE; }
+    *bytes = prompt_bytes(cfg, (rows + 63) / 64 * 64);
+    return PV_OK;
+}
+
 extern "C" int pv_model_bytes(const pv_model_config *cfg, size_t *weight_bytes, size_t *staging_bytes)
 {
     int rc = check_config(cfg);
     if (rc != PV_OK) return rc;
     if (!weight_bytes || !staging_bytes) { pv_set_error("null output pointer"); return PV_EINVAL; }
-    *weight_bytes = layout_arena(cfg, nullptr);
+    *weight_bytes = layout_arena(cfg, nullptr) + prompt_bytes(cfg, PV_PRE_ROWS);
     *staging_bytes = resolve_path(cfg) >= PV_PATH_MATRIX ? STAGING_BYTES : 256;
     return PV_OK;
 }
@@ -144,6 +162,7 @@ extern "C" int pv_model_create(const pv_model_config *cfg, void *d_weights, size
     if (((uintptr_t)d_weights | (uintptr_t)d_staging) & 255) { pv_set_error("device buffers must be 256-byte aligned"); return PV_EINVAL; }
     size_t need_w, need_s;
     pv_model_bytes(cfg, &need_w, &need_s);
+    need_w = layout_arena(cfg, nullptr);                     // (the prompts' part is optional)
     if (weight_bytes < need_w || staging_bytes < need_s) { pv_set_error("arena %zu < %zu or staging %zu < %zu", weight_bytes, need_w, staging_bytes, need_s); return PV_ENOMEM; }
     pv_model *m = new (std::nothrow) pv_model();
     if (!m) return PV_ENOMEM;
@@ -154,6 +173,8 @@ extern "C" int pv_model_create(const pv_model_config *cfg, void *d_weights, size
     m->layer = (pv_tensor_ref *)calloc((size_t)cfg->n_layers * PV_T_NKINDS, sizeof(pv_tensor_ref));
     if (!m->layer) { delete m; return PV_ENOMEM; }
     layout_arena(cfg, m);
+    m->pre_base = m->d_weights + need_w; m->pre_rows = PV_PRE_ROWS;
+    while (m->pre_rows > 0 && (prompt_bytes(cfg, m->pre_rows) == 0 || need_w + prompt_bytes(cfg, m->pre_rows) > weight_bytes)) m->pre_rows -= 64;
     int dev = 0; hipDeviceProp_t prop;
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) {
         pv_set_error("no HIP device"); free(m->layer); delete m; return PV_EHIP;
@@ -302,7 +323,7 @@ extern "C" int pv_cache_bytes(const pv_model *m, int32_t max_tokens, size_t *pag
     const pv_model_config &c = m->cfg;
     const int n_pages = (max_tokens + c.page_tokens - 1) / c.page_tokens;
     *page_pool_bytes = align_up((size_t)c.n_layers * n_pages * c.n_kv_heads * 2 * c.page_tokens * c.head_dim * m->elt, 256);
-    *workspace_bytes = layout_ws(m, rows_cap_of(m), units_cap_of(m), n_pages, nullptr, nullptr) + pv_pre_bytes(m, max_tokens);
+    *workspace_bytes = layout_ws(m, rows_cap_of(m), units_cap_of(m), n_pages, nullptr, nullptr);
     return PV_OK;
 }
 
@@ -317,14 +338,14 @@ extern "C" int pv_cache_create(const pv_model *m, void *d_page_pool, size_t page
     if (page_pool_bytes < need_p || workspace_bytes < need_w) { pv_set_error("pool %zu < %zu or workspace %zu < %zu", page_pool_bytes, need_p, workspace_bytes, need_w); return PV_ENOMEM; }
     if (m->path >= PV_PATH_MATRIX && (rc = pv_mat_attention_init(m->cfg.head_dim)) != PV_OK) return rc;
     if (m->path >= PV_PATH_MATRIX && m->wbits == 4 && (rc = pv_mat_gemm_init()) != PV_OK) return rc;
-    if (pv_pre_rows(m, max_tokens) && (rc = pv_pre_init(m)) != PV_OK) return rc;
+    if (m->pre_rows && (rc = pv_pre_init(m)) != PV_OK) return rc;
     pv_cache *c = new (std::nothrow) pv_cache();
     if (!c) return PV_ENOMEM;
     c->m = m; c->d_pool = (char *)d_page_pool; c->pool_bytes = page_pool_bytes;
     c->d_ws = (char *)d_workspace; c->ws_bytes = workspace_bytes;
     c->max_tokens = max_tokens; c->n_pages = (max_tokens + m->cfg.page_tokens - 1) / m->cfg.page_tokens;
     c->rows_cap = rows_cap_of(m); c->units_cap = units_cap_of(m);
-    c->pre_base = c->d_ws + layout_ws(m, c->rows_cap, c->units_cap, c->n_pages, &c->ws, c->d_ws); c->pre_rows = pv_pre_rows(m, max_tokens);
+    layout_ws(m, c->rows_cap, c->units_cap, c->n_pages, &c->ws, c->d_ws);
     c->len = 0; c->pending = -1; c->last_rows = 0; c->blk_start = 0; c->blk_rows = 0; c->blk_units = 0; c->blk_seq_rows = 0; c->attn_keys = 0; c->in_flight = false; c->flight_stream = nullptr; c->io = nullptr;
     c->prof_kind = PV_PROF_NONE; c->prof_pending = 0; c->prof_ev = nullptr; c->prof_ms = 0; c->prof_launches = 0;
     c->use_graphs = true; c->cap_stream = nullptr;
@@ -589,16 +610,19 @@ extern "C" int pv_prefill(pv_cache *c, const int32_t *tokens, int32_t n, void *h
     hipStream_t s = (hipStream_t)hip_stream;
     const int chunk = prefill_rows_of(c->m);
     int off = 0;
-    // a long prompt goes in with as few passes over the weights as the cache's buffers allow; its last rows (as many as the
-    // last block would have if all were blocks of `chunk` rows) end up as the running block, with logits and a prediction
-    while (c->pre_rows && n - off > PV_PRE_MIN) {
-        const int rows = n - off < c->pre_rows ? n - off : c->pre_rows;
+    // a long prompt goes in with as few passes over the weights as the model's buffers allow; its last rows (as many as the
+    // last block would have if all were blocks of `chunk` rows) end up as the running block, with logits and a prediction.
+    // Prompts of several caches at once (threads) take turns pass by pass; a pass is through on the device when it ends.
+    while (c->m->pre_rows && n - off > PV_PRE_MIN) {
+        const int rows = n - off < c->m->pre_rows ? n - off : c->m->pre_rows;
         const int keep = off + rows == n ? (rows - 1) % chunk + 1 : 0;
+        std::lock_guard<std::mutex> turn(c->m->pre_mu);
         memcpy(c->io->prompt, tokens + off, sizeof(int32_t) * rows);
         c->io->hdr[2] = keep; c->io->hdr[3] = keep ? PV_MODE_PREFILL_LAST : PV_MODE_PREFILL_MID;
         rc = pv_mat_run_prompt(c, rows, keep, s);
+        const hipError_t e = hipStreamSynchronize(s);
         if (rc != PV_OK) return rc;
-        PV_HIP(hipStreamSynchronize(s));
+        PV_HIP(e);
         c->len += rows - keep;
         if (rows > keep) c->pending = -1;
         c->last_rows = keep;

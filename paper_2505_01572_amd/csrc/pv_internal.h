@@ -3,10 +3,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <mutex>
 #include "pipeverify.h"
 
 #define PV_MAX_ROWS 64          // hard cap on rows per block (max_gamma)
-#define PV_PRE_ROWS 2048        // most rows of one long-prompt pass (its buffers are part of a cache's workspace: 88 KiB a row for an 8B shape, and 32 MiB)
+#define PV_PRE_ROWS 2048        // most rows of one long-prompt pass (its buffers: pv_prompt_bytes)
 #define PV_KEY_BUCKETS 24       // attention grids of recorded steps are sized for the next power of two of (length + rows)
 #define PV_ROW_PAD 16           // activation buffers are padded to a multiple of this many rows
 
@@ -89,6 +90,8 @@ struct pv_model {
     int n_cus;
     size_t q4_flag_off;         // 4-bit models: a word of the arena, not 0 once a scale was loaded that the f16 form of the weights does not hold ...
     uint32_t q4_wide;           // ... and its copy, read after every load
+    char *pre_base; int32_t pre_rows;  // long-prompt buffers behind the weights, and the rows they hold (0: none) ...
+    mutable std::mutex pre_mu;  // ... which the prompts of this model's caches use in turn
 };
 
 struct pv_ws {                  // pointers into the caller's workspace
@@ -107,7 +110,6 @@ struct pv_cache {
     int32_t max_tokens, n_pages, rows_cap;
     int32_t units_cap;          // attention row-group units the workspace's partial arrays hold
     pv_ws ws;
-    char *pre_base; int32_t pre_rows;  // long-prompt buffers behind the step's workspace, and the rows they hold (0: none)
     pv_host_io *io;             // pinned host memory, mapped into the device's address space
     pv_host_io *d_io;           // the same mailbox as the kernels address it
     int32_t len, pending, last_rows;

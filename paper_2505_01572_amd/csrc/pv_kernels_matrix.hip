@@ -1145,7 +1145,7 @@ int pv_mat_run_prompt(pv_cache *c, int rows, int keep, hipStream_t s)
     mat_ws mw;
     mat_ws_layout(m, c->rows_cap, c->units_cap, c->n_pages * f.page_tokens, c->ws.part, &mw);
     pv_pre_out out;
-    int rc = pv_pre_block(c, c->pre_base, c->d_io->prompt, rows, keep, &out, s);
+    int rc = pv_pre_block(c, c->d_io->prompt, rows, keep, &out, s);
     if (rc != PV_OK || keep == 0) return rc;
     // the head of the kept rows (whatever their number, as column tiles of 16 rows: the layout of the prompt's operand)
     gemm_args g = {};

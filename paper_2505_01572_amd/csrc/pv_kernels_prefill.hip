@@ -895,13 +895,6 @@ k_pre_attn(const pre_attn_args a)
 
 // ------------------------------- host side ----------------------------------------
 
-int pv_pre_rows(const pv_model *m, int max_tokens)
-{
-    if (m->path < PV_PATH_MATRIX) return 0;
-    const int rows = std::min(PV_PRE_ROWS, (max_tokens + 63) / 64 * 64);
-    return rows > PV_PRE_MIN ? rows : 0;
-}
-
 struct pre_ws {
     int32_t *tokens;
     float2 *rope;
@@ -936,10 +929,9 @@ static size_t pre_layout(const pv_model *m, int rows, char *base, pre_ws *w)
     return off;
 }
 
-size_t pv_pre_bytes(const pv_model *m, int max_tokens)
+size_t pv_pre_bytes(const pv_model *m, int rows)
 {
-    const int rows = pv_pre_rows(m, max_tokens);
-    return rows ? pre_layout(m, rows, nullptr, nullptr) : 0;
+    return m->path >= PV_PATH_MATRIX && rows > PV_PRE_MIN ? pre_layout(m, rows, nullptr, nullptr) : 0;
 }
 
 template <int WR, int WF, int RT, int FT, int NST>
@@ -1090,7 +1082,7 @@ static int pre_attention(const pre_attn_args &a, int kv_heads, hipStream_t s)
     return PV_OK;
 }
 
-int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows, int keep, pv_pre_out *out, hipStream_t s)
+int pv_pre_block(pv_cache *c, const int32_t *d_host_tokens, int rows, int keep, pv_pre_out *out, hipStream_t s)
 {
     const pv_model *m = c->m;
     const pv_model_config &f = m->cfg;
@@ -1098,7 +1090,7 @@ int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows
     const char *Wb = m->d_weights;
     auto gainp = [&](int kind, int l) { return (const uint16_t *)(Wb + pv_tref(m, kind, l).off); };
     pre_ws w = {};
-    pre_layout(m, pv_pre_rows(m, c->max_tokens), base, &w);
+    pre_layout(m, m->pre_rows, m->pre_base, &w);
 
     k_pre_tokens<<<1, 1024, 0, s>>>(d_host_tokens, w.tokens, rows);
     PV_HIP(hipGetLastError());

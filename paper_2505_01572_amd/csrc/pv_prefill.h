@@ -6,9 +6,8 @@
 
 struct pv_pre_out { const uint16_t *xop; const float *ssq; };   // LM-head operand and sums of squares of the kept rows
 
-int pv_pre_rows(const pv_model *m, int max_tokens);       // rows a cache's buffers are laid out for (0: no long-prompt path)
-size_t pv_pre_bytes(const pv_model *m, int max_tokens);
+size_t pv_pre_bytes(const pv_model *m, int rows);         // buffers of passes of up to `rows` rows (a multiple of 64; 0: no long-prompt path)
 int pv_pre_init(const pv_model *m);
 // rows tokens through all layers; the first rows - keep are committed, the last `keep` (a multiple of 16 rows behind the
 // start) are left as the cache's running block
-int pv_pre_block(pv_cache *c, char *base, const int32_t *d_host_tokens, int rows, int keep, pv_pre_out *out, hipStream_t s);
+int pv_pre_block(pv_cache *c, const int32_t *d_host_tokens, int rows, int keep, pv_pre_out *out, hipStream_t s);

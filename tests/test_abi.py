@@ -43,3 +43,23 @@ def test_config_validation_without_gpu():
     assert L.pv_model_bytes(ctypes.byref(cfg), ctypes.byref(wb), ctypes.byref(sb)) == -1
     cfg.max_gamma = 16; cfg.page_tokens = 12
     assert L.pv_model_bytes(ctypes.byref(cfg), ctypes.byref(wb), ctypes.byref(sb)) == -1
+
+
+def test_prompt_part_of_the_arena_without_gpu():
+    """The long prompts' buffers are an optional part behind the weights, once per model."""
+    from paper_2505_01572_amd import binding
+    from pv_inputs import CONFIGS
+    L = binding.lib()
+
+    def sizes(s, rows, dtype=binding.PV_BF16):
+        cfg = binding.pv_model_config(s.n_layers, s.d_model, s.n_q_heads, s.n_kv_heads, s.head_dim, s.ffn_dim, s.vocab, s.rms_eps, s.rope_base, dtype, 16, 16, 0)
+        wb, sb, pb = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
+        assert L.pv_model_bytes(ctypes.byref(cfg), ctypes.byref(wb), ctypes.byref(sb)) == 0
+        return L.pv_prompt_bytes(ctypes.byref(cfg), rows, ctypes.byref(pb)), wb.value, pb.value
+    s = CONFIGS["8b"]
+    rc, wb, pb = sizes(s, 2048)
+    assert rc == 0 and 0 <= wb - pb - 2 * s.n_params() < 1 << 20 and pb < 212 << 20
+    got = [sizes(s, r)[2] for r in (0, 64, 65, 128, 129, 192, 2000, 2048)]
+    assert got[0] == got[1] == 0 and got[2] == got[3] < got[4] == got[5] < got[6] == got[7]
+    assert sizes(s, -1)[0] == sizes(s, 2049)[0] == -3
+    assert sizes(CONFIGS["tiny"], 2048, binding.PV_F32)[2] == 0

@@ -98,7 +98,7 @@ static size_t layout_arena(const pv_model_config *c, pv_model *m)
     size_t off = 0;
     auto place = [&](int kind, int layer) {
         int64_t r, k; tensor_dims(c, kind, &r, &k);
-        pv_tensor_ref t; t.off = off; t.rows = r; t.cols = k; t.loaded_rows = 0; t.strip_mul = 1; t.strip_add = 0;
+        pv_tensor_ref t; t.off = off; t.rows = r; t.cols = k; t.loaded_rows = 0; t.strip_mul = 1; t.strip_add = 0; t.wide = 0;
         const size_t bytes = (c->weight_bits == 4 && pv_is_q4_kind(kind)) ? (size_t)(r / 16) * (k / 128) * PV_Q4_BATCH : (size_t)r * k * elt;
         off = align_up(off + bytes, 256);
         if (m) { if (layer < 0) m->global[kind] = t; else m->layer[(size_t)layer * PV_T_NKINDS + kind] = t; }
@@ -186,7 +186,6 @@ extern "C" int pv_model_create(const pv_model_config *cfg, void *d_weights, size
     for (int i = 0; i < half; ++i) inv[i] = pow(cfg->rope_base, -2.0 * (double)i / (double)cfg->head_dim);
     hipError_t e = hipMemcpy(m->d_weights + m->inv_freq_off, inv, sizeof(double) * half, hipMemcpyHostToDevice);
     free(inv);
-    if (e == hipSuccess && m->wbits == 4) e = hipMemset(m->d_weights + m->q4_flag_off, 0, sizeof(uint32_t));
     if (e != hipSuccess) { pv_set_error("upload of rotary table failed: %s", hipGetErrorString(e)); free(m->layer); delete m; return PV_EHIP; }
     *out = m;
     return PV_OK;
@@ -257,11 +256,13 @@ extern "C" int pv_load_weights_q4(pv_model *m, int32_t kind, int32_t layer, int6
     hipStream_t s = (hipStream_t)hip_stream;
     PV_HIP(hipMemcpyAsync(m->d_staging, host_codes, cbytes, hipMemcpyHostToDevice, s));
     PV_HIP(hipMemcpyAsync(m->d_staging + soff, host_scales, sbytes, hipMemcpyHostToDevice, s));
-    uint32_t *wide = (uint32_t *)(m->d_weights + m->q4_flag_off);
+    uint32_t *wide = (uint32_t *)(m->d_weights + m->q4_flag_off), found = 0;
+    PV_HIP(hipMemsetAsync(wide, 0, sizeof(uint32_t), s));
     int rc = pv_mat_repack_q4(m, t, kind, row_begin, row_count, soff, wide, s);
     if (rc != PV_OK) return rc;
-    PV_HIP(hipMemcpyAsync(&m->q4_wide, wide, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    PV_HIP(hipMemcpyAsync(&found, wide, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     PV_HIP(hipStreamSynchronize(s));
+    t.wide = found | (row_begin == 0 ? 0 : t.wide);
     t.loaded_rows = row_begin + row_count;
     return PV_OK;
 }

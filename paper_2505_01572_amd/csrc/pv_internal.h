@@ -75,6 +75,7 @@ struct pv_tensor_ref {
     // matrix path: 16-row strip i of this tensor is strip (i*strip_mul + strip_add) of the tiled
     // region starting at `off` (gate/up are interleaved strip by strip; q,k,v are concatenated)
     int32_t strip_mul, strip_add;
+    uint32_t wide;              // 4-bit tensors: not 0 if some scale is outside what the f16 form of the weights holds
 };
 
 struct pv_model {
@@ -88,8 +89,7 @@ struct pv_model {
     pv_tensor_ref global[PV_T_NKINDS];
     size_t inv_freq_off;        // double[head_dim/2]
     int n_cus;
-    size_t q4_flag_off;         // 4-bit models: a word of the arena, not 0 once a scale was loaded that the f16 form of the weights does not hold ...
-    uint32_t q4_wide;           // ... and its copy, read after every load
+    size_t q4_flag_off;         // 4-bit models: a word of the arena in which a load reports such a scale
     char *pre_base; int32_t pre_rows;  // long-prompt buffers behind the weights, and the rows they hold (0: none) ...
     mutable std::mutex pre_mu;  // ... which the prompts of this model's caches use in turn
 };

@@ -263,7 +263,7 @@ k_pre_gemm(const gemm_args a, const pre_gemm_args p)
 }
 
 // ------------------------------------------------------------------------------------------
-// The same for 4-bit weights (of models with scales that k_pre_gemm_h4 below does not hold): 128 rows x 64 FT features, 2 x 4 waves, each 4
+// The same for 4-bit weights (of matrices with scales that k_pre_gemm_h4 below does not hold): 128 rows x 64 FT features, 2 x 4 waves, each 4
 // row tiles x FT strips.
 // Arithmetic as in k_gemm<WB = 4> (codes enter as 16 + c on top of -24 x the row sums, product taken
 // transposed, scaled per K-tile); the row sums of the operand come from k_pre_rowsum.  Per K-tile a
@@ -1028,14 +1028,14 @@ int pv_pre_init(const pv_model *m)
 }
 
 template <int EPI>
-static int pre_gemm(const pv_model *m, const gemm_args &g, int strips, const float *rscale, float *rowsum, int rows, int len, size_t part_floats, hipStream_t s)
+static int pre_gemm(const pv_model *m, const gemm_args &g, bool wide, int strips, const float *rscale, float *rowsum, int rows, int len, size_t part_floats, hipStream_t s)
 {
     const int mtiles = (rows + 15) / 16;
     gemm_args ga = g;
     ga.nstrips = strips;
     pre_gemm_args pa = {};
     pa.rscale = rscale; pa.part = (float4 *)g.tile_part; pa.mtiles = mtiles; pa.run = pre_run(g.ktiles); pa.rows = rows; pa.len = len;
-    const bool h4 = m->wbits == 4 && !m->q4_wide;      // every scale of the model fits the f16 form of its weights
+    const bool h4 = m->wbits == 4 && !wide;            // every scale of the GEMM's matrices fits the f16 form of its weights
     if (h4) {
         float *rinv = rowsum, *part = rowsum + (mtiles + 7) / 8 * 128;       // (in the place of the row sums)
         pa.rinv = rinv;
@@ -1089,6 +1089,7 @@ int pv_pre_block(pv_cache *c, const int32_t *d_host_tokens, int rows, int keep, 
     const int d = f.d_model, hd = f.head_dim, qd = f.n_q_heads * hd, kvd = f.n_kv_heads * hd, F = f.ffn_dim, mtiles = (rows + 15) / 16, len = c->len;
     const char *Wb = m->d_weights;
     auto gainp = [&](int kind, int l) { return (const uint16_t *)(Wb + pv_tref(m, kind, l).off); };
+    auto wide = [&](int kind, int l) { return pv_tref(m, kind, l).wide != 0; };
     pre_ws w = {};
     pre_layout(m, m->pre_rows, m->pre_base, &w);
 
@@ -1116,7 +1117,7 @@ int pv_pre_block(pv_cache *c, const int32_t *d_host_tokens, int rows, int keep, 
         PV_HIP(hipGetLastError());
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WQ, l).off); g.xop = (const uint4 *)w.xop; g.ktiles = d / 32; g.layer = l;
         if ((rc = pv_prof_mark(c, PV_PROF_QKV, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_QKV>(m, g, (qd + 2 * kvd) / 16, w.rscale, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_QKV>(m, g, wide(PV_T_WQ, l) || wide(PV_T_WK, l) || wide(PV_T_WV, l), (qd + 2 * kvd) / 16, w.rscale, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_QKV, l, 1, s)) != PV_OK) return rc;
         at.layer = l;
         if ((rc = pv_prof_mark(c, PV_PROF_ATTENTION, l, 0, s)) != PV_OK) return rc;
@@ -1125,18 +1126,18 @@ int pv_pre_block(pv_cache *c, const int32_t *d_host_tokens, int rows, int keep, 
         if ((rc = pv_prof_mark(c, PV_PROF_ATTENTION, l, 1, s)) != PV_OK) return rc;
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WO, l).off); g.xop = (const uint4 *)w.xop_o; g.ktiles = qd / 32; g.gain_next = gainp(PV_T_FFN_NORM, l);
         if ((rc = pv_prof_mark(c, PV_PROF_OPROJ, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_RESID>(m, g, wide(PV_T_WO, l), d / 16, nullptr, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_OPROJ, l, 1, s)) != PV_OK) return rc;
         k_pre_rscale<<<mtiles, 256, 0, s>>>(w.ssq, w.rscale, d / 16, g.inv_d, g.eps);
         PV_HIP(hipGetLastError());
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WG, l).off); g.xop = (const uint4 *)w.xop; g.ktiles = d / 32;
         if ((rc = pv_prof_mark(c, PV_PROF_GATEUP, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_SWIGLU>(m, g, F / 8, w.rscale, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_SWIGLU>(m, g, wide(PV_T_WG, l) || wide(PV_T_WU, l), F / 8, w.rscale, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_GATEUP, l, 1, s)) != PV_OK) return rc;
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WD, l).off); g.xop = (const uint4 *)w.xop_d; g.ktiles = F / 32;
         g.gain_next = (l + 1 < f.n_layers) ? gainp(PV_T_ATTN_NORM, l + 1) : (const uint16_t *)(Wb + m->global[PV_T_FINAL_NORM].off);
         if ((rc = pv_prof_mark(c, PV_PROF_DOWN, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_RESID>(m, g, d / 16, nullptr, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_RESID>(m, g, wide(PV_T_WD, l), d / 16, nullptr, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_DOWN, l, 1, s)) != PV_OK) return rc;
     }
     k_pre_commit<<<1, 64, 0, s>>>(c->ws.state, rows, keep);

@@ -209,3 +209,63 @@ def test_values_of_wide_blocks_against_64_bits(d, rows):
     for i in range(0, n, rows):
         c.prefill(toks[i:i + rows])
     assert np.count_nonzero(c.export()[0, 1] != want) < 2.1e-4 * want.size
+
+
+def _reload(gm, rm, shape, kind, layer, bits):
+    """The tensor again with one scale replaced (None: none), on both sides."""
+    codes, scales = pv_inputs.quantize_q4(pv_inputs.fill_tensor(shape, kind, layer).reshape(pv_inputs.tensor_shape(shape, kind)))
+    if bits is not None:
+        scales[5, 3] = bits
+    rm.set_tensor(kind, layer, ref.dequant_q4(codes, scales))
+    step = gm.chunk_rows(2 * codes.shape[1])
+    for r0 in range(0, codes.shape[0], step):
+        gm.load_weights_q4(kind, max(layer, 0), r0, codes[r0:r0 + step], scales[r0:r0 + step])
+
+
+@pytest.mark.parametrize("kind,layer,scaled", [("lm_head", -1, set()), ("wk", 1, {"k_pre_gemm_q4<4, 0>"}), ("wd", 0, {"k_pre_gemm_q4<4, 1>"}), ("wu", 1, {"k_pre_gemm_q4<4, 2>"})])
+def test_a_scale_decides_for_its_own_matrices(kind, layer, scaled):
+    """One scale of 2^-20: the GEMM with that matrix takes the kernel that scales its products, once in the two layers, all others keep
+    the weights as 16-bit floats (the vocabulary projection has no part in it); and so does that one when the tensor is loaded again without it."""
+    import torch
+    import paper_2505_01572_amd as pv
+    from gpu_helpers import paired_models
+    shape = SHAPES["q4"]
+    gm, rm = paired_models(shape)
+    toks = pv_inputs.uniform_tokens(77, 200, shape.vocab)
+    for bits, expected in ((0x3580, scaled), (None, set())):
+        _reload(gm, rm, shape, kind, layer, bits)
+        c = pv.Cache(gm, 256)
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU, torch.profiler.ProfilerActivity.CUDA]) as p:
+            c.prefill(toks)
+        names = [e.name.replace("void ", "").split("(")[0] for e in p.events()]
+        got = [n for n in names if n.startswith("k_pre_gemm_q4")]
+        assert set(got) == expected and len(got) == len(expected)
+        assert len([n for n in names if n.startswith("k_pre_gemm_h4")]) == 8 - len(expected)
+
+
+Q4_LONG = S("pr_q4_long", 1, 1408, 8, 2, 64, 1664, 1008, rope_base=500000.0, seed=7107, weight_bits=4)
+
+
+@pytest.mark.parametrize("before,n,bits", [(40, 2048, 0x3580), (0, 2048 + 300, 0x4600), (40, 2048, None)])
+def test_long_prompts_of_4bit_models_with_an_uncut_k(before, n, bits):
+    """2048 rows and 208 gate/up strips: 208 rectangles, so K (44 K-tiles, no multiple of the 8 of an accumulator) is not cut; several row
+    rectangles on every XCD.  With a scale that does not fit 16-bit floats in each matrix (2^-20 or 2^13), and without."""
+    import paper_2505_01572_amd as pv
+    from gpu_helpers import logit_scale, paired_models
+    shape = Q4_LONG
+    gm, rm = paired_models(shape)
+    for kind in ("wq", "wo", "wg", "wd") if bits else ():
+        _reload(gm, rm, shape, kind, 0, bits)
+    toks = pv_inputs.uniform_tokens(78, before + n, shape.vocab)
+    a, b = pv.Cache(gm, before + n + 8), pv.Cache(gm, before + n + 8)
+    rc = ref.RefCache(rm, before + n + 8, ref.KV_BF16)
+    for c in (a, b):
+        if before:
+            c.prefill(toks[:before])
+    a.prefill(toks[before:])
+    for i in range(before, before + n, 64):
+        b.prefill(toks[i:min(i + 64, before + n)])
+    last, la, lb = rc.prefill(toks), a.debug_logits(), b.debug_logits()
+    assert (np.abs(la[-1] - last) / logit_scale(last)).max() < 2e-3 and (np.abs(la - lb) / logit_scale(lb)).max() < 2e-3
+    ka, kb = (pv_inputs.bf16_bits_to_f32(c.export()).astype(np.float64) for c in (a, b))
+    assert np.mean(ka != kb) < 0.02 and np.abs(ka - kb).max() <= 2.0 ** -7 * np.abs(kb).max()

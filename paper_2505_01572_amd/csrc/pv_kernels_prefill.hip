@@ -447,8 +447,10 @@ k_pre_rowsum(const uint4 *xop, int ktiles, float *rowsum, int rsum_rows)
 // 4-bit weights as 16-bit floats.  (c - 8) x scale has at most 11 significant bits (3 of the code, 8 of the bf16
 // scale), which is what f16 holds, so for scales inside f16's range the weight itself enters the matrix core, exactly,
 // and nothing is left to do per product: the vector ALU, which bounds k_pre_gemm_q4 (scaling every product), only
-// expands the codes.  The activations become f16 hi + lo pairs (22 bits; the bf16 pairs have 16) of rows that are
-// scaled by a power of two so that a row's largest value lies in [2^14, 2^15); the rows' sums are scaled back in the epilogue.  128
+// expands the codes.  The activations become f16 hi + lo pairs of rows that are scaled by a power of two so that a
+// row's largest value lies in [2^14, 2^15); the rows' sums are scaled back in the epilogue.  Such a pair holds the 16 bits of the bf16
+// pair it is made from exactly down to 2^-22 of the row's largest value; smaller elements are off by up to 2^-39 of that value (the
+// step of f16's subnormals is 2^-24), which is 2^22 times less than the largest element's own rounding to 16 bits.  128
 // rows x 64 FT features, 2 x 4 waves of 4 row tiles x FT strips; the codes of K-tile k + 1 are expanded, one strip per row tile,
 // among the MFMAs of K-tile k.  70B-shaped gate/up, 1000 rows: 1.82 -> 1.71 ms (16-bit weights: 1.45), and fewer K/V
 // values off by a rounding step against 64 bits (1.43 % for 1.66 %, 1.62 % in blocks of 64 rows).
@@ -523,7 +525,8 @@ k_pre_gemm_h4(const gemm_args a, const pre_gemm_args p)
         }
     };
     // the codes of one strip and K-tile (the odd or the even one of the pair) as weights.  A nibble OR-ed into 1024.0 (0x6400) counts ones in the lowest
-    // mantissa bits and sixteens in the next: 1024 + c and 1024 + 16 c; less 1032 or 1152 that is c - 8 or 16 (c - 8), exactly
+    // mantissa bits and sixteens in the next: 1024 + c and 1024 + 16 c; less 1032 or 1152 that is c - 8 or 16 (c - 8), exactly (the exponent that
+    // makes the spacing of the floats one or a sixteenth of an integer: the old way to convert an integer without a conversion instruction)
     auto expand = [&](int f, bool odd) {
         const uint32_t c = odd ? cd[f].y : cd[f].x, c8 = c >> 8;
         const float sc = __uint_as_float(odd ? (sp[f] & 0xFFFF0000u) : (sp[f] << 16));

@@ -269,3 +269,29 @@ def test_long_prompts_of_4bit_models_with_an_uncut_k(before, n, bits):
     assert (np.abs(la[-1] - last) / logit_scale(last)).max() < 2e-3 and (np.abs(la - lb) / logit_scale(lb)).max() < 2e-3
     ka, kb = (pv_inputs.bf16_bits_to_f32(c.export()).astype(np.float64) for c in (a, b))
     assert np.mean(ka != kb) < 0.02 and np.abs(ka - kb).max() <= 2.0 ** -7 * np.abs(kb).max()
+
+
+@pytest.mark.parametrize("spread", [8, 20, 30])
+def test_rows_of_a_4bit_model_with_a_wide_spread(spread):
+    """Norm gains of 2^-spread to 1 side by side: a row's elements differ by as much before they become 16-bit floats, down to below the
+    2^-22 of the largest from which on those hold fewer bits.  As exact as blocks of 64 tokens, against the oracle."""
+    import paper_2505_01572_amd as pv
+    from gpu_helpers import logit_scale, paired_models
+    shape = SHAPES["q4"]
+    gm, rm = paired_models(shape)
+    rng = np.random.default_rng(spread)
+    for kind in ("attn_norm", "ffn_norm"):
+        for layer in range(shape.n_layers):
+            gain = ((127 - rng.integers(0, spread + 1, (1, shape.d_model))) << 7).astype(np.uint16)
+            gm.load_weights(kind, layer, 0, gain)
+            rm.set_tensor(kind, layer, gain.reshape(-1))
+    toks = pv_inputs.uniform_tokens(79, 200, shape.vocab)
+    a, b, rc = pv.Cache(gm, 256), pv.Cache(gm, 256), ref.RefCache(rm, 256, ref.KV_BF16)
+    a.prefill(toks)
+    for i in range(0, 200, 64):
+        b.prefill(toks[i:i + 64])
+    last, la, lb = rc.prefill(toks), a.debug_logits(), b.debug_logits()
+    ea, eb = (np.sqrt((((x[-1] - last) / logit_scale(last)) ** 2).mean()) for x in (la, lb))
+    assert (np.abs(la - lb) / logit_scale(lb)).max() < 2e-3 and ea < 2 * eb + 1e-5, (ea, eb)
+    ka, kb = (pv_inputs.bf16_bits_to_f32(c.export()).astype(np.float64) for c in (a, b))
+    assert np.mean(ka != kb) < 0.02 and np.abs(ka - kb).max() <= 2.0 ** -7 * np.abs(kb).max()

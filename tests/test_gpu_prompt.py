@@ -99,6 +99,46 @@ def test_rollback_and_readmit_after_a_long_prompt():
     a.prefill(toks[150:])
     b.prefill(toks[:150]); b.prefill(toks[150:])
     assert a.state() == b.state() and np.array_equal(a.export(), b.export())
+    # the block on record is the prompt's last one of 64: all of it is committed, so there is nothing but its end to go to
+    c = pv.Cache(gm, 480)
+    for n in (300, 100):
+        c.prefill(toks[:n])
+        for bad in (len(c) - 1, len(c) + 1):
+            with pytest.raises(pv.PVError) as e:
+                c.readmit(bad)
+            assert e.value.status == -3
+        c.readmit(len(c), pending=9)
+        assert c.state()[1] == 9
+    c.rollback(350)
+    with pytest.raises(pv.PVError) as e:
+        c.readmit(400)
+    assert e.value.status == -2 and c.state() == (350, -1)
+    # a last block that was not committed can be re-admitted, wholly or in part: its keys and values are there
+    good = pv_inputs.fill_tensor(shape, "final_norm", -1, gains="perturbed").reshape(1, -1)
+    for before, n, to in ((0, 300, 300), (0, 300, 257), (7, 2048 + 100, 7 + 2048 + 64 + 30)):
+        full = pv_inputs.uniform_tokens(74, before + n, shape.vocab)
+        c, d = pv.Cache(gm, before + n + 8), pv.Cache(gm, before + n + 8)
+        gm.load_weights("final_norm", 0, 0, np.full((1, shape.d_model), 0x7FC0, dtype=np.uint16))
+        if before:
+            with pytest.raises(pv.PVError):
+                c.prefill(full[:before])
+            c.readmit(before)
+        with pytest.raises(pv.PVError):
+            c.prefill(full[before:])
+        kept = before + n - ((n - 1) % 64 + 1)
+        assert c.state() == (kept, -1)
+        for bad in (kept - 1, before + n + 1):
+            with pytest.raises(pv.PVError) as e:
+                c.readmit(bad)
+            assert e.value.status == -3
+        c.readmit(to, pending=5)
+        assert c.state() == (to, 5)
+        gm.load_weights("final_norm", 0, 0, good)
+        if before:
+            d.prefill(full[:before])
+        d.prefill(full[before:])
+        d.rollback(to); d.set_pending(5)
+        assert c.verify(to, [5, 1, 2]) == d.verify(to, [5, 1, 2]) and np.array_equal(c.debug_logits(), d.debug_logits())
 
 
 @pytest.mark.parametrize("bits", [0x3580, 0x4600, 0x8000, 0xBC00], ids=["small", "large", "minus_zero", "negative"])

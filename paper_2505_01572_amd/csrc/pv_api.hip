@@ -286,16 +286,13 @@ static size_t layout_ws(const pv_model *m, int rows_cap, int units_cap, int n_pa
     const pv_model_config &c = m->cfg;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return base ? base + o : (char *)nullptr; };
-    const size_t qd = (size_t)c.n_q_heads * c.head_dim, kvd = (size_t)c.n_kv_heads * c.head_dim, R = rows_cap;
+    const size_t qd = (size_t)c.n_q_heads * c.head_dim, R = rows_cap;
     char *p;
     p = take(sizeof(pv_dev_state)); if (w) w->state = (pv_dev_state *)p;
     p = take(sizeof(int32_t) * n_pages); if (w) w->page_table = (int32_t *)p;
     p = take(sizeof(float2) * R * (c.head_dim / 2)); if (w) w->rope = (float2 *)p;
     p = take(4 * R * c.d_model); if (w) w->x = (float *)p;
-    p = take(4 * R * c.d_model); if (w) w->h = (float *)p;
     p = take(4 * R * qd); if (w) w->q = (float *)p;
-    p = take(4 * R * kvd); if (w) w->k = (float *)p;
-    p = take(4 * R * kvd); if (w) w->v = (float *)p;
     p = take(4 * R * qd); if (w) w->attn = (float *)p;
     p = take(4 * R * c.ffn_dim); if (w) w->gate = (float *)p;
     p = take(4 * R * c.ffn_dim); if (w) w->up = (float *)p;

@@ -98,7 +98,7 @@ struct pv_ws {                  // pointers into the caller's workspace
     pv_dev_state *state;
     int32_t *page_table;
     float2 *rope;               // [rows][head_dim/2] (cos, sin)
-    float *x, *h, *q, *k, *v, *attn, *gate, *up, *logits;
+    float *x, *q, *attn, *gate, *up, *logits;
     float *part;                // matrix path: operands, partial sums, attention partials
     size_t part_floats;
 };

@@ -180,7 +180,7 @@ k_vec_head(const vec_norm a, const ST *W, float *logits, int N, float *cand_val,
     }
 }
 
-// y[g][n] = (res ? res[g][n] : 0) + sum_k x[g][k] * W[n][k]   for g < G rows; one wavefront per n.
+// y[g][n] = res[g][n] + sum_k x[g][k] * W[n][k]   for g < G rows; one wavefront per n.
 // K must be a multiple of 4.  Rows >= `rows` are computed from padding and not stored.
 template <typename ST, int G>
 __global__ void __launch_bounds__(256)
@@ -205,7 +205,7 @@ k_linear(const ST *W, const float *x, const float *res, float *y, int N, int K, 
     for (int g = 0; g < G; ++g) {
         float a = acc[g];
         for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
-        if (lane == 0 && g < rows) y[(size_t)g * N + n] = (res ? res[(size_t)g * N + n] : 0.f) + a;
+        if (lane == 0 && g < rows) y[(size_t)g * N + n] = res[(size_t)g * N + n] + a;
     }
 }
 
@@ -286,7 +286,7 @@ static int launch_linear(const pv_model *m, const pv_tensor_ref &t, const float 
     const unsigned grid = (unsigned)((N + 3) / 4);
     for (int r0 = 0; r0 < rows; r0 += 16) {
         const int r = rows - r0 < 16 ? rows - r0 : 16;
-        const float *xr = x + (size_t)r0 * K, *rr = res ? res + (size_t)r0 * N : nullptr;
+        const float *xr = x + (size_t)r0 * K, *rr = res + (size_t)r0 * N;
         float *yr = y + (size_t)r0 * N;
         if (r <= 1) k_linear<ST, 1><<<grid, 256, 0, s>>>(W, xr, rr, yr, N, K, r);
         else if (r <= 4) k_linear<ST, 4><<<grid, 256, 0, s>>>(W, xr, rr, yr, N, K, r);

@@ -964,7 +964,9 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         } else {
             // 4-bit weights, 9..64 rows: activation tiles shared through LDS, two strips per wave.  Few strips: cut along K.  Up to 32 rows two
             // workgroups fit on a CU (120 registers): at most 512 of them in one round (8B shape, 4 layers: 13 rows 396 -> 356 us a
-            // step against 256 and one per CU, 24 rows 483 -> 442); more rows: one per CU, at most 256
+            // step against 256 and one per CU, 24 rows 483 -> 442); more rows: one per CU, at most 256 (K = 4096, 48 rows, us for a projection and its
+            // sum, one slice / two: 129 groups of 16 strips 77.6 / 85.5, 172 groups 78.1 / 88.5, 224 groups 83 / 79; 13 rows, one / two / three: 129 groups
+            // 41.5 / 36.1 / 31.9, 172 groups 42.8 / 39.6 / 39.4, 224 groups 44.3 / 43.2 / 42.4)
             const int nbat = g.ktiles / 4, ngroups = (strips + 15) / 16;
             int slices = g.tile_part == nullptr ? 1 : max(1, min(TILE_MAX_SLICES, (CT <= 2 ? 512 : 256) / ngroups));
             int bps = max(CT <= 2 ? 2 : 4, (nbat + slices - 1) / slices);
@@ -984,7 +986,10 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         if constexpr (CT >= 2) {
             // Activation tiles shared through LDS; few strips: cut along K, into at most 256 workgroups, one a CU: with a few more (288 for the
             // 8B-shaped QKV projection, 344 for the 7B-shaped gate/up) some CUs have two and the others wait for them (4 layers, us a step: 8B 32
-            // rows 542 -> 528, 48 rows 632 -> 614; 7B 24 rows 552 -> 492; up to 512 workgroups: 570, 663, 567)
+            // rows 542 -> 528, 48 rows 632 -> 614; 7B 24 rows 552 -> 492; up to 512 workgroups: 570, 663, 567).  From 129 groups of eight strips
+            // on that is one slice, on every second CU at first: K = 4096, us for a projection and its sum with 24 / 48 rows, one slice / two / three:
+            // 129 groups 38.5 / 46.4 / 37.7 and 50.6 / 55.3 / 45.3, 140 groups 39.4 / 49.0 / 39.2 and 50.1 / 58.1 / 46.5, 172 groups 41.0 / 50.0 /
+            // 51.8 and 52.4 / 59.7 / 61.2, 224 groups 47.0 / 57.2 / 57.0 and 55.1 / 67.0 / 67.5 (128 groups, two slices: 33.8 and 38.8)
             if (g.ktiles >= 16) {
                 const int ngroups = (strips + 7) / 8;
                 int slices = g.tile_part == nullptr ? 1 : max(1, min(TILE_MAX_SLICES, 256 / ngroups));

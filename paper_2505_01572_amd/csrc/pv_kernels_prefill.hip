@@ -1051,12 +1051,13 @@ static int pre_gemm(const pv_model *m, const gemm_args &g, bool wide, int strips
         k_pre_rowsum<<<dim3((g.ktiles + 3) / 4, mtiles), 256, 0, s>>>(g.xop, g.ktiles, rowsum, pa.rsum_rows);
         PV_HIP(hipGetLastError());
     }
-    // The rectangle and the number of K-slices with the smallest estimated time.  Unit: one MFMA pair's share of a 256 x 256 rectangle
-    // (3.85 ns per 16 x 16 outputs and K-tile of a workgroup).  Measured (4096 x 4096 and 4096 x 14336 weights, few workgroups): per
-    // K-tile 0.99, 0.77, 0.53 and 0.30 us, on top of 20, 16, 14 and 9 us for the start, the epilogue and the end; partial
-    // sums: 3 us and 0.2 ns for each 16 x 16 of them.  Where more workgroups than CUs come out, they run in rounds.
+    // The rectangle and the number of K-slices with the smallest estimated time, in units of 3.85 ns.  The constants stand for 0.53, 0.41 and 0.30 us a K-tile of a 128 x 256, 128 x 192 and 128 x 128 rectangle,
+    // 4-bit weights 0.79 and 0.61, on top of 13, 11 and 9.5 us for the start, the epilogue and the end; partial sums: 3 us and 0.2 ns for
+    // each 16 x 16 of them.  Where more workgroups than CUs come out, they run in rounds.  Measured with 4096 x 4096 and 4096 x 14336 weights:
+    // 0.58, 0.51 and 0.38 us on 64 to 128 CUs, 0.63, 0.56 and 0.47 us on twice as many, on top of 16 to 18, 13 and 10 to 11 us; 4-bit
+    // weights on 128 and 176 CUs 0.81 and 0.66 us, and 0.88 us in k_pre_gemm_q4, on top of 16 to 20 us.
     struct rect { int br, bf; double cost; };
-    static const rect R16[3] = {{8, 16, 1.07}, {8, 12, 1.12}, {8, 8, 1.22}}, R4[2] = {{8, 16, 1.6}, {8, 12, 1.65}};      // 4-bit weights: 0.81 us a K-tile
+    static const rect R16[3] = {{8, 16, 1.07}, {8, 12, 1.12}, {8, 8, 1.22}}, R4[2] = {{8, 16, 1.6}, {8, 12, 1.65}};
     const rect *R = m->wbits == 4 ? R4 : R16;
     const int kinds = h4 ? 2 : m->wbits == 4 ? 1 : 3;
     double best = 1e30; int shape = 0, cut = 1;

@@ -525,8 +525,8 @@ k_pre_gemm_h4(const gemm_args a, const pre_gemm_args p)
         }
     };
     // the codes of one strip and K-tile (the odd or the even one of the pair) as weights.  A nibble OR-ed into 1024.0 (0x6400) counts ones in the lowest
-    // mantissa bits and sixteens in the next: 1024 + c and 1024 + 16 c; less 1032 or 1152 that is c - 8 or 16 (c - 8), exactly (the exponent that
-    // makes the spacing of the floats one or a sixteenth of an integer: the old way to convert an integer without a conversion instruction)
+    // mantissa bits and sixteens in the next: 1024 + c and 1024 + 16 c; less 1032 or 1152 that is c - 8 or 16 (c - 8), exactly (integers to
+    // floats without a conversion instruction, as in Y. J. Kim et al., "Who Says Elephants Can't Run", arXiv 2211.10017, for 8- and 4-bit weights)
     auto expand = [&](int f, bool odd) {
         const uint32_t c = odd ? cd[f].y : cd[f].x, c8 = c >> 8;
         const float sc = __uint_as_float(odd ? (sp[f] & 0xFFFF0000u) : (sp[f] << 16));

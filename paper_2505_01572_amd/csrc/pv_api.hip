@@ -370,6 +370,9 @@ extern "C" int pv_cache_create(const pv_model *m, void *d_page_pool, size_t page
     c->io->single.seq[0].gamma = 0; c->io->single.seq[0].row0 = 0; c->io->single.seq[0].n_pages = c->n_pages; c->io->single.seq[0].unit0 = 0;
     st.blk = c->io->single;
     if (e == hipSuccess) e = hipMemcpy(c->ws.state, &st, sizeof(st), hipMemcpyHostToDevice);
+    // The stream on which the cache's steps are recorded: some 90 us, which the first step would have (eight steps on a new cache, 4 layers:
+    // 7B shape 3.58 -> 3.46 ms, 8B shape 3.77 -> 3.71).  Not while a prompt's kernels run: a new hardware queue stopped them for 2 to 7 ms.
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
     if (e != hipSuccess) { pv_set_error("cache initialisation failed: %s", hipGetErrorString(e)); (void)hipHostFree(c->io); delete c; return PV_EHIP; }
     *out = c;
     return PV_OK;
@@ -416,13 +419,6 @@ static int record_block(pv_cache *c, int rows, int mode, hipStream_t s)
     return c->m->path >= PV_PATH_MATRIX ? pv_mat_run_block(c, s) : pv_vec_run_block(c, s);
 }
 
-// the stream on which the cache's steps are recorded, created when it is first needed (some 90 us)
-static int capture_stream(pv_cache *c)
-{
-    if (!c->cap_stream) PV_HIP(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
-    return PV_OK;
-}
-
 static int enqueue_block(pv_cache *c, const int32_t *tokens, int rows, int mode, hipStream_t s)
 {
     const pv_model *m = c->m;
@@ -443,8 +439,6 @@ static int enqueue_block(pv_cache *c, const int32_t *tokens, int rows, int mode,
         c->attn_keys = 1 << bucket;
         hipGraphExec_t &ge = c->gexec[rows][mode][bucket - 8];
         if (!ge) {
-            const int crc = capture_stream(c);
-            if (crc != PV_OK) return crc;
             PV_HIP(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
             const int rrc = record_block(c, rows, mode, c->cap_stream);
             hipGraph_t g = nullptr;
@@ -626,9 +620,6 @@ extern "C" int pv_prefill(pv_cache *c, const int32_t *tokens, int32_t n, void *h
         memcpy(c->io->prompt, tokens + off, sizeof(int32_t) * rows);
         c->io->hdr[2] = keep; c->io->hdr[3] = keep ? PV_MODE_PREFILL_LAST : PV_MODE_PREFILL_MID;
         rc = pv_mat_run_prompt(c, rows, keep, s);
-        // while the pass runs: nothing of a long prompt is recorded, but the step that follows is (eight steps on a new
-        // cache, 4 layers: 7B shape 3.58 -> 3.46 ms, 8B shape 3.77 -> 3.71)
-        if (rc == PV_OK && c->use_graphs) rc = capture_stream(c);
         const hipError_t e = hipStreamSynchronize(s);
         if (rc != PV_OK) return rc;
         PV_HIP(e);

@@ -6,7 +6,7 @@
 // of a GEMM are as before (16-bit weights in MFMA tile order, activations as bf16 hi + lo pairs,
 // fp32 accumulators), but a workgroup owns a rectangle of 128 rows x 128 to 256 features, and both operands
 // pass through LDS, loaded by direct global -> LDS copies.  2048 tokens through four 8B-shaped layers:
-// 20.7 -> 6.6 ms; the gate/up GEMM then takes 0.70 ms, 1370 TFLOP/s of MFMAs (hi and lo counted).
+// 20.7 -> 6.7 ms; the gate/up GEMM then takes 0.73 ms, 1310 TFLOP/s of MFMAs (hi and lo counted).
 #include "pv_gemm_epilogue.h"
 #include "pv_prefill.h"
 #include <algorithm>
@@ -54,12 +54,16 @@ __device__ inline int xcd_order(int bid, int total)
 constexpr int pre_stage_tiles(int br, int bf) { return (2 * br + bf + 7) / 8 * 8; }
 
 // K-tiles added up in one accumulator before it is added to the total.  An accumulator that ran over the whole K would carry
-// a rounding error of the size of the operands' own.  Blocks of 64 rows cut K over workgroups, into runs of at least 8 (K of 2048) to 16 (4096)
-// tiles for the projections with few strips; a prompt's values must not be further off.  Keys and values of a first layer that are not the rounded
-// 64-bit result, 1000 tokens, runs of 16 / runs of 8 / blocks of 64 rows: K = 2048 2.16 / 1.76 / 1.76e-4, K = 2080 2.19 / 1.82 /
-// 1.85e-4, K = 4096 2.41 / 1.97 / 2.22e-4 (one accumulator for each slice of K, as those blocks had: 2.68e-4), K = 8192 2.62 / 2.05 / 2.53e-4
-// (4.34e-4).  Runs of 8 take 2 % more time (8B shape, 2048 tokens: 6.60 -> 6.73 ms), hence only where they are needed.
-static inline int pre_run(int ktiles) { return ktiles < 128 ? 8 : 16; }
+// a rounding error of the size of the operands' own.  Blocks of 64 rows cut K over workgroups when strips are few, into up to 16 runs
+// of 8 tiles or more; a prompt's values must not be further off than theirs were without a second level: runs of 8 where those were shorter
+// than 16.  Keys and values of a first layer that are not the rounded 64-bit result, 1000 tokens, runs of 16 / runs of 8 / blocks of 64 rows (their
+// run): K = 2048 2.16 / 1.76 / 1.76e-4 (8), K = 2080 2.19 / 1.82 / 1.85e-4 (8), K = 4096 2.41 / 1.97 / 2.68e-4 (22), K = 8192 2.62 / 2.05 /
+// 4.34e-4 (64).  Runs of 8 take 2 % more time (8B shape, 2048 tokens: 6.60 -> 6.73 ms), hence only where they are needed.
+static inline int pre_run(int ktiles, int strips)
+{
+    const int groups = (strips + 7) / 8, runs = std::min(16, (256 + groups - 1) / groups);
+    return ktiles < 16 * runs ? 8 : 16;
+}
 
 struct pre_gemm_args {
     const float *rscale;        // RMSNorm scale of each row (QKV, SWIGLU)
@@ -1037,7 +1041,7 @@ static int pre_gemm(const pv_model *m, const gemm_args &g, bool wide, int strips
     gemm_args ga = g;
     ga.nstrips = strips;
     pre_gemm_args pa = {};
-    pa.rscale = rscale; pa.part = (float4 *)g.tile_part; pa.mtiles = mtiles; pa.run = pre_run(g.ktiles); pa.rows = rows; pa.len = len;
+    pa.rscale = rscale; pa.part = (float4 *)g.tile_part; pa.mtiles = mtiles; pa.run = pre_run(g.ktiles, strips); pa.rows = rows; pa.len = len;
     const bool h4 = m->wbits == 4 && !wide;            // every scale of the GEMM's matrices fits the f16 form of its weights
     if (h4) {
         float *rinv = rowsum, *part = rowsum + (mtiles + 7) / 8 * 128;       // (in the place of the row sums)

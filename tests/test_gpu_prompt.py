@@ -222,7 +222,7 @@ def _first_values(d, n):
     return gpu_model(shape, gains="perturbed"), toks, want.to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
 
 
-@pytest.mark.parametrize("d", [1024, 2048, 2080, 3072])
+@pytest.mark.parametrize("d", [1024, 2048, 2080])
 def test_values_of_a_long_prompt_are_as_exact_as_those_of_short_blocks(d):
     """As many of a first layer's values are not the rounded 64-bit result as with blocks of 64 tokens, give or take
     a tenth.  (Some 1400 of 8 million at d = 2048, a standard deviation of 4 % for the ratio; accumulators over 16 K-tiles, twice

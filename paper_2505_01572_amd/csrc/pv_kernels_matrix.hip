@@ -7,7 +7,8 @@
 // owns one or a few strips, its wavefronts split K, accumulate in fp32, and are summed in wave
 // order through LDS, so the owner sees complete outputs and the whole epilogue (RMSNorm scale,
 // rotary embedding + KV append, SwiGLU, residual add, vocabulary arg-max) is fused into the
-// GEMM.  17..64 rows (k_gemm_tile; with 4-bit weights k_gemm_tile_q4, from 9 rows on): the waves
+// GEMM.  9..64 rows and many strips (k_gemm_wide): the same with one workgroup per CU.  17..64 rows
+// and few strips (k_gemm_tile; with 4-bit weights k_gemm_tile_q4, from 9 rows on): the waves
 // of a workgroup own different strips, walk K together and share the activation tiles through LDS.
 //
 // Activations enter as the B operand.  To keep fp32-grade accuracy with bf16 matrix cores an
@@ -559,7 +560,127 @@ k_gemm(const gemm_args a)
 }
 
 // ------------------------------------------------------------------------------------------
-// Blocks of 17..64 rows (CT = 2 or 4 column tiles of 16 rows, a hi and a lo operand each): 2 CT
+// Projections with three or more strips a CU (gate/up, the vocabulary, the QKV projection without shared heads), 9..64 rows (CT column
+// tiles of 16 rows, a hi and a lo operand each): one workgroup per CU owns S strips and its NW waves split K, so
+// that each activation tile enters the CU once, for S strips, and straight into the registers of the one wave
+// that uses it: no LDS and no barrier before the final sum over the waves.
+// A CU has some 32 KiB of loads in flight (its L1's size: 56 GB/s of HBM latency, 130 GB/s of L2 latency, whatever the waves ask for), so what counts is
+// bytes per CU times their latency: S + 2 CT tiles per K-tile here, 8 + 2 CT with the same CU count short of 12 % in k_gemm_tile (224 groups of eight
+// for 1792 strips).  Two K-tiles per wave (one used, one on its way) are enough for that; three or four measured the same.
+// 8B-shaped gate/up, 235 MB, us: 16 rows 45.6 (two strips a workgroup) -> 37.5, 32 rows 43.8 (k_gemm_tile) -> 41.0, 48 rows 52.2 -> 46.8 (three
+// column tiles instead of four; 64 rows 53.2 -> 50.3); 1024-strip vocabulary 26.1 -> 24.0, 34.2 -> 26.5, 39.0 -> 31.1, 39.8 -> 37.8.
+// Loads go through buffer descriptors: a K-tile past the end of the slice gets an offset past the buffer's end,
+// for which zeros come back and nothing is fetched, so every load of the loop is unconditional.
+// ------------------------------------------------------------------------------------------
+__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00020000); }
+#define BUFFER_END 0xC0000000u                     // past the end of every buffer (wide_fits), and no sum with an offset inside one wraps
+template <int AUX> __device__ inline uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t base)
+{
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, base, AUX));
+}
+#define LOAD_ONCE 2                                // the non-temporal bit (see load_once)
+
+constexpr int wide_waves(int ct, int s) { return ct <= 2 || s <= 4 ? 8 : 4; }              // (what the registers of one workgroup per CU hold)
+constexpr int wide_lds(int ct, int s) { return wide_waves(ct, s) * s * ct * 1024; }
+static inline bool wide_fits(int ktiles) { return ktiles <= (1 << 16); }                   // the largest buffer: 8 arrays of K-tiles of 1 KiB = 0.5 GiB
+
+template <int CT, int S, int EPI>
+__global__ void __launch_bounds__(wide_waves(CT, S) * 64) __attribute__((amdgpu_waves_per_eu(wide_waves(CT, S) / 4, wide_waves(CT, S) / 4)))
+k_gemm_wide(const gemm_args a)
+{
+    constexpr int NW = wide_waves(CT, S), NX = 2 * CT;
+    constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LMHEAD);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int KT = a.ktiles, nst = (KT + NW - 1) / NW;          // K-tiles of a wave: wave, wave + NW, ... (some waves' last one is past the end)
+    const int rot = (int)((blockIdx.x * 5u) % (unsigned)nst);   // workgroups start at different ones, or all would stream from addresses a power of two apart
+    const int strip0 = blockIdx.x * S;
+    extern __shared__ f32x4 wide_red[];                         // [NW][S * CT][64]
+    __shared__ float ssq_s[NW][CT][16];
+
+    ssq_loads<CT == 4 ? 4 : 32 / NW> sl[CT];
+    if (NORM) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) ssq_issue(a.ssq + (size_t)ct * a.ssq_parts * 16, a.ssq_parts, threadIdx.x, NW * 64, sl[ct]);
+    }
+    const uint32_t tb = (uint32_t)KT * 1024;                    // bytes of a strip, and of an operand array
+    const int mine = min(S, a.nstrips - strip0);                // (strips past the end re-read the last one; dropped below)
+    const __amdgpu_buffer_rsrc_t W = buffer_of((const char *)a.W + (size_t)strip0 * tb, (uint32_t)mine * tb), X = buffer_of(a.xop, NX * tb);
+    uint32_t wo[S];
+#pragma unroll
+    for (int si = 0; si < S; ++si) wo[si] = (uint32_t)min(si, mine - 1) * tb;
+
+    // 17 rows and more: an accumulator takes 8 K-tiles, then it is added to the total (the reason and its figures: k_gemm_tile).  Up to 16
+    // rows the waves' accumulators are as long as in k_gemm
+    constexpr bool TWO = CT >= 2;
+    f32x4 acc[S][CT], tot[S][CT];
+#pragma unroll
+    for (int si = 0; si < S; ++si)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[si][ct] = tot[si][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    struct stage { uint4 w[S], x[NX]; };
+    auto issue = [&](stage &q, int i) {
+        const int k = i + rot, t = (k < nst ? k : k - nst) * NW + wave;
+        const uint32_t off = lane * 16 + (i < nst && t < KT ? (uint32_t)t * 1024 : BUFFER_END);
+#pragma unroll
+        for (int si = 0; si < S; ++si) q.w[si] = buffer_load16<LOAD_ONCE>(W, off, wo[si]);
+#pragma unroll
+        for (int r = 0; r < NX; ++r) q.x[r] = buffer_load16<0>(X, off, r * tb);
+        asm volatile("" ::: "memory");
+    };
+    auto use = [&](const stage &q) {
+#pragma unroll
+        for (int r = 0; r < NX; ++r)
+#pragma unroll
+            for (int si = 0; si < S; ++si) acc[si][r >> 1] = mfma16(q.w[si], q.x[r], acc[si][r >> 1]);
+    };
+    stage q0, q1;
+    issue(q0, 0);
+    issue(q1, 1);
+    if (NORM) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            const float4 s4 = ssq_finish(a.ssq + (size_t)ct * a.ssq_parts * 16, a.ssq_parts, threadIdx.x, NW * 64, sl[ct]);
+            if (lane < 4) *(float4 *)&ssq_s[wave][ct][4 * lane] = s4;
+        }
+    }
+    for (int i = 0; i < nst;) {
+        const int e = min(i + 8, nst);
+        for (; i < e; i += 2) {
+            use(q0); issue(q0, i + 2);
+            if (i + 1 < e) use(q1);
+            issue(q1, i + 3);
+        }
+        if (TWO) {
+#pragma unroll
+            for (int si = 0; si < S; ++si)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) { tot[si][ct] += acc[si][ct]; acc[si][ct] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+        }
+    }
+#pragma unroll
+    for (int si = 0; si < S; ++si)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) wide_red[(wave * S * CT + si * CT + ct) * 64 + lane] = TWO ? tot[si][ct] : acc[si][ct];
+    __syncthreads();
+    for (int u = wave; u < mine * CT; u += NW) {                // the waves' sums in wave order; a wave finishes every NW-th (strip, column tile)
+        const int si = u / CT, ct = u - si * CT;
+        f32x4 v = wide_red[u * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += wide_red[(w * S * CT + u) * 64 + lane];
+        epi_pre pre;
+        epi_prefetch<EPI>(a, strip0 + si, lane, pre, ct);
+        if (NORM) {
+            float s = ssq_s[0][ct][lane & 15];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) s += ssq_s[w][ct][lane & 15];
+            pre.rj = 1.0f / sqrtf(s * a.inv_d + a.eps);
+        }
+        epi_apply<2, EPI>(a, strip0 + si, lane, v, pre, ct);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// Blocks of 17..64 rows (CT = 2, 3 or 4 column tiles of 16 rows, a hi and a lo operand each): 2 CT
 // activation tiles go with every weight tile.  Fetched per wave they outgrow the weight stream
 // in the CU's load path, so here the 8 waves of a workgroup walk the same K range in step, each
 // with its own S strips, and every activation tile is fetched once per workgroup and shared
@@ -574,8 +695,8 @@ template <int CT, int S, int EPI>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
 k_gemm_tile(const gemm_args a, int tps, float4 *part)
 {
-    constexpr int NW = 8, U = 2, D = 4, TPS = U * CT * 2, NLD = TPS / NW;    // TPS activation tiles per step, NLD of them per wave
-    static_assert((NLD == 1 || (NLD == 2 && CT * 2 == NW)) && TPS == NLD * NW, "a wave loads one tile of the step, or two of the same operand array");
+    constexpr int NW = 8, U = 2, D = 4, TPS = U * CT * 2;                    // TPS activation tiles per step: wave w brings in tiles w and w + 8, where there are as many
+    static_assert(TPS >= NW && TPS <= 2 * NW, "a wave loads one or two tiles of the step");
     constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LMHEAD);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int KT = a.ktiles, t0 = blockIdx.y * tps, t1 = min(KT, t0 + tps);  // this slice's K-tiles (not empty: the launch sees to it)
@@ -614,11 +735,9 @@ k_gemm_tile(const gemm_args a, int tps, float4 *part)
     auto first_tile = [&](int step) { int k = step + rot; if (k >= nsteps) k -= nsteps; return t0 + k * U; };
     auto issue = [&](slot &q, int step) {             // loads of (rotated) step `step`; a tile past the slice's end re-reads its last one
         const int tb = first_tile(step);
-        {   // tile t of the step: K-tile t / (2 CT) of it, operand array t % (2 CT); the wave takes tiles wave and wave + 8
-            const int u = wave / (CT * 2), r = wave % (CT * 2);
-            q.x0 = B[(size_t)r * arr + (size_t)min(tb + u, t1 - 1) * 64];
-            if (NLD == 2) q.x1 = B[(size_t)r * arr + (size_t)min(tb + u + 1, t1 - 1) * 64];   // CT = 4: 8 more tiles = the next K-tile, same array
-        }
+        auto tile = [&](int t) { return B[(size_t)(t % (CT * 2)) * arr + (size_t)min(tb + t / (CT * 2), t1 - 1) * 64]; };   // K-tile t / (2 CT) of the step, operand array t % (2 CT)
+        q.x0 = tile(wave);
+        if (TPS > NW) q.x1 = tile(min(wave + NW, TPS - 1));     // (CT = 3: 12 tiles, the last four waves read the last one again)
 #pragma unroll
         for (int si = 0; si < S; ++si)
 #pragma unroll
@@ -627,7 +746,7 @@ k_gemm_tile(const gemm_args a, int tps, float4 *part)
     };
     auto use = [&](const slot &q, int buf, int step) {   // q holds step `step`: share its activation tiles through sa[buf], multiply
         sa[buf][wave][lane] = make_uint4(q.x0.x, q.x0.y, q.x0.z, q.x0.w);
-        if (NLD == 2) sa[buf][wave + NW][lane] = make_uint4(q.x1.x, q.x1.y, q.x1.z, q.x1.w);
+        if (TPS > NW && wave + NW < TPS) sa[buf][wave + NW][lane] = make_uint4(q.x1.x, q.x1.y, q.x1.z, q.x1.w);
         __syncthreads();
         const int tb = first_tile(step);
 #pragma unroll
@@ -919,11 +1038,45 @@ static int allow_tile_q4_lds()
     return PV_OK;
 }
 
+// Strips a workgroup of k_gemm_wide, 0: the GEMM goes elsewhere.  Workgroups run in rounds of one per CU; per K-tile a CU takes in S weight tiles and 2 CT
+// activation tiles, and one of those costs about 0.3 of a weight tile (L2 against HBM latency).  The lines, in us with the sum of the K-slices:
+// 640 strips (K = 8192) 35.4 in k_gemm_tile, 41.1 here with 32 rows, 42.8 and 50.6 with 48 (16 rows: 32.3 and 32.2); 750 strips (K = 4096) 26.8 and 22.6, 33.3
+// and 27.0; 768 strips 26.6 and 23.2, 34.0 and 28.9.  Up to 16 rows there are no slices to save: K = 2048, 1024 strips 14.5 in k_gemm, 15.8 here; K = 4096
+// 26.1 and 24.0.  Strips a workgroup for 1376 strips, 16 / 32 / 48 rows: six (230 workgroups) 30.8 / 34.4 / 40.8, seven (197) 32.3 / 36.3 / 44.2.
+static int wide_strips(const pv_model *m, int strips, int ktiles, int ct)
+{
+    if (!wide_fits(ktiles) || ktiles < (ct == 1 ? 128 : 16) || strips < 704) return 0;
+    int best = 0;
+    double least = 1e30;
+    for (int S : {7, 6, 4, 3}) {
+        const int rounds = ((strips + S - 1) / S + m->n_cus - 1) / m->n_cus;
+        const double t = rounds * (S + 0.6 * ct);
+        if (t < least) { least = t; best = S; }
+    }
+    return best;
+}
+
+template <int CT, int S, int EPI>
+static int allow_wide_lds()
+{
+    PV_HIP(hipFuncSetAttribute((const void *)k_gemm_wide<CT, S, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, wide_lds(CT, S)));
+    return PV_OK;
+}
+template <int CT, int EPI>
+static int allow_wide_all()
+{
+    int rc;
+    if ((rc = allow_wide_lds<CT, 3, EPI>()) != PV_OK || (rc = allow_wide_lds<CT, 4, EPI>()) != PV_OK || (rc = allow_wide_lds<CT, 6, EPI>()) != PV_OK) return rc;
+    return allow_wide_lds<CT, 7, EPI>();
+}
+
 // once per device before the first launch (and outside any stream capture): the wide-block kernels for 4-bit
 // weights use more dynamic LDS than the default limit
+template <int CT> static int allow_wide() { int rc; if ((rc = allow_wide_all<CT, EPI_QKV>()) != PV_OK || (rc = allow_wide_all<CT, EPI_SWIGLU>()) != PV_OK) return rc; return allow_wide_all<CT, EPI_LMHEAD>(); }
 int pv_mat_gemm_init(void)
 {
     int rc;
+    if ((rc = allow_wide<1>()) != PV_OK || (rc = allow_wide<2>()) != PV_OK || (rc = allow_wide<3>()) != PV_OK || (rc = allow_wide<4>()) != PV_OK) return rc;
     if ((rc = allow_tile_q4_lds<1, EPI_QKV>()) != PV_OK || (rc = allow_tile_q4_lds<1, EPI_RESID>()) != PV_OK ||
         (rc = allow_tile_q4_lds<1, EPI_SWIGLU>()) != PV_OK || (rc = allow_tile_q4_lds<1, EPI_LMHEAD>()) != PV_OK ||
         (rc = allow_tile_q4_lds<2, EPI_QKV>()) != PV_OK || (rc = allow_tile_q4_lds<2, EPI_RESID>()) != PV_OK ||
@@ -961,6 +1114,9 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
             else if (strips >= 512 && g.ktiles >= 64) k_gemm<1, 1, 2, EPI, 8, 4><<<(strips + 1) / 2, 512, 0, s>>>(ga);
             else if (g.ktiles >= 64) k_gemm<1, 1, 1, EPI, 16, 4><<<strips, 1024, 0, s>>>(ga);
             else k_gemm<1, 1, 1, EPI, 8, 4><<<strips, 512, 0, s>>>(ga);
+        } else if constexpr (CT == 3) {
+            pv_set_error("4-bit weights have no kernel for three column tiles");       // (their blocks of 33..48 rows run as four)
+            return PV_EINVAL;
         } else {
             // 4-bit weights, 9..64 rows: activation tiles shared through LDS, two strips per wave.  Few strips: cut along K.  Up to 32 rows two
             // workgroups fit on a CU (120 registers): at most 512 of them in one round (8B shape, 4 layers: 13 rows 396 -> 356 us a
@@ -983,14 +1139,26 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         // tiles per batch tile are matched by as many weight tiles (S = 2 or 4); a GEMM with few
         // strips keeps one strip per workgroup and more waves instead.
         constexpr int S = CT == 1 ? 2 : 4, NW = CT == 1 ? 8 : 4;
+        if constexpr (EPI != EPI_RESID) {
+            const int ws = wide_strips(m, strips, g.ktiles, CT);
+            if (ws) {
+                const int groups = (strips + ws - 1) / ws;
+                constexpr int threads4 = wide_waves(CT, 4) * 64, threads7 = wide_waves(CT, 7) * 64;
+                if (ws == 3) k_gemm_wide<CT, 3, EPI><<<groups, threads4, wide_lds(CT, 3), s>>>(ga);
+                else if (ws == 4) k_gemm_wide<CT, 4, EPI><<<groups, threads4, wide_lds(CT, 4), s>>>(ga);
+                else if (ws == 6) k_gemm_wide<CT, 6, EPI><<<groups, threads7, wide_lds(CT, 6), s>>>(ga);
+                else k_gemm_wide<CT, 7, EPI><<<groups, threads7, wide_lds(CT, 7), s>>>(ga);
+                PV_HIP(hipGetLastError());
+                return PV_OK;
+            }
+        }
         if constexpr (CT >= 2) {
             // Activation tiles shared through LDS; few strips: cut along K, into at most 256 workgroups, one a CU: with a few more (288 for the
-            // 8B-shaped QKV projection, 344 for the 7B-shaped gate/up) some CUs have two and the others wait for them (4 layers, us a step: 8B 32
-            // rows 542 -> 528, 48 rows 632 -> 614; 7B 24 rows 552 -> 492; up to 512 workgroups: 570, 663, 567).  From 129 groups of eight strips
-            // on that is one slice, on every second CU at first: K = 4096, us for a projection and its sum with 24 / 48 rows, one slice / two / three:
-            // 129 groups 38.5 / 46.4 / 37.7 and 50.6 / 55.3 / 45.3, 140 groups 39.4 / 49.0 / 39.2 and 50.1 / 58.1 / 46.5, 172 groups 41.0 / 50.0 /
-            // 51.8 and 52.4 / 59.7 / 61.2, 224 groups 47.0 / 57.2 / 57.0 and 55.1 / 67.0 / 67.5 (128 groups, two slices: 33.8 and 38.8)
-            if (g.ktiles >= 16) {
+            // 8B-shaped QKV projection) some CUs have two and the others wait for them (4 layers, us a step: 32 rows 542 -> 528, 48 rows 632 -> 614;
+            // up to 512 workgroups: 570, 663).  From 129 groups of eight strips on that is one slice (K = 4096, us for a projection
+            // and its sum with 24 / 48 rows, one slice / two: 129 groups 38.5 / 46.4 and 50.6 / 55.3, 224 groups 47.0 / 57.2 and 55.1 / 67.0).
+            // Three column tiles for 33..48 rows instead of four, 48 rows, 8B shape, us: QKV 16.9 -> 15.0, O 12.7 -> 11.2, down 28.3 -> 25.5.
+            if (CT == 3 || g.ktiles >= 16) {
                 const int ngroups = (strips + 7) / 8;
                 int slices = g.tile_part == nullptr ? 1 : max(1, min(TILE_MAX_SLICES, 256 / ngroups));
                 int tps = (g.ktiles + slices - 1) / slices;
@@ -1023,9 +1191,11 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
                 return PV_OK;
             }
         }
-        if (strips >= 256 * S) k_gemm<NB, CT, S, EPI, NW><<<(strips + S - 1) / S, NW * 64, 0, s>>>(ga);
-        else if (CT == 1 && g.ktiles >= 64) k_gemm<NB, CT, 1, EPI, 16><<<strips, 1024, 0, s>>>(ga);
-        else k_gemm<NB, CT, 1, EPI, 8><<<strips, 512, 0, s>>>(ga);
+        if constexpr (CT != 3) {
+            if (strips >= 256 * S) k_gemm<NB, CT, S, EPI, NW><<<(strips + S - 1) / S, NW * 64, 0, s>>>(ga);
+            else if (CT == 1 && g.ktiles >= 64) k_gemm<NB, CT, 1, EPI, 16><<<strips, 1024, 0, s>>>(ga);
+            else k_gemm<NB, CT, 1, EPI, 8><<<strips, 512, 0, s>>>(ga);
+        }
     } else {
         // Eight waves, each three batches deep (two workgroups per CU at <= 128 registers): measured
         // 1 - 8 % faster per GEMM than sixteen waves that load and use one batch at a time; a short K
@@ -1140,6 +1310,7 @@ int pv_mat_run_block(pv_cache *c, hipStream_t s)
     if (rows <= 8) return run_block<1, 1>(c, s);
     if (rows <= 16) return run_block<2, 1>(c, s);
     if (rows <= 32) return run_block<2, 2>(c, s);
+    if (rows <= 48 && c->m->wbits == 16) return run_block<2, 3>(c, s);
     return run_block<2, 4>(c, s);
 }
 

@@ -42,7 +42,7 @@ struct attn_args {
     float *part_ml;             // [n_kv_heads][MP][max_chunks][32][2]  (max, sum)
     uint16_t *xop_o;            // merge output: operand of the output projection, K = n_q_heads*hd
     int n_pages;                // entries of the page table
-    int lo_off;                 // column offset of the lo halves in the output operand's tiles (packed rows)
+    int rows;                   // rows of the block (the output operand's tiles of packed rows)
 };
 
 __device__ inline void split8(const float v[8], uint4 &hi, uint4 &lo)
@@ -229,7 +229,7 @@ __device__ inline void attn_chunk(const attn_args &a, int c, int kvh, int z, int
             for (int w = 1; w < NWM; ++w) L += sh_l[t * NWM + w][r];
             const float inv = 1.0f / L, y[4] = {acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv};
             const int alr = mr / gamma, jr = mr - alr * gamma;
-            store_operand4<(NB == 1 ? 1 : 2)>(a.xop_o, a.n_q_heads * HD, row0 + jr, (kvh * a.group + alr) * HD + 4 * c4, y, a.lo_off);
+            store_operand4<(NB == 1 ? 1 : 2)>(a.xop_o, a.n_q_heads * HD, row0 + jr, (kvh * a.group + alr) * HD + 4 * c4, y, a.rows);
         }
     }
     if (NB == 0 && threadIdx.x < TILES * 16) {
@@ -320,6 +320,6 @@ __device__ inline void attn_merge_unit(const attn_args &a, int r, int aq, int n_
     }
     const float inv = 1.0f / L;
     const float y[4] = {acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
-    store_operand4<NB>(a.xop_o, a.n_q_heads * HD, r, aq * HD + 4 * t, y, a.lo_off);
+    store_operand4<NB>(a.xop_o, a.n_q_heads * HD, r, aq * HD + 4 * t, y, a.rows);
 }
 

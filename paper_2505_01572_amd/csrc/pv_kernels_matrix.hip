@@ -204,7 +204,7 @@ k_mat_begin(pv_dev_state *st, const int32_t *mailbox, int rows, int mode, const 
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = pv_bf16_to_f32(e[r]);
     }
-    emit_x<NB>(lane, rows, strip, d, v, *(const uint2 *)(gain + strip * 16 + 4 * g), x, ssq, xop, ct, pv_lo_off(rows));
+    emit_x<NB>(lane, rows, strip, d, v, *(const uint2 *)(gain + strip * 16 + 4 * g), x, ssq, xop, ct, rows);
     if (ct != 0) return;
     for (int idx = blockIdx.x * 64 + lane; idx < rows * half; idx += gridDim.x * 64) {
         const int jj = idx / half, i = idx - jj * half;
@@ -249,6 +249,23 @@ __device__ inline void k_walk(int cnt, Q &q0, Q &q1, Q &q2, FI issue, FC consume
     }
 }
 
+// Loads through buffer descriptors: the lane's offset in a register, the wave's in a scalar, zeros (and no traffic) past the end.
+__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00020000); }
+#define BUFFER_END 0xC0000000u                     // past the end of every buffer (wide_fits), and no sum with an offset inside one wraps
+template <int AUX> __device__ inline uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t base)
+{
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, base, AUX));
+}
+#define LOAD_ONCE 2                                // the non-temporal bit (see load_once)
+
+// Where lane l of the B operand reads inside a packed tile of R rows, in uint4s: its columns 0..7 are the rows' hi parts, 8..15 their
+// lo parts (R <= 8; the columns in between read the last row again: no further line, and their results are never used).
+__device__ inline int packed_lane(int lane, int R)
+{
+    const int col = lane & 15;
+    return (lane >> 4) * 2 * R + (col < 8 ? min(col, R - 1) : R + min(col - 8, R - 1));
+}
+
 // ------------------------------------------------------------------------------------------
 // The streaming GEMM: a workgroup owns S adjacent strips, its NW waves split K in batches of U
 // tiles.
@@ -283,7 +300,7 @@ k_gemm(const gemm_args a)
     static_assert(NB == 2 || CT == 1, "packed rows come in one tile");
     static_assert(S <= NW, "one epilogue wave per strip");
     static_assert(WB == 16 || (WB == 4 && CT == 1), "4-bit weights: one column tile");
-    static_assert(!HF || ((WB == 4 || DP > 1) && S >= 2), "half strips: walked batches");
+    static_assert(!HF || WB == 4 || DP > 1, "half strips: walked batches");
     constexpr int U = (S * CT >= 16) ? 1 : (S * CT >= 4) ? 2 : (DP > 1 && (S >= 2 || NB == 2)) ? 2 : 4;   // tiles per batch (16-bit weights)
     constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LMHEAD);
     constexpr bool PARK = (CT == 1);                 // epilogue inputs fetched early (by the wave that will run the strip's epilogue) and parked in LDS
@@ -291,21 +308,17 @@ k_gemm(const gemm_args a)
     // its neighbour (strips a.half_base ...), so that a GEMM with (k + 1/2) x 256 strips puts the
     // same bytes on every CU; the lanes of the other half duplicate the owned half's loads for
     // that slot and their rows of the product are not stored.
-    const int strip0 = blockIdx.x * (HF ? S - 1 : S), wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int strip0 = blockIdx.x * (HF ? S - 1 : S), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int hstrip = HF ? a.half_base + ((int)blockIdx.x >> 1) : 0, hsel = blockIdx.x & 1;
     const int hl = HF ? ((lane & ~8) | (hsel << 3)) - lane : 0;    // half slot: the lanes of the other half read the owned half's lines again (no further bytes)
     const int KT = a.ktiles, nbat = KT / U;        // whole batches of U tiles; a ragged rest goes to the last wave
-    int b, bend, bstep;
-    if (a.interleave) { b = wave; bend = nbat; bstep = NW; }
-    else { const int per = (nbat + NW - 1) / NW; b = min(nbat, wave * per); bend = min(nbat, b + per); bstep = 1; }
     const size_t arr = (size_t)KT * 64;             // tiles of one strip = elements of one operand array, in uint4
     const uint4 *A = a.W + (size_t)strip0 * arr + lane;
-    // tile ct: hi at B + (2 ct) arr, lo at B + (2 ct + 1) arr   (NB == 2).  Packed rows of a block of at most 4: hi and lo sit in
-    // columns 0..3 and 4..7 of a tile; the lanes of columns 8..11 read the lo columns again, so that the epilogue finds them
-    // where a block of 8 has them, and those of 12..15 anything in the same 128-byte line (their columns are never used): half the lines
-    int bl = lane;
-    if (NB == 1 && a.lo_off == 4) { const int col = lane & 15; bl = (lane & ~15) | (col < 8 ? col : col < 12 ? col - 4 : col - 8); }
-    const uint4 *B = a.xop + bl;
+    // tile ct: hi at B + (2 ct) arr, lo at B + (2 ct + 1) arr   (NB == 2)
+    const uint4 *B = a.xop + lane;
+    const uint32_t xs = NB == 1 ? 128u * (uint32_t)a.rows : 1024u, xl = (NB == 1 ? packed_lane(lane, a.rows) : lane) * 16;   // bytes of an operand tile, the lane's place in it
+    const __amdgpu_buffer_rsrc_t P = buffer_of(a.xop, NB * (uint32_t)KT * xs);
+    auto operand = [&](int t) { return buffer_load16<0>(P, xl, (uint32_t)t * xs); };        // one column tile: K-tile t, the lo halves of a 16-row tile at KT + t (the same t for the whole wave)
     // a ragged last workgroup re-reads its first strip for the missing ones and drops the result
     size_t so[S];
 #pragma unroll
@@ -336,10 +349,10 @@ k_gemm(const gemm_args a)
         // The product is taken transposed here (activation rows x features): all four results
         // of a lane then belong to one feature, and the lane needs one scale per tile.
         struct qbatch { uint4 c[S]; uint2 s[S]; uint4 bh[4], bl[NB == 2 ? 4 : 1]; };
-        const int nb4 = KT >> 2, wv = __builtin_amdgcn_readfirstlane(wave);    // batch addresses in scalar registers
+        const int nb4 = KT >> 2;
         int first, cnt, bstride;
-        if (a.interleave) { first = wv; bstride = NW; cnt = wv < nb4 ? (nb4 - wv + NW - 1) / NW : 0; }
-        else { const int per = (nb4 + NW - 1) / NW; first = min(nb4, wv * per); cnt = min(nb4, first + per) - first; bstride = 1; }
+        if (a.interleave) { first = wave; bstride = NW; cnt = wave < nb4 ? (nb4 - wave + NW - 1) / NW : 0; }
+        else { const int per = (nb4 + NW - 1) / NW; first = min(nb4, wave * per); cnt = min(nb4, first + per) - first; bstride = 1; }
         size_t qo[S];
 #pragma unroll
         for (int si = 0; si < S; ++si) qo[si] = (HF && si == S - 1) ? (size_t)(hstrip - strip0) * qstrip : (strip0 + si < a.nstrips) ? (size_t)si * qstrip : 0;
@@ -354,9 +367,8 @@ k_gemm(const gemm_args a)
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const size_t o = (size_t)(bt * 4 + u) * 64;
-                q.bh[u] = B[o];
-                if (NB == 2) q.bl[NB == 2 ? u : 0] = B[arr + o];
+                q.bh[u] = operand(bt * 4 + u);
+                if (NB == 2) q.bl[NB == 2 ? u : 0] = operand(KT + bt * 4 + u);
             }
             asm volatile("" ::: "memory");           // the loads go out here, ahead of the arithmetic that follows
         };
@@ -411,18 +423,17 @@ k_gemm(const gemm_args a)
     } else if constexpr (DP > 1) {
         static_assert(CT == 1, "deep variant: one column tile");
         struct wbatch { uint4 w[S][U], x[U], xl[NB == 2 ? U : 1]; };     // xl: the lo halves of a 16-row tile
-        const int wv = __builtin_amdgcn_readfirstlane(wave);
         int first, cnt, bstride;
-        if (a.interleave) { first = wv; bstride = NW; cnt = wv < nbat ? (nbat - wv + NW - 1) / NW : 0; }
-        else { const int per = (nbat + NW - 1) / NW; first = min(nbat, wv * per); cnt = min(nbat, first + per) - first; bstride = 1; }
+        if (a.interleave) { first = wave; bstride = NW; cnt = wave < nbat ? (nbat - wave + NW - 1) / NW : 0; }
+        else { const int per = (nbat + NW - 1) / NW; first = min(nbat, wave * per); cnt = min(nbat, first + per) - first; bstride = 1; }
         auto issue = [&](wbatch &q, int k) {
             const size_t o = (size_t)(first + k * bstride) * U * 64;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
 #pragma unroll
                 for (int si = 0; si < S; ++si) q.w[si][u] = load_once(&A[so[si] + o + u * 64 + ((HF && si == S - 1) ? hl : 0)]);
-                q.x[u] = B[o + u * 64];
-                if (NB == 2) q.xl[NB == 2 ? u : 0] = B[arr + o + u * 64];
+                q.x[u] = operand((first + k * bstride) * U + u);
+                if (NB == 2) q.xl[NB == 2 ? u : 0] = operand(KT + (first + k * bstride) * U + u);
             }
             asm volatile("" ::: "memory");
         };
@@ -449,9 +460,9 @@ k_gemm(const gemm_args a)
         });
         if (wave == NW - 1) {
             for (int t = nbat * U; t < KT; ++t) {
-                const uint4 x = B[(size_t)t * 64];
+                const uint4 x = operand(t);
                 uint4 xl = x;
-                if (NB == 2) xl = B[arr + (size_t)t * 64];
+                if (NB == 2) xl = operand(KT + t);
 #pragma unroll
                 for (int si = 0; si < S; ++si) {
                     const uint4 w = load_once(&A[so[si] + (size_t)t * 64 + ((HF && si == S - 1) ? hl : 0)]);
@@ -461,6 +472,9 @@ k_gemm(const gemm_args a)
             }
         }
     } else {
+    int b, bend, bstep;
+    if (a.interleave) { b = wave; bend = nbat; bstep = NW; }
+    else { const int per = (nbat + NW - 1) / NW; b = min(nbat, wave * per); bend = min(nbat, b + per); bstep = 1; }
     uint4 ra[S][U], rb[CT][U], rc[CT][U];
     auto load_batch = [&](int t) {
 #pragma unroll
@@ -470,7 +484,7 @@ k_gemm(const gemm_args a)
             for (int si = 0; si < S; ++si) ra[si][u] = load_once(&A[so[si] + o]);
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
-                rb[ct][u] = B[(size_t)(2 * ct) * arr + o];
+                rb[ct][u] = NB == 1 ? operand(t + u) : B[(size_t)(2 * ct) * arr + o];
                 if (NB == 2) rc[ct][u] = B[(size_t)(2 * ct + 1) * arr + o];
             }
         }
@@ -515,7 +529,7 @@ k_gemm(const gemm_args a)
             const size_t o = (size_t)t * 64;
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
-                const uint4 bh = B[(size_t)(2 * ct) * arr + o];
+                const uint4 bh = NB == 1 ? operand(t) : B[(size_t)(2 * ct) * arr + o];
                 uint4 bl = bh;
                 if (NB == 2) bl = B[(size_t)(2 * ct + 1) * arr + o];
 #pragma unroll
@@ -549,13 +563,14 @@ k_gemm(const gemm_args a)
         if (PARK) epi_unpark<EPI>(&pre_s[wave][lane], pre);
         else epi_prefetch<EPI>(a, strip, lane, pre, ct);
         if (NORM) {
-            float tot = ssq_s[0][ct][lane & 15];
+            auto col = [&](int w) { return NB == 1 ? ssq_s[w][ct][lane & 7] + ssq_s[w][ct][8 + (lane & 7)] : ssq_s[w][ct][lane & 15]; };   // (two halves of a strip: emit_x)
+            float tot = col(0);
 #pragma unroll
-            for (int w = 1; w < NW; ++w) tot += ssq_s[w][ct][lane & 15];
+            for (int w = 1; w < NW; ++w) tot += col(w);
             pre.rj = 1.0f / sqrtf(tot * a.inv_d + a.eps);
         }
         if (hslot && (lane >> 5) != hsel) pre.rows = 0;           // features 4 (lane / 16) .. + 3 of the other half: nothing to store
-        epi_apply<NB, EPI>(a, strip, lane, sum, pre, ct);
+        epi_apply<NB, EPI>(a, strip, lane, sum, pre, ct, hslot ? hsel : -1);
     }
 }
 
@@ -572,13 +587,6 @@ k_gemm(const gemm_args a)
 // Loads go through buffer descriptors: a K-tile past the end of the slice gets an offset past the buffer's end,
 // for which zeros come back and nothing is fetched, so every load of the loop is unconditional.
 // ------------------------------------------------------------------------------------------
-__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00020000); }
-#define BUFFER_END 0xC0000000u                     // past the end of every buffer (wide_fits), and no sum with an offset inside one wraps
-template <int AUX> __device__ inline uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t base)
-{
-    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, base, AUX));
-}
-#define LOAD_ONCE 2                                // the non-temporal bit (see load_once)
 
 constexpr int wide_waves(int ct, int s) { return ct <= 2 || s <= 4 ? 8 : 4; }              // (what the registers of one workgroup per CU hold)
 constexpr int wide_lds(int ct, int s) { return wide_waves(ct, s) * s * ct * 1024; }
@@ -1227,6 +1235,16 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
                 return PV_OK;
             }
         }
+        if constexpr (EPI == EPI_RESID) {
+            // at most half as many strips as CUs: a workgroup per 8-feature half (every CU works, on half the weights: 128 strips, one row,
+            // K = 2048 and 8192 together 14.9 -> 13.6 us)
+            if (g.ktiles >= 64 && 2 * strips <= m->n_cus) {
+                ga.half_base = 0;
+                k_gemm<NB, CT, 1, EPI, 8, 16, 3, true><<<2 * strips, 512, 0, s>>>(ga);
+                PV_HIP(hipGetLastError());
+                return PV_OK;
+            }
+        }
         auto fill = [](int wgs) { return (double)wgs / (double)(((wgs + 255) / 256) * 256); };
         const bool two = strips >= 512 && fill((strips + 1) / 2) >= fill(strips);
         if (g.ktiles >= 64 && two) k_gemm<NB, CT, 2, EPI, 8, 16, 2><<<(strips + 1) / 2, 512, 0, s>>>(ga);
@@ -1254,7 +1272,7 @@ static int run_block(pv_cache *c, hipStream_t s)
 
     gemm_args g = {};
     int prc;
-    g.st = c->ws.state; g.lo_off = pv_lo_off(rows); g.inv_d = 1.0f / (float)d; g.eps = (float)f.rms_eps; g.ssq_parts = d / 16;
+    g.st = c->ws.state; g.rows = rows; g.inv_d = 1.0f / (float)d; g.eps = (float)f.rms_eps; g.ssq_parts = d / 16;
     g.q_hi = (uint16_t *)c->ws.q; g.q_lo = g.q_hi + (size_t)c->rows_cap * qd; g.pool = (uint16_t *)c->d_pool; g.page_table = c->ws.page_table; g.rope = c->ws.rope; g.geom = pv_geom(c);
     g.n_q_heads = f.n_q_heads; g.q_strips = qd / 16; g.k_strips = kvd / 16;
     g.x = c->ws.x; g.d = d; g.xop_act = mw.xop_d; g.F = F;
@@ -1325,7 +1343,7 @@ int pv_mat_run_prompt(pv_cache *c, int rows, int keep, hipStream_t s)
     if (rc != PV_OK || keep == 0) return rc;
     // the head of the kept rows (whatever their number, as column tiles of 16 rows: the layout of the prompt's operand)
     gemm_args g = {};
-    g.st = c->ws.state; g.lo_off = 8; g.inv_d = 1.0f / (float)f.d_model; g.eps = (float)f.rms_eps; g.ssq_parts = f.d_model / 16;
+    g.st = c->ws.state; g.inv_d = 1.0f / (float)f.d_model; g.eps = (float)f.rms_eps; g.ssq_parts = f.d_model / 16;
     g.logits = c->ws.logits; g.pmax_val = mw.pmax_val; g.pmax_idx = mw.pmax_idx; g.vocab = f.vocab; g.tile_part = mw.tile_part;
     g.W = (const uint4 *)(m->d_weights + m->global[PV_T_LM_HEAD].off); g.xop = (const uint4 *)out.xop; g.ktiles = f.d_model / 32; g.ssq = out.ssq;
     if ((rc = pv_prof_mark(c, PV_PROF_LMHEAD, 0, 0, s)) != PV_OK) return rc;

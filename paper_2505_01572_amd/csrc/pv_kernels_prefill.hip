@@ -1108,7 +1108,7 @@ int pv_pre_block(pv_cache *c, const int32_t *d_host_tokens, int rows, int keep, 
     PV_HIP(hipGetLastError());
 
     gemm_args g = {};
-    g.st = c->ws.state; g.lo_off = 8; g.inv_d = 1.0f / (float)d; g.eps = (float)f.rms_eps; g.ssq_parts = d / 16;
+    g.st = c->ws.state; g.inv_d = 1.0f / (float)d; g.eps = (float)f.rms_eps; g.ssq_parts = d / 16;
     g.q_hi = w.q_hi; g.q_lo = w.q_lo; g.pool = (uint16_t *)c->d_pool; g.page_table = c->ws.page_table; g.rope = w.rope; g.geom = pv_geom(c);
     g.n_q_heads = f.n_q_heads; g.q_strips = qd / 16; g.k_strips = kvd / 16;
     g.x = w.x; g.d = d; g.xop_act = w.xop_d; g.F = F; g.tile_part = w.part; g.ssq = w.ssq; g.ssq_out = w.ssq; g.xop_out = w.xop;

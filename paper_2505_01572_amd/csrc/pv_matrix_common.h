@@ -30,10 +30,12 @@ __device__ inline uint2 load_once(const uint2 *p)
 
 // ------------------------------------------------------------------------------------------
 // Operand writers.  Element (row j, K-index k) of an activation lives at
-//   arr[(k/32)*512 + (col + 16*((k%32)/8))*8 + k%8],  col = j (hi) / j + lo_off (lo) when NB == 1
-//   (at most 8 rows; lo_off = 8, or 4 for blocks of at most 4 rows: columns 0..7 are then all a
-//   reader needs, half the 128-byte lines of a tile).  When NB == 2 the rows come in column tiles of 16: tile j/16 owns a hi
-//   array followed by a lo array ((K/32)*512 elements each), col = j%16 in both.
+//   arr[(k/32)*512 + (j%16 + 16*((k%32)/8))*8 + k%8]            (NB == 2: rows in column tiles of 16, tile j/16 has a hi
+//   array and behind it a lo array of (K/32)*512 elements each)
+//   arr[(k/32)*64*R + (col + 2*R*((k%32)/8))*8 + k%8],  col = j (hi) / j + R (lo)      (NB == 1: a block of R <= 8 rows)
+// A packed tile holds the columns of its R rows and nothing else: R lines of 128 bytes.  What every workgroup reads again
+// from L2 beside its weights is then in proportion to the rows (with half tiles up to 4 rows and whole ones from 5 on, one row read 4 lines and
+// five read 8): one row of the 1B shape (8 layers) 459 -> 449 us a step, five rows of the 7B shape (4 layers) 414 -> 402.
 // ------------------------------------------------------------------------------------------
 __device__ inline uint16_t bf16_rne(float f) { return pv_f32_to_bf16(f); }
 
@@ -47,20 +49,18 @@ __device__ inline void split2(float a, float b, uint32_t &hi, uint32_t &lo)
     lo = pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
 }
 
-// four consecutive k (k0 % 4 == 0) of row j
-// lo column offset of a packed-row block of `rows` rows
-__host__ __device__ inline int pv_lo_off(int rows) { return rows <= 4 ? 4 : 8; }
-
+// four consecutive k (k0 % 4 == 0) of row j; R: rows of the block (packed rows)
 template <int NB>
-__device__ inline void store_operand4(uint16_t *xop, int K, int j, int k0, const float y[4], int lo_off)
+__device__ inline void store_operand4(uint16_t *xop, int K, int j, int k0, const float y[4], int R)
 {
-    const size_t tile = (size_t)(k0 >> 5) * 512, in = (size_t)(((k0 & 31) >> 3) * 16) * 8 + (k0 & 7);
+    const int tile_elems = NB == 1 ? 64 * R : 512, cols = NB == 1 ? 2 * R : 16;
+    const size_t tile = (size_t)(k0 >> 5) * tile_elems, in = (size_t)(((k0 & 31) >> 3) * cols) * 8 + (k0 & 7);
     uint2 vh, vl;
     split2(y[0], y[1], vh.x, vl.x);
     split2(y[2], y[3], vh.y, vl.y);
     if (NB == 1) {
         *(uint2 *)(xop + tile + in + (size_t)j * 8) = vh;
-        *(uint2 *)(xop + tile + in + (size_t)(j + lo_off) * 8) = vl;
+        *(uint2 *)(xop + tile + in + (size_t)(j + R) * 8) = vl;
     } else {
         const size_t arr = (size_t)(K / 32) * 512;
         uint16_t *base = xop + (size_t)(j >> 4) * 2 * arr + tile + in + (size_t)(j & 15) * 8;

@@ -82,6 +82,14 @@ def test_matrix_path_matches_oracle(pvlib, shape, path):
     _check_against_oracle(pvlib, shape, path, 16, 37, (8, 13, 1, 5, 16, 3), 96)   # prefill chunks of 16, 16, 5 rows
 
 
+@pytest.mark.parametrize("name", ["mat_a", "mat_b", "fuse_b", "q4_b"])
+def test_packed_rows_match_oracle(pvlib, name):
+    """Every number of rows that is packed into one operand tile; the down projections of mat_b (129 K-tiles, 64 strips) and
+    fuse_b (264) run as half strips."""
+    shape = {"mat_a": MAT_A, "mat_b": MAT_B, "fuse_b": FUSE_B, "q4_b": Q4_B}[name]
+    _check_against_oracle(pvlib, shape, 0, 16, 21, (2, 7, 4, 6, 1, 3, 5, 8), 96)
+
+
 def test_wide_blocks_match_oracle(pvlib, wide_shape):
     """Blocks of 17..64 rows (two and four 16-row column tiles per weight pass; with 4-bit weights one
     weight pass per column tile), next to narrow ones on the same cache; the prompt is prefilled in

@@ -575,8 +575,8 @@ k_gemm(const gemm_args a)
 }
 
 // ------------------------------------------------------------------------------------------
-// Projections with three or more strips a CU (gate/up, the vocabulary, the QKV projection without shared heads), 9..64 rows (CT column
-// tiles of 16 rows, a hi and a lo operand each): one workgroup per CU owns S strips and its NW waves split K, so
+// Projections with three or more strips a CU (gate/up, the vocabulary, the QKV projection without shared heads), 9..64 rows (NB = 2: CT column
+// tiles of 16 rows, a hi and a lo operand each), and up to 8 (NB = 1) from four strips a CU on: one workgroup per CU owns S strips and its NW waves split K, so
 // that each activation tile enters the CU once, for S strips, and straight into the registers of the one wave
 // that uses it: no LDS and no barrier before the final sum over the waves.
 // A CU has some 32 KiB of loads in flight (its L1's size: 56 GB/s of HBM latency, 130 GB/s of L2 latency, whatever the waves ask for), so what counts is
@@ -592,11 +592,12 @@ constexpr int wide_waves(int ct, int s) { return ct <= 2 || s <= 4 ? 8 : 4; }   
 constexpr int wide_lds(int ct, int s) { return wide_waves(ct, s) * s * ct * 1024; }
 static inline bool wide_fits(int ktiles) { return ktiles <= (1 << 16); }                   // the largest buffer: 8 arrays of K-tiles of 1 KiB = 0.5 GiB
 
-template <int CT, int S, int EPI>
+template <int NB, int CT, int S, int EPI>
 __global__ void __launch_bounds__(wide_waves(CT, S) * 64) __attribute__((amdgpu_waves_per_eu(wide_waves(CT, S) / 4, wide_waves(CT, S) / 4)))
 k_gemm_wide(const gemm_args a)
 {
-    constexpr int NW = wide_waves(CT, S), NX = 2 * CT;
+    static_assert(NB == 2 || CT == 1, "packed rows come in one tile");
+    constexpr int NW = wide_waves(CT, S), NX = NB == 1 ? 1 : 2 * CT;
     constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LMHEAD);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int KT = a.ktiles, nst = (KT + NW - 1) / NW;          // K-tiles of a wave: wave, wave + NW, ... (some waves' last one is past the end)
@@ -612,7 +613,9 @@ k_gemm_wide(const gemm_args a)
     }
     const uint32_t tb = (uint32_t)KT * 1024;                    // bytes of a strip, and of an operand array
     const int mine = min(S, a.nstrips - strip0);                // (strips past the end re-read the last one; dropped below)
-    const __amdgpu_buffer_rsrc_t W = buffer_of((const char *)a.W + (size_t)strip0 * tb, (uint32_t)mine * tb), X = buffer_of(a.xop, NX * tb);
+    const __amdgpu_buffer_rsrc_t W = buffer_of((const char *)a.W + (size_t)strip0 * tb, (uint32_t)mine * tb);
+    const uint32_t xs = NB == 1 ? 128u * (uint32_t)a.rows : 1024u, xl = (NB == 1 ? packed_lane(lane, a.rows) : lane) * 16;   // as in k_gemm
+    const __amdgpu_buffer_rsrc_t X = buffer_of(a.xop, NX * (uint32_t)KT * xs);
     uint32_t wo[S];
 #pragma unroll
     for (int si = 0; si < S; ++si) wo[si] = (uint32_t)min(si, mine - 1) * tb;
@@ -628,11 +631,12 @@ k_gemm_wide(const gemm_args a)
     struct stage { uint4 w[S], x[NX]; };
     auto issue = [&](stage &q, int i) {
         const int k = i + rot, t = (k < nst ? k : k - nst) * NW + wave;
-        const uint32_t off = lane * 16 + (i < nst && t < KT ? (uint32_t)t * 1024 : BUFFER_END);
+        const bool in = i < nst && t < KT;
+        const uint32_t off = lane * 16 + (in ? (uint32_t)t * 1024 : BUFFER_END), offx = xl + (in ? (uint32_t)t * xs : BUFFER_END);
 #pragma unroll
         for (int si = 0; si < S; ++si) q.w[si] = buffer_load16<LOAD_ONCE>(W, off, wo[si]);
 #pragma unroll
-        for (int r = 0; r < NX; ++r) q.x[r] = buffer_load16<0>(X, off, r * tb);
+        for (int r = 0; r < NX; ++r) q.x[r] = buffer_load16<0>(X, offx, r * tb);
         asm volatile("" ::: "memory");
     };
     auto use = [&](const stage &q) {
@@ -678,12 +682,13 @@ k_gemm_wide(const gemm_args a)
         epi_pre pre;
         epi_prefetch<EPI>(a, strip0 + si, lane, pre, ct);
         if (NORM) {
-            float s = ssq_s[0][ct][lane & 15];
+            auto col = [&](int w) { return NB == 1 ? ssq_s[w][ct][lane & 7] + ssq_s[w][ct][8 + (lane & 7)] : ssq_s[w][ct][lane & 15]; };   // (two halves of a strip: emit_x)
+            float s = col(0);
 #pragma unroll
-            for (int w = 1; w < NW; ++w) s += ssq_s[w][ct][lane & 15];
+            for (int w = 1; w < NW; ++w) s += col(w);
             pre.rj = 1.0f / sqrtf(s * a.inv_d + a.eps);
         }
-        epi_apply<2, EPI>(a, strip0 + si, lane, v, pre, ct);
+        epi_apply<NB, EPI>(a, strip0 + si, lane, v, pre, ct);
     }
 }
 
@@ -1064,34 +1069,50 @@ static int wide_strips(const pv_model *m, int strips, int ktiles, int ct)
     return best;
 }
 
-template <int CT, int S, int EPI>
+template <int NB, int CT, int S, int EPI>
 static int allow_wide_lds()
 {
-    PV_HIP(hipFuncSetAttribute((const void *)k_gemm_wide<CT, S, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, wide_lds(CT, S)));
+    if (wide_lds(CT, S) > 65536) PV_HIP(hipFuncSetAttribute((const void *)k_gemm_wide<NB, CT, S, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, wide_lds(CT, S)));
     return PV_OK;
 }
-template <int CT, int EPI>
+template <int NB, int CT, int EPI>
 static int allow_wide_all()
 {
     int rc;
-    if ((rc = allow_wide_lds<CT, 3, EPI>()) != PV_OK || (rc = allow_wide_lds<CT, 4, EPI>()) != PV_OK || (rc = allow_wide_lds<CT, 6, EPI>()) != PV_OK) return rc;
-    return allow_wide_lds<CT, 7, EPI>();
+    if ((rc = allow_wide_lds<NB, CT, 3, EPI>()) != PV_OK || (rc = allow_wide_lds<NB, CT, 4, EPI>()) != PV_OK || (rc = allow_wide_lds<NB, CT, 6, EPI>()) != PV_OK) return rc;
+    return allow_wide_lds<NB, CT, 7, EPI>();
 }
 
-// once per device before the first launch (and outside any stream capture): the wide-block kernels for 4-bit
-// weights use more dynamic LDS than the default limit
-template <int CT> static int allow_wide() { int rc; if ((rc = allow_wide_all<CT, EPI_QKV>()) != PV_OK || (rc = allow_wide_all<CT, EPI_SWIGLU>()) != PV_OK) return rc; return allow_wide_all<CT, EPI_LMHEAD>(); }
-int pv_mat_gemm_init(void)
+template <int NB, int CT, int EPI>
+static int launch_wide(const gemm_args &ga, int strips, int ws, hipStream_t s)
+{
+    const int groups = (strips + ws - 1) / ws;
+    constexpr int threads4 = wide_waves(CT, 4) * 64, threads7 = wide_waves(CT, 7) * 64;
+    if (ws == 3) k_gemm_wide<NB, CT, 3, EPI><<<groups, threads4, wide_lds(CT, 3), s>>>(ga);
+    else if (ws == 4) k_gemm_wide<NB, CT, 4, EPI><<<groups, threads4, wide_lds(CT, 4), s>>>(ga);
+    else if (ws == 6) k_gemm_wide<NB, CT, 6, EPI><<<groups, threads7, wide_lds(CT, 6), s>>>(ga);
+    else k_gemm_wide<NB, CT, 7, EPI><<<groups, threads7, wide_lds(CT, 7), s>>>(ga);
+    PV_HIP(hipGetLastError());
+    return PV_OK;
+}
+
+// once per device before the first launch (and outside any stream capture): kernels that use more dynamic LDS than the default limit
+template <int NB, int CT> static int allow_wide() { int rc; if ((rc = allow_wide_all<NB, CT, EPI_QKV>()) != PV_OK || (rc = allow_wide_all<NB, CT, EPI_SWIGLU>()) != PV_OK) return rc; return allow_wide_all<NB, CT, EPI_LMHEAD>(); }
+template <int CT> static int allow_tile_q4()
 {
     int rc;
-    if ((rc = allow_wide<1>()) != PV_OK || (rc = allow_wide<2>()) != PV_OK || (rc = allow_wide<3>()) != PV_OK || (rc = allow_wide<4>()) != PV_OK) return rc;
-    if ((rc = allow_tile_q4_lds<1, EPI_QKV>()) != PV_OK || (rc = allow_tile_q4_lds<1, EPI_RESID>()) != PV_OK ||
-        (rc = allow_tile_q4_lds<1, EPI_SWIGLU>()) != PV_OK || (rc = allow_tile_q4_lds<1, EPI_LMHEAD>()) != PV_OK ||
-        (rc = allow_tile_q4_lds<2, EPI_QKV>()) != PV_OK || (rc = allow_tile_q4_lds<2, EPI_RESID>()) != PV_OK ||
-        (rc = allow_tile_q4_lds<2, EPI_SWIGLU>()) != PV_OK || (rc = allow_tile_q4_lds<2, EPI_LMHEAD>()) != PV_OK ||
-        (rc = allow_tile_q4_lds<4, EPI_QKV>()) != PV_OK || (rc = allow_tile_q4_lds<4, EPI_RESID>()) != PV_OK ||
-        (rc = allow_tile_q4_lds<4, EPI_SWIGLU>()) != PV_OK || (rc = allow_tile_q4_lds<4, EPI_LMHEAD>()) != PV_OK) return rc;
-    return PV_OK;
+    if ((rc = allow_tile_q4_lds<CT, EPI_QKV>()) != PV_OK || (rc = allow_tile_q4_lds<CT, EPI_RESID>()) != PV_OK || (rc = allow_tile_q4_lds<CT, EPI_SWIGLU>()) != PV_OK) return rc;
+    return allow_tile_q4_lds<CT, EPI_LMHEAD>();
+}
+int pv_mat_gemm_init(int wbits)
+{
+    int rc;
+    if (wbits == 4) {
+        if ((rc = allow_tile_q4<1>()) != PV_OK || (rc = allow_tile_q4<2>()) != PV_OK) return rc;
+        return allow_tile_q4<4>();
+    }
+    if ((rc = allow_wide<1, 1>()) != PV_OK || (rc = allow_wide<2, 1>()) != PV_OK || (rc = allow_wide<2, 2>()) != PV_OK || (rc = allow_wide<2, 3>()) != PV_OK) return rc;
+    return allow_wide<2, 4>();
 }
 
 template <int NB, int CT, int EPI>
@@ -1149,16 +1170,7 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         constexpr int S = CT == 1 ? 2 : 4, NW = CT == 1 ? 8 : 4;
         if constexpr (EPI != EPI_RESID) {
             const int ws = wide_strips(m, strips, g.ktiles, CT);
-            if (ws) {
-                const int groups = (strips + ws - 1) / ws;
-                constexpr int threads4 = wide_waves(CT, 4) * 64, threads7 = wide_waves(CT, 7) * 64;
-                if (ws == 3) k_gemm_wide<CT, 3, EPI><<<groups, threads4, wide_lds(CT, 3), s>>>(ga);
-                else if (ws == 4) k_gemm_wide<CT, 4, EPI><<<groups, threads4, wide_lds(CT, 4), s>>>(ga);
-                else if (ws == 6) k_gemm_wide<CT, 6, EPI><<<groups, threads7, wide_lds(CT, 6), s>>>(ga);
-                else k_gemm_wide<CT, 7, EPI><<<groups, threads7, wide_lds(CT, 7), s>>>(ga);
-                PV_HIP(hipGetLastError());
-                return PV_OK;
-            }
+            if (ws) return launch_wide<NB, CT, EPI>(ga, strips, ws, s);
         }
         if constexpr (CT >= 2) {
             // Activation tiles shared through LDS; few strips: cut along K, into at most 256 workgroups, one a CU: with a few more (288 for the
@@ -1223,10 +1235,16 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
                 return PV_OK;
             }
         }
+        if constexpr (EPI != EPI_RESID) {
+            // four to seven strips a CU: one workgroup each, which takes in the operand once (8 rows, K = 4096, us: 1792 strips 38.6 -> 37.8, 1024
+            // strips 25.6 -> 24.6; 5 rows, 1376 strips 31.9 -> 30.2).  Three strips a CU: the same as below (768 strips: 18.2); more rounds
+            // than one: no better, or worse, than workgroups that start as others end (K = 8192, 3584 strips 137.5 both; K = 4096, 8016 strips 175 -> 179)
+            if (strips >= 4 * m->n_cus && strips <= 7 * m->n_cus)
+                if (const int ws = wide_strips(m, strips, g.ktiles, 1)) return launch_wide<NB, CT, EPI>(ga, strips, ws, s);
+        }
         if constexpr (EPI == EPI_SWIGLU) {
             // 3.5 x G strips, G a multiple of the CUs: three whole strips and a half per workgroup, so that every CU holds
-            // the same number of equal workgroups from start to end (70B-shaped gate/up: 156.5 -> 153.7 us; 8B-shaped, 1792
-            // strips, which one strip per workgroup spreads as seven per CU, two at a time: 44.0 -> 41.5 us)
+            // the same number of equal workgroups from start to end (70B-shaped gate/up: 156.5 -> 153.7 us)
             if (g.ktiles >= 128 && (2 * strips) % 7 == 0 && (2 * strips / 7) % 256 == 0) {
                 const int G = 2 * strips / 7;
                 ga.half_base = 3 * G;

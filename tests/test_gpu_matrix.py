@@ -97,18 +97,19 @@ def test_wide_blocks_match_oracle(pvlib, wide_shape):
     _check_against_oracle(pvlib, wide_shape, 0, 64, 100, (32, 17, 64, 8, 40, 1, 33), 320)
 
 
-# A workgroup per CU with 3, 6, 7 and 4 strips (vocabularies of 705, 1500, 1601 and 1009 strips), ragged in the strips, with 17 K-tiles (not a multiple
+# A workgroup per CU with 3, 6, 7, 4 and 7 strips (vocabularies of 705, 1500, 1601, 1009 and 1537 strips), ragged in the strips, with 17 K-tiles (not a multiple
 # of the waves) or 129 (9..16 rows take that kernel from 128 on); in the first shape the QKV and gate/up projections (720 and 708 strips) as well.
 WIDE = [pv_inputs.ModelShape("wide_3", 1, 544, 60, 60, 64, 5664, 705 * 16, dtype="bf16", seed=5801),
         pv_inputs.ModelShape("wide_6", 1, 544, 8, 2, 32, 352, 1500 * 16, dtype="bf16", seed=5802),
         pv_inputs.ModelShape("wide_7", 1, 544, 8, 2, 32, 352, 1601 * 16, dtype="bf16", seed=5803),
-        pv_inputs.ModelShape("wide_k", 1, 4128, 8, 2, 32, 352, 1009 * 16, dtype="bf16", seed=5804)]
+        pv_inputs.ModelShape("wide_k", 1, 4128, 8, 2, 32, 352, 1009 * 16, dtype="bf16", seed=5804),
+        pv_inputs.ModelShape("wide_p", 1, 4128, 8, 2, 32, 352, 1537 * 16, dtype="bf16", seed=5805)]
 
 
 @pytest.mark.parametrize("shape", WIDE, ids=lambda v: v.name)
 def test_one_workgroup_per_cu_matches_oracle(pvlib, shape):
-    """Every number of column tiles at its first and last row count (33..48 rows: three)."""
-    _check_against_oracle(pvlib, shape, 0, 64, 20, (17, 32, 33, 48, 49, 64, 9, 16), 320)
+    """Every number of column tiles at its first and last row count (33..48 rows: three); up to 8 rows from 1024 strips and 128 K-tiles on."""
+    _check_against_oracle(pvlib, shape, 0, 64, 20, (17, 32, 33, 48, 49, 64, 9, 16, 8, 1, 5), 320)
 
 
 LONG_A = pv_inputs.ModelShape("long_a", 1, 128, 8, 2, 32, 352, 512, rope_base=500000.0, dtype="bf16", seed=5757)

@@ -5,7 +5,6 @@
 #include "pv_matrix_common.h"
 
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3 };
-#define PV_SEQ_TAG_SHIFT 26     // physical page numbers stay below 2^26; the bits above carry a row's sequence in a batched step
 
 struct gemm_args {
     const uint4 *W;             // tiled region, strip-major
@@ -16,7 +15,7 @@ struct gemm_args {
     float *tile_part;           // scratch for the K-slice partial sums of k_gemm_tile
     int nstrips;                // strips of this GEMM (a workgroup may own several; the last one may be ragged)
     const pv_dev_state *st;
-    int rows;                   // packed rows (NB == 1): rows of the block
+    int rows;                   // rows of the block: an argument, because a kernel that reads them waits for memory before it can ask for the rows' data
     // RMSNorm scale of the input rows (QKV, SWIGLU, LMHEAD)
     const float *ssq; int ssq_parts; float inv_d, eps;
     // QKV
@@ -109,28 +108,19 @@ __device__ inline void epi_prefetch(const gemm_args &a, int strip, int lane, epi
     p.xo = make_float4(0.f, 0.f, 0.f, 0.f); p.gn = make_uint2(0u, 0u);
 #pragma unroll
     for (int r = 0; r < 4; ++r) p.cs[r] = make_float2(1.f, 0.f);
-    p.rows = a.st->gamma;
+    p.rows = a.rows;
     if (EPI == EPI_RESID) {
         const int n = strip * 16 + 4 * g;
         if (j < p.rows) p.xo = *(const float4 *)(a.x + (size_t)j * a.d + n);
         p.gn = *(const uint2 *)(a.gain_next + n);
     }
     if (EPI == EPI_QKV) {
-        // position and pages of row j: the cache's own, or in a batched step those of the row's sequence
-        const int nseq = a.st->blk.n_seq;
-        const int32_t *pt = a.page_table;
-        int tag = 0;
-        p.pos = a.st->len + j;
-        if (nseq > 1 && j < p.rows) {
-            const int sidx = a.st->rowseq[j];
-            p.pos = a.st->rowpos[j]; pt = a.st->blk.seq[sidx].page_table; tag = (sidx + 1) << PV_SEQ_TAG_SHIFT;
-        }
         if (j < p.rows) {
-            if (strip >= a.q_strips) p.phys = pt[p.pos >> a.geom.page_shift] | tag;
+            if (strip >= a.q_strips) { p.pos = a.st->rowpos[j]; p.phys = a.st->rowphys[j]; }
             if (strip < a.q_strips + a.k_strips) {
                 const int spH = a.geom.head_dim >> 4, tt = strip % spH, e = tt * 8 + 4 * (g >> 1);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) p.cs[r] = a.rope[(size_t)j * (a.geom.head_dim >> 1) + e + r];
+                const float4 *q = (const float4 *)(a.rope + (uint32_t)(j * (a.geom.head_dim >> 1) + e)), c0 = q[0], c1 = q[1];
+                p.cs[0] = make_float2(c0.x, c0.y); p.cs[1] = make_float2(c0.z, c0.w); p.cs[2] = make_float2(c1.x, c1.y); p.cs[3] = make_float2(c1.z, c1.w);
             }
         }
     }

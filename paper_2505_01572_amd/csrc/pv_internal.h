@@ -21,6 +21,7 @@ enum { PV_MODE_VERIFY = 0, PV_MODE_PREFILL_LAST = 1, PV_MODE_PREFILL_MID = 2, PV
 // step (pv_verify_batch) stacks the blocks of several caches of one model into one pass over the
 // weights: rows row0 .. row0 + gamma - 1 of the stacked block belong to this sequence, their keys and
 // values live in this sequence's pages, their positions follow this sequence's length.
+#define PV_SEQ_TAG_SHIFT 26     // physical page numbers stay below 2^26
 struct pv_dev_state;
 struct pv_seq_ref {
     pv_dev_state *st;           // the sequence's own state (len, pending; accepted / next_token on return)
@@ -47,8 +48,8 @@ struct pv_dev_state {
     int32_t pad[2];
     int32_t draft[PV_MAX_ROWS];
     int32_t pred[PV_MAX_ROWS];
-    int32_t rowseq[PV_MAX_ROWS];    // sequence of each row and the cache slot (absolute position) its K/V go to (written by the block set-up)
-    int32_t rowpos[PV_MAX_ROWS];
+    int32_t rowphys[PV_MAX_ROWS];   // physical page and cache slot (absolute position) that each row's K/V go to (written by the block set-up);
+    int32_t rowpos[PV_MAX_ROWS];    // batched step: the page has 1 + the row's sequence in the bits from PV_SEQ_TAG_SHIFT on
     uint64_t rowmask[PV_MAX_ROWS];  // which of its sequence's block slots a row may attend to: bit q = the slot at (sequence length + q).
                                     // A chain: slots 0 .. the row's own; a draft tree: the row's ancestors and itself
     int32_t parent[PV_MAX_ROWS];    // draft tree (PV_MODE_TREE): parent row of each row, -1 = a child of the committed prefix

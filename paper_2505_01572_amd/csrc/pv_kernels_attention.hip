@@ -15,7 +15,6 @@ __global__ void __launch_bounds__(256)
 k_attn_merge(const attn_args a, int n_units)
 {
     __shared__ float smem[256 + (256 / (HD / 4)) * (HD / 4) * 5];
-    if ((int)blockIdx.x >= a.st->gamma) return;
     attn_merge_unit<NB, HD, 256>(a, blockIdx.x, blockIdx.y, n_units, threadIdx.x, smem);
 }
 
@@ -103,7 +102,7 @@ int pv_mat_attention(pv_cache *c, int layer, int rows, float *part, uint16_t *xo
     a.scale = 1.0f / sqrtf((float)f.head_dim);
     a.part_o = part;
     a.part_ml = part + (size_t)f.n_kv_heads * c->units_cap * a.max_chunks * 32 * f.head_dim;
-    a.xop_o = xop_o; a.n_pages = c->n_pages; a.rows = rows;
+    a.xop_o = xop_o; a.n_pages = c->n_pages; a.rows = rows; a.batched = c->blk_units != 0;
     const bool nb1 = rows <= 8;
     switch (f.head_dim) {
     case 32: return nb1 ? launch<1, 32>(c, a, rows, s) : launch<2, 32>(c, a, rows, s);

@@ -175,7 +175,7 @@ int pv_mat_repack_q4(const pv_model *m, const pv_tensor_ref &t, int kind, int64_
 template <int NB>
 __global__ void __launch_bounds__(64)
 k_mat_begin(pv_dev_state *st, const int32_t *mailbox, int rows, int mode, const uint16_t *embed, const uint16_t *gain, const double *inv_freq,
-            float *x, float *ssq, uint16_t *xop, float2 *rope, int d, int half)
+            float *x, float *ssq, uint16_t *xop, float2 *rope, int d, int half, const int32_t *page_table, int page_shift)
 {
     const int lane = threadIdx.x, ct = blockIdx.y, j = ct * 16 + (lane & 15), g = lane >> 4, strip = blockIdx.x;
     const int nseq = st->blk.n_seq;
@@ -190,7 +190,10 @@ k_mat_begin(pv_dev_state *st, const int32_t *mailbox, int rows, int mode, const 
     auto depth_of = [&](int r) { int dpt = 0; for (int q = parent[r]; q >= 0 && dpt < PV_MAX_ROWS; q = parent[q]) ++dpt; return dpt; };
     if (blockIdx.x == 0 && ct == 0) {
         for (int i = lane; i < rows; i += 64) {
-            st->draft[i] = mailbox[i]; st->rowseq[i] = nseq <= 1 ? 0 : seq_of(i); st->rowpos[i] = slot_of(i);
+            const int pos = slot_of(i);
+            st->draft[i] = mailbox[i]; st->rowpos[i] = pos;
+            if (nseq <= 1) st->rowphys[i] = page_table[pos >> page_shift];
+            else { const int sidx = seq_of(i); st->rowphys[i] = st->blk.seq[sidx].page_table[pos >> page_shift] | (sidx + 1) << PV_SEQ_TAG_SHIFT; }
             uint64_t m;
             if (tree) { m = 1ull << i; for (int q = parent[i], k = 0; q >= 0 && k < PV_MAX_ROWS; q = parent[q], ++k) m |= 1ull << q; st->parent[i] = parent[i]; }
             else { const int jj = i - (nseq <= 1 ? 0 : st->blk.seq[seq_of(i)].row0); m = jj >= 63 ? ~0ull : (2ull << jj) - 1; }
@@ -294,7 +297,7 @@ __device__ inline int packed_lane(int lane, int R)
 // features) so that a lane's four results share one feature, hence one scale; the accumulators
 // are turned back on their way through the LDS reduction.
 template <int NB, int CT, int S, int EPI, int NW, int WB = 16, int DP = 1, bool HF = false>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NB == 1 && S == 1 && WB == 16 && DP == 1) ? 8 : (S * CT >= 16) ? 2 : 4)))   // packed bf16 rows, one strip: <= 64 VGPRs, two 16-wave workgroups per CU; 16 accumulator tiles (wide blocks with a short K): more than 128
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NB == 1 && S == 1 && WB == 16 && DP == 1) ? 6 : (S * CT >= 16) ? 2 : 4)))   // packed bf16 rows, one strip, a short K: latency is hidden by resident waves (three workgroups per CU at <= 80 VGPRs); 16 accumulator tiles (wide blocks with a short K): more than 128
 k_gemm(const gemm_args a)
 {
     static_assert(NB == 2 || CT == 1, "packed rows come in one tile");
@@ -1285,13 +1288,13 @@ static int run_block(pv_cache *c, hipStream_t s)
     auto gainp = [&](int kind, int l) { return (const uint16_t *)(Wb + pv_tref(m, kind, l).off); };
 
     k_mat_begin<NB><<<dim3(d / 16, CT), 64, 0, s>>>(c->ws.state, c->d_io->draft, rows, c->io->hdr[3], (const uint16_t *)(Wb + m->global[PV_T_EMBED].off), gainp(PV_T_ATTN_NORM, 0),
-                                           (const double *)(Wb + m->inv_freq_off), c->ws.x, mw.ssq0, mw.xop_a, c->ws.rope, d, hd / 2);
+                                           (const double *)(Wb + m->inv_freq_off), c->ws.x, mw.ssq0, mw.xop_a, c->ws.rope, d, hd / 2, c->ws.page_table, pv_geom(c).page_shift);
     PV_HIP(hipGetLastError());
 
     gemm_args g = {};
     int prc;
     g.st = c->ws.state; g.rows = rows; g.inv_d = 1.0f / (float)d; g.eps = (float)f.rms_eps; g.ssq_parts = d / 16;
-    g.q_hi = (uint16_t *)c->ws.q; g.q_lo = g.q_hi + (size_t)c->rows_cap * qd; g.pool = (uint16_t *)c->d_pool; g.page_table = c->ws.page_table; g.rope = c->ws.rope; g.geom = pv_geom(c);
+    g.q_hi = (uint16_t *)c->ws.q; g.q_lo = g.q_hi + (size_t)c->rows_cap * qd; g.pool = (uint16_t *)c->d_pool; g.rope = c->ws.rope; g.geom = pv_geom(c);
     g.n_q_heads = f.n_q_heads; g.q_strips = qd / 16; g.k_strips = kvd / 16;
     g.x = c->ws.x; g.d = d; g.xop_act = mw.xop_d; g.F = F;
     g.logits = c->ws.logits; g.pmax_val = mw.pmax_val; g.pmax_idx = mw.pmax_idx; g.vocab = f.vocab;
@@ -1361,7 +1364,7 @@ int pv_mat_run_prompt(pv_cache *c, int rows, int keep, hipStream_t s)
     if (rc != PV_OK || keep == 0) return rc;
     // the head of the kept rows (whatever their number, as column tiles of 16 rows: the layout of the prompt's operand)
     gemm_args g = {};
-    g.st = c->ws.state; g.inv_d = 1.0f / (float)f.d_model; g.eps = (float)f.rms_eps; g.ssq_parts = f.d_model / 16;
+    g.st = c->ws.state; g.rows = keep; g.inv_d = 1.0f / (float)f.d_model; g.eps = (float)f.rms_eps; g.ssq_parts = f.d_model / 16;
     g.logits = c->ws.logits; g.pmax_val = mw.pmax_val; g.pmax_idx = mw.pmax_idx; g.vocab = f.vocab; g.tile_part = mw.tile_part;
     g.W = (const uint4 *)(m->d_weights + m->global[PV_T_LM_HEAD].off); g.xop = (const uint4 *)out.xop; g.ktiles = f.d_model / 32; g.ssq = out.ssq;
     if ((rc = pv_prof_mark(c, PV_PROF_LMHEAD, 0, 0, s)) != PV_OK) return rc;

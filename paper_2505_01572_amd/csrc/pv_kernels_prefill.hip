@@ -77,7 +77,7 @@ struct pre_gemm_args {
     const float *rinv;          // 16-bit float operand: what its rows' sums have to be multiplied with (null: nothing)
 };
 
-// What the epilogue of a strip needs from memory.  Rows, length and the row's page are known here (epi_prefetch reads them
+// What the epilogue of a strip needs from memory.  Length and the row's page are known here (epi_prefetch reads them
 // from the step's state in memory, which the stores of the previous strip might have changed, for all the compiler knows).
 template <int EPI>
 __device__ inline void pre_fetch(const gemm_args &a, const pre_gemm_args &p, int strip, int lane, int ct, int phys, float rj, epi_pre &e)

@@ -7,8 +7,8 @@
 // owns one or a few strips, its wavefronts split K, accumulate in fp32, and are summed in wave
 // order through LDS, so the owner sees complete outputs and the whole epilogue (RMSNorm scale,
 // rotary embedding + KV append, SwiGLU, residual add, vocabulary arg-max) is fused into the
-// GEMM.  9..64 rows and many strips (k_gemm_wide): the same with one workgroup per CU.  17..64 rows
-// and few strips (k_gemm_tile; with 4-bit weights k_gemm_tile_q4, from 9 rows on): the waves
+// GEMM.  9..64 rows and many strips (k_gemm_wide): the same with one workgroup per CU; 4-bit weights and up
+// to 16 rows: k_gemm_q4.  17..64 rows and few strips (k_gemm_tile; with 4-bit weights k_gemm_tile_q4): the waves
 // of a workgroup own different strips, walk K together and share the activation tiles through LDS.
 //
 // Activations enter as the B operand.  To keep fp32-grade accuracy with bf16 matrix cores an
@@ -259,6 +259,10 @@ template <int AUX> __device__ inline uint4 buffer_load16(__amdgpu_buffer_rsrc_t 
 {
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, base, AUX));
 }
+template <int AUX> __device__ inline uint2 buffer_load8(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t base)
+{
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(r, off, base, AUX));
+}
 #define LOAD_ONCE 2                                // the non-temporal bit (see load_once)
 
 // Where lane l of the B operand reads inside a packed tile of R rows, in uint4s: its columns 0..7 are the rows' hi parts, 8..15 their
@@ -283,28 +287,18 @@ __device__ inline int packed_lane(int lane, int R)
 // then reads its strips as advancing windows).
 // ------------------------------------------------------------------------------------------
 //
-// DP > 1 (16-bit weights, one column tile): the wave keeps DP batches in registers and loads
+// DP > 1 (one column tile): the wave keeps DP batches in registers and loads
 // ahead (k_walk): bytes in flight come from depth per wave rather than from the number of
 // resident waves.  HF: the last of the S strips is an 8-feature half (see below).
 //
-// WB == 4: the strip is a run of batches of 4-bit codes and bf16 group scales (one scale per
-// output feature and K-tile); the wave walks them with k_walk, two or three batches deep.  A
-// code c enters the matrix core as the bf16 number 16 + c (the nibble OR-ed into the top
-// mantissa bits of 16.0 = 0x4180: exact).  Per K-tile the accumulator is started by the product
-// of the activation tile with an all -24 operand (= -24 x row sums, shared by the S strips), so
-// that the codes' product on top of it is sum_k (c_k - 8) * x_k; the vector ALU only multiplies
-// that by the tile's scale and adds.  The product is taken transposed (activation rows x
-// features) so that a lane's four results share one feature, hence one scale; the accumulators
-// are turned back on their way through the LDS reduction.
-template <int NB, int CT, int S, int EPI, int NW, int WB = 16, int DP = 1, bool HF = false>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NB == 1 && S == 1 && WB == 16 && DP == 1) ? 6 : (S * CT >= 16) ? 2 : 4)))   // packed bf16 rows, one strip, a short K: latency is hidden by resident waves (three workgroups per CU at <= 80 VGPRs); 16 accumulator tiles (wide blocks with a short K): more than 128
+template <int NB, int CT, int S, int EPI, int NW, int DP = 1, bool HF = false>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NB == 1 && S == 1 && DP == 1) ? 6 : (S * CT >= 16) ? 2 : 4)))   // packed bf16 rows, one strip, a short K: latency is hidden by resident waves (three workgroups per CU at <= 80 VGPRs); 16 accumulator tiles (wide blocks with a short K): more than 128
 k_gemm(const gemm_args a)
 {
     static_assert(NB == 2 || CT == 1, "packed rows come in one tile");
     static_assert(S <= NW, "one epilogue wave per strip");
-    static_assert(WB == 16 || (WB == 4 && CT == 1), "4-bit weights: one column tile");
-    static_assert(!HF || WB == 4 || DP > 1, "half strips: walked batches");
-    constexpr int U = (S * CT >= 16) ? 1 : (S * CT >= 4) ? 2 : (DP > 1 && (S >= 2 || NB == 2)) ? 2 : 4;   // tiles per batch (16-bit weights)
+    static_assert(!HF || DP > 1, "half strips: walked batches");
+    constexpr int U = (S * CT >= 16) ? 1 : (S * CT >= 4) ? 2 : (DP > 1 && (S >= 2 || NB == 2)) ? 2 : 4;   // tiles per batch
     constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LMHEAD);
     constexpr bool PARK = (CT == 1);                 // epilogue inputs fetched early (by the wave that will run the strip's epilogue) and parked in LDS
     // HF: the workgroup owns S - 1 whole strips and one 8-feature half of a strip it shares with
@@ -338,92 +332,13 @@ k_gemm(const gemm_args a)
 
     // RMSNorm of the input rows: every wave takes its share of the per-strip sums of squares; the
     // loads go out ahead of the weight stream and are folded in behind its first batch
-    ssq_loads<(WB == 4 && NW <= 8) ? 16 / NW * 2 : 2> sl[CT];   // d up to 8192 without a serial tail of loads
+    ssq_loads<2> sl[CT];
     if (NORM) {
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) ssq_issue(a.ssq + (size_t)ct * a.ssq_parts * 16, a.ssq_parts, threadIdx.x, NW * 64, sl[ct]);
     }
 
-    const size_t qstrip = (size_t)(KT / 4) * PV_Q4_BATCH;
-    const char *Aq = (const char *)a.W + (size_t)strip0 * qstrip;
-    if constexpr (WB == 4) {
-        // One batch = 4 K-tiles.  A wave keeps three batches in registers: while one is used the
-        // loads of the next two are in flight, so that the wave always has bytes on the way.
-        // The product is taken transposed here (activation rows x features): all four results
-        // of a lane then belong to one feature, and the lane needs one scale per tile.
-        struct qbatch { uint4 c[S]; uint2 s[S]; uint4 bh[4], bl[NB == 2 ? 4 : 1]; };
-        const int nb4 = KT >> 2;
-        int first, cnt, bstride;
-        if (a.interleave) { first = wave; bstride = NW; cnt = wave < nb4 ? (nb4 - wave + NW - 1) / NW : 0; }
-        else { const int per = (nb4 + NW - 1) / NW; first = min(nb4, wave * per); cnt = min(nb4, first + per) - first; bstride = 1; }
-        size_t qo[S];
-#pragma unroll
-        for (int si = 0; si < S; ++si) qo[si] = (HF && si == S - 1) ? (size_t)(hstrip - strip0) * qstrip : (strip0 + si < a.nstrips) ? (size_t)si * qstrip : 0;
-        auto issue = [&](qbatch &q, int k) {          // k-th batch of this wave
-            const int bt = first + k * bstride;
-#pragma unroll
-            for (int si = 0; si < S; ++si) {
-                const char *p = Aq + qo[si] + (size_t)bt * PV_Q4_BATCH;
-                const int ln = lane + ((HF && si == S - 1) ? hl : 0);
-                q.c[si] = load_once((const uint4 *)(p + ln * 16));
-                q.s[si] = load_once((const uint2 *)(p + 1024 + (ln & 15) * 8));
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                q.bh[u] = operand(bt * 4 + u);
-                if (NB == 2) q.bl[NB == 2 ? u : 0] = operand(KT + bt * 4 + u);
-            }
-            asm volatile("" ::: "memory");           // the loads go out here, ahead of the arithmetic that follows
-        };
-        // -24 in every element: its product with the activation tile starts the accumulator at
-        // -24 x (row sums), on top of which the codes' product lands as sum (c - 8) x
-        const uint4 neg24 = make_uint4(0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u);
-        auto consume = [&](const qbatch &q) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                f32x4 T0 = {0.f, 0.f, 0.f, 0.f};
-                T0 = mfma16(q.bh[u], neg24, T0);
-                if (NB == 2) T0 = mfma16(q.bl[NB == 2 ? u : 0], neg24, T0);
-#pragma unroll
-                for (int si = 0; si < S; ++si) {
-                    const uint4 c4 = q.c[si];
-                    const uint32_t cw = u == 0 ? c4.x : u == 1 ? c4.y : u == 2 ? c4.z : c4.w;
-                    const uint32_t sw = (u & 2) ? q.s[si].y : q.s[si].x;
-                    const float sc = __uint_as_float((u & 1) ? (sw & 0xFFFF0000u) : (sw << 16));
-                    // operand dword t = bf16 pair (16 + c_2t, 16 + c_2t+1): nibble t of each half into the top mantissa bits of 16.0
-                    const uint4 wa = make_uint4(((cw << 3) & 0x00780078u) | 0x41804180u, ((cw >> 1) & 0x00780078u) | 0x41804180u,
-                                                ((cw >> 5) & 0x00780078u) | 0x41804180u, ((cw >> 9) & 0x00780078u) | 0x41804180u);
-                    f32x4 T = mfma16(q.bh[u], wa, T0);
-                    if (NB == 2) T = mfma16(q.bl[NB == 2 ? u : 0], wa, T);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[si][0][r] = fmaf(sc, T[r], acc[si][0][r]);
-                }
-            }
-        };
-        constexpr int DEPTH = (NB == 2 || S >= 3) ? 2 : 3;   // what fits in 128 registers
-        qbatch q0, q1, q2;
-        k_walk<DEPTH>(cnt, q0, q1, q2, issue, consume, [&]() {
-            if (NORM) {
-                const float4 s4 = ssq_finish(a.ssq, a.ssq_parts, threadIdx.x, NW * 64, sl[0]);
-                if (lane < 4) *(float4 *)&ssq_s[wave][0][4 * lane] = s4;
-            }
-            if (PARK && wave < S) {
-                epi_pre pre;
-                epi_prefetch<EPI>(a, (HF && wave == S - 1) ? hstrip : min(strip0 + wave, a.nstrips - 1), lane, pre, 0);
-                epi_park<EPI>(&pre_s[wave][lane], pre);
-            }
-        });
-        // acc is (row 4 g + r, feature f) for lane (g, f); the sum below and the epilogues take
-        // (feature 4 g' + r', row j) from lane (g', j): store transposed
-        {
-            float *rf = (float *)&red[wave][0][0][0];
-            const int g = lane >> 4, f = lane & 15;
-#pragma unroll
-            for (int si = 0; si < S; ++si)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) rf[si * 256 + ((f >> 2) * 16 + 4 * g + r) * 4 + (f & 3)] = acc[si][0][r];
-        }
-    } else if constexpr (DP > 1) {
+    if constexpr (DP > 1) {
         static_assert(CT == 1, "deep variant: one column tile");
         struct wbatch { uint4 w[S][U], x[U], xl[NB == 2 ? U : 1]; };     // xl: the lo halves of a 16-row tile
         int first, cnt, bstride;
@@ -544,16 +459,14 @@ k_gemm(const gemm_args a)
             }
         }
     }
-    }   // WB == 16
+    }
 
     // sum the NW K-slices (and the NW shares of the sums of squares) in wave order; wave si runs
     // the epilogue of strip strip0 + si
-    if (WB == 16) {
 #pragma unroll
-        for (int si = 0; si < S; ++si)
+    for (int si = 0; si < S; ++si)
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) red[wave][si][ct][lane] = acc[si][ct];
-    }
+        for (int ct = 0; ct < CT; ++ct) red[wave][si][ct][lane] = acc[si][ct];
     __syncthreads();
     const bool hslot = HF && wave == S - 1;
     if (wave >= S || (!hslot && strip0 + wave >= a.nstrips)) return;
@@ -696,6 +609,120 @@ k_gemm_wide(const gemm_args a)
 }
 
 // ------------------------------------------------------------------------------------------
+// 4-bit weights, up to 16 rows: a workgroup owns S strips and reads the operand once for them; its NW waves split the batches of a strip (4 K-tiles of
+// codes and bf16 group scales, one scale per output feature and K-tile).  A code c enters the matrix core as the bf16 number
+// 16 + c (the nibble OR-ed into the top mantissa bits of 16.0 = 0x4180: exact).  Per K-tile the accumulator is started by the product of
+// the activation tile with an all -24 operand (= -24 x row sums, shared by the S strips), so that the codes' product on top of it is
+// sum_k (c_k - 8) * x_k; the vector ALU only multiplies that by the tile's scale and adds.  The product is taken transposed (activation rows x
+// features) so that a lane's four results share one feature, hence one scale; the accumulators are turned back on their way through LDS.
+// Bound by the code stream (5.1 TB/s beyond the 4.5 us that a kernel takes in any case) and by the vector ALU beside it, 13 instructions per weight tile: so sixteen
+// waves a CU (two workgroups of 8 where there are enough) with one batch each in registers and no loads ahead, the other waves' work covering a wave's latency.  That takes at
+// most 128 registers, which seven strips fit only if the multiply-adds stay behind their products (left alone, the compiler moves all of them to the end of the batch
+// and holds every product: 100 - 120 registers more, spilled; two batches deep at 200 registers and two waves per SIMD the 8B-shaped gate/up took 21.7 us instead of 18.9).
+// 8B shape, 13 rows, us, with the sum of the K-slices that k_gemm_tile_q4 needs: QKV 15.0 -> 9.1, O 11.2 -> 7.2, gate/up 24.6 -> 18.9; 70B shape 23.1 -> 17.5, 18.4 -> 14.4, 65.5 -> 56.4;
+// 8 rows (before: two or three batches deep, at most three and a half strips a workgroup, 126 registers): 8B gate/up 19.0 -> 16.4, 70B 56.2 -> 51.2.
+// ------------------------------------------------------------------------------------------
+template <int NB, int S, int EPI, int NW = 8>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_gemm_q4(const gemm_args a)
+{
+    static_assert(S <= NW, "one epilogue wave per strip");
+    constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LMHEAD);
+    constexpr bool EARLY = S <= 4;                              // the epilogue's inputs are fetched beside the first batch (more strips: no registers for them)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int KT = a.ktiles, nb4 = KT >> 2, nst = (nb4 + NW - 1) / NW;      // batches of a wave: wave, wave + NW, ... (some waves' last one is past the end)
+    const int rot = (int)((blockIdx.x * 5u) % (unsigned)nst);   // workgroups start at different ones, or all would stream from addresses a power of two apart
+    const int strip0 = blockIdx.x * S, mine = min(S, a.nstrips - strip0);   // (strips past the end re-read the last one; dropped below)
+    __shared__ f32x4 red[NW][S][64];
+    __shared__ float ssq_s[NW][16];
+
+    ssq_loads<32 / NW> sl;                                      // d up to 8192 without a serial tail of loads
+    if (NORM) ssq_issue(a.ssq, a.ssq_parts, threadIdx.x, NW * 64, sl);
+    const uint32_t qs = (uint32_t)nb4 * PV_Q4_BATCH;            // bytes of a strip
+    const uint32_t xs = NB == 1 ? 128u * (uint32_t)a.rows : 1024u, xl = (NB == 1 ? packed_lane(lane, a.rows) : lane) * 16;   // as in k_gemm
+    const __amdgpu_buffer_rsrc_t W = buffer_of((const char *)a.W + (size_t)strip0 * qs, (uint32_t)mine * qs), X = buffer_of(a.xop, NB * (uint32_t)KT * xs);
+    f32x4 acc[S];
+#pragma unroll
+    for (int si = 0; si < S; ++si) acc[si] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    struct batch { uint4 c[S]; uint2 s[S]; uint4 h[4], l[NB == 2 ? 4 : 1]; };
+    auto issue = [&](batch &q, int i) {
+        const int k = i + rot, t = (k < nst ? k : k - nst) * NW + wave;
+        const bool in = t < nb4;                                // (past the end: codes, scales and activations of zero, nothing fetched)
+        const uint32_t off = in ? (uint32_t)t * PV_Q4_BATCH : BUFFER_END, offx = xl + (in ? (uint32_t)t * 4 * xs : BUFFER_END);
+#pragma unroll
+        for (int si = 0; si < S; ++si) {
+            q.c[si] = buffer_load16<LOAD_ONCE>(W, off + lane * 16, (uint32_t)min(si, mine - 1) * qs);
+            q.s[si] = buffer_load8<LOAD_ONCE>(W, off + 1024 + (lane & 15) * 8, (uint32_t)min(si, mine - 1) * qs);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            q.h[u] = buffer_load16<0>(X, offx, u * xs);
+            if (NB == 2) q.l[NB == 2 ? u : 0] = buffer_load16<0>(X, offx, (uint32_t)(KT + u) * xs);
+        }
+        asm volatile("" ::: "memory");
+    };
+    const uint4 neg24 = make_uint4(0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u);
+    uint32_t sixteen = 0x41804180u, nibble = 0x00780078u;       // (kept in registers, so that mask-and-merge is one instruction)
+    asm volatile("" : "+v"(sixteen), "+s"(nibble));
+    auto use = [&](const batch &q) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (S > 4) __builtin_amdgcn_sched_barrier(0);       // (nor does work of the next tile move up)
+            f32x4 T0 = {0.f, 0.f, 0.f, 0.f};
+            T0 = mfma16(q.h[u], neg24, T0);
+            if (NB == 2) T0 = mfma16(q.l[NB == 2 ? u : 0], neg24, T0);
+#pragma unroll
+            for (int si = 0; si < S; ++si) {
+                const uint4 c4 = q.c[si];
+                const uint32_t cw = u == 0 ? c4.x : u == 1 ? c4.y : u == 2 ? c4.z : c4.w, sw = (u & 2) ? q.s[si].y : q.s[si].x;
+                const float sc = __uint_as_float((u & 1) ? (sw & 0xFFFF0000u) : (sw << 16));
+                // operand dword t = bf16 pair (16 + c_2t, 16 + c_2t+1): nibble t of each half into the top mantissa bits of 16.0
+                const uint4 wa = make_uint4(((cw << 3) & nibble) | sixteen, ((cw >> 1) & nibble) | sixteen, ((cw >> 5) & nibble) | sixteen, ((cw >> 9) & nibble) | sixteen);
+                f32x4 T = mfma16(q.h[u], wa, T0);
+                if (NB == 2) T = mfma16(q.l[NB == 2 ? u : 0], wa, T);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[si][r] = fmaf(sc, T[r], acc[si][r]);
+                asm volatile("" : "+v"(acc[si]));               // the multiply-adds stay here
+            }
+        }
+    };
+    batch q;
+    issue(q, 0);
+    epi_pre pre;
+    if (EARLY && wave < mine) epi_prefetch<EPI>(a, strip0 + wave, lane, pre, 0);
+    if (NORM) {
+        const float4 s4 = ssq_finish(a.ssq, a.ssq_parts, threadIdx.x, NW * 64, sl);
+        if (lane < 4) *(float4 *)&ssq_s[wave][4 * lane] = s4;
+    }
+    for (int i = 0;;) {
+        use(q);
+        if (++i == nst) break;
+        issue(q, i);
+    }
+    {   // acc is (row 4 g + r, feature f) for lane (g, f); the sum below and the epilogues take (feature 4 g' + r', row j) from lane (g', j): store transposed
+        const int g = lane >> 4, f = lane & 15;
+#pragma unroll
+        for (int si = 0; si < S; ++si)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ((float *)red[wave][si])[((f >> 2) * 16 + 4 * g + r) * 4 + (f & 3)] = acc[si][r];
+    }
+    __syncthreads();
+    if (wave >= mine) return;
+    f32x4 v = red[0][wave][lane];                               // the waves' sums in wave order
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += red[w][wave][lane];
+    if (!EARLY) epi_prefetch<EPI>(a, strip0 + wave, lane, pre, 0);
+    if (NORM) {
+        auto col = [&](int w) { return NB == 1 ? ssq_s[w][lane & 7] + ssq_s[w][8 + (lane & 7)] : ssq_s[w][lane & 15]; };   // (two halves of a strip: emit_x)
+        float t = col(0);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t += col(w);
+        pre.rj = 1.0f / sqrtf(t * a.inv_d + a.eps);
+    }
+    epi_apply<NB, EPI>(a, strip0 + wave, lane, v, pre, 0);
+}
+
+// ------------------------------------------------------------------------------------------
 // Blocks of 17..64 rows (CT = 2, 3 or 4 column tiles of 16 rows, a hi and a lo operand each): 2 CT
 // activation tiles go with every weight tile.  Fetched per wave they outgrow the weight stream
 // in the CU's load path, so here the 8 waves of a workgroup walk the same K range in step, each
@@ -835,13 +862,13 @@ k_gemm_tile(const gemm_args a, int tps, float4 *part)
 }
 
 // ------------------------------------------------------------------------------------------
-// The same for 4-bit weights (9..64 rows, CT = 1, 2 or 4): the 8 waves of a workgroup own two strips each and walk
+// The same for 4-bit weights (17..64 rows, and 9..16 where k_gemm_q4 is not faster; CT = 1, 2 or 4): the 8 waves of a workgroup own two strips each and walk
 // the strips' batches (4 K-tiles of codes + scales, 1152 bytes) in step; the 8 CT activation tiles of
 // a step are fetched once per workgroup and shared through LDS (two buffers, one barrier per step).
 // Per weight byte a 4-bit strip needs 3.6 times the activation bytes of a 16-bit one, on the L2 -> CU
 // path as well as out of LDS: hence two strips per wave.  A step is long (72 MFMAs at 64 rows), so the
 // weights are loaded two steps ahead and the activation tiles one (their registers are free once they sit in LDS).
-// Arithmetic as in k_gemm<WB = 4>: a code c enters as the bf16 number 16 + c, the product is taken
+// Arithmetic as in k_gemm_q4: a code c enters as the bf16 number 16 + c, the product is taken
 // transposed (activation rows x features) on top of -24 x (row sums), scaled per K-tile; the row sums
 // are the same for every strip and are taken once per workgroup by the wave that brings the tile in.
 // The accumulators are turned back through LDS before the epilogue (or before they are stored as a
@@ -1118,6 +1145,33 @@ int pv_mat_gemm_init(int wbits)
     return allow_wide<2, 4>();
 }
 
+// Strips a workgroup of k_gemm_q4: a CU takes its workgroups two at a time, one round for each per CU; a strip takes 0.0145 us per K-tile, the operand 0.006
+// (16 rows).  Eight waves, two workgroups a CU where there are that many (sixteen waves and one or two strips: 8 rows, K = 14336 14.5 us against 14.2, but
+// up to 4 rows, whose operand is small, 11.2 against 13.7).
+template <int NB, int EPI>
+static int launch_q4(const pv_model *m, const gemm_args &ga, int strips, hipStream_t s)
+{
+    constexpr bool SEVEN = NB == 1 || EPI != EPI_LMHEAD;       // (the vocabulary's epilogue is two registers short)
+    int best = 1;
+    double least = 1e30;
+    for (int S : {7, 4, 3, 2, 1}) {
+        const int rounds = ((strips + S - 1) / S + m->n_cus - 1) / m->n_cus;
+        if ((S <= 2 && rounds > 1) || (S == 7 && !SEVEN)) continue;
+        const double t = rounds * (S + 0.4);
+        if (t < least) { least = t; best = S; }
+    }
+    const int groups = (strips + best - 1) / best;
+    if (NB == 1 && best == 1 && ga.rows <= 4) k_gemm_q4<NB, 1, EPI, 16><<<groups, 1024, 0, s>>>(ga);
+    else if (NB == 1 && best == 2 && ga.rows <= 4) k_gemm_q4<NB, 2, EPI, 16><<<groups, 1024, 0, s>>>(ga);
+    else if (best == 1) k_gemm_q4<NB, 1, EPI><<<groups, 512, 0, s>>>(ga);
+    else if (best == 2) k_gemm_q4<NB, 2, EPI><<<groups, 512, 0, s>>>(ga);
+    else if (best == 3) k_gemm_q4<NB, 3, EPI><<<groups, 512, 0, s>>>(ga);
+    else if (best == 4) k_gemm_q4<NB, 4, EPI><<<groups, 512, 0, s>>>(ga);
+    else if constexpr (SEVEN) k_gemm_q4<NB, 7, EPI><<<groups, 512, 0, s>>>(ga);
+    PV_HIP(hipGetLastError());
+    return PV_OK;
+}
+
 template <int NB, int CT, int EPI>
 static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStream_t s)
 {
@@ -1125,36 +1179,20 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
     ga.nstrips = strips;
     ga.interleave = g.ktiles > 128;                          // long strips: measured 0.3 % faster per step, short ones 0.3 % slower
     if (m->wbits == 4) {
+        // 9..16 rows: k_gemm_q4 is ahead of tiles shared through LDS and K-slices up to K = 12800 or so (13 rows, us: 256 strips, K = 4096 7.3 and 11.2, K =
+        // 14336 18.8 and 18.2; 512 strips, K = 8192 14.4 and 18.4, K = 28672 43 and 36; 3584 strips, K = 8192 56 and 65), and up to as many strips as
+        // leave shared tiles a workgroup of sixteen on not all CUs (K = 4096, 2000 strips 21.5 and 25.8, 8016 strips 78 and 61)
+        if constexpr (CT == 1) if (NB == 1 || (strips <= 14 * m->n_cus && (strips > 2 * m->n_cus || g.ktiles <= 400))) return launch_q4<NB, EPI>(m, ga, strips, s);
         if constexpr (NB == 1) {
-            // Several strips per workgroup share every activation tile from registers (one strip:
-            // 4 KiB of tiles from L2 per 1.1 KiB of weights), as many as still leave a workgroup per CU.
-            if constexpr (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
-                // strips = (k + 1/2) x G with G a multiple of the 256 CUs: G workgroups of k whole strips and
-                // half of a shared one put the same bytes on every CU (see the 16-bit launch below)
-                for (int k = (strips >= 1024 ? 3 : 2); k >= 1 && g.ktiles >= 64; --k) {
-                    const int G = 2 * strips / (2 * k + 1);
-                    if (2 * strips % (2 * k + 1) != 0 || G % 256 != 0 || G == 0) continue;
-                    ga.half_base = k * G;
-                    if (k == 3) k_gemm<1, 1, 4, EPI, 8, 4, 1, true><<<G, 512, 0, s>>>(ga);
-                    else if (k == 2) k_gemm<1, 1, 3, EPI, 8, 4, 1, true><<<G, 512, 0, s>>>(ga);
-                    else k_gemm<1, 1, 2, EPI, 8, 4, 1, true><<<G, 512, 0, s>>>(ga);
-                    PV_HIP(hipGetLastError());
-                    return PV_OK;
-                }
-            }
-            if (strips >= 1024 && g.ktiles >= 64) k_gemm<1, 1, 4, EPI, 8, 4><<<(strips + 3) / 4, 512, 0, s>>>(ga);
-            else if (strips >= 512 && g.ktiles >= 64) k_gemm<1, 1, 2, EPI, 8, 4><<<(strips + 1) / 2, 512, 0, s>>>(ga);
-            else if (g.ktiles >= 64) k_gemm<1, 1, 1, EPI, 16, 4><<<strips, 1024, 0, s>>>(ga);
-            else k_gemm<1, 1, 1, EPI, 8, 4><<<strips, 512, 0, s>>>(ga);
+            return PV_EINVAL;                                  // (not reached)
         } else if constexpr (CT == 3) {
             pv_set_error("4-bit weights have no kernel for three column tiles");       // (their blocks of 33..48 rows run as four)
             return PV_EINVAL;
         } else {
-            // 4-bit weights, 9..64 rows: activation tiles shared through LDS, two strips per wave.  Few strips: cut along K.  Up to 32 rows two
-            // workgroups fit on a CU (120 registers): at most 512 of them in one round (8B shape, 4 layers: 13 rows 396 -> 356 us a
-            // step against 256 and one per CU, 24 rows 483 -> 442); more rows: one per CU, at most 256 (K = 4096, 48 rows, us for a projection and its
-            // sum, one slice / two: 129 groups of 16 strips 77.6 / 85.5, 172 groups 78.1 / 88.5, 224 groups 83 / 79; 13 rows, one / two / three: 129 groups
-            // 41.5 / 36.1 / 31.9, 172 groups 42.8 / 39.6 / 39.4, 224 groups 44.3 / 43.2 / 42.4)
+            // Activation tiles shared through LDS, two strips per wave.  Few strips: cut along K.  Up to 32 rows two
+            // workgroups fit on a CU (120 registers): at most 512 of them in one round (8B shape, 4 layers, 24 rows: 483 -> 442 us a
+            // step against 256 and one per CU); more rows: one per CU, at most 256 (K = 4096, 48 rows, us for a projection and its
+            // sum, one slice / two: 129 groups of 16 strips 77.6 / 85.5, 172 groups 78.1 / 88.5, 224 groups 83 / 79)
             const int nbat = g.ktiles / 4, ngroups = (strips + 15) / 16;
             int slices = g.tile_part == nullptr ? 1 : max(1, min(TILE_MAX_SLICES, (CT <= 2 ? 512 : 256) / ngroups));
             int bps = max(CT <= 2 ? 2 : 4, (nbat + slices - 1) / slices);
@@ -1202,14 +1240,14 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
                 if constexpr (EPI == EPI_QKV) {       // (k + 1/2) x 256 strips: half strips as for the packed rows
                     if (strips % 256 == 128 && strips / 256 >= 1 && strips / 256 <= 2) {
                         ga.half_base = (strips / 256) * 256;
-                        if (strips / 256 == 1) k_gemm<NB, CT, 2, EPI, 8, 16, 3, true><<<256, 512, 0, s>>>(ga);
-                        else k_gemm<NB, CT, 3, EPI, 8, 16, 2, true><<<256, 512, 0, s>>>(ga);
+                        if (strips / 256 == 1) k_gemm<NB, CT, 2, EPI, 8, 3, true><<<256, 512, 0, s>>>(ga);
+                        else k_gemm<NB, CT, 3, EPI, 8, 2, true><<<256, 512, 0, s>>>(ga);
                         done = true;
                     }
                 }
                 if (done) ;
-                else if (strips >= 512) k_gemm<NB, CT, 2, EPI, 8, 16, 2><<<(strips + 1) / 2, 512, 0, s>>>(ga);
-                else k_gemm<NB, CT, 1, EPI, 8, 16, 3><<<strips, 512, 0, s>>>(ga);
+                else if (strips >= 512) k_gemm<NB, CT, 2, EPI, 8, 2><<<(strips + 1) / 2, 512, 0, s>>>(ga);
+                else k_gemm<NB, CT, 1, EPI, 8, 3><<<strips, 512, 0, s>>>(ga);
                 PV_HIP(hipGetLastError());
                 return PV_OK;
             }
@@ -1232,8 +1270,8 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         if constexpr (EPI == EPI_QKV) {
             if (g.ktiles >= 64 && strips % 256 == 128 && strips / 256 >= 1 && strips / 256 <= 2) {
                 ga.half_base = (strips / 256) * 256;
-                if (strips / 256 == 1) k_gemm<NB, CT, 2, EPI, 8, 16, 3, true><<<256, 512, 0, s>>>(ga);
-                else k_gemm<NB, CT, 3, EPI, 8, 16, 2, true><<<256, 512, 0, s>>>(ga);
+                if (strips / 256 == 1) k_gemm<NB, CT, 2, EPI, 8, 3, true><<<256, 512, 0, s>>>(ga);
+                else k_gemm<NB, CT, 3, EPI, 8, 2, true><<<256, 512, 0, s>>>(ga);
                 PV_HIP(hipGetLastError());
                 return PV_OK;
             }
@@ -1251,7 +1289,7 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
             if (g.ktiles >= 128 && (2 * strips) % 7 == 0 && (2 * strips / 7) % 256 == 0) {
                 const int G = 2 * strips / 7;
                 ga.half_base = 3 * G;
-                k_gemm<NB, CT, 4, EPI, 8, 16, 2, true><<<G, 512, 0, s>>>(ga);
+                k_gemm<NB, CT, 4, EPI, 8, 2, true><<<G, 512, 0, s>>>(ga);
                 PV_HIP(hipGetLastError());
                 return PV_OK;
             }
@@ -1261,15 +1299,15 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
             // K = 2048 and 8192 together 14.9 -> 13.6 us)
             if (g.ktiles >= 64 && 2 * strips <= m->n_cus) {
                 ga.half_base = 0;
-                k_gemm<NB, CT, 1, EPI, 8, 16, 3, true><<<2 * strips, 512, 0, s>>>(ga);
+                k_gemm<NB, CT, 1, EPI, 8, 3, true><<<2 * strips, 512, 0, s>>>(ga);
                 PV_HIP(hipGetLastError());
                 return PV_OK;
             }
         }
         auto fill = [](int wgs) { return (double)wgs / (double)(((wgs + 255) / 256) * 256); };
         const bool two = strips >= 512 && fill((strips + 1) / 2) >= fill(strips);
-        if (g.ktiles >= 64 && two) k_gemm<NB, CT, 2, EPI, 8, 16, 2><<<(strips + 1) / 2, 512, 0, s>>>(ga);
-        else if (g.ktiles >= 64) k_gemm<NB, CT, 1, EPI, 8, 16, 3><<<strips, 512, 0, s>>>(ga);
+        if (g.ktiles >= 64 && two) k_gemm<NB, CT, 2, EPI, 8, 2><<<(strips + 1) / 2, 512, 0, s>>>(ga);
+        else if (g.ktiles >= 64) k_gemm<NB, CT, 1, EPI, 8, 3><<<strips, 512, 0, s>>>(ga);
         else k_gemm<NB, CT, 1, EPI, 8><<<strips, 512, 0, s>>>(ga);
     }
     PV_HIP(hipGetLastError());

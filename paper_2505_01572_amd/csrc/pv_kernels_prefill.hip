@@ -269,7 +269,7 @@ k_pre_gemm(const gemm_args a, const pre_gemm_args p)
 // ------------------------------------------------------------------------------------------
 // The same for 4-bit weights (of matrices with scales that k_pre_gemm_h4 below does not hold): 128 rows x 64 FT features, 2 x 4 waves, each 4
 // row tiles x FT strips.
-// Arithmetic as in k_gemm<WB = 4> (codes enter as 16 + c on top of -24 x the row sums, product taken
+// Arithmetic as in k_gemm_q4 (codes enter as 16 + c on top of -24 x the row sums, product taken
 // transposed, scaled per K-tile); the row sums of the operand come from k_pre_rowsum.  Per K-tile a
 // wave expands FT code tiles (9 vector instructions each) and scales 4 FT products (4 each) beside 8 FT MFMAs: the
 // vector ALU is busy 80 % of the time that the matrix cores need, so the products are scaled one group of strips

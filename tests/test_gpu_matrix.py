@@ -247,6 +247,20 @@ def test_q4_weights_match_oracle(pvlib, shape):
     _check_against_oracle(pvlib, shape, 0, 16, 37, (8, 13, 1, 5, 16, 3), 96)
 
 
+# Two, three (one round of workgroups and two), four and seven strips a workgroup (vocabularies of 300, 705, 1300 and 1009 strips, 1616 strips of gate/up), ragged
+# in the strips; 1, 5 or 9 batches along K for eight waves; 404 K-tiles and 3700 strips, where 9..16 rows go back to shared tiles.
+Q4_STRIPS = [pv_inputs.ModelShape("q4_s2", 1, 1152, 8, 2, 64, 384, 300 * 16, dtype="bf16", seed=7581, weight_bits=4),
+             pv_inputs.ModelShape("q4_s3", 1, 640, 8, 2, 64, 12928, 705 * 16, dtype="bf16", seed=7582, weight_bits=4),
+             pv_inputs.ModelShape("q4_s3b", 1, 128, 8, 2, 32, 384, 1300 * 16, dtype="bf16", seed=7583, weight_bits=4),
+             pv_inputs.ModelShape("q4_s4", 1, 1152, 8, 2, 64, 384, 1009 * 16, dtype="bf16", seed=7584, weight_bits=4),
+             pv_inputs.ModelShape("q4_sx", 1, 128, 8, 2, 32, 384, 3700 * 16, dtype="bf16", seed=7585, weight_bits=4)]
+
+
+@pytest.mark.parametrize("shape", Q4_STRIPS, ids=lambda v: v.name)
+def test_q4_strips_of_a_workgroup_match_oracle(pvlib, shape):
+    _check_against_oracle(pvlib, shape, 0, 16, 20, (8, 16, 1, 4, 5, 9), 96)
+
+
 def test_q4_model_is_smaller_and_rejects_plain_loads(pvlib):
     import paper_2505_01572_amd as pv
     m4 = pv.Model(Q4_B, max_gamma=16)

@@ -23,6 +23,8 @@ struct gemm_args {
     int layer, n_q_heads, q_strips, k_strips;
     // RESID
     float *x; const uint16_t *gain_next; float *ssq_out; uint16_t *xop_out; int d;
+    // output projection that merges the attention's chunks itself (pv_attn_split)
+    const float *part_o, *part_ml; int chunks, max_chunks, chunk_shift, units;
     // SWIGLU
     uint16_t *xop_act; int F;
     // LMHEAD

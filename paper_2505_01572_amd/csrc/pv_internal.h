@@ -187,7 +187,9 @@ size_t pv_attn_part_floats(const pv_model *m, int units_cap, int max_tokens);
 int pv_attn_units(const pv_model *m, int rows);              // attention row-group units of one sequence with `rows` rows
 int pv_mat_attention_init(int head_dim);
 int pv_mat_gemm_init(int wbits);
-int pv_mat_attention(pv_cache *c, int layer, int rows, float *part, uint16_t *xop_o, hipStream_t s);
+struct pv_attn_split_info { const float *part_o, *part_ml; int chunks, max_chunks, chunk_shift, units; };   // partial results: chunks launched, room per unit, log2 keys a chunk, row groups
+pv_attn_split_info pv_attn_split(const pv_cache *c, int rows, const float *part);   // how the attention of a plain step cuts its keys
+int pv_mat_attention(pv_cache *c, int layer, int rows, float *part, uint16_t *xop_o, bool merge, hipStream_t s);   // merge: false leaves the partial results to the output projection
 void pv_set_error(const char *fmt, ...);
 
 #define PV_HIP(call)                                                                        \

@@ -35,8 +35,22 @@ size_t pv_attn_part_floats(const pv_model *m, int units_cap, int max_tokens)
 }
 
 // rows: rows of the block; a batched step also gives its unit count and the most rows any one sequence has
+// Keys the launch has to cover (the host's bound, not the whole cache), cut into chunks of 256 (up to 16 query rows per kv head) or 128
+pv_attn_split_info pv_attn_split(const pv_cache *c, int rows, const float *part)
+{
+    const pv_model_config &f = c->m->cfg;
+    const int nrows = f.n_q_heads / f.n_kv_heads * rows, keys = c->attn_keys > 0 && c->attn_keys < c->max_tokens ? c->attn_keys : c->max_tokens;
+    pv_attn_split_info i;
+    i.chunk_shift = nrows <= 16 ? 8 : 7;
+    i.chunks = (keys + (1 << i.chunk_shift) - 1) >> i.chunk_shift;
+    i.max_chunks = (c->max_tokens + (1 << i.chunk_shift) - 1) >> i.chunk_shift;
+    i.units = (nrows + 31) / 32;
+    i.part_o = part; i.part_ml = part + (size_t)f.n_kv_heads * c->units_cap * ((c->max_tokens + 127) / 128) * 32 * f.head_dim;
+    return i;
+}
+
 template <int NB, int HD>
-static int launch(pv_cache *c, attn_args &a, int rows, hipStream_t s)
+static int launch(pv_cache *c, attn_args &a, int rows, bool merge, hipStream_t s)
 {
     const pv_model_config &f = c->m->cfg;
     const int seq_rows = c->blk_units ? c->blk_seq_rows : rows;
@@ -49,7 +63,7 @@ static int launch(pv_cache *c, attn_args &a, int rows, hipStream_t s)
     // Up to two chunks: one workgroup per kv head and row group goes through them and there is nothing to merge.  Measured per layer
     // against chunks and merge (8B and 1B shapes): one chunk -3.5 us, two -2 us, four +3 us, eight +10 us (a chunk costs its
     // workgroup 2 us, mostly latency; loading the next keys ahead did not help).
-    if (keys <= (nrows <= 16 ? 512 : 256)) {
+    if (merge && keys <= (nrows <= 16 ? 512 : 256)) {
         if (nrows <= 16) k_attn<HD, 1, NB><<<dim3(1, f.n_kv_heads, units), 512, lds, s>>>(a);
         else k_attn<HD, 2, NB><<<dim3(1, f.n_kv_heads, units), 512, lds, s>>>(a);
         PV_HIP(hipGetLastError());
@@ -63,6 +77,7 @@ static int launch(pv_cache *c, attn_args &a, int rows, hipStream_t s)
         k_attn<HD, 2, 0><<<dim3((keys + 127) / 128, f.n_kv_heads, units), 512, lds, s>>>(a);
     }
     PV_HIP(hipGetLastError());
+    if (!merge) return PV_OK;
     k_attn_merge<NB, HD><<<dim3(rows, f.n_q_heads), 256, 0, s>>>(a, units);
     PV_HIP(hipGetLastError());
     return PV_OK;
@@ -91,7 +106,7 @@ int pv_mat_attention_init(int head_dim)
 }
 
 // q (bf16 hi + lo, rotated) -> xop_o; part = scratch of pv_attn_part_floats floats
-int pv_mat_attention(pv_cache *c, int layer, int rows, float *part, uint16_t *xop_o, hipStream_t s)
+int pv_mat_attention(pv_cache *c, int layer, int rows, float *part, uint16_t *xop_o, bool merge, hipStream_t s)
 {
     const pv_model_config &f = c->m->cfg;
     attn_args a;
@@ -105,9 +120,9 @@ int pv_mat_attention(pv_cache *c, int layer, int rows, float *part, uint16_t *xo
     a.xop_o = xop_o; a.n_pages = c->n_pages; a.rows = rows; a.batched = c->blk_units != 0;
     const bool nb1 = rows <= 8;
     switch (f.head_dim) {
-    case 32: return nb1 ? launch<1, 32>(c, a, rows, s) : launch<2, 32>(c, a, rows, s);
-    case 64: return nb1 ? launch<1, 64>(c, a, rows, s) : launch<2, 64>(c, a, rows, s);
-    case 128: return nb1 ? launch<1, 128>(c, a, rows, s) : launch<2, 128>(c, a, rows, s);
+    case 32: return nb1 ? launch<1, 32>(c, a, rows, merge, s) : launch<2, 32>(c, a, rows, merge, s);
+    case 64: return nb1 ? launch<1, 64>(c, a, rows, merge, s) : launch<2, 64>(c, a, rows, merge, s);
+    case 128: return nb1 ? launch<1, 128>(c, a, rows, merge, s) : launch<2, 128>(c, a, rows, merge, s);
     default: pv_set_error("matrix path: unsupported head_dim %d", f.head_dim); return PV_EINVAL;
     }
 }

@@ -219,7 +219,7 @@ k_mat_begin(pv_dev_state *st, const int32_t *mailbox, int rows, int mode, const 
 
 // A wave's K walk with DEPTH register buffers: while one batch is used, the loads of the next
 // DEPTH - 1 are in flight.  issue(q, k) starts the loads of the wave's k-th batch into q,
-// consume(q) uses it; between() runs once behind the first loads (work that may wait on older,
+// consume(q, k) uses it; between() runs once behind the first loads (work that may wait on older,
 // shorter loads).  Buffers rotate by name, so the steady state is unrolled DEPTH times and every
 // issue in it is unconditional: the wait before a consume then only covers that batch's loads.
 template <int DEPTH, typename Q, typename FI, typename FC, typename FB>
@@ -231,24 +231,24 @@ __device__ inline void k_walk(int cnt, Q &q0, Q &q1, Q &q2, FI issue, FC consume
     int i = 0;
     if constexpr (DEPTH == 3) {
         for (; i + 4 < cnt; i += 3) {                // q0 and q1 hold batches i and i + 1, in flight or landed
-            issue(q2, i + 2); consume(q0);
-            issue(q0, i + 3); consume(q1);
-            issue(q1, i + 4); consume(q2);
+            issue(q2, i + 2); consume(q0, i);
+            issue(q0, i + 3); consume(q1, i + 1);
+            issue(q1, i + 4); consume(q2, i + 2);
         }
         if (i + 2 < cnt) issue(q2, i + 2);            // at most four batches are left
-        if (i < cnt) consume(q0);
+        if (i < cnt) consume(q0, i);
         if (i + 3 < cnt) issue(q0, i + 3);
-        if (i + 1 < cnt) consume(q1);
-        if (i + 2 < cnt) consume(q2);
-        if (i + 3 < cnt) consume(q0);
+        if (i + 1 < cnt) consume(q1, i + 1);
+        if (i + 2 < cnt) consume(q2, i + 2);
+        if (i + 3 < cnt) consume(q0, i + 3);
     } else {
         for (; i + 2 < cnt; i += 2) {                // q0 holds batch i
-            issue(q1, i + 1); consume(q0);
-            issue(q0, i + 2); consume(q1);
+            issue(q1, i + 1); consume(q0, i);
+            issue(q0, i + 2); consume(q1, i + 1);
         }
         if (i + 1 < cnt) issue(q1, i + 1);            // at most two batches are left
-        if (i < cnt) consume(q0);
-        if (i + 1 < cnt) consume(q1);
+        if (i < cnt) consume(q0, i);
+        if (i + 1 < cnt) consume(q1, i + 1);
     }
 }
 
@@ -273,6 +273,54 @@ __device__ inline int packed_lane(int lane, int R)
     return (lane >> 4) * 2 * R + (col < 8 ? min(col, R - 1) : R + min(col - 8, R - 1));
 }
 
+// The attention's chunks of a small block, merged by every workgroup of the output projection for itself, into operand tiles in LDS.  A thread takes
+// IT (row, four features) items at a time, all their up to MG chunks in flight at once, beside the first weights.  Arithmetic of
+// attn_merge_unit.  A chunk beyond the keys has left nothing: its weight is 0 and its values are not used.
+constexpr int merge_items(int mg) { return 8 / mg; }
+template <int MG, int NT>
+__device__ inline void merge_chunks(const gemm_args &a, uint16_t *dst)
+{
+    constexpr int IT = merge_items(MG);
+    const int R = a.rows, hd = a.geom.head_dim, K = a.ktiles * 32, group = a.n_q_heads / a.geom.n_kv_heads, items = R * (K >> 2);
+    const int len = a.st->len;
+    for (int i0 = threadIdx.x; i0 < items; i0 += NT * IT) {
+        float2 ml[IT][MG];
+        float4 o[IT][MG];
+#pragma unroll
+        for (int v = 0; v < IT; ++v) {
+            const int i = min(i0 + v * NT, items - 1), j = i / (K >> 2), k = (i - j * (K >> 2)) * 4, aq = k / hd, kvh = aq / group, m = (aq - kvh * group) * R + j;
+            const size_t unit0 = ((size_t)kvh * a.units + (m >> 5)) * a.max_chunks;
+#pragma unroll
+            for (int c = 0; c < MG; ++c) {
+                const size_t at = (unit0 + min(c, a.chunks - 1)) * 32 + (m & 31);
+                ml[v][c] = *(const float2 *)(a.part_ml + at * 2);
+                o[v][c] = *(const float4 *)(a.part_o + at * hd + (k - aq * hd));
+            }
+        }
+        const int n = (len + R + (1 << a.chunk_shift) - 1) >> a.chunk_shift;
+#pragma unroll
+        for (int v = 0; v < IT; ++v) {
+            const int i = i0 + v * NT, j = i / (K >> 2), k = (i - j * (K >> 2)) * 4;
+            if (i >= items) break;
+            float M = ml[v][0].x;
+#pragma unroll
+            for (int c = 1; c < MG; ++c) if (c < n) M = fmaxf(M, ml[v][c].x);
+            float L = 0.f, y[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < MG; ++c)
+                if (c < n) {
+                    const float w = (ml[v][c].x == -INFINITY) ? 0.f : expf(ml[v][c].x - M);
+                    L += ml[v][c].y * w;
+                    y[0] += w * o[v][c].x; y[1] += w * o[v][c].y; y[2] += w * o[v][c].z; y[3] += w * o[v][c].w;
+                }
+            const float inv = 1.0f / L;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) y[r] *= inv;
+            store_operand4<1>(dst, K, j, k, y, R);
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // The streaming GEMM: a workgroup owns S adjacent strips, its NW waves split K in batches of U
 // tiles.
@@ -291,13 +339,14 @@ __device__ inline int packed_lane(int lane, int R)
 // ahead (k_walk): bytes in flight come from depth per wave rather than from the number of
 // resident waves.  HF: the last of the S strips is an 8-feature half (see below).
 //
-template <int NB, int CT, int S, int EPI, int NW, int DP = 1, bool HF = false>
+template <int NB, int CT, int S, int EPI, int NW, int DP = 1, bool HF = false, int MG = 0>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NB == 1 && S == 1 && DP == 1) ? 6 : (S * CT >= 16) ? 2 : 4)))   // packed bf16 rows, one strip, a short K: latency is hidden by resident waves (three workgroups per CU at <= 80 VGPRs); 16 accumulator tiles (wide blocks with a short K): more than 128
 k_gemm(const gemm_args a)
 {
     static_assert(NB == 2 || CT == 1, "packed rows come in one tile");
     static_assert(S <= NW, "one epilogue wave per strip");
     static_assert(!HF || DP > 1, "half strips: walked batches");
+    static_assert(MG == 0 || (NB == 1 && DP > 1 && EPI == EPI_RESID), "merged operand: packed rows, output projection");
     constexpr int U = (S * CT >= 16) ? 1 : (S * CT >= 4) ? 2 : (DP > 1 && (S >= 2 || NB == 2)) ? 2 : 4;   // tiles per batch
     constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LMHEAD);
     constexpr bool PARK = (CT == 1);                 // epilogue inputs fetched early (by the wave that will run the strip's epilogue) and parked in LDS
@@ -329,6 +378,7 @@ k_gemm(const gemm_args a)
     __shared__ f32x4 red[NW][S][CT][64];
     __shared__ float ssq_s[NW][CT][16];
     __shared__ epi_pre pre_s[PARK ? S : 1][PARK ? 64 : 1];
+    extern __shared__ uint4 merged[];               // MG > 0: the operand's packed tiles
 
     // RMSNorm of the input rows: every wave takes its share of the per-strip sums of squares; the
     // loads go out ahead of the weight stream and are folded in behind its first batch
@@ -350,22 +400,24 @@ k_gemm(const gemm_args a)
             for (int u = 0; u < U; ++u) {
 #pragma unroll
                 for (int si = 0; si < S; ++si) q.w[si][u] = load_once(&A[so[si] + o + u * 64 + ((HF && si == S - 1) ? hl : 0)]);
-                q.x[u] = operand((first + k * bstride) * U + u);
+                if (MG == 0) q.x[u] = operand((first + k * bstride) * U + u);
                 if (NB == 2) q.xl[NB == 2 ? u : 0] = operand(KT + (first + k * bstride) * U + u);
             }
             asm volatile("" ::: "memory");
         };
-        auto consume = [&](const wbatch &q) {
+        auto consume = [&](const wbatch &q, int k) {
+            (void)k;
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int si = 0; si < S; ++si) {
-                    acc[si][0] = mfma16(q.w[si][u], q.x[u], acc[si][0]);
+                    acc[si][0] = mfma16(q.w[si][u], MG > 0 ? merged[((first + k * bstride) * U + u) * (xs >> 4) + (xl >> 4)] : q.x[u], acc[si][0]);
                     if (NB == 2) acc[si][0] = mfma16(q.w[si][u], q.xl[NB == 2 ? u : 0], acc[si][0]);
                 }
         };
         wbatch q0, q1, q2;
         k_walk<DP>(cnt, q0, q1, q2, issue, consume, [&]() {
+            if constexpr (MG > 0) { merge_chunks<MG, NW * 64>(a, (uint16_t *)merged); __syncthreads(); }      // (every wave comes here once)
             if (NORM) {
                 const float4 s4 = ssq_finish(a.ssq, a.ssq_parts, threadIdx.x, NW * 64, sl[0]);
                 if (lane < 4) *(float4 *)&ssq_s[wave][0][4 * lane] = s4;
@@ -378,7 +430,7 @@ k_gemm(const gemm_args a)
         });
         if (wave == NW - 1) {
             for (int t = nbat * U; t < KT; ++t) {
-                const uint4 x = operand(t);
+                const uint4 x = MG > 0 ? merged[t * (xs >> 4) + (xl >> 4)] : operand(t);
                 uint4 xl = x;
                 if (NB == 2) xl = operand(KT + t);
 #pragma unroll
@@ -1297,6 +1349,19 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         if constexpr (EPI == EPI_RESID) {
             // at most half as many strips as CUs: a workgroup per 8-feature half (every CU works, on half the weights: 128 strips, one row,
             // K = 2048 and 8192 together 14.9 -> 13.6 us)
+            if (ga.chunks > 0) {                                 // (merges_in_oproj)
+                const int lds = ga.rows * g.ktiles * 128;
+                const bool half = 2 * strips <= m->n_cus;
+                ga.half_base = 0;
+                auto go = [&](auto mg) {
+                    if (half) k_gemm<NB, CT, 1, EPI, 8, 3, true, mg.value><<<2 * strips, 512, lds, s>>>(ga);
+                    else k_gemm<NB, CT, 1, EPI, 8, 3, false, mg.value><<<strips, 512, lds, s>>>(ga);
+                };
+                if (ga.chunks <= 4) go(std::integral_constant<int, 4>());
+                else go(std::integral_constant<int, 8>());
+                PV_HIP(hipGetLastError());
+                return PV_OK;
+            }
             if (g.ktiles >= 64 && 2 * strips <= m->n_cus) {
                 ga.half_base = 0;
                 k_gemm<NB, CT, 1, EPI, 8, 3, true><<<2 * strips, 512, 0, s>>>(ga);
@@ -1312,6 +1377,18 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
     }
     PV_HIP(hipGetLastError());
     return PV_OK;
+}
+
+// Whether the output projection of a block merges the attention's chunks itself, so that a layer has five kernels instead of six.  Every workgroup of it then reads
+// the chunks of all heads, rows x K x chunks x 4 bytes, which pays while its threads have them in flight all at once: attention's
+// merge and output projection, us: 1B shape, one row, 5 chunks 8.7 -> 6.5, two rows, 4 chunks 9.3 -> 7.4; 8B shape, one row, 4 chunks 11.9 -> 10.1; but in two rounds
+// (8 chunks; two rows, 3 chunks) 12.0 -> 11.7 and 11.9 -> 12.1.  Up to two chunks the attention needs no merge.
+static bool merges_in_oproj(const pv_cache *c, int rows, const pv_attn_split_info &sp)
+{
+    const pv_model_config &f = c->m->cfg;
+    const int qd = f.n_q_heads * f.head_dim;
+    if (c->blk_units != 0 || rows > 8 || c->m->wbits != 16 || sp.chunks < 3 || sp.chunks > 8) return false;
+    return qd >= 64 * 32 && f.d_model / 16 < 512 && rows * qd <= 4 * 512 * merge_items(sp.chunks <= 4 ? 4 : 8);      // (and the operand is at most 16 KiB)
 }
 
 template <int NB, int CT>
@@ -1337,6 +1414,9 @@ static int run_block(pv_cache *c, hipStream_t s)
     g.x = c->ws.x; g.d = d; g.xop_act = mw.xop_d; g.F = F;
     g.logits = c->ws.logits; g.pmax_val = mw.pmax_val; g.pmax_idx = mw.pmax_idx; g.vocab = f.vocab;
     g.tile_part = mw.tile_part;
+    const pv_attn_split_info sp = pv_attn_split(c, rows, mw.attn_part);
+    const bool fused = NB == 1 && merges_in_oproj(c, rows, sp);
+    g.part_o = sp.part_o; g.part_ml = sp.part_ml; g.max_chunks = sp.max_chunks; g.chunk_shift = sp.chunk_shift; g.units = sp.units;
 
     for (int l = 0; l < f.n_layers; ++l) {
         // fused QKV projection: RMSNorm scale, rotary embedding, KV append
@@ -1347,15 +1427,16 @@ static int run_block(pv_cache *c, hipStream_t s)
         if ((prc = pv_prof_mark(c, PV_PROF_QKV, l, 1, s)) != PV_OK) return prc;
         // attention over the paged cache -> operand of the output projection
         if ((prc = pv_prof_mark(c, PV_PROF_ATTENTION, l, 0, s)) != PV_OK) return prc;
-        int rc = pv_mat_attention(c, l, rows, mw.attn_part, mw.xop_o, s);
+        int rc = pv_mat_attention(c, l, rows, mw.attn_part, mw.xop_o, !fused, s);
         if (rc != PV_OK) return rc;
         if ((prc = pv_prof_mark(c, PV_PROF_ATTENTION, l, 1, s)) != PV_OK) return prc;
         // output projection + residual; emits the FFN operand and sum of squares
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WO, l).off); g.xop = (const uint4 *)mw.xop_o; g.ktiles = qd / 32;
-        g.gain_next = gainp(PV_T_FFN_NORM, l); g.ssq_out = mw.ssq1; g.xop_out = mw.xop_f;
+        g.gain_next = gainp(PV_T_FFN_NORM, l); g.ssq_out = mw.ssq1; g.xop_out = mw.xop_f; g.chunks = fused ? sp.chunks : 0;
         if ((prc = pv_prof_mark(c, PV_PROF_OPROJ, l, 0, s)) != PV_OK) return prc;
         if ((prc = launch_gemm<NB, CT, EPI_RESID>(m, g, d / 16, s)) != PV_OK) return prc;
         if ((prc = pv_prof_mark(c, PV_PROF_OPROJ, l, 1, s)) != PV_OK) return prc;
+        g.chunks = 0;
         // gate/up projection + SwiGLU
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WG, l).off); g.xop = (const uint4 *)mw.xop_f; g.ktiles = d / 32;
         g.ssq = mw.ssq1;

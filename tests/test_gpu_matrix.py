@@ -90,6 +90,35 @@ def test_packed_rows_match_oracle(pvlib, name):
     _check_against_oracle(pvlib, shape, 0, 16, 21, (2, 7, 4, 6, 1, 3, 5, 8), 96)
 
 
+# Output projections that merge the attention's chunks: K = 2048 as half strips and as whole ones (130), 4096 features with one row; 3..8 chunks of 256 keys
+MERGE = [pv_inputs.ModelShape("merge_h", 1, 1024, 32, 8, 64, 352, 512, dtype="bf16", seed=5901),
+         pv_inputs.ModelShape("merge_w", 1, 2080, 16, 2, 128, 352, 512, dtype="bf16", seed=5902),
+         pv_inputs.ModelShape("merge_k", 1, 512, 32, 4, 128, 352, 512, dtype="bf16", seed=5903)]
+
+
+@pytest.mark.parametrize("shape", MERGE, ids=lambda v: v.name)
+@pytest.mark.parametrize("graphs", [True, False])
+@pytest.mark.parametrize("prefix", [509, 700, 1022, 1500, 2046])
+def test_merged_chunks_match_oracle(pvlib, shape, graphs, prefix):
+    """One and two rows around the edges of the chunks; recorded steps cover chunks beyond the keys (of an earlier, longer prefix), plain ones do not."""
+    from gpu_helpers import gpu_model
+    gm, rm = gpu_model(shape, gains="perturbed", max_gamma=16), ref_model(shape, gains="perturbed")
+    gc, rc = pvlib.Cache(gm, 2112), ref.RefCache(rm, 2112, ref.KV_BF16)
+    gc.use_graphs(graphs)
+    prompt = pv_inputs.uniform_tokens(81, 2048, shape.vocab)
+    gc.prefill(prompt)
+    gc.verify(2048, prompt[:1])
+    gc.rollback(prefix)
+    rc.prefill(prompt[:prefix])
+    for step, gamma in enumerate((1, 2, 1, 3)):
+        T = len(rc)
+        d = pv_inputs.uniform_tokens(82 + step, gamma, shape.vocab)
+        _, _, _, lg_r = rc.verify(T, d, want_logits=True)
+        n, _ = gc.verify(T, d)
+        assert _rel_err(pvlib, gc.debug_logits(), lg_r) < 2e-3, f"gamma {gamma} at {T}"
+        gc.rollback(T); rc.rollback(T)
+
+
 def test_wide_blocks_match_oracle(pvlib, wide_shape):
     """Blocks of 17..64 rows (two and four 16-row column tiles per weight pass; with 4-bit weights one
     weight pass per column tile), next to narrow ones on the same cache; the prompt is prefilled in

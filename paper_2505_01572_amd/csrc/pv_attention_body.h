@@ -265,45 +265,53 @@ __device__ inline void attn_merge_unit(const attn_args &a, int r, int aq, int n_
     float (*sh_acc)[TPC][5] = (float (*)[TPC][5])(smem + NT);        // [NG][TPC][5]
     const int t = tid % TPC, cg = tid / TPC;
     float acc[4] = {0.f, 0.f, 0.f, 0.f}, L = 0.f;
-    // Up to 64 chunks: lane c of every wave holds chunk c's (max, sum); the global max, the
+    // Up to 256 chunks: lane c of every wave holds (max, sum) of the chunks c, c + 64, ...; the global max, the
     // weights and the total come from wave shuffles (every wave redundantly, no barrier), and
-    // the partial outputs are fetched four chunks at a time with nothing depending on them.  Statistics and the first outputs go out beside the
+    // the partial outputs are fetched eight chunks at a time with nothing depending on them.  Statistics and the first outputs go out beside the
     // length, whatever it turns out to be (the partials have room for every chunk of the cache): one memory round trip instead of three
     // (with the rows as an argument 3462 -> 3442 us for 8 steps of four 8B-shaped layers; the kernel stays at the 4.6 us that any small kernel takes here).
+    // More than 64 chunks, or 32 (128 features), were a loop of round trips before: 65 chunks 6.4 -> 4.7 us, 94 chunks 7.5 -> 5.8.
+    constexpr int SL = 4, FL = 8;
     const int lane = tid & 63;
-    float2 ml = *(const float2 *)(a.part_ml + ((unit0 + min(lane, a.max_chunks - 1)) * 32 + row) * 2);
-    float4 o[4];
+    float2 ml[SL];
+#pragma unroll
+    for (int q = 0; q < SL; ++q) {
+        ml[q] = make_float2(-INFINITY, 0.f);
+        if (q == 0 || 64 * q < a.max_chunks) ml[q] = *(const float2 *)(a.part_ml + ((unit0 + min(64 * q + lane, a.max_chunks - 1)) * 32 + row) * 2);
+    }
+    float4 o[FL];
     auto fetch = [&](int base) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) o[u] = *(const float4 *)(a.part_o + ((unit0 + min(base + cg + u * NG, a.max_chunks - 1)) * 32 + row) * HD + 4 * t);
+        for (int u = 0; u < FL; ++u)
+            if (u == 0 || base + u * NG < a.max_chunks) o[u] = *(const float4 *)(a.part_o + ((unit0 + min(base + cg + u * NG, a.max_chunks - 1)) * 32 + row) * HD + 4 * t);
     };
     fetch(0);
     asm volatile("" ::: "memory");
     const int nchunks = (len + gamma + (1 << a.chunk_shift) - 1) >> a.chunk_shift;
-    if (nchunks <= 64) {
-        if (lane >= nchunks) ml = make_float2(-INFINITY, 0.f);
-        float M = ml.x;
+    if (nchunks <= 64 * SL) {
+        float M = -INFINITY, wl[SL];
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
-        const float wl = (ml.x == -INFINITY) ? 0.f : expf(ml.x - M);
-        L = ml.y * wl;
+        for (int q = 0; q < SL; ++q) { if (64 * q + lane >= nchunks) ml[q] = make_float2(-INFINITY, 0.f); M = fmaxf(M, ml[q].x); }
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) L += __shfl_xor(L, o, 64);
-        for (int base = 0; base < nchunks; base += 4 * NG) {      // same trip count in every lane: the shuffles below need all lanes
-            float w[4];
+        for (int d = 1; d < 64; d <<= 1) M = fmaxf(M, __shfl_xor(M, d, 64));
+#pragma unroll
+        for (int q = 0; q < SL; ++q) { wl[q] = (ml[q].x == -INFINITY) ? 0.f : expf(ml[q].x - M); L += ml[q].y * wl[q]; }
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) L += __shfl_xor(L, d, 64);
+        for (int base = 0; base < nchunks; base += FL * NG) {     // same trip count in every lane: the shuffles below need all lanes
             if (base > 0) fetch(base);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int c = base + cg + u * NG;
-                w[u] = __shfl(wl, c < nchunks ? c : 0, 64);
-                if (c >= nchunks) { w[u] = 0.f; o[u] = make_float4(0.f, 0.f, 0.f, 0.f); }        // (never written this step: anything)
+            for (int u = 0; u < FL; ++u) {
+                const int c0 = base + u * NG, c = c0 + cg;        // (NG divides 64: c0 / 64 = c / 64)
+                if (c0 >= nchunks) break;
+                const float v = c0 < 64 ? wl[0] : c0 < 128 ? wl[1] : c0 < 192 ? wl[2] : wl[3];
+                const float w = __shfl(v, c & 63, 64);
+                if (c < nchunks) { acc[0] += w * o[u].x; acc[1] += w * o[u].y; acc[2] += w * o[u].z; acc[3] += w * o[u].w; }      // (others were never written this step: anything)
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { acc[0] += w[u] * o[u].x; acc[1] += w[u] * o[u].y; acc[2] += w[u] * o[u].z; acc[3] += w[u] * o[u].w; }
         }
         if (cg != 0) L = 0.f;                     // the total is added up over the chunk groups below: count it once
     } else {
-        // many chunks: each thread looks at chunks tid, tid+NT, ... and a tree in LDS finishes the max
+        // more: each thread looks at chunks tid, tid+NT, ... and a tree in LDS finishes the max
         float M = -INFINITY;
         for (int c = tid; c < nchunks; c += NT) M = fmaxf(M, a.part_ml[((unit0 + c) * 32 + row) * 2]);
         sh_m[tid] = M;

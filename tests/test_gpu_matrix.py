@@ -90,6 +90,25 @@ def test_packed_rows_match_oracle(pvlib, name):
     _check_against_oracle(pvlib, shape, 0, 16, 21, (2, 7, 4, 6, 1, 3, 5, 8), 96)
 
 
+def test_chunks_beyond_four_per_lane(pvlib):
+    """33000 cached positions: 259 chunks of 128 keys (gamma 8) take the merge's general path, 130 of 256 keys (gamma 4) do not.  Against the vector path, which
+    has no chunks."""
+    from gpu_helpers import gpu_model
+    T0 = 33000
+    prompt = pv_inputs.uniform_tokens(65, T0, LONG_A.vocab)
+    caches = [pvlib.Cache(gpu_model(LONG_A, gains="perturbed", kernel_path=p, max_gamma=16), T0 + 64) for p in (pvlib.PATH_AUTO, pvlib.PATH_VECTOR)]
+    for c in caches:
+        c.prefill(prompt)
+    for step, gamma in enumerate((8, 4)):
+        d = pv_inputs.uniform_tokens(66 + step, gamma, LONG_A.vocab)
+        lg = []
+        for c in caches:
+            c.verify(T0, d)
+            lg.append(c.debug_logits())
+            c.rollback(T0)
+        assert _rel_err(pvlib, lg[0], lg[1]) < 2e-3, f"gamma {gamma}"
+
+
 # Output projections that merge the attention's chunks: K = 2048 as half strips and as whole ones (130), 4096 features with one row; 3..8 chunks of 256 keys
 MERGE = [pv_inputs.ModelShape("merge_h", 1, 1024, 32, 8, 64, 352, 512, dtype="bf16", seed=5901),
          pv_inputs.ModelShape("merge_w", 1, 2080, 16, 2, 128, 352, 512, dtype="bf16", seed=5902),
@@ -146,8 +165,7 @@ LONG_A = pv_inputs.ModelShape("long_a", 1, 128, 8, 2, 32, 352, 512, rope_base=50
 
 def test_long_prefix_many_attention_chunks(pvlib):
     """8300 cached positions: with 32 query rows per kv head (gamma 8, group 4) attention makes 65
-    chunks of 128 keys, more than the lanes of a wave, and the chunk merge takes its general path;
-    with 16 rows (gamma 4) it makes 33 chunks of 256 keys and takes the wave-shuffle path."""
+    chunks of 128 keys, more than the lanes of a wave; with 16 rows (gamma 4) it makes 33 chunks of 256 keys."""
     from gpu_helpers import gpu_model
     gm = gpu_model(LONG_A, gains="perturbed", kernel_path=0, max_gamma=64)
     rm = ref_model(LONG_A, gains="perturbed")

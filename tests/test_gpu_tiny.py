@@ -50,6 +50,26 @@ def test_tiny_logits_and_decisions_match_oracle(pvlib, tiny_pair):
     assert (n_g, t_g) == (n_r, t_r) and gc.state() == (len(rc), rc.pending)
 
 
+@pytest.mark.parametrize("hd,page_tokens", [(32, 4), (64, 16), (128, 64), (128, 4), (64, 2), (48, 16), (32, 2048)])
+def test_vector_attention_at_the_edges_of_its_passes(pvlib, hd, page_tokens):
+    """128 keys a pass, pages looked up for 1024; the last two but one shapes take the kernel for other heads and pages."""
+    from gpu_helpers import gpu_model
+    shape = pv_inputs.ModelShape(f"vec_{hd}_{page_tokens}", 1, 64, 4, 2, hd, 96, 128, dtype="f32", seed=9000 + hd + page_tokens, page_tokens=page_tokens)
+    gm, rm = gpu_model(shape, gains="perturbed"), ref_model(shape, gains="perturbed")
+    n = 2052
+    prompt = pv_inputs.uniform_tokens(91, n, shape.vocab)
+    gc, rc = pvlib.Cache(gm, n + 16), ref.RefCache(rm, n + 16)
+    gc.set_page_table(np.random.default_rng(5).permutation(-(-(n + 16) // page_tokens)).astype(np.int32))
+    gc.prefill(prompt); rc.prefill(prompt)
+    for T in (2050, 2046, 1024, 1022, 257, 128, 126, 3, 1):
+        gc.rollback(T); rc.rollback(T)
+        d = pv_inputs.uniform_tokens(92, 4, shape.vocab)
+        _, _, _, lg_r = rc.verify(T, d, want_logits=True)
+        gc.verify(T, d)
+        assert np.abs(gc.debug_logits() - lg_r).max() < 1e-4, T
+        gc.rollback(T); rc.rollback(T)
+
+
 def test_tiny_config1_100_steps(pvlib):
     """Config 1: prefix 64, gamma 4, alpha 0.7, 100 verify(+rollback) steps; outputs bit-exact vs oracle,
     and everything committed equals the oracle's greedy continuation (lossless acceptance)."""

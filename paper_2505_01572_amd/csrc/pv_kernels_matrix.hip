@@ -1229,7 +1229,9 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
 {
     gemm_args ga = g;
     ga.nstrips = strips;
-    ga.interleave = g.ktiles > 128;                          // long strips: measured 0.3 % faster per step, short ones 0.3 % slower
+    // long strips: measured 0.3 % faster per step, short ones 0.3 % slower; a whole vocabulary (8016 strips, K = 4096) 176 -> 172 us: there the contiguous
+    // runs of many workgroups, a power of two apart, advance in step
+    ga.interleave = g.ktiles > 128 || (NB == 1 && EPI == EPI_LMHEAD && strips >= 2048);
     if (m->wbits == 4) {
         // 9..16 rows: k_gemm_q4 is ahead of tiles shared through LDS and K-slices up to K = 12800 or so (13 rows, us: 256 strips, K = 4096 7.3 and 11.2, K =
         // 14336 18.8 and 18.2; 512 strips, K = 8192 14.4 and 18.4, K = 28672 43 and 36; 3584 strips, K = 8192 56 and 65), and up to as many strips as
@@ -1371,7 +1373,10 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         }
         auto fill = [](int wgs) { return (double)wgs / (double)(((wgs + 255) / 256) * 256); };
         const bool two = strips >= 512 && fill((strips + 1) / 2) >= fill(strips);
-        if (g.ktiles >= 64 && two) k_gemm<NB, CT, 2, EPI, 8, 2><<<(strips + 1) / 2, 512, 0, s>>>(ga);
+        // (three batches deep, us: K = 2048, 1024 strips of gate/up 13.2 -> 12.8, 8016 of the vocabulary 83.0 -> 80.7, K = 4096, 2048 strips 47.5 -> 46.5; K = 8192, 512 strips with the
+        // residual 23.4 -> 24.3)
+        constexpr int D2 = EPI == EPI_RESID ? 2 : 3;
+        if (g.ktiles >= 64 && two) k_gemm<NB, CT, 2, EPI, 8, D2><<<(strips + 1) / 2, 512, 0, s>>>(ga);
         else if (g.ktiles >= 64) k_gemm<NB, CT, 1, EPI, 8, 3><<<strips, 512, 0, s>>>(ga);
         else k_gemm<NB, CT, 1, EPI, 8><<<strips, 512, 0, s>>>(ga);
     }

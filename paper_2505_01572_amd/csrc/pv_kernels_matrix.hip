@@ -1227,6 +1227,7 @@ static int launch_q4(const pv_model *m, const gemm_args &ga, int strips, hipStre
 template <int NB, int CT, int EPI>
 static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStream_t s)
 {
+    if (g.ktiles > (1 << 20)) { pv_set_error("a projection over more than 2^25 features: past the 32-bit offsets of its buffers"); return PV_ERANGE; }
     gemm_args ga = g;
     ga.nstrips = strips;
     // long strips: measured 0.3 % faster per step, short ones 0.3 % slower; a whole vocabulary (8016 strips, K = 4096) 176 -> 172 us: there the contiguous

@@ -42,6 +42,7 @@ struct attn_args {
     float *part_ml;             // [n_kv_heads][MP][max_chunks][32][2]  (max, sum)
     uint16_t *xop_o;            // merge output: operand of the output projection, K = n_q_heads*hd
     int n_pages;                // entries of the page table
+    int chunks;                 // chunks launched: the host's bound of a step's keys, at most max_chunks
     int rows, batched;          // rows of the block; several sequences in it (their rows, lengths and pages are in the state's description).  Arguments, so
                                 // that what depends on them only is asked for at once, not a memory round trip later
 };
@@ -268,8 +269,9 @@ __device__ inline void attn_merge_unit(const attn_args &a, int r, int aq, int n_
     // Up to 256 chunks: lane c of every wave holds (max, sum) of the chunks c, c + 64, ...; the global max, the
     // weights and the total come from wave shuffles (every wave redundantly, no barrier), and
     // the partial outputs are fetched eight chunks at a time with nothing depending on them.  Statistics and the first outputs go out beside the
-    // length, whatever it turns out to be (the partials have room for every chunk of the cache): one memory round trip instead of three
+    // length, for as many chunks as were launched, whatever the length turns out to be: one memory round trip instead of three
     // (with the rows as an argument 3462 -> 3442 us for 8 steps of four 8B-shaped layers; the kernel stays at the 4.6 us that any small kernel takes here).
+    // Not for as many as the cache has room for: 1000 of 32768 tokens, 64 rows, two layers, 70B shape 975 -> 924 us, 8B shape 369 -> 342 a step.
     // More than 64 chunks, or 32 (128 features), were a loop of round trips before: 65 chunks 6.4 -> 4.7 us, 94 chunks 7.5 -> 5.8.
     constexpr int SL = 4, FL = 8;
     const int lane = tid & 63;
@@ -277,13 +279,13 @@ __device__ inline void attn_merge_unit(const attn_args &a, int r, int aq, int n_
 #pragma unroll
     for (int q = 0; q < SL; ++q) {
         ml[q] = make_float2(-INFINITY, 0.f);
-        if (q == 0 || 64 * q < a.max_chunks) ml[q] = *(const float2 *)(a.part_ml + ((unit0 + min(64 * q + lane, a.max_chunks - 1)) * 32 + row) * 2);
+        if (q == 0 || 64 * q < a.chunks) ml[q] = *(const float2 *)(a.part_ml + ((unit0 + min(64 * q + lane, a.chunks - 1)) * 32 + row) * 2);
     }
     float4 o[FL];
     auto fetch = [&](int base) {
 #pragma unroll
         for (int u = 0; u < FL; ++u)
-            if (u == 0 || base + u * NG < a.max_chunks) o[u] = *(const float4 *)(a.part_o + ((unit0 + min(base + cg + u * NG, a.max_chunks - 1)) * 32 + row) * HD + 4 * t);
+            if (u == 0 || base + u * NG < a.chunks) o[u] = *(const float4 *)(a.part_o + ((unit0 + min(base + cg + u * NG, a.chunks - 1)) * 32 + row) * HD + 4 * t);
     };
     fetch(0);
     asm volatile("" ::: "memory");

@@ -70,11 +70,11 @@ static int launch(pv_cache *c, attn_args &a, int rows, bool merge, hipStream_t s
         return PV_OK;
     }
     if (nrows <= 16) {
-        a.chunk_shift = 8; a.max_chunks = (c->max_tokens + 255) / 256;
-        k_attn<HD, 1, 0><<<dim3((keys + 255) / 256, f.n_kv_heads, units), 512, lds, s>>>(a);
+        a.chunk_shift = 8; a.max_chunks = (c->max_tokens + 255) / 256; a.chunks = (keys + 255) / 256;
+        k_attn<HD, 1, 0><<<dim3(a.chunks, f.n_kv_heads, units), 512, lds, s>>>(a);
     } else {
-        a.chunk_shift = 7; a.max_chunks = (c->max_tokens + 127) / 128;
-        k_attn<HD, 2, 0><<<dim3((keys + 127) / 128, f.n_kv_heads, units), 512, lds, s>>>(a);
+        a.chunk_shift = 7; a.max_chunks = (c->max_tokens + 127) / 128; a.chunks = (keys + 127) / 128;
+        k_attn<HD, 2, 0><<<dim3(a.chunks, f.n_kv_heads, units), 512, lds, s>>>(a);
     }
     PV_HIP(hipGetLastError());
     if (!merge) return PV_OK;
@@ -113,7 +113,7 @@ int pv_mat_attention(pv_cache *c, int layer, int rows, float *part, uint16_t *xo
     a.st = c->ws.state; a.page_table = c->ws.page_table; a.q_hi = (const uint16_t *)c->ws.q; a.q_lo = a.q_hi + (size_t)c->rows_cap * f.n_q_heads * f.head_dim; a.pool = (const uint16_t *)c->d_pool;
     a.geom = pv_geom(c); a.layer = layer; a.n_q_heads = f.n_q_heads; a.group = f.n_q_heads / f.n_kv_heads;
     a.max_chunks = (c->max_tokens + 127) / 128;        // sizes the partial arrays; the launch sets the chunking in use
-    a.chunk_shift = 7;
+    a.chunk_shift = 7; a.chunks = a.max_chunks;
     a.scale = 1.0f / sqrtf((float)f.head_dim);
     a.part_o = part;
     a.part_ml = part + (size_t)f.n_kv_heads * c->units_cap * a.max_chunks * 32 * f.head_dim;

@@ -1134,21 +1134,35 @@ static int allow_tile_q4_lds()
 }
 
 // Strips a workgroup of k_gemm_wide, 0: the GEMM goes elsewhere.  Workgroups run in rounds of one per CU; per K-tile a CU takes in S weight tiles and 2 CT
-// activation tiles, and one of those costs about 0.3 of a weight tile (L2 against HBM latency).  The lines, in us with the sum of the K-slices:
-// 640 strips (K = 8192) 35.4 in k_gemm_tile, 41.1 here with 32 rows, 42.8 and 50.6 with 48 (16 rows: 32.3 and 32.2); 750 strips (K = 4096) 26.8 and 22.6, 33.3
-// and 27.0; 768 strips 26.6 and 23.2, 34.0 and 28.9.  Up to 16 rows there are no slices to save: K = 2048, 1024 strips 14.5 in k_gemm, 15.8 here; K = 4096
-// 26.1 and 24.0.  Strips a workgroup for 1376 strips, 16 / 32 / 48 rows: six (230 workgroups) 30.8 / 34.4 / 40.8, seven (197) 32.3 / 36.3 / 44.2.
+// activation tiles, and one of those costs about 0.3 of a weight tile (L2 against HBM latency).  Strips a workgroup for 1376 strips, 16 / 32 / 48 rows: six (230
+// workgroups) 30.8 / 34.4 / 40.8 us, seven (197) 32.3 / 36.3 / 44.2.
+// Up to 16 rows the alternative is k_gemm: K = 2048, 1024 strips 14.5 there, 15.8 here; K = 4096 26.1 and 24.0.
+// More rows: k_gemm_tile, a workgroup of eight strips on every CU or, up to four strips a CU, two or more that share a CU's strips along K.  What decides is how many
+// strips the CU with the most of them goes through, S a round here and 8 a round there (gate/up and vocabulary, us, there / here):
+//  - up to four strips a CU the slices leave no CU idle and cost one more kernel: K = 4096, 1024 strips, 32 / 48 / 64 rows 34.6 / 31.3, 37.1 / 36.3, 39.9 / 39.6;
+//    K = 5120 37.0 / 34.7, 40.9 / 40.4, 44.9 / 45.7; K = 8192 54.3 / 54.3, 56.6 / 62.2, 61.0 / 69.6.  Below 2 3/4 strips a CU (640 strips, K = 5120) 28.8 / 30.3, 31.5 / 34.7, 34.7 / 38.3;
+//  - three quarters of the strips or less: always (K = 4096, 1376 strips 40.8 / 37.2, 47.4 / 43.5, 52.0 / 47.5; 2560 strips 80.7 / 67.8, 87.6 / 82.8, 94.0 / 91.1);
+//  - seven eighths: up to 32 rows (K = 4096, 3584 strips 87.2 / 82.0, 5120 strips 125.7 / 119.4), in one round with more rows as well (1792 strips 50.8 / 49.2 and 55.1 / 53.1),
+//    in several up to 48 rows from K = 5120 on (3584 strips, K = 4096 96.9 / 99.0, K = 8192 174.7 / 171.0), and with 64 rows in one round up to K = 6656 (K = 8192 97.5 / 99.4);
+//  - as many or more: never (K = 4096, 2000 strips 50.9 / 55.0, 52.8 / 66.7, 56.7 / 73.8; 8016 strips 184 / 192, 200 / 229, 212 / 249).
 static int wide_strips(const pv_model *m, int strips, int ktiles, int ct)
 {
-    if (!wide_fits(ktiles) || ktiles < (ct == 1 ? 128 : 16) || strips < 704) return 0;
-    int best = 0;
+    const int cus = m->n_cus;
+    if (!wide_fits(ktiles) || ktiles < (ct == 1 ? 128 : 16) || 4 * strips < 11 * cus) return 0;
+    int best = 0, through = 0;
     double least = 1e30;
     for (int S : {7, 6, 4, 3}) {
-        const int rounds = ((strips + S - 1) / S + m->n_cus - 1) / m->n_cus;
+        const int rounds = ((strips + S - 1) / S + cus - 1) / cus;
         const double t = rounds * (S + 0.6 * ct);
-        if (t < least) { least = t; best = S; }
+        if (t < least) { least = t; best = S; through = rounds * S; }
     }
-    return best;
+    if (ct == 1) return best;
+    const int there = ((strips + 7) / 8 + cus - 1) / cus * 8;
+    if (strips <= 4 * cus) return ktiles <= 160 ? best : 0;
+    if (4 * through <= 3 * there) return best;
+    if (8 * through > 7 * there) return 0;
+    if (ct == 2 || (ct == 3 && (there == 8 || ktiles >= 160)) || (ct == 4 && there == 8 && ktiles <= 208)) return best;
+    return 0;
 }
 
 template <int NB, int CT, int S, int EPI>

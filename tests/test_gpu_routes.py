@@ -1,0 +1,100 @@
+"""Which kernel a projection takes, at both sides of the lines that the launches draw: a line in the wrong place is a block that takes up to twice its time
+and fails no other test.  (Where the lines lie, and the measurements on both sides, stands at the launches.)  The block's logits are compared with those of
+the same rows in blocks of eight, which run other kernels."""
+import re
+
+import numpy as np
+import pytest
+
+import pv_inputs
+
+pytestmark = pytest.mark.gpu
+
+LMHEAD = 3          # the epilogue's number among a kernel's template arguments
+EPI_AT = {"k_gemm": 3, "k_gemm_wide": 3, "k_gemm_tile": 2, "k_gemm_q4": 2, "k_gemm_tile_q4": 1}
+
+
+def _model(k, strips, bits=16):
+    """One layer of width k with a vocabulary of `strips` strips; every matrix is windows of one pool of normal draws."""
+    import torch
+    import paper_2505_01572_amd as pv
+    shape = pv_inputs.ModelShape("route", 1, k, k // 128, 1, 128, 256, 16 * strips, weight_bits=bits)
+    m = pv.Model(shape, max_gamma=64, prompt_rows=0)
+    rng = np.random.default_rng(77)
+    pool = torch.from_numpy(rng.standard_normal(1 << 22, dtype=np.float32) * 0.02).to(torch.bfloat16).view(torch.uint16).numpy()
+    for kind, layer in pv_inputs.iter_tensors(shape):
+        dims = pv_inputs.tensor_shape(shape, kind)
+        rows, cols = (1, dims[0]) if len(dims) == 1 else dims
+        if rows == 1:
+            m.load_weights(kind, layer, 0, np.full((1, cols), 0x3F80, np.uint16))
+            continue
+        step = max(16, min(m.chunk_rows(cols), pool.size // cols // 16 * 16))
+        for r0 in range(0, rows, step):
+            n = min(step, rows - r0)
+            at = int(rng.integers(0, max(1, pool.size - n * cols)))
+            w = np.resize(pool[at:at + n * cols], (n, cols))
+            if bits == 4 and kind in pv_inputs.Q4_KINDS:
+                m.load_weights_q4(kind, layer, r0, *pv_inputs.quantize_q4(w))
+            else:
+                m.load_weights(kind, layer, r0, w)
+    return m
+
+
+def _head_kernel(call):
+    """Name and template arguments of the kernel that multiplies with the vocabulary."""
+    import torch
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU, torch.profiler.ProfilerActivity.CUDA]) as p:
+        call()
+    found = set()
+    for e in p.events():
+        hit = re.match(r"(?:void )?(k_gemm\w*)<([^>]*)>", e.name)
+        if hit and hit[1] in EPI_AT:
+            args = [int(v) if v.strip().isdigit() else v.strip() for v in hit[2].split(",")]
+            if args[EPI_AT[hit[1]]] == LMHEAD:
+                found.add((hit[1], *args))
+    assert len(found) == 1, found
+    return found.pop()
+
+
+def _check(model, rows, logits=True):
+    import paper_2505_01572_amd as pv
+    from gpu_helpers import logit_scale
+    v = model.shape.vocab
+    prompt, block = pv_inputs.uniform_tokens(5, 5, v), pv_inputs.uniform_tokens(6, rows, v)
+    a, b = pv.Cache(model, 96), pv.Cache(model, 96)
+    a.use_graphs(False)
+    for c in (a, b):
+        c.prefill(prompt)
+    name = _head_kernel(lambda: a.verify(5, block))
+    if logits:
+        got, want = a.debug_logits(), []
+        for r0 in range(0, rows, 8):
+            b.prefill(block[r0:r0 + 8])
+            want.append(b.debug_logits())
+        want = np.concatenate(want)
+        assert (np.abs(got - want) / logit_scale(want)).max() < 2e-3
+    a.close(); b.close()
+    return name
+
+
+# K, strips -> {rows: takes k_gemm_wide}
+WIDE_LINES = [
+    (1024, 704, {32: True, 48: True, 64: True}), (1024, 700, {32: False, 64: False}),
+    (1024, 1792, {32: True, 48: True, 64: True}), (1024, 2000, {32: False, 48: False, 64: False}),
+    (1024, 2560, {32: True, 48: True, 64: True}), (1024, 3584, {32: True, 48: False, 64: False}),
+    (1024, 4096, {32: False, 64: False}), (1024, 5120, {32: True, 48: False, 64: False}), (1024, 8016, {32: False, 48: False, 64: False}),
+    (5120, 1024, {32: True, 64: True}), (5248, 1024, {32: False, 64: False}),
+    (5120, 3584, {48: True}), (6656, 1792, {64: True}), (6784, 1792, {48: True, 64: False}),
+    (4096, 704, {16: True}), (3968, 704, {16: False}),
+]
+
+
+@pytest.mark.parametrize("k,strips,expected", WIDE_LINES, ids=lambda v: str(v) if isinstance(v, int) else "")
+def test_one_workgroup_per_cu_where_it_is_the_faster_one(k, strips, expected):
+    m = _model(k, strips)
+    for rows, wide in expected.items():
+        name = _check(m, rows)
+        assert (name[0] == "k_gemm_wide") == wide, (rows, name)
+        if name[0] == "k_gemm_tile":
+            assert name[1] == (rows + 15) // 16, name
+    m.close()

@@ -1213,7 +1213,8 @@ int pv_mat_gemm_init(int wbits)
 
 // Strips a workgroup of k_gemm_q4: a CU takes its workgroups two at a time, one round for each per CU; a strip takes 0.0145 us per K-tile, the operand 0.006
 // (16 rows).  Eight waves, two workgroups a CU where there are that many (sixteen waves and one or two strips: 8 rows, K = 14336 14.5 us against 14.2, but
-// up to 4 rows, whose operand is small, 11.2 against 13.7).
+// up to 4 rows, whose operand is small, 11.2 against 13.7; but not below K = 2048, where sixteen waves have no batch each: 4 rows, K = 512, 256 strips 7.4 against
+// 6.7, 512 strips 8.2 against 7.3, K = 1024 7.4 and 8.3 against 6.8 and 7.4, K = 2048 7.7 and 8.5 against 7.7 and 8.7).
 template <int NB, int EPI>
 static int launch_q4(const pv_model *m, const gemm_args &ga, int strips, hipStream_t s)
 {
@@ -1227,8 +1228,9 @@ static int launch_q4(const pv_model *m, const gemm_args &ga, int strips, hipStre
         if (t < least) { least = t; best = S; }
     }
     const int groups = (strips + best - 1) / best;
-    if (NB == 1 && best == 1 && ga.rows <= 4) k_gemm_q4<NB, 1, EPI, 16><<<groups, 1024, 0, s>>>(ga);
-    else if (NB == 1 && best == 2 && ga.rows <= 4) k_gemm_q4<NB, 2, EPI, 16><<<groups, 1024, 0, s>>>(ga);
+    const bool sixteen = NB == 1 && best <= 2 && ga.rows <= 4 && ga.ktiles >= 64;
+    if (sixteen && best == 1) k_gemm_q4<NB, 1, EPI, 16><<<groups, 1024, 0, s>>>(ga);
+    else if (sixteen) k_gemm_q4<NB, 2, EPI, 16><<<groups, 1024, 0, s>>>(ga);
     else if (best == 1) k_gemm_q4<NB, 1, EPI><<<groups, 512, 0, s>>>(ga);
     else if (best == 2) k_gemm_q4<NB, 2, EPI><<<groups, 512, 0, s>>>(ga);
     else if (best == 3) k_gemm_q4<NB, 3, EPI><<<groups, 512, 0, s>>>(ga);

@@ -98,3 +98,14 @@ def test_one_workgroup_per_cu_where_it_is_the_faster_one(k, strips, expected):
         if name[0] == "k_gemm_tile":
             assert name[1] == (rows + 15) // 16, name
     m.close()
+
+
+# 4-bit weights, up to 4 rows: K, strips -> waves of a workgroup
+@pytest.mark.parametrize("k,strips,waves", [(512, 200, 8), (1920, 256, 8), (2048, 256, 16), (512, 512, 8), (1920, 300, 8), (2048, 512, 16), (2048, 513, 8)])
+def test_sixteen_waves_where_each_has_a_batch(k, strips, waves):
+    m = _model(k, strips, bits=4)
+    for rows in (1, 4):
+        name = _check(m, rows)
+        assert name[0] == "k_gemm_q4" and name[4] == waves, (rows, name)
+    assert _check(m, 5)[4] == 8
+    m.close()

@@ -1211,31 +1211,63 @@ int pv_mat_gemm_init(int wbits)
     return allow_wide<2, 4>();
 }
 
-// Strips a workgroup of k_gemm_q4: a CU takes its workgroups two at a time, one round for each per CU; a strip takes 0.0145 us per K-tile, the operand 0.006
-// (16 rows).  Eight waves, two workgroups a CU where there are that many (sixteen waves and one or two strips: 8 rows, K = 14336 14.5 us against 14.2, but
-// up to 4 rows, whose operand is small, 11.2 against 13.7; but not below K = 2048, where sixteen waves have no batch each: 4 rows, K = 512, 256 strips 7.4 against
-// 6.7, 512 strips 8.2 against 7.3, K = 1024 7.4 and 8.3 against 6.8 and 7.4, K = 2048 7.7 and 8.5 against 7.7 and 8.7).
-template <int NB, int EPI>
-static int launch_q4(const pv_model *m, const gemm_args &ga, int strips, hipStream_t s)
+// Strips a workgroup of k_gemm_q4, in rounds of one workgroup per CU: a round takes as long as its strips and the operand, which costs an eighth of a strip a row (the
+// packed tiles hold the rows and nothing else), two strips as 16-row tiles.  Without that, 13 rows, 1376 strips: three strips and two rounds, K = 4096 / 8192 20.4 / 34.4 us,
+// seven and one 19.0 / 30.5; 8 rows, K = 8192 28.7 and 27.2; 1 row, K = 4096 16.8 and 17.5.  Below K = 2048 an operand of any size is there by the time the codes are
+// (K = 1024, three strips and seven, 8 rows 9.1 and 9.6, 13 rows 10.0 and 10.3).  One or two strips: in one round only.
+struct q4_split { int S, rounds; };
+static q4_split q4_strips(const pv_model *m, int strips, int ktiles, int rows, bool seven)
 {
-    constexpr bool SEVEN = NB == 1 || EPI != EPI_LMHEAD;       // (the vocabulary's epilogue is two registers short)
-    int best = 1;
+    const double operand = ktiles < 64 ? 0.4 : rows <= 8 ? 0.125 * rows : 2.0;
+    q4_split best = {1, 1};
     double least = 1e30;
     for (int S : {7, 4, 3, 2, 1}) {
         const int rounds = ((strips + S - 1) / S + m->n_cus - 1) / m->n_cus;
-        if ((S <= 2 && rounds > 1) || (S == 7 && !SEVEN)) continue;
-        const double t = rounds * (S + 0.4);
-        if (t < least) { least = t; best = S; }
+        if ((S <= 2 && rounds > 1) || (S == 7 && !seven)) continue;
+        const double t = rounds * (S + operand);
+        if (t < least) { least = t; best = {S, rounds}; }
     }
-    const int groups = (strips + best - 1) / best;
-    const bool sixteen = NB == 1 && best <= 2 && ga.rows <= 4 && ga.ktiles >= 64;
-    if (sixteen && best == 1) k_gemm_q4<NB, 1, EPI, 16><<<groups, 1024, 0, s>>>(ga);
-    else if (sixteen) k_gemm_q4<NB, 2, EPI, 16><<<groups, 1024, 0, s>>>(ga);
-    else if (best == 1) k_gemm_q4<NB, 1, EPI><<<groups, 512, 0, s>>>(ga);
-    else if (best == 2) k_gemm_q4<NB, 2, EPI><<<groups, 512, 0, s>>>(ga);
-    else if (best == 3) k_gemm_q4<NB, 3, EPI><<<groups, 512, 0, s>>>(ga);
-    else if (best == 4) k_gemm_q4<NB, 4, EPI><<<groups, 512, 0, s>>>(ga);
-    else if constexpr (SEVEN) k_gemm_q4<NB, 7, EPI><<<groups, 512, 0, s>>>(ga);
+    return best;
+}
+template <int NB, int EPI> static constexpr bool q4_seven() { return NB == 1 || EPI != EPI_LMHEAD; }       // (the vocabulary's epilogue is two registers short)
+
+// 9..16 rows: whether k_gemm_q4 is ahead of k_gemm_tile_q4, whose slices leave no CU idle whatever the strips but cost one more kernel.  13 rows, us, there / here:
+//  - up to two strips a CU: up to K = 12800 (256 strips, K = 4096 10.8 / 7.7, K = 12288 18.3 / 18.8, K = 14336 18.2 / 18.8; 512 strips, K = 12288 27.5 / 24.8, K = 28672 36.8 / 47.2);
+//  - more: what a round of the operand costs grows with K, so fewer rounds the longer it is: one up to K = 16384 (1024 strips 44.2 / 41.2; K = 28672 58.9 / 65.6), two up to
+//    8192 (2048 strips 42.6 / 40.5; K = 12288 55.7 / 57.6), three (2560 strips, K = 4096 32.6 / 30.9, K = 6144 41.4 / 43.6, K = 8192 50.7 / 55.7), four (3584 strips, K = 4096
+//    40.1 / 40.0, K = 5120 46.3 / 48.7, K = 8192 65.0 / 73.0); with seven strips at any K where the shared tiles' CUs get as many eighths (3584 strips, K = 8192 65.3 / 57.8, K = 16384 115.7 / 104.0);
+//  - past fourteen strips a CU only gate/up and QKV would gain, and only in part (K = 4096, 4352 strips 54.5 / 42.8, 7168 strips 59.3 / 56.5, 8016 strips 61.1 / 66.8;
+//    vocabulary 55.1 / 48.9, 59.4 / 70.8, 61.5 / 78.3): not taken.
+static bool q4_unshared(const pv_model *m, int strips, int ktiles, q4_split q)
+{
+    if (strips > 14 * m->n_cus) return false;
+    if (strips <= 2 * m->n_cus) return ktiles <= 400;
+    if (q.rounds * ktiles <= 512) return true;
+    const int groups = (strips + 15) / 16, slices = max(1, min(TILE_MAX_SLICES, 2 * m->n_cus / groups)), there = (groups * slices + m->n_cus - 1) / m->n_cus * 16;      // (strips a CU, times the slices)
+    return q.S == 7 && 8 * q.S * q.rounds * slices <= 7 * there;
+}
+
+// Eight waves, two workgroups a CU where there are that many.  Sixteen waves and one or two strips up to 4 rows, whose operand is small (K = 14336, 256 strips 16.4 -> 13.8; 8
+// rows 16.8 and 16.5), but not below K = 2048, where sixteen waves have no batch each: 4 rows, K = 512, 256 strips 7.4 against
+// 6.7, 512 strips 8.2 against 7.3, K = 1024 7.4 and 8.3 against 6.8 and 7.4, K = 2048 7.7 and 8.5 against 7.7 and 8.7.
+template <int NB, int EPI>
+static int launch_q4(const gemm_args &ga, int strips, q4_split q, hipStream_t s)
+{
+    const int groups = (strips + q.S - 1) / q.S;
+    bool done = false;
+    if constexpr (NB == 1) {
+        if (q.S <= 2 && ga.rows <= 4 && ga.ktiles >= 64) {
+            if (q.S == 1) k_gemm_q4<NB, 1, EPI, 16><<<groups, 1024, 0, s>>>(ga);
+            else k_gemm_q4<NB, 2, EPI, 16><<<groups, 1024, 0, s>>>(ga);
+            done = true;
+        }
+    }
+    if (done) ;
+    else if (q.S == 1) k_gemm_q4<NB, 1, EPI><<<groups, 512, 0, s>>>(ga);
+    else if (q.S == 2) k_gemm_q4<NB, 2, EPI><<<groups, 512, 0, s>>>(ga);
+    else if (q.S == 3) k_gemm_q4<NB, 3, EPI><<<groups, 512, 0, s>>>(ga);
+    else if (q.S == 4) k_gemm_q4<NB, 4, EPI><<<groups, 512, 0, s>>>(ga);
+    else if constexpr (q4_seven<NB, EPI>()) k_gemm_q4<NB, 7, EPI><<<groups, 512, 0, s>>>(ga);
     PV_HIP(hipGetLastError());
     return PV_OK;
 }
@@ -1250,10 +1282,10 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
     // runs of many workgroups, a power of two apart, advance in step
     ga.interleave = g.ktiles > 128 || (NB == 1 && EPI == EPI_LMHEAD && strips >= 2048);
     if (m->wbits == 4) {
-        // 9..16 rows: k_gemm_q4 is ahead of tiles shared through LDS and K-slices up to K = 12800 or so (13 rows, us: 256 strips, K = 4096 7.3 and 11.2, K =
-        // 14336 18.8 and 18.2; 512 strips, K = 8192 14.4 and 18.4, K = 28672 43 and 36; 3584 strips, K = 8192 56 and 65), and up to as many strips as
-        // leave shared tiles a workgroup of sixteen on not all CUs (K = 4096, 2000 strips 21.5 and 25.8, 8016 strips 78 and 61)
-        if constexpr (CT == 1) if (NB == 1 || (strips <= 14 * m->n_cus && (strips > 2 * m->n_cus || g.ktiles <= 400))) return launch_q4<NB, EPI>(m, ga, strips, s);
+        if constexpr (CT == 1) {
+            const q4_split q = q4_strips(m, strips, g.ktiles, NB == 1 ? g.rows : 16, q4_seven<NB, EPI>());
+            if (NB == 1 || q4_unshared(m, strips, g.ktiles, q)) return launch_q4<NB, EPI>(ga, strips, q, s);
+        }
         if constexpr (NB == 1) {
             return PV_EINVAL;                                  // (not reached)
         } else if constexpr (CT == 3) {

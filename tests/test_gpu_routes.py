@@ -109,3 +109,24 @@ def test_sixteen_waves_where_each_has_a_batch(k, strips, waves):
         assert name[0] == "k_gemm_q4" and name[4] == waves, (rows, name)
     assert _check(m, 5)[4] == 8
     m.close()
+
+
+# 4-bit weights, 9..16 rows: K, strips -> strips a workgroup of k_gemm_q4, 0 where the tiles are shared
+@pytest.mark.parametrize("k,strips,each", [(12800, 64, 1), (12928, 64, 0), (512, 1376, 3), (8192, 1100, 3), (8320, 1100, 0), (5376, 2304, 3), (5504, 2304, 0),
+                                           (4096, 3300, 4), (4224, 3300, 0), (2048, 3584, 4), (512, 3584, 3), (512, 3585, 0)])
+def test_unshared_tiles_of_4bit_blocks_of_9_to_16_rows(k, strips, each):
+    m = _model(k, strips, bits=4)
+    for rows in (9, 16):
+        name = _check(m, rows)
+        assert name[:3] == (("k_gemm_q4", 2, each) if each else ("k_gemm_tile_q4", 1, LMHEAD)), (rows, name)
+    m.close()
+
+
+# 4-bit weights, up to 8 rows: K, strips -> {rows: strips a workgroup}
+@pytest.mark.parametrize("k,strips,each", [(2048, 1376, {1: 3, 7: 3, 8: 7}), (1920, 1376, {8: 3}), (2048, 1024, {1: 4, 8: 4}), (2048, 1025, {1: 3, 8: 7}), (512, 2000, {2: 4, 8: 4}),
+                                           (2048, 3600, {1: 3, 8: 4}), (512, 8016, {1: 4, 8: 4})])
+def test_strips_of_a_workgroup_by_the_rows(k, strips, each):
+    m = _model(k, strips, bits=4)
+    for rows, s in each.items():
+        assert _check(m, rows)[2] == s, rows
+    m.close()

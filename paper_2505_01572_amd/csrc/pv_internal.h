@@ -182,6 +182,16 @@ static inline bool pv_is_q4_kind(int kind)
     return kind == PV_T_WQ || kind == PV_T_WK || kind == PV_T_WV || kind == PV_T_WO || kind == PV_T_WG || kind == PV_T_WU ||
            kind == PV_T_WD || kind == PV_T_LM_HEAD;
 }
+// Kernels that read through buffer descriptors have 32-bit offsets, and one past every buffer for loads that are not to happen.  Up to 2^19 K-tiles (2^24 features) the largest
+// buffer has 1008 MiB (seven strips of 4-bit weights; 1 GiB with the operand's hi and lo arrays) and no offset comes to 2^32.  A wider model runs all its blocks of up to 16
+// rows as 16-row tiles, its wide projections in the kernels that read through 64-bit addresses.
+#define PV_OFFSET_KTILES (1 << 19)
+static inline bool pv_offsets_fit(int ktiles) { return ktiles <= PV_OFFSET_KTILES; }
+// whether a block's rows are packed, hi and lo halves into one operand tile
+static inline bool pv_packs_rows(const pv_model *m, int rows)
+{
+    return rows <= 8 && pv_offsets_fit(m->cfg.d_model / 32) && pv_offsets_fit(m->cfg.n_q_heads * m->cfg.head_dim / 32) && pv_offsets_fit(m->cfg.ffn_dim / 32);
+}
 size_t pv_mat_part_floats(const pv_model *m, int rows_cap, int units_cap, int max_tokens);
 size_t pv_attn_part_floats(const pv_model *m, int units_cap, int max_tokens);
 int pv_attn_units(const pv_model *m, int rows);              // attention row-group units of one sequence with `rows` rows

@@ -118,7 +118,7 @@ int pv_mat_attention(pv_cache *c, int layer, int rows, float *part, uint16_t *xo
     a.part_o = part;
     a.part_ml = part + (size_t)f.n_kv_heads * c->units_cap * a.max_chunks * 32 * f.head_dim;
     a.xop_o = xop_o; a.n_pages = c->n_pages; a.rows = rows; a.batched = c->blk_units != 0;
-    const bool nb1 = rows <= 8;
+    const bool nb1 = pv_packs_rows(c->m, rows);
     switch (f.head_dim) {
     case 32: return nb1 ? launch<1, 32>(c, a, rows, merge, s) : launch<2, 32>(c, a, rows, merge, s);
     case 64: return nb1 ? launch<1, 64>(c, a, rows, merge, s) : launch<2, 64>(c, a, rows, merge, s);

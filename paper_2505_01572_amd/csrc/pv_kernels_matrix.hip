@@ -254,7 +254,7 @@ __device__ inline void k_walk(int cnt, Q &q0, Q &q1, Q &q2, FI issue, FC consume
 
 // Loads through buffer descriptors: the lane's offset in a register, the wave's in a scalar, zeros (and no traffic) past the end.
 __device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00020000); }
-#define BUFFER_END 0xC0000000u                     // past the end of every buffer (wide_fits), and no sum with an offset inside one wraps
+#define BUFFER_END 0xC0000000u                     // past the end of every buffer, and no sum with an offset inside one wraps: k_gemm_wide up to wide_fits, k_gemm_q4 up to pv_offsets_fit
 template <int AUX> __device__ inline uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t base)
 {
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, base, AUX));
@@ -1240,7 +1240,7 @@ template <int NB, int EPI> static constexpr bool q4_seven() { return NB == 1 || 
 //    vocabulary 55.1 / 48.9, 59.4 / 70.8, 61.5 / 78.3): not taken.
 static bool q4_unshared(const pv_model *m, int strips, int ktiles, q4_split q)
 {
-    if (strips > 14 * m->n_cus) return false;
+    if (strips > 14 * m->n_cus || !pv_offsets_fit(ktiles)) return false;
     if (strips <= 2 * m->n_cus) return ktiles <= 400;
     if (q.rounds * ktiles <= 512) return true;
     const int groups = (strips + 15) / 16, slices = max(1, min(TILE_MAX_SLICES, 2 * m->n_cus / groups)), there = (groups * slices + m->n_cus - 1) / m->n_cus * 16;      // (strips a CU, times the slices)
@@ -1275,7 +1275,6 @@ static int launch_q4(const gemm_args &ga, int strips, q4_split q, hipStream_t s)
 template <int NB, int CT, int EPI>
 static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStream_t s)
 {
-    if (g.ktiles > (1 << 20)) { pv_set_error("a projection over more than 2^25 features: past the 32-bit offsets of its buffers"); return PV_ERANGE; }
     gemm_args ga = g;
     ga.nstrips = strips;
     // long strips: measured 0.3 % faster per step, short ones 0.3 % slower; a whole vocabulary (8016 strips, K = 4096) 176 -> 172 us: there the contiguous
@@ -1338,7 +1337,7 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         }
         if constexpr (CT == 1) {
             // one column tile: batches walked several deep, like the packed rows (measured 2 - 3 % per step)
-            if (g.ktiles >= 64) {
+            if (g.ktiles >= 64 && pv_offsets_fit(g.ktiles)) {
                 bool done = false;
                 if constexpr (EPI == EPI_QKV) {       // (k + 1/2) x 256 strips: half strips as for the packed rows
                     if (strips % 256 == 128 && strips / 256 >= 1 && strips / 256 <= 2) {
@@ -1355,7 +1354,7 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
                 return PV_OK;
             }
         }
-        if constexpr (CT != 3) {
+        if constexpr (CT != 3) {           // a short K, or (one column tile) one past the buffers' offsets
             if (strips >= 256 * S) k_gemm<NB, CT, S, EPI, NW><<<(strips + S - 1) / S, NW * 64, 0, s>>>(ga);
             else if (CT == 1 && g.ktiles >= 64) k_gemm<NB, CT, 1, EPI, 16><<<strips, 1024, 0, s>>>(ga);
             else k_gemm<NB, CT, 1, EPI, 8><<<strips, 512, 0, s>>>(ga);
@@ -1519,7 +1518,7 @@ int pv_mat_run_block(pv_cache *c, hipStream_t s)
 {
     const int rows = c->last_rows;
     if (rows > 64) { pv_set_error("matrix path handles at most 64 rows per block"); return PV_ERANGE; }
-    if (rows <= 8) return run_block<1, 1>(c, s);
+    if (pv_packs_rows(c->m, rows)) return run_block<1, 1>(c, s);
     if (rows <= 16) return run_block<2, 1>(c, s);
     if (rows <= 32) return run_block<2, 2>(c, s);
     if (rows <= 48 && c->m->wbits == 16) return run_block<2, 3>(c, s);

@@ -557,7 +557,8 @@ k_gemm(const gemm_args a)
 // ------------------------------------------------------------------------------------------
 
 constexpr int wide_waves(int ct, int s) { return ct <= 2 || s <= 4 ? 8 : 4; }              // (what the registers of one workgroup per CU hold)
-constexpr int wide_lds(int ct, int s) { return wide_waves(ct, s) * s * ct * 1024; }
+constexpr int wide_lds(int ct, int s) { return wide_waves(ct, s) * s * ct * 1024; }       // dynamic: the waves' sums
+constexpr int wide_ssq_lds(int ct, int s) { return wide_waves(ct, s) * ct * 64; }         // static: the waves' shares of the rows' sums of squares
 static inline bool wide_fits(int ktiles) { return ktiles <= (1 << 16); }                   // the largest buffer: 8 arrays of K-tiles of 1 KiB = 0.5 GiB
 
 template <int NB, int CT, int S, int EPI>
@@ -573,6 +574,7 @@ k_gemm_wide(const gemm_args a)
     const int strip0 = blockIdx.x * S;
     extern __shared__ f32x4 wide_red[];                         // [NW][S * CT][64]
     __shared__ float ssq_s[NW][CT][16];
+    static_assert(sizeof(ssq_s) == wide_ssq_lds(CT, S), "the launches count it");
 
     ssq_loads<CT == 4 ? 4 : 32 / NW> sl[CT];
     if (NORM) {
@@ -1168,7 +1170,7 @@ static int wide_strips(const pv_model *m, int strips, int ktiles, int ct)
 template <int NB, int CT, int S, int EPI>
 static int allow_wide_lds()
 {
-    if (wide_lds(CT, S) > 65536) PV_HIP(hipFuncSetAttribute((const void *)k_gemm_wide<NB, CT, S, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, wide_lds(CT, S)));
+    if (wide_lds(CT, S) + wide_ssq_lds(CT, S) > 65536) PV_HIP(hipFuncSetAttribute((const void *)k_gemm_wide<NB, CT, S, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, wide_lds(CT, S)));
     return PV_OK;
 }
 template <int NB, int CT, int EPI>

@@ -1177,21 +1177,24 @@ template <int NB, int CT, int EPI>
 static int allow_wide_all()
 {
     int rc;
-    if ((rc = allow_wide_lds<NB, CT, 3, EPI>()) != PV_OK || (rc = allow_wide_lds<NB, CT, 4, EPI>()) != PV_OK || (rc = allow_wide_lds<NB, CT, 6, EPI>()) != PV_OK) return rc;
+    if constexpr (NB == 2) if ((rc = allow_wide_lds<NB, CT, 3, EPI>()) != PV_OK) return rc;
+    if ((rc = allow_wide_lds<NB, CT, 4, EPI>()) != PV_OK || (rc = allow_wide_lds<NB, CT, 6, EPI>()) != PV_OK) return rc;
     return allow_wide_lds<NB, CT, 7, EPI>();
 }
 
+template <int NB, int CT, int EPI, int S>
+static int launch_wide_s(const gemm_args &ga, int strips, hipStream_t s)
+{
+    k_gemm_wide<NB, CT, S, EPI><<<(strips + S - 1) / S, wide_waves(CT, S) * 64, wide_lds(CT, S), s>>>(ga);
+    PV_HIP(hipGetLastError());
+    return PV_OK;
+}
 template <int NB, int CT, int EPI>
 static int launch_wide(const gemm_args &ga, int strips, int ws, hipStream_t s)
 {
-    const int groups = (strips + ws - 1) / ws;
-    constexpr int threads4 = wide_waves(CT, 4) * 64, threads7 = wide_waves(CT, 7) * 64;
-    if (ws == 3) k_gemm_wide<NB, CT, 3, EPI><<<groups, threads4, wide_lds(CT, 3), s>>>(ga);
-    else if (ws == 4) k_gemm_wide<NB, CT, 4, EPI><<<groups, threads4, wide_lds(CT, 4), s>>>(ga);
-    else if (ws == 6) k_gemm_wide<NB, CT, 6, EPI><<<groups, threads7, wide_lds(CT, 6), s>>>(ga);
-    else k_gemm_wide<NB, CT, 7, EPI><<<groups, threads7, wide_lds(CT, 7), s>>>(ga);
-    PV_HIP(hipGetLastError());
-    return PV_OK;
+    if constexpr (NB == 2) if (ws == 3) return launch_wide_s<NB, CT, EPI, 3>(ga, strips, s);      // (packed rows have four to seven strips a CU: never three)
+    if (ws <= 4) return launch_wide_s<NB, CT, EPI, 4>(ga, strips, s);
+    return ws == 6 ? launch_wide_s<NB, CT, EPI, 6>(ga, strips, s) : launch_wide_s<NB, CT, EPI, 7>(ga, strips, s);
 }
 
 // once per device before the first launch (and outside any stream capture): kernels that use more dynamic LDS than the default limit
@@ -1358,7 +1361,6 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         }
         if constexpr (CT != 3) {           // a short K, or (one column tile) one past the buffers' offsets
             if (strips >= 256 * S) k_gemm<NB, CT, S, EPI, NW><<<(strips + S - 1) / S, NW * 64, 0, s>>>(ga);
-            else if (CT == 1 && g.ktiles >= 64) k_gemm<NB, CT, 1, EPI, 16><<<strips, 1024, 0, s>>>(ga);
             else k_gemm<NB, CT, 1, EPI, 8><<<strips, 512, 0, s>>>(ga);
         }
     } else {
@@ -1438,11 +1440,12 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
 // the chunks of all heads, rows x K x chunks x 4 bytes, which pays while its threads have them in flight all at once: attention's
 // merge and output projection, us: 1B shape, one row, 5 chunks 8.7 -> 6.5, two rows, 4 chunks 9.3 -> 7.4; 8B shape, one row, 4 chunks 11.9 -> 10.1; but in two rounds
 // (8 chunks; two rows, 3 chunks) 12.0 -> 11.7 and 11.9 -> 12.1.  Up to two chunks the attention needs no merge.
+// (Packed rows: the caller sees to it.)
 static bool merges_in_oproj(const pv_cache *c, int rows, const pv_attn_split_info &sp)
 {
     const pv_model_config &f = c->m->cfg;
     const int qd = f.n_q_heads * f.head_dim;
-    if (c->blk_units != 0 || rows > 8 || c->m->wbits != 16 || sp.chunks < 3 || sp.chunks > 8) return false;
+    if (c->blk_units != 0 || c->m->wbits != 16 || sp.chunks < 3 || sp.chunks > 8) return false;
     return qd >= 64 * 32 && f.d_model / 16 < 512 && rows * qd <= 4 * 512 * merge_items(sp.chunks <= 4 ? 4 : 8);      // (and the operand is at most 16 KiB)
 }
 

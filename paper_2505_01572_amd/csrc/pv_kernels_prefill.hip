@@ -117,7 +117,7 @@ __device__ inline void pre_swiglu2(const gemm_args &a, const pre_gemm_args &p, i
         const float gate = odd ? other : mine, up = odd ? mine : other;
         act[r] = gate / (1.0f + expf(-gate)) * up;
     }
-    if (j < p.rows) store_operand4<2>(a.xop_act, a.F, j, (strip + odd) * 8 + 4 * (g >> 1), act, 8);
+    if (j < p.rows) store_operand4<2>(a.xop_act, a.F, j, (strip + odd) * 8 + 4 * (g >> 1), act);
 }
 
 // factor of this lane's row: its RMSNorm scale, and what takes the scaling of a 16-bit float operand back

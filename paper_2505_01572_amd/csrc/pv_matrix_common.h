@@ -51,7 +51,7 @@ __device__ inline void split2(float a, float b, uint32_t &hi, uint32_t &lo)
 
 // four consecutive k (k0 % 4 == 0) of row j; R: rows of the block (packed rows)
 template <int NB>
-__device__ inline void store_operand4(uint16_t *xop, int K, int j, int k0, const float y[4], int R)
+__device__ inline void store_operand4(uint16_t *xop, int K, int j, int k0, const float y[4], int R = 0)
 {
     const int tile_elems = NB == 1 ? 64 * R : 512, cols = NB == 1 ? 2 * R : 16;
     const size_t tile = (size_t)(k0 >> 5) * tile_elems, in = (size_t)(((k0 & 31) >> 3) * cols) * 8 + (k0 & 7);

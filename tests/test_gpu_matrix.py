@@ -138,6 +138,37 @@ def test_merged_chunks_match_oracle(pvlib, shape, graphs, prefix):
         gc.rollback(T); rc.rollback(T)
 
 
+# The same with chunks of 128 keys: more than 16 query rows per kv head, in one group of 32 (16 heads and two rows, 32 heads and one) or two (32 heads and two)
+MERGE_128 = [pv_inputs.ModelShape("merge_g", 1, 1024, 32, 2, 64, 352, 512, dtype="bf16", seed=5904),
+             pv_inputs.ModelShape("merge_u", 1, 1024, 32, 1, 64, 352, 512, dtype="bf16", seed=5905)]
+
+
+@pytest.mark.parametrize("shape", MERGE_128, ids=lambda v: v.name)
+@pytest.mark.parametrize("graphs", [True, False])
+@pytest.mark.parametrize("prefix", [256, 383, 509, 700, 1021])
+def test_merged_chunks_of_128_keys_match_oracle(pvlib, shape, graphs, prefix):
+    """256 .. 510 keys are three or four chunks, merged by the output projection for one row and for two; up to 1023 five to eight, for one."""
+    test_merged_chunks_match_oracle(pvlib, shape, graphs, prefix)
+
+
+def test_chunks_of_128_keys_are_merged_by_the_output_projection(pvlib):
+    """Which kernel that test is about: the last template argument is the most chunks it merges."""
+    import re
+    import torch
+    from gpu_helpers import gpu_model
+    for shape, merges in zip(MERGE_128, ({(2, 300): 4, (2, 600): 0, (1, 300): 0, (1, 600): 4}, {(1, 300): 4, (2, 300): 4, (1, 600): 8, (2, 600): 0})):
+        gc = pvlib.Cache(gpu_model(shape, max_gamma=16), 1100)
+        gc.use_graphs(False)
+        gc.prefill(pv_inputs.uniform_tokens(83, 1000, shape.vocab))
+        for (rows, prefix), most in sorted(merges.items(), key=lambda v: -v[0][1]):
+            gc.rollback(prefix)
+            with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU, torch.profiler.ProfilerActivity.CUDA]) as p:
+                gc.verify(prefix, pv_inputs.uniform_tokens(84, rows, shape.vocab))
+            found = [re.match(r"(?:void )?k_gemm<([^>]*)>", e.name) for e in p.events()]
+            got = [int(f[1].split(",")[7]) for f in found if f and f[1].split(",")[3].strip() == "1"]
+            assert sorted(got) == sorted([0, most]), (shape.name, rows, prefix, got)
+
+
 def test_wide_blocks_match_oracle(pvlib, wide_shape):
     """Blocks of 17..64 rows (two and four 16-row column tiles per weight pass; with 4-bit weights one
     weight pass per column tile), next to narrow ones on the same cache; the prompt is prefilled in
@@ -158,6 +189,16 @@ WIDE = [pv_inputs.ModelShape("wide_3", 1, 544, 60, 60, 64, 5664, 705 * 16, dtype
 def test_one_workgroup_per_cu_matches_oracle(pvlib, shape):
     """Every number of column tiles at its first and last row count (33..48 rows: three); up to 8 rows from 1024 strips and 128 K-tiles on."""
     _check_against_oracle(pvlib, shape, 0, 64, 20, (17, 32, 33, 48, 49, 64, 9, 16, 8, 1, 5), 320)
+
+
+# Packed rows, one workgroup per CU with four strips (1024: where that begins) and six (1376, ragged)
+WIDE_PACKED = [pv_inputs.ModelShape("wide_p4", 1, 4128, 8, 2, 32, 352, 1024 * 16, dtype="bf16", seed=5806),
+               pv_inputs.ModelShape("wide_p6", 1, 4128, 8, 2, 32, 352, 1376 * 16, dtype="bf16", seed=5807)]
+
+
+@pytest.mark.parametrize("shape", WIDE_PACKED, ids=lambda v: v.name)
+def test_packed_rows_with_one_workgroup_per_cu_match_oracle(pvlib, shape):
+    _check_against_oracle(pvlib, shape, 0, 16, 20, (8, 1, 2, 3, 4, 5, 6, 7), 320)
 
 
 LONG_A = pv_inputs.ModelShape("long_a", 1, 128, 8, 2, 32, 352, 512, rope_base=500000.0, dtype="bf16", seed=5757)

@@ -100,6 +100,16 @@ def test_one_workgroup_per_cu_where_it_is_the_faster_one(k, strips, expected):
     m.close()
 
 
+# up to 8 rows: K, strips -> strips a workgroup of k_gemm_wide, 0 where k_gemm has them
+@pytest.mark.parametrize("k,strips,each", [(4096, 1023, 0), (4096, 1024, 4), (3968, 1024, 0), (4096, 1376, 6), (4096, 1537, 7), (4096, 1792, 7), (4096, 1793, 0)])
+def test_packed_rows_with_one_workgroup_per_cu(k, strips, each):
+    m = _model(k, strips)
+    for rows in (1, 8):
+        name = _check(m, rows, logits=False)                   # (the same rows in blocks of eight would be the same kernel: the oracle tests have these)
+        assert name[:4] == ("k_gemm_wide", 1, 1, each) if each else name[0] == "k_gemm", (rows, name)
+    m.close()
+
+
 # 4-bit weights, up to 4 rows: K, strips -> waves of a workgroup
 @pytest.mark.parametrize("k,strips,waves", [(512, 200, 8), (1920, 256, 8), (2048, 256, 16), (512, 512, 8), (1920, 300, 8), (2048, 512, 16), (2048, 513, 8)])
 def test_sixteen_waves_where_each_has_a_batch(k, strips, waves):

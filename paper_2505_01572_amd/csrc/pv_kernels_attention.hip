@@ -34,7 +34,6 @@ size_t pv_attn_part_floats(const pv_model *m, int units_cap, int max_tokens)
     return (size_t)f.n_kv_heads * units_cap * chunks * 32 * (f.head_dim + 2);
 }
 
-// rows: rows of the block; a batched step also gives its unit count and the most rows any one sequence has
 // Keys the launch has to cover (the host's bound, not the whole cache), cut into chunks of 256 (up to 16 query rows per kv head) or 128
 pv_attn_split_info pv_attn_split(const pv_cache *c, int rows, const float *part)
 {
@@ -49,6 +48,7 @@ pv_attn_split_info pv_attn_split(const pv_cache *c, int rows, const float *part)
     return i;
 }
 
+// rows: rows of the block; a batched step also gives its unit count and the most rows any one sequence has
 template <int NB, int HD>
 static int launch(pv_cache *c, attn_args &a, int rows, bool merge, hipStream_t s)
 {

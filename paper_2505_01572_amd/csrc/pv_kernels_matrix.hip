@@ -7,16 +7,15 @@
 // owns one or a few strips, its wavefronts split K, accumulate in fp32, and are summed in wave
 // order through LDS, so the owner sees complete outputs and the whole epilogue (RMSNorm scale,
 // rotary embedding + KV append, SwiGLU, residual add, vocabulary arg-max) is fused into the
-// GEMM.  9..64 rows and many strips (k_gemm_wide): the same with one workgroup per CU; 4-bit weights and up
-// to 16 rows: k_gemm_q4.  17..64 rows and few strips (k_gemm_tile; with 4-bit weights k_gemm_tile_q4): the waves
+// GEMM.  Many strips, where whole rounds of CUs come out of them (k_gemm_wide): the same with one workgroup per CU;
+// 4-bit weights and up to 16 rows: k_gemm_q4.  Else, from 17 rows on (k_gemm_tile; with 4-bit weights k_gemm_tile_q4): the waves
 // of a workgroup own different strips, walk K together and share the activation tiles through LDS.
 //
 // Activations enter as the B operand.  To keep fp32-grade accuracy with bf16 matrix cores an
 // activation a is carried as two bf16 numbers hi = bf16(a), lo = bf16(a - hi) (16 mantissa
-// bits).  For rows <= 8 the 16 operand columns hold hi of row j in column j and lo in column
-// j+8 (rows <= 4: j+4, and the loads mirror columns 4..7 into 8..11: half the bytes), so one
-// MFMA does both and the epilogue adds the two column halves; for 9..16 rows hi
-// and lo are separate operands and two MFMAs accumulate into the same registers.
+// bits).  A block of R <= 8 rows is packed: a tile of 2 R columns holds hi of row j in column j and lo in column
+// R + j (store_operand4; packed_lane puts them where one MFMA does both and the epilogue adds the two halves);
+// for more rows hi and lo are separate operands and two MFMAs accumulate into the same registers.
 //
 // RMSNorm is folded in: the producer of x writes (gain * x) as the next operand plus per-strip
 // partial sums of x^2; the consumer multiplies its outputs by rsqrt(mean + eps), which
@@ -544,7 +543,7 @@ k_gemm(const gemm_args a)
 
 // ------------------------------------------------------------------------------------------
 // Projections with three or more strips a CU (gate/up, the vocabulary, the QKV projection without shared heads), 9..64 rows (NB = 2: CT column
-// tiles of 16 rows, a hi and a lo operand each), and up to 8 (NB = 1) from four strips a CU on: one workgroup per CU owns S strips and its NW waves split K, so
+// tiles of 16 rows, a hi and a lo operand each; which of them: wide_strips), and up to 8 (NB = 1) with four to seven strips a CU: one workgroup per CU owns S strips and its NW waves split K, so
 // that each activation tile enters the CU once, for S strips, and straight into the registers of the one wave
 // that uses it: no LDS and no barrier before the final sum over the waves.
 // A CU has some 32 KiB of loads in flight (its L1's size: 56 GB/s of HBM latency, 130 GB/s of L2 latency, whatever the waves ask for), so what counts is
@@ -669,12 +668,15 @@ k_gemm_wide(const gemm_args a)
 // the activation tile with an all -24 operand (= -24 x row sums, shared by the S strips), so that the codes' product on top of it is
 // sum_k (c_k - 8) * x_k; the vector ALU only multiplies that by the tile's scale and adds.  The product is taken transposed (activation rows x
 // features) so that a lane's four results share one feature, hence one scale; the accumulators are turned back on their way through LDS.
-// Bound by the code stream (5.1 TB/s beyond the 4.5 us that a kernel takes in any case) and by the vector ALU beside it, 13 instructions per weight tile: so sixteen
-// waves a CU (two workgroups of 8 where there are enough) with one batch each in registers and no loads ahead, the other waves' work covering a wave's latency.  That takes at
-// most 128 registers, which seven strips fit only if the multiply-adds stay behind their products (left alone, the compiler moves all of them to the end of the batch
+// Sixteen waves a CU (two workgroups of 8 where there are enough), each with one batch in registers and no loads ahead, the other waves' work covering a wave's latency.  That
+// takes at most 128 registers, which seven strips fit only if the multiply-adds stay behind their products (left alone, the compiler moves all of them to the end of the batch
 // and holds every product: 100 - 120 registers more, spilled; two batches deep at 200 registers and two waves per SIMD the 8B-shaped gate/up took 21.7 us instead of 18.9).
+// Many strips: no unit is at its limit.  The 70B-shaped gate/up with 8 rows (264 MB, 51.5 us, 4.5 of which a kernel takes in any case) streams 5.6 of 7 TB/s, a CU takes in 33 GB/s of
+// the 45 - 56 it can have outstanding, and the vector ALU's 13 instructions per weight tile are 19 us of issue: a wave's loads drain once a batch, and four waves a SIMD in
+// like phases do not hide all of that.  One or two strips (the 70B-shaped down projection, 33.8 us): the L2 -> CU path, 917 KB of operand beside 516 KB of codes per CU at 50 GB/s.
 // 8B shape, 13 rows, us, with the sum of the K-slices that k_gemm_tile_q4 needs: QKV 15.0 -> 9.1, O 11.2 -> 7.2, gate/up 24.6 -> 18.9; 70B shape 23.1 -> 17.5, 18.4 -> 14.4, 65.5 -> 56.4;
-// 8 rows (before: two or three batches deep, at most three and a half strips a workgroup, 126 registers): 8B gate/up 19.0 -> 16.4, 70B 56.2 -> 51.2.
+// 8 rows (before: two or three batches deep, at most three and a half strips a workgroup, 126 registers): 8B gate/up 19.0 -> 16.4, 70B 56.2 -> 51.2.  With one strip a workgroup and
+// a long K that earlier form was ahead (8 rows, 256 strips, K = 14336 15.8 and 16.8, K = 28672 25.6 and 27.4); gate/up, twice the weights, gained more than that in every shape measured.
 // ------------------------------------------------------------------------------------------
 template <int NB, int S, int EPI, int NW = 8>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))

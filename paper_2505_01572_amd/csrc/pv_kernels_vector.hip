@@ -220,7 +220,8 @@ __device__ inline float4 ld4(const uint16_t *p, size_t i)
 // Causal attention for one (query head, row): keys 0 .. len+j, 128 at a time, streaming softmax.  K/V come from the paged pool.  Bound by latency: so the pages of 1024 keys
 // are looked up at once, a pass has all its keys and values in flight together (four lanes share a key, 16 bytes a load; along a
 // value row 4 tokens a load, split over 256 / HD groups), and it takes one barrier: behind the scores, whose maximum, weights and sum every wave works out for itself.
-// 104 keys, four heads of 64: 9.0 -> 5.2 us.
+// 104 keys, four heads of 64: 9.0 -> 5.2 us.  Passes of 1024 keys (k_attention_any) are behind at every length: a step of two layers with 4 rows and 8 heads of 32 / 64 / 128, us,
+// 30 keys 79 / 81 / 85 -> 76 / 77 / 83, 1000 keys 124 / 164 / 266 -> 99 / 113 / 144, 8200 keys 554 / 937 / 1673 -> 303 / 416 / 614.
 template <typename ST, int HD>
 __global__ void __launch_bounds__(256)
 k_attention(const pv_dev_state *st, const int32_t *page_table, const float *q, const ST *pool, float *out,

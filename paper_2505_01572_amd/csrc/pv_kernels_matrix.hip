@@ -543,7 +543,7 @@ k_gemm(const gemm_args a)
 
 // ------------------------------------------------------------------------------------------
 // Projections with three or more strips a CU (gate/up, the vocabulary, the QKV projection without shared heads), 9..64 rows (NB = 2: CT column
-// tiles of 16 rows, a hi and a lo operand each; which of them: wide_strips), and up to 8 (NB = 1) with four to seven strips a CU: one workgroup per CU owns S strips and its NW waves split K, so
+// tiles of 16 rows, a hi and a lo operand each; which of them: wide_strips), and up to 8 (NB = 1) with more than four and up to seven strips a CU (packed_wide): one workgroup per CU owns S strips and its NW waves split K, so
 // that each activation tile enters the CU once, for S strips, and straight into the registers of the one wave
 // that uses it: no LDS and no barrier before the final sum over the waves.
 // A CU has some 32 KiB of loads in flight (its L1's size: 56 GB/s of HBM latency, 130 GB/s of L2 latency, whatever the waves ask for), so what counts is
@@ -1169,6 +1169,27 @@ static int wide_strips(const pv_model *m, int strips, int ktiles, int ct)
     return 0;
 }
 
+// How evenly workgroups, one per CU a round, fill their rounds
+static double even(const pv_model *m, int wgs) { const int rounds = (wgs + m->n_cus - 1) / m->n_cus; return (double)wgs / ((double)rounds * m->n_cus); }
+
+// Packed rows in k_gemm_wide: more than four and up to seven strips a CU, in one round of six or seven each, so that the operand enters a CU once.  us, K = 4096 / 5120 / 8192, one
+// strip a workgroup there against here: 1088 strips, one row 25.6 / 31.5 / 48.2 against 24.9 / 29.1 / 45.7, 8 rows 28.6 / 36.0 / 55.6 against 25.5 / 29.8 / 47.0; 1600 strips, 8 rows
+// 39.4 / 49.7 / 77.5 against 33.6 / 40.8 / 63.0.  Elsewhere, since whole rounds of smaller workgroups leave nothing to gain by it and these overlap their starts and ends:
+//  - up to four strips a CU (1024 strips in four each 24.3 / 27.7 / 44.2, in two each 22.8 / 27.1 / 43.5);
+//  - one strip a workgroup in even rounds, up to 4 rows and K = 4608 (K = 4096, 1280 strips 27.4 / 28.5, K = 4608 29.5 / 30.2, but K = 5120 33.0 / 33.1; 1792 strips 36.7 / 37.6);
+//  - two in even rounds, up to 4 rows and K = 7168 (K = 5120, 1536 strips 38.5 / 39.9, K = 7168 53.3 / 54.1, but K = 8192, 1440 strips 59.3 / 58.0), with more rows at K = 4096
+//    (8 rows, 1536 strips 32.8 / 33.6, but K = 5120, 1440 strips 38.1 / 36.8);
+//  - half strips in even rounds, from there up to K = 7168 (1792 strips of gate/up, one row and 8: K = 4096 38.8 / 37.6 and 38.4 / 37.5, K = 4608 40.7 / 42.8 and 40.5 / 41.8, K = 5120
+//    45.2 / 46.0 and 45.2 / 45.5, K = 7168 61.6 / 63.0 and 61.6 / 62.2, K = 8192 71.1 / 70.5 and 71.0 / 69.8).
+static bool one_strip_even(const pv_model *m, int strips, int ktiles, int rows) { return rows <= 4 && ktiles <= 144 && strips <= 7 * m->n_cus && even(m, strips) >= 15. / 16; }
+static bool half_strips_even(int strips) { return (2 * strips) % 7 == 0 && (2 * strips / 7) % 256 == 0; }
+static bool packed_wide(const pv_model *m, int strips, int ktiles, int rows, bool gate_up)
+{
+    if (strips <= 4 * m->n_cus || strips > 7 * m->n_cus || one_strip_even(m, strips, ktiles, rows)) return false;
+    if (ktiles <= 224 && (rows <= 4 || ktiles <= 128) && even(m, (strips + 1) / 2) >= 15. / 16) return false;
+    return !(gate_up && half_strips_even(strips) && ktiles > 128 && ktiles <= 224);
+}
+
 template <int NB, int CT, int S, int EPI>
 static int allow_wide_lds()
 {
@@ -1179,8 +1200,8 @@ template <int NB, int CT, int EPI>
 static int allow_wide_all()
 {
     int rc;
-    if constexpr (NB == 2) if ((rc = allow_wide_lds<NB, CT, 3, EPI>()) != PV_OK) return rc;
-    if ((rc = allow_wide_lds<NB, CT, 4, EPI>()) != PV_OK || (rc = allow_wide_lds<NB, CT, 6, EPI>()) != PV_OK) return rc;
+    if constexpr (NB == 2) if ((rc = allow_wide_lds<NB, CT, 3, EPI>()) != PV_OK || (rc = allow_wide_lds<NB, CT, 4, EPI>()) != PV_OK) return rc;
+    if ((rc = allow_wide_lds<NB, CT, 6, EPI>()) != PV_OK) return rc;
     return allow_wide_lds<NB, CT, 7, EPI>();
 }
 
@@ -1194,8 +1215,7 @@ static int launch_wide_s(const gemm_args &ga, int strips, hipStream_t s)
 template <int NB, int CT, int EPI>
 static int launch_wide(const gemm_args &ga, int strips, int ws, hipStream_t s)
 {
-    if constexpr (NB == 2) if (ws == 3) return launch_wide_s<NB, CT, EPI, 3>(ga, strips, s);      // (packed rows have four to seven strips a CU: never three)
-    if (ws <= 4) return launch_wide_s<NB, CT, EPI, 4>(ga, strips, s);
+    if constexpr (NB == 2) if (ws <= 4) return ws == 3 ? launch_wide_s<NB, CT, EPI, 3>(ga, strips, s) : launch_wide_s<NB, CT, EPI, 4>(ga, strips, s);      // (packed rows: packed_wide)
     return ws == 6 ? launch_wide_s<NB, CT, EPI, 6>(ga, strips, s) : launch_wide_s<NB, CT, EPI, 7>(ga, strips, s);
 }
 
@@ -1385,16 +1405,14 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
             }
         }
         if constexpr (EPI != EPI_RESID) {
-            // four to seven strips a CU: one workgroup each, which takes in the operand once (8 rows, K = 4096, us: 1792 strips 38.6 -> 37.8, 1024
-            // strips 25.6 -> 24.6; 5 rows, 1376 strips 31.9 -> 30.2).  Three strips a CU: the same as below (768 strips: 18.2); more rounds
-            // than one: no better, or worse, than workgroups that start as others end (K = 8192, 3584 strips 137.5 both; K = 4096, 8016 strips 175 -> 179)
-            if (strips >= 4 * m->n_cus && strips <= 7 * m->n_cus)
+            // (more rounds than one: no better, or worse, than workgroups that start as others end: K = 8192, 3584 strips 137.5 both; K = 4096, 8016 strips 175 / 179)
+            if (packed_wide(m, strips, g.ktiles, g.rows, EPI == EPI_SWIGLU))
                 if (const int ws = wide_strips(m, strips, g.ktiles, 1)) return launch_wide<NB, CT, EPI>(ga, strips, ws, s);
         }
         if constexpr (EPI == EPI_SWIGLU) {
             // 3.5 x G strips, G a multiple of the CUs: three whole strips and a half per workgroup, so that every CU holds
             // the same number of equal workgroups from start to end (70B-shaped gate/up: 156.5 -> 153.7 us)
-            if (g.ktiles >= 128 && (2 * strips) % 7 == 0 && (2 * strips / 7) % 256 == 0) {
+            if (g.ktiles >= 128 && half_strips_even(strips) && !one_strip_even(m, strips, g.ktiles, g.rows)) {
                 const int G = 2 * strips / 7;
                 ga.half_base = 3 * G;
                 k_gemm<NB, CT, 4, EPI, 8, 2, true><<<G, 512, 0, s>>>(ga);
@@ -1425,8 +1443,7 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
                 return PV_OK;
             }
         }
-        auto fill = [](int wgs) { return (double)wgs / (double)(((wgs + 255) / 256) * 256); };
-        const bool two = strips >= 512 && fill((strips + 1) / 2) >= fill(strips);
+        const bool two = strips >= 512 && even(m, (strips + 1) / 2) >= even(m, strips);
         // (three batches deep, us: K = 2048, 1024 strips of gate/up 13.2 -> 12.8, 8016 of the vocabulary 83.0 -> 80.7, K = 4096, 2048 strips 47.5 -> 46.5; K = 8192, 512 strips with the
         // residual 23.4 -> 24.3)
         constexpr int D2 = EPI == EPI_RESID ? 2 : 3;

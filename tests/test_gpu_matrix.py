@@ -187,11 +187,11 @@ WIDE = [pv_inputs.ModelShape("wide_3", 1, 544, 60, 60, 64, 5664, 705 * 16, dtype
 
 @pytest.mark.parametrize("shape", WIDE, ids=lambda v: v.name)
 def test_one_workgroup_per_cu_matches_oracle(pvlib, shape):
-    """Every number of column tiles at its first and last row count (33..48 rows: three); up to 8 rows from 1024 strips and 128 K-tiles on."""
+    """Every number of column tiles at its first and last row count (33..48 rows: three); up to 8 rows from 1025 strips and 128 K-tiles on."""
     _check_against_oracle(pvlib, shape, 0, 64, 20, (17, 32, 33, 48, 49, 64, 9, 16, 8, 1, 5), 320)
 
 
-# Packed rows, one workgroup per CU with four strips (1024: where that begins) and six (1376, ragged)
+# Packed rows at the lower end of one workgroup per CU (1024 strips: two a workgroup) and inside (1376: six, ragged)
 WIDE_PACKED = [pv_inputs.ModelShape("wide_p4", 1, 4128, 8, 2, 32, 352, 1024 * 16, dtype="bf16", seed=5806),
                pv_inputs.ModelShape("wide_p6", 1, 4128, 8, 2, 32, 352, 1376 * 16, dtype="bf16", seed=5807)]
 

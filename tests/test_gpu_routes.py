@@ -10,15 +10,15 @@ import pv_inputs
 
 pytestmark = pytest.mark.gpu
 
-LMHEAD = 3          # the epilogue's number among a kernel's template arguments
+SWIGLU, LMHEAD = 2, 3          # the epilogue's number among a kernel's template arguments
 EPI_AT = {"k_gemm": 3, "k_gemm_wide": 3, "k_gemm_tile": 2, "k_gemm_q4": 2, "k_gemm_tile_q4": 1}
 
 
-def _model(k, strips, bits=16):
-    """One layer of width k with a vocabulary of `strips` strips; every matrix is windows of one pool of normal draws."""
+def _model(k, strips, bits=16, ffn=256):
+    """One layer of width k with a vocabulary of `strips` strips (gate/up: ffn / 8); every matrix is windows of one pool of normal draws."""
     import torch
     import paper_2505_01572_amd as pv
-    shape = pv_inputs.ModelShape("route", 1, k, k // 128, 1, 128, 256, 16 * strips, weight_bits=bits)
+    shape = pv_inputs.ModelShape("route", 1, k, k // 128, 1, 128, ffn, 16 * strips, weight_bits=bits)
     m = pv.Model(shape, max_gamma=64, prompt_rows=0)
     rng = np.random.default_rng(77)
     pool = torch.from_numpy(rng.standard_normal(1 << 22, dtype=np.float32) * 0.02).to(torch.bfloat16).view(torch.uint16).numpy()
@@ -40,8 +40,8 @@ def _model(k, strips, bits=16):
     return m
 
 
-def _head_kernel(call):
-    """Name and template arguments of the kernel that multiplies with the vocabulary."""
+def _head_kernel(call, epi=LMHEAD):
+    """Name and template arguments of the kernel that multiplies with the vocabulary (of another projection: epi)."""
     import torch
     with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU, torch.profiler.ProfilerActivity.CUDA]) as p:
         call()
@@ -50,13 +50,13 @@ def _head_kernel(call):
         hit = re.match(r"(?:void )?(k_gemm\w*)<([^>]*)>", e.name)
         if hit and hit[1] in EPI_AT:
             args = [int(v) if v.strip().isdigit() else v.strip() for v in hit[2].split(",")]
-            if args[EPI_AT[hit[1]]] == LMHEAD:
+            if args[EPI_AT[hit[1]]] == epi:
                 found.add((hit[1], *args))
     assert len(found) == 1, found
     return found.pop()
 
 
-def _check(model, rows, logits=True):
+def _check(model, rows, logits=True, epi=LMHEAD):
     import paper_2505_01572_amd as pv
     from gpu_helpers import logit_scale
     v = model.shape.vocab
@@ -65,7 +65,7 @@ def _check(model, rows, logits=True):
     a.use_graphs(False)
     for c in (a, b):
         c.prefill(prompt)
-    name = _head_kernel(lambda: a.verify(5, block))
+    name = _head_kernel(lambda: a.verify(5, block), epi)
     if logits:
         got, want = a.debug_logits(), []
         for r0 in range(0, rows, 8):
@@ -100,13 +100,31 @@ def test_one_workgroup_per_cu_where_it_is_the_faster_one(k, strips, expected):
     m.close()
 
 
-# up to 8 rows: K, strips -> strips a workgroup of k_gemm_wide, 0 where k_gemm has them
-@pytest.mark.parametrize("k,strips,each", [(4096, 1023, 0), (4096, 1024, 4), (3968, 1024, 0), (4096, 1376, 6), (4096, 1537, 7), (4096, 1792, 7), (4096, 1793, 0)])
-def test_packed_rows_with_one_workgroup_per_cu(k, strips, each):
+# up to 8 rows: K, strips -> {rows: strips a workgroup, negative: of k_gemm_wide}
+PACKED_LINES = [
+    (4096, 1023, {1: 2, 8: 2}), (4096, 1024, {1: 2, 8: 2}), (4096, 1025, {1: -6, 8: -6}), (3968, 1088, {1: 1, 8: 1}), (4096, 1793, {1: 2, 8: 2}),
+    (4096, 1199, {4: -6}), (4096, 1200, {4: 1, 5: -6}), (4608, 1280, {4: 1, 5: -6}), (4736, 1280, {1: -6}),
+    (4096, 1376, {1: -6, 8: -6}), (4096, 1439, {1: 2, 8: 2}), (4224, 1440, {1: 2, 4: 2, 5: -6}), (7168, 1536, {1: 2, 8: -6}), (7296, 1536, {1: -6}),
+    (4096, 1537, {1: -7, 8: -7}), (4096, 1679, {1: -7}), (4096, 1792, {1: 1, 5: -7, 8: -7}), (4736, 1792, {1: -7, 8: -7}),
+]
+
+
+@pytest.mark.parametrize("k,strips,expected", PACKED_LINES, ids=lambda v: str(v) if isinstance(v, int) else "")
+def test_packed_rows_with_one_workgroup_per_cu(k, strips, expected):
     m = _model(k, strips)
-    for rows in (1, 8):
+    for rows, each in expected.items():
         name = _check(m, rows, logits=False)                   # (the same rows in blocks of eight would be the same kernel: the oracle tests have these)
-        assert name[:4] == ("k_gemm_wide", 1, 1, each) if each else name[0] == "k_gemm", (rows, name)
+        assert (name[0], name[3]) == ("k_gemm_wide" if each < 0 else "k_gemm", abs(each)), (rows, name)
+    m.close()
+
+
+# up to 8 rows, gate/up in 3 1/2 strips a workgroup: K -> {rows: strips a workgroup (4: the half ones), negative: of k_gemm_wide}
+@pytest.mark.parametrize("k,expected", [(4096, {4: 1, 5: -7, 8: -7}), (4608, {4: 1, 5: 4, 8: 4}), (4736, {1: 4, 8: 4}), (7168, {1: 4, 8: 4}), (7296, {1: -7, 8: -7})])
+def test_packed_gate_up_of_half_strips(k, expected):
+    m = _model(k, 32, ffn=1792 * 8)
+    for rows, each in expected.items():
+        name = _check(m, rows, logits=False, epi=SWIGLU)
+        assert (name[0], name[3]) == ("k_gemm_wide" if each < 0 else "k_gemm", abs(each)), (rows, name)
     m.close()
 
 

@@ -1444,10 +1444,14 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
             }
         }
         const bool two = strips >= 512 && even(m, (strips + 1) / 2) >= even(m, strips);
-        // (three batches deep, us: K = 2048, 1024 strips of gate/up 13.2 -> 12.8, 8016 of the vocabulary 83.0 -> 80.7, K = 4096, 2048 strips 47.5 -> 46.5; K = 8192, 512 strips with the
-        // residual 23.4 -> 24.3)
-        constexpr int D2 = EPI == EPI_RESID ? 2 : 3;
-        if (g.ktiles >= 64 && two) k_gemm<NB, CT, 2, EPI, 8, D2><<<(strips + 1) / 2, 512, 0, s>>>(ga);
+        // (three batches deep, us: K = 2048, 1024 strips of gate/up 13.2 -> 12.8, 8016 of the vocabulary 83.0 -> 80.7; K = 4096, 4096 strips with one row
+        // 86.2 -> 87.9, K = 5120 96.7 -> 96.8, K = 8192 162.1 -> 164.2, 1376 strips 56.4 -> 58.1; 512 with the residual 23.4 -> 24.3)
+        bool done = false;
+        if constexpr (EPI != EPI_RESID) {
+            if (g.ktiles >= 64 && g.ktiles < 128 && two) { k_gemm<NB, CT, 2, EPI, 8, 3><<<(strips + 1) / 2, 512, 0, s>>>(ga); done = true; }
+        }
+        if (done) ;
+        else if (g.ktiles >= 64 && two) k_gemm<NB, CT, 2, EPI, 8, 2><<<(strips + 1) / 2, 512, 0, s>>>(ga);
         else if (g.ktiles >= 64) k_gemm<NB, CT, 1, EPI, 8, 3><<<strips, 512, 0, s>>>(ga);
         else k_gemm<NB, CT, 1, EPI, 8><<<strips, 512, 0, s>>>(ga);
     }

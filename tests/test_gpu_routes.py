@@ -118,6 +118,16 @@ def test_packed_rows_with_one_workgroup_per_cu(k, strips, expected):
     m.close()
 
 
+# up to 8 rows, two strips a workgroup: K -> batches a wave keeps in flight
+@pytest.mark.parametrize("k,depth", [(2048, 3), (3968, 3), (4096, 2), (5120, 2)])
+def test_depth_of_two_packed_strips(k, depth):
+    m = _model(k, 1024)
+    for rows in (1, 8):
+        name = _check(m, rows, logits=False)
+        assert name[:7] == ("k_gemm", 1, 1, 2, LMHEAD, 8, depth), (rows, name)
+    m.close()
+
+
 # up to 8 rows, gate/up in 3 1/2 strips a workgroup: K -> {rows: strips a workgroup (4: the half ones), negative: of k_gemm_wide}
 @pytest.mark.parametrize("k,expected", [(4096, {4: 1, 5: -7, 8: -7}), (4608, {4: 1, 5: 4, 8: 4}), (4736, {1: 4, 8: 4}), (7168, {1: 4, 8: 4}), (7296, {1: -7, 8: -7})])
 def test_packed_gate_up_of_half_strips(k, expected):

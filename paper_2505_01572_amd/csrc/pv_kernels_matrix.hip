@@ -1446,6 +1446,9 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         const bool two = strips >= 512 && even(m, (strips + 1) / 2) >= even(m, strips);
         // (three batches deep, us: K = 2048, 1024 strips of gate/up 13.2 -> 12.8, 8016 of the vocabulary 83.0 -> 80.7; K = 4096, 4096 strips with one row
         // 86.2 -> 87.9, K = 5120 96.7 -> 96.8, K = 8192 162.1 -> 164.2, 1376 strips 56.4 -> 58.1; 512 with the residual 23.4 -> 24.3)
+        // Their waves' batches interleaved from K = 4096 on, us: gate/up, 8 rows, 2000 strips 45.3 -> 41.5, 4096 strips 86.4 -> 79.8 (one strip a workgroup, vocabulary, 768 strips:
+        // 21.4 -> 21.9; two below K = 4096: no difference)
+        if (two) ga.interleave |= g.ktiles >= 128;
         bool done = false;
         if constexpr (EPI != EPI_RESID) {
             if (g.ktiles >= 64 && g.ktiles < 128 && two) { k_gemm<NB, CT, 2, EPI, 8, 3><<<(strips + 1) / 2, 512, 0, s>>>(ga); done = true; }

@@ -1177,8 +1177,9 @@ static double even(const pv_model *m, int wgs) { const int rounds = (wgs + m->n_
 // 39.4 / 49.7 / 77.5 against 33.6 / 40.8 / 63.0.  Elsewhere, since whole rounds of smaller workgroups leave nothing to gain by it and these overlap their starts and ends:
 //  - up to four strips a CU (1024 strips in four each 24.3 / 27.7 / 44.2, in two each 22.8 / 27.1 / 43.5);
 //  - one strip a workgroup in even rounds, up to 4 rows and K = 4608 (K = 4096, 1280 strips 27.4 / 28.5, K = 4608 29.5 / 30.2, but K = 5120 33.0 / 33.1; 1792 strips 36.7 / 37.6);
-//  - two in even rounds, up to 4 rows and K = 7168 (K = 5120, 1536 strips 38.5 / 39.9, K = 7168 53.3 / 54.1, but K = 8192, 1440 strips 59.3 / 58.0), with more rows at K = 4096
-//    (8 rows, 1536 strips 32.8 / 33.6, but K = 5120, 1440 strips 38.1 / 36.8);
+//  - two in even rounds, up to K = 7168 (one row, K = 5120, 1536 strips 38.5 / 39.9, K = 7168 53.3 / 54.1, but K = 8192, 1440 strips 59.3 / 58.0); how even goes with the operand:
+//    K = 4096, 1376 strips, one row 30.0 / 31.2, 8 rows 31.1 / 30.6, 1440 strips 31.5 / 31.4; K = 5120, 1376 strips, one row 35.5 / 35.8, 1440 strips 36.6 / 37.3, 8 rows 38.1 / 36.8,
+//    1536 strips, 5 rows 38.5 / 39.8;
 //  - half strips in even rounds, from there up to K = 7168 (1792 strips of gate/up, one row and 8: K = 4096 38.8 / 37.6 and 38.4 / 37.5, K = 4608 40.7 / 42.8 and 40.5 / 41.8, K = 5120
 //    45.2 / 46.0 and 45.2 / 45.5, K = 7168 61.6 / 63.0 and 61.6 / 62.2, K = 8192 71.1 / 70.5 and 71.0 / 69.8).
 static bool one_strip_even(const pv_model *m, int strips, int ktiles, int rows) { return rows <= 4 && ktiles <= 144 && strips <= 7 * m->n_cus && even(m, strips) >= 15. / 16; }
@@ -1186,7 +1187,8 @@ static bool half_strips_even(int strips) { return (2 * strips) % 7 == 0 && (2 * 
 static bool packed_wide(const pv_model *m, int strips, int ktiles, int rows, bool gate_up)
 {
     if (strips <= 4 * m->n_cus || strips > 7 * m->n_cus || one_strip_even(m, strips, ktiles, rows)) return false;
-    if (ktiles <= 224 && (rows <= 4 || ktiles <= 128) && even(m, (strips + 1) / 2) >= 15. / 16) return false;
+    const double line = ktiles <= 128 ? (rows <= 4 ? 0.88 : 0.935) : (rows <= 4 ? 0.935 : 0.965);
+    if (ktiles <= 224 && even(m, (strips + 1) / 2) >= line) return false;
     return !(gate_up && half_strips_even(strips) && ktiles > 128 && ktiles <= 224);
 }
 

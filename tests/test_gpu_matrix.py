@@ -191,7 +191,7 @@ def test_one_workgroup_per_cu_matches_oracle(pvlib, shape):
     _check_against_oracle(pvlib, shape, 0, 64, 20, (17, 32, 33, 48, 49, 64, 9, 16, 8, 1, 5), 320)
 
 
-# Packed rows at the lower end of one workgroup per CU (1024 strips: two a workgroup) and inside (1376: six, ragged)
+# Packed rows at the lower end of one workgroup per CU (1024 strips: two a workgroup) and inside (1376: six, ragged; K = 4128)
 WIDE_PACKED = [pv_inputs.ModelShape("wide_p4", 1, 4128, 8, 2, 32, 352, 1024 * 16, dtype="bf16", seed=5806),
                pv_inputs.ModelShape("wide_p6", 1, 4128, 8, 2, 32, 352, 1376 * 16, dtype="bf16", seed=5807)]
 

@@ -104,7 +104,8 @@ def test_one_workgroup_per_cu_where_it_is_the_faster_one(k, strips, expected):
 PACKED_LINES = [
     (4096, 1023, {1: 2, 8: 2}), (4096, 1024, {1: 2, 8: 2}), (4096, 1025, {1: -6, 8: -6}), (3968, 1088, {1: 1, 8: 1}), (4096, 1793, {1: 2, 8: 2}),
     (4096, 1199, {4: -6}), (4096, 1200, {4: 1, 5: -6}), (4608, 1280, {4: 1, 5: -6}), (4736, 1280, {1: -6}),
-    (4096, 1376, {1: -6, 8: -6}), (4096, 1439, {1: 2, 8: 2}), (4224, 1440, {1: 2, 4: 2, 5: -6}), (7168, 1536, {1: 2, 8: -6}), (7296, 1536, {1: -6}),
+    (4096, 1350, {1: -6}), (4096, 1376, {1: 2, 4: 2, 5: -6, 8: -6}), (4096, 1439, {1: 2, 8: 2}), (4224, 1376, {1: -6}), (4224, 1440, {1: 2, 4: 2, 5: -6}),
+    (5120, 1480, {8: -6}), (5120, 1488, {8: 2}), (7168, 1536, {1: 2, 8: 2}), (7296, 1536, {1: -6, 8: -6}),
     (4096, 1537, {1: -7, 8: -7}), (4096, 1679, {1: -7}), (4096, 1792, {1: 1, 5: -7, 8: -7}), (4736, 1792, {1: -7, 8: -7}),
 ]
 

@@ -353,6 +353,10 @@ k_gemm(const gemm_args a)
     // its neighbour (strips a.half_base ...), so that a GEMM with (k + 1/2) x 256 strips puts the
     // same bytes on every CU; the lanes of the other half duplicate the owned half's loads for
     // that slot and their rows of the product are not stored.
+    // Two strips a workgroup and a short K: many workgroups with little to do each.  All arguments are asked for at once; left alone, the compiler asks for the weights' only
+    // behind the first loads, one more trip to memory a workgroup (13 rows, gate/up, us: K = 512, 1376 strips 8.9 -> 8.4, 1536 strips 9.2 -> 9.0; K = 1024, 11.8 -> 11.5, 13.2 -> 13.0).
+    // Elsewhere no difference or, with one strip, up to 0.1 us more.
+    if constexpr (NB == 2 && CT == 1 && S == 2 && DP == 1) asm volatile("" :: "s"(a.W), "s"(a.xop), "s"(a.ktiles), "s"(a.interleave), "s"(a.nstrips), "s"(a.rows), "s"(a.ssq), "s"(a.ssq_parts));
     const int strip0 = blockIdx.x * (HF ? S - 1 : S), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int hstrip = HF ? a.half_base + ((int)blockIdx.x >> 1) : 0, hsel = blockIdx.x & 1;
     const int hl = HF ? ((lane & ~8) | (hsel << 3)) - lane : 0;    // half slot: the lanes of the other half read the owned half's lines again (no further bytes)

@@ -672,18 +672,18 @@ k_gemm_wide(const gemm_args a)
 // the activation tile with an all -24 operand (= -24 x row sums, shared by the S strips), so that the codes' product on top of it is
 // sum_k (c_k - 8) * x_k; the vector ALU only multiplies that by the tile's scale and adds.  The product is taken transposed (activation rows x
 // features) so that a lane's four results share one feature, hence one scale; the accumulators are turned back on their way through LDS.
-// Sixteen waves a CU (two workgroups of 8 where there are enough), each with one batch in registers and no loads ahead, the other waves' work covering a wave's latency.  That
-// takes at most 128 registers, which seven strips fit only if the multiply-adds stay behind their products (left alone, the compiler moves all of them to the end of the batch
-// and holds every product: 100 - 120 registers more, spilled; two batches deep at 200 registers and two waves per SIMD the 8B-shaped gate/up took 21.7 us instead of 18.9).
-// Many strips: no unit is at its limit.  The 70B-shaped gate/up with 8 rows (264 MB, 51.5 us, 4.5 of which a kernel takes in any case) streams 5.6 of 7 TB/s, a CU takes in 33 GB/s of
-// the 45 - 56 it can have outstanding, and the vector ALU's 13 instructions per weight tile are 19 us of issue: a wave's loads drain once a batch, and four waves a SIMD in
-// like phases do not hide all of that.  One or two strips (the 70B-shaped down projection, 33.8 us): the L2 -> CU path, 917 KB of operand beside 516 KB of codes per CU at 50 GB/s.
-// 8B shape, 13 rows, us, with the sum of the K-slices that k_gemm_tile_q4 needs: QKV 15.0 -> 9.1, O 11.2 -> 7.2, gate/up 24.6 -> 18.9; 70B shape 23.1 -> 17.5, 18.4 -> 14.4, 65.5 -> 56.4;
-// 8 rows (before: two or three batches deep, at most three and a half strips a workgroup, 126 registers): 8B gate/up 19.0 -> 16.4, 70B 56.2 -> 51.2.  With one strip a workgroup and
-// a long K that earlier form was ahead (8 rows, 256 strips, K = 14336 15.8 and 16.8, K = 28672 25.6 and 27.4); gate/up, twice the weights, gained more than that in every shape measured.
+// A wave goes through a batch in two halves, two K-tiles of every strip each, and loads every piece for its next batch as soon as it is dead: two K-tiles of the operand and the scales
+// behind the first half, a strip's codes behind its last tile, the other two K-tiles at the end.  So there are loads in flight while it multiplies; with a batch loaded, used up and loaded again
+// they drained once a batch (70B-shaped gate/up, 264 MB, 8 rows, inside the kernel 50.0 -> 43.1 us; without the products and the operand 37.0, 7.1 TB/s; 8B shape, 13 rows, 17.4 -> 14.7).
+// The scales of up to eight strips come in one load and go through LDS to the lanes of their features: as a load a strip (8 bytes of 16 lanes) they took 6 of the 50 us.
+// A product is scaled and added while the next one runs.  128 registers hold seven strips of packed rows, two workgroups of eight waves a CU; seven strips of 16-row tiles take 169 and one
+// workgroup a CU (70B shape, 13 rows, a step of two layers: 326 us before and now).  The multiply-adds are pinned behind their products: left alone, the compiler moves all of them to the end
+// of the batch and holds every product.
+// One or two strips (the 70B-shaped down projection, 30.6 us, before 32.0): the L2 -> CU path, 917 KB of operand beside 516 KB of codes per CU at 50 GB/s.
+// Against k_gemm_tile_q4 and the sum of its K-slices, 13 rows, us, before the loads went out early: 8B shape QKV 15.0 -> 9.1, O 11.2 -> 7.2, gate/up 24.6 -> 18.9; 70B shape 23.1 -> 17.5, 18.4 -> 14.4, 65.5 -> 56.4.
 // ------------------------------------------------------------------------------------------
 template <int NB, int S, int EPI, int NW = 8>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NB == 2 && S == 7) ? 2 : 4, (NB == 2 && S == 7) ? 2 : 4)))
 k_gemm_q4(const gemm_args a)
 {
     static_assert(S <= NW, "one epilogue wave per strip");
@@ -704,61 +704,90 @@ k_gemm_q4(const gemm_args a)
     f32x4 acc[S];
 #pragma unroll
     for (int si = 0; si < S; ++si) acc[si] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    struct batch { uint4 c[S]; uint2 s[S]; uint4 h[4], l[NB == 2 ? 4 : 1]; };
-    auto issue = [&](batch &q, int i) {
+    // The wave's batch: codes and scales of its strips, the operand's four K-tiles.  Each piece is loaded again for the next batch as soon as it is dead.
+    uint4 c[S], h[4], l[NB == 2 ? 4 : 1], sv;
+    uint4 *scs = (uint4 *)red[wave][0];                         // the wave's scales of the batch in use: [strip][feature][K-tile], in its own piece of the sums' place
+    struct place { uint32_t off, offx, offs; };
+    const uint32_t sl8 = (uint32_t)min(lane >> 3, mine - 1) * qs + 1024 + (lane & 7) * 16;
+    auto place_of = [&](int i) {
         const int k = i + rot, t = (k < nst ? k : k - nst) * NW + wave;
         const bool in = t < nb4;                                // (past the end: codes, scales and activations of zero, nothing fetched)
-        const uint32_t off = in ? (uint32_t)t * PV_Q4_BATCH : BUFFER_END, offx = xl + (in ? (uint32_t)t * 4 * xs : BUFFER_END);
+        return place{in ? (uint32_t)t * PV_Q4_BATCH : BUFFER_END, xl + (in ? (uint32_t)t * 4 * xs : BUFFER_END), in ? (uint32_t)t * PV_Q4_BATCH + sl8 : BUFFER_END};
+    };
+    auto load_strip = [&](place p, int si) {
+        c[si] = buffer_load16<LOAD_ONCE>(W, p.off + lane * 16, (uint32_t)min(si, mine - 1) * qs);
+        asm volatile("" ::: "memory");
+    };
+    auto load_scales = [&](place p) { sv = buffer_load16<LOAD_ONCE>(W, p.offs, 0); asm volatile("" ::: "memory"); };       // of up to eight strips at once
+    auto load_x = [&](place p, int half) {
 #pragma unroll
-        for (int si = 0; si < S; ++si) {
-            q.c[si] = buffer_load16<LOAD_ONCE>(W, off + lane * 16, (uint32_t)min(si, mine - 1) * qs);
-            q.s[si] = buffer_load8<LOAD_ONCE>(W, off + 1024 + (lane & 15) * 8, (uint32_t)min(si, mine - 1) * qs);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            q.h[u] = buffer_load16<0>(X, offx, u * xs);
-            if (NB == 2) q.l[NB == 2 ? u : 0] = buffer_load16<0>(X, offx, (uint32_t)(KT + u) * xs);
+        for (int u = 2 * half; u < 2 * half + 2; ++u) {
+            h[u] = buffer_load16<0>(X, p.offx, u * xs);
+            if (NB == 2) l[NB == 2 ? u : 0] = buffer_load16<0>(X, p.offx, (uint32_t)(KT + u) * xs);
         }
         asm volatile("" ::: "memory");
     };
     const uint4 neg24 = make_uint4(0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u);
     uint32_t sixteen = 0x41804180u, nibble = 0x00780078u;       // (kept in registers, so that mask-and-merge is one instruction)
     asm volatile("" : "+v"(sixteen), "+s"(nibble));
-    auto use = [&](const batch &q) {
+    // Half a batch: two K-tiles of every strip.  A product is scaled and added one product later, when it is there.
+    auto use_half = [&](auto hc, auto more, place next) {
+        constexpr int half = decltype(hc)::value;
+        f32x4 T0[2], T, P;
+        float sp = 0.f;
+        const uint32_t *sr = (const uint32_t *)scs + (lane & 15) * 2 + half;
+        uint32_t sw = sr[0], sn = S > 1 ? sr[32] : 0;           // (one strip ahead)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (S > 4) __builtin_amdgcn_sched_barrier(0);       // (nor does work of the next tile move up)
-            f32x4 T0 = {0.f, 0.f, 0.f, 0.f};
-            T0 = mfma16(q.h[u], neg24, T0);
-            if (NB == 2) T0 = mfma16(q.l[NB == 2 ? u : 0], neg24, T0);
+        for (int v = 0; v < 2; ++v) {
+            const int u = 2 * half + v;
+            T0[v] = mfma16(h[u], neg24, (f32x4){0.f, 0.f, 0.f, 0.f});
+            if (NB == 2) T0[v] = mfma16(l[NB == 2 ? u : 0], neg24, T0[v]);
+        }
 #pragma unroll
-            for (int si = 0; si < S; ++si) {
-                const uint4 c4 = q.c[si];
-                const uint32_t cw = u == 0 ? c4.x : u == 1 ? c4.y : u == 2 ? c4.z : c4.w, sw = (u & 2) ? q.s[si].y : q.s[si].x;
-                const float sc = __uint_as_float((u & 1) ? (sw & 0xFFFF0000u) : (sw << 16));
+        for (int j = 0; j <= 2 * S; ++j) {
+            const int si = j >> 1, u = 2 * half + (j & 1);
+            float s1 = 0.f;
+            if (j < 2 * S) {
+                const uint32_t cw = half == 0 ? ((j & 1) ? c[si].y : c[si].x) : ((j & 1) ? c[si].w : c[si].z);
+                s1 = __uint_as_float((j & 1) ? (sw & 0xFFFF0000u) : (sw << 16));
                 // operand dword t = bf16 pair (16 + c_2t, 16 + c_2t+1): nibble t of each half into the top mantissa bits of 16.0
                 const uint4 wa = make_uint4(((cw << 3) & nibble) | sixteen, ((cw >> 1) & nibble) | sixteen, ((cw >> 5) & nibble) | sixteen, ((cw >> 9) & nibble) | sixteen);
-                f32x4 T = mfma16(q.h[u], wa, T0);
-                if (NB == 2) T = mfma16(q.l[NB == 2 ? u : 0], wa, T);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[si][r] = fmaf(sc, T[r], acc[si][r]);
-                asm volatile("" : "+v"(acc[si]));               // the multiply-adds stay here
+                T = mfma16(h[u], wa, T0[j & 1]);
+                if (NB == 2) T = mfma16(l[NB == 2 ? u : 0], wa, T);
             }
+            __builtin_amdgcn_sched_barrier(0);
+            if (j > 0) {
+                const int sj = (j - 1) >> 1;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[sj][r] = fmaf(sp, P[r], acc[sj][r]);
+                asm volatile("" : "+v"(acc[sj]));               // the multiply-adds stay here
+            }
+            P = T; sp = s1;
+            if ((j & 1) && j < 2 * S) { sw = sn; if (si + 2 < S) sn = sr[(si + 2) * 32]; }
+            if (half == 1 && decltype(more)::value && (j & 1) && j < 2 * S) load_strip(next, si);
         }
     };
-    batch q;
-    issue(q, 0);
+    auto use = [&](auto more, place next) {
+        scs[lane] = sv;                                   // (a wave's LDS traffic stays in order: no barrier)
+        use_half(std::integral_constant<int, 0>(), more, next);
+        if (decltype(more)::value) { load_x(next, 0); load_scales(next); }
+        use_half(std::integral_constant<int, 1>(), more, next);
+        if (decltype(more)::value) load_x(next, 1);
+    };
+    const place first = place_of(0);
+    load_x(first, 0);
+    load_scales(first);
+#pragma unroll
+    for (int si = 0; si < S; ++si) load_strip(first, si);
+    load_x(first, 1);
     epi_pre pre;
     if (EARLY && wave < mine) epi_prefetch<EPI>(a, strip0 + wave, lane, pre, 0);
     if (NORM) {
         const float4 s4 = ssq_finish(a.ssq, a.ssq_parts, threadIdx.x, NW * 64, sl);
         if (lane < 4) *(float4 *)&ssq_s[wave][4 * lane] = s4;
     }
-    for (int i = 0;;) {
-        use(q);
-        if (++i == nst) break;
-        issue(q, i);
-    }
+    for (int i = 1; i < nst; ++i) use(std::true_type(), place_of(i));
+    use(std::false_type(), first);
     {   // acc is (row 4 g + r, feature f) for lane (g, f); the sum below and the epilogues take (feature 4 g' + r', row j) from lane (g', j): store transposed
         const int g = lane >> 4, f = lane & 15;
 #pragma unroll

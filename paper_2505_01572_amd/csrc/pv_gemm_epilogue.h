@@ -19,7 +19,7 @@ struct gemm_args {
     // RMSNorm scale of the input rows (QKV, SWIGLU, LMHEAD)
     const float *ssq; int ssq_parts; float inv_d, eps;
     // QKV
-    uint16_t *q_hi, *q_lo; uint16_t *pool; const int32_t *page_table; const float2 *rope; pv_kv_geom geom;
+    uint16_t *q_hi, *q_lo; int q_rows; uint16_t *pool; const int32_t *page_table; const float2 *rope; pv_kv_geom geom;      // queries: q_at
     int layer, n_q_heads, q_strips, k_strips;
     // RESID
     float *x; const uint16_t *gain_next; float *ssq_out; uint16_t *xop_out; int d;
@@ -198,7 +198,7 @@ __device__ inline void epi_apply(const gemm_args &a, int strip, int lane, f32x4 
                     uint2 qh, ql;
                     split2(o[0], o[1], qh.x, ql.x);
                     split2(o[2], o[3], qh.y, ql.y);
-                    const size_t qo = ((size_t)j * a.n_q_heads + h) * hd + e + side * half;
+                    const size_t qo = q_at(h, j, e + side * half, hd, a.q_rows);
                     *(uint2 *)(a.q_hi + qo) = qh;
                     *(uint2 *)(a.q_lo + qo) = ql;
                 } else {

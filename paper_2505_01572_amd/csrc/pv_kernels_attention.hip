@@ -14,8 +14,8 @@ template <int NB, int HD>
 __global__ void __launch_bounds__(256)
 k_attn_merge(const attn_args a, int n_units)
 {
-    __shared__ float smem[256 + (256 / (HD / 4)) * (HD / 4) * 5];
-    attn_merge_unit<NB, HD, 256>(a, blockIdx.x, blockIdx.y, n_units, threadIdx.x, smem);
+    __shared__ float4 smem4[64 + 4 * (HD / 4) * 2];
+    attn_merge_unit<NB, HD, 256>(a, blockIdx.x, blockIdx.y, n_units, threadIdx.x, (float *)smem4);
 }
 
 // ------------------------------- host side ----------------------------------------
@@ -114,7 +114,7 @@ int pv_mat_attention(pv_cache *c, int layer, int rows, float *part, uint16_t *xo
     a.geom = pv_geom(c); a.layer = layer; a.n_q_heads = f.n_q_heads; a.group = f.n_q_heads / f.n_kv_heads;
     a.max_chunks = (c->max_tokens + 127) / 128;        // sizes the partial arrays; the launch sets the chunking in use
     a.chunk_shift = 7; a.chunks = a.max_chunks;
-    a.scale = 1.0f / sqrtf((float)f.head_dim);
+    a.scale = 1.0f / sqrtf((float)f.head_dim); a.block_bytes = (size_t)f.page_tokens * f.head_dim * 2; a.page_bytes = (size_t)(2 * f.n_kv_heads) * a.block_bytes;
     a.part_o = part;
     a.part_ml = part + (size_t)f.n_kv_heads * c->units_cap * a.max_chunks * 32 * f.head_dim;
     a.xop_o = xop_o; a.n_pages = c->n_pages; a.rows = rows; a.batched = c->blk_units != 0;

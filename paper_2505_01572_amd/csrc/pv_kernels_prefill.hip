@@ -12,34 +12,12 @@
 #include <algorithm>
 #include <type_traits>
 
-// One 1 KiB operand tile (64 lanes x 16 bytes) from global memory straight into LDS.  Written in assembly (there is
-// no vector output register) because the compiler otherwise waits for every copy in flight before any LDS read; the
-// kernels wait for the copies by count (pre_wait).  src is uniform, voff the lane's byte offset behind it.  m0 is put back:
-// the compiler may hold a value of its own in it, and a clobber list does not tell it otherwise (m0 is a reserved register there: it
-// warns, and reuses the value all the same).  0.3 % of a prompt's time (8B shape, 2048 tokens: 6.68 -> 6.70 ms); 0.9 % with an s_nop behind
-// it, which only an instruction that reads m0 next would need: tests/test_lds_copies.py sees to it that there is none.
-__device__ inline void dma_tile(uint32_t lds, const void *src, uint32_t voff)
-{
-    uint32_t m0;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
-                 : "=&s"(m0) : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(src) : "memory");
-}
-
-__device__ inline uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }
-
 // all but the newest N copies of this wave have landed, its LDS reads are done, and so it is for every wave of the workgroup
 template <int N> __device__ inline void pre_wait()
 {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-}
-
-template <typename T> __device__ inline const T *uniform_ptr(const T *p)
-{
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));   // (the builtin returns a signed int)
-    return (const T *)((uint64_t)hi << 32 | lo);
 }
 
 // workgroup number -> position in the work list: the 8 XCDs take workgroups in turn, so each gets a contiguous run of the list (its
@@ -791,9 +769,11 @@ k_pre_attn(const pre_attn_args a)
     for (int t = 0; t < RT; ++t) {
         const int m = min(m0 + wave * 32 + t * 16 + jl, nrows - 1);
         j[t] = m / a.group; al[t] = m - j[t] * a.group;
-        const size_t qo = ((size_t)j[t] * a.n_q_heads + kvh * a.group + al[t]) * HD + g * 8;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) { qh[t][ks] = *(const uint4 *)(a.q_hi + qo + ks * 32); ql[t][ks] = *(const uint4 *)(a.q_lo + qo + ks * 32); }
+        for (int ks = 0; ks < KS; ++ks) {
+            const size_t qo = q_at(kvh * a.group + al[t], j[t], ks * 32 + g * 8, HD, a.rows);
+            qh[t][ks] = *(const uint4 *)(a.q_hi + qo); ql[t][ks] = *(const uint4 *)(a.q_lo + qo);
+        }
     }
     // Q is here before the loop starts: a wait for it inside would also wait for the copies of the next step
     asm volatile("" ::: "memory");
@@ -1109,7 +1089,7 @@ int pv_pre_block(pv_cache *c, const int32_t *d_host_tokens, int rows, int keep, 
 
     gemm_args g = {};
     g.st = c->ws.state; g.inv_d = 1.0f / (float)d; g.eps = (float)f.rms_eps; g.ssq_parts = d / 16;
-    g.q_hi = w.q_hi; g.q_lo = w.q_lo; g.pool = (uint16_t *)c->d_pool; g.page_table = c->ws.page_table; g.rope = w.rope; g.geom = pv_geom(c);
+    g.q_hi = w.q_hi; g.q_lo = w.q_lo; g.q_rows = rows; g.pool = (uint16_t *)c->d_pool; g.page_table = c->ws.page_table; g.rope = w.rope; g.geom = pv_geom(c);
     g.n_q_heads = f.n_q_heads; g.q_strips = qd / 16; g.k_strips = kvd / 16;
     g.x = w.x; g.d = d; g.xop_act = w.xop_d; g.F = F; g.tile_part = w.part; g.ssq = w.ssq; g.ssq_out = w.ssq; g.xop_out = w.xop;
 

@@ -28,6 +28,43 @@ __device__ inline uint2 load_once(const uint2 *p)
     return make_uint2(v.x, v.y);
 }
 
+// One 1 KiB operand tile (64 lanes x 16 bytes) from global memory straight into LDS.  Written in assembly (there is
+// no vector output register) because the compiler otherwise waits for every copy in flight before any LDS read; the
+// kernels wait for the copies by count (pre_wait).  src is uniform, voff the lane's byte offset behind it.  m0 is put back:
+// the compiler may hold a value of its own in it, and a clobber list does not tell it otherwise (m0 is a reserved register there: it
+// warns, and reuses the value all the same).  0.3 % of a prompt's time (8B shape, 2048 tokens: 6.68 -> 6.70 ms); 0.9 % with an s_nop behind
+// it, which only an instruction that reads m0 next would need: tests/test_lds_copies.py sees to it that there is none.
+__device__ inline void dma_tile(uint32_t lds, const void *src, uint32_t voff)
+{
+    uint32_t m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0) : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(src) : "memory");
+}
+
+// N of them in a row, on both sides (the offset in the instruction counts for the LDS address as well): N KiB
+template <int N> __device__ inline void dma_tiles(uint32_t lds, const void *src, uint32_t voff)
+{
+    static_assert(N == 1 || N == 2 || N == 4, "");
+    uint32_t m0;
+    if constexpr (N == 1) { dma_tile(lds, src, voff); return; }
+    else if constexpr (N == 2)
+        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024\n\ts_mov_b32 m0, %0"
+                     : "=&s"(m0) : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(src) : "memory");
+    else
+        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %2, %3 offset:2048\n\tglobal_load_lds_dwordx4 %2, %3 offset:3072\n\ts_mov_b32 m0, %0"
+                     : "=&s"(m0) : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(src) : "memory");
+}
+
+__device__ inline uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }
+
+template <typename T> __device__ inline const T *uniform_ptr(const T *p)
+{
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));   // (the builtin returns a signed int)
+    return (const T *)((uint64_t)hi << 32 | lo);
+}
+
 // ------------------------------------------------------------------------------------------
 // Operand writers.  Element (row j, K-index k) of an activation lives at
 //   arr[(k/32)*512 + (j%16 + 16*((k%32)/8))*8 + k%8]            (NB == 2: rows in column tiles of 16, tile j/16 has a hi
@@ -69,3 +106,28 @@ __device__ inline void store_operand4(uint16_t *xop, int K, int j, int k0, const
     }
 }
 
+// Where feature e (of hd) of row j (of rows) of query head h lies in the queries' hi and lo arrays: [head][8 features][row][8].  A lane of the attention reads 8 features of one
+// row, its neighbours the next rows: 256 bytes for 16 lanes.  With each row's features in one piece every lane had a line of its own, and the address path, which takes a cycle a line and 16
+// lanes, a third of k_attn's time (eight rows, groups of four heads).
+__device__ inline size_t q_at(int h, int j, int e, int hd, int rows) { return (((size_t)h * (hd >> 3) + (e >> 3)) * rows + j) * 8 + (e & 7); }
+
+// The other lane's value combined with the own one, for lanes 16 or 32 apart, or n apart within a row of 16 (a rotation): vector instructions, where a shuffle goes through LDS (some
+// 120 cycles each, and they come in chains).
+template <typename F> __device__ inline float with_lane32(float v, F op)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <typename F> __device__ inline float with_lane16(float v, F op)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <int N, typename F> __device__ inline float with_rotated(float v, F op) { return op(v, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x120 + N, 0xF, 0xF, true))); }
+template <typename F> __device__ inline float over_wave(float v, F op)
+{
+    v = with_rotated<1>(v, op); v = with_rotated<2>(v, op); v = with_rotated<4>(v, op); v = with_rotated<8>(v, op);
+    return with_lane32(with_lane16(v, op), op);
+}
+__device__ inline float op_max(float a, float b) { return fmaxf(a, b); }
+__device__ inline float op_add(float a, float b) { return a + b; }

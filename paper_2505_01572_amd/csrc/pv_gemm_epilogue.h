@@ -44,8 +44,7 @@ __device__ inline void emit_x(int lane, int rows, int strip, int d, const float 
     const bool live = j < rows;
     if (live) *(float4 *)(x + (size_t)j * d + n) = make_float4(v[0], v[1], v[2], v[3]);
     float ss = live ? (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]) : 0.f;
-    ss += __shfl_xor(ss, 16, 64);
-    ss += __shfl_xor(ss, 32, 64);
+    ss = with_lane32(with_lane16(ss, op_add), op_add);
     if (NB == 1 && hsel >= 0) ss = __shfl(ss, lane & 7, 64);
     if (lane < 16 && (NB == 2 || hsel < 0 || (lane >> 3) == hsel)) ssq[((size_t)ct * (d >> 4) + strip) * 16 + jl] = ss;
     if (live) {
@@ -84,11 +83,8 @@ __device__ inline float4 ssq_finish(const float *ssq, int parts, int tid, int nt
         if (tid + u * nthreads < n4) { s.x += L.v[u].x; s.y += L.v[u].y; s.z += L.v[u].z; s.w += L.v[u].w; }
     }
     for (int i = tid + N * nthreads; i < n4; i += nthreads) { const float4 v = q[i]; s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w; }
-#pragma unroll
-    for (int o = 4; o <= 32; o <<= 1) {
-        s.x += __shfl_xor(s.x, o, 64); s.y += __shfl_xor(s.y, o, 64); s.z += __shfl_xor(s.z, o, 64); s.w += __shfl_xor(s.w, o, 64);
-    }
-    return s;
+    auto rows_of = [](float v) { return with_lane32(with_lane16(with_rotated<8>(with_rotated<4>(v, op_add), op_add), op_add), op_add); };
+    return make_float4(rows_of(s.x), rows_of(s.y), rows_of(s.z), rows_of(s.w));
 }
 
 // What an epilogue needs from memory (rj is filled in after the reduction from the waves' sums
@@ -166,7 +162,7 @@ __device__ inline void epi_apply(const gemm_args &a, int strip, int lane, f32x4 
     const int j = ct * 16 + (lane & 15), g = lane >> 4, rows = p.rows;
     float v[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = (NB == 1) ? sum[r] + __shfl_down(sum[r], 8, 64) : sum[r];   // hi + lo columns (the loads put the lo columns into 8 .. 15)
+    for (int r = 0; r < 4; ++r) v[r] = (NB == 1) ? with_rotated<8>(sum[r], op_add) : sum[r];   // hi + lo columns (the loads put the lo columns into 8 .. 15)
     const bool live = j < rows;          // NB == 1 implies rows <= 8, so live lanes hold the combined value
     if (NORM) {
 #pragma unroll
@@ -189,7 +185,7 @@ __device__ inline void epi_apply(const gemm_args &a, int strip, int lane, f32x4 
             float o[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float partner = __shfl_xor(v[r], 16, 64);
+                const float partner = of_lane16(v[r], side);
                 o[r] = side ? v[r] * p.cs[r].x + partner * p.cs[r].y : v[r] * p.cs[r].x - partner * p.cs[r].y;
             }
             if (live) {
@@ -220,7 +216,7 @@ __device__ inline void epi_apply(const gemm_args &a, int strip, int lane, f32x4 
         float act[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float up = __shfl_xor(v[r], 16, 64);
+            const float up = of_lane16(v[r], g & 1);
             act[r] = v[r] / (1.0f + expf(-v[r])) * up;
         }
         if (live && !(g & 1)) store_operand4<NB>(a.xop_act, a.F, j, strip * 8 + 4 * (g >> 1), act, a.rows);
@@ -233,11 +229,13 @@ __device__ inline void epi_apply(const gemm_args &a, int strip, int lane, f32x4 
             const float val = (v[r] == v[r]) ? v[r] : -INFINITY;
             if (val > bv || (val == bv && n + r < bi)) { bv = val; bi = n + r; }
         }
-#pragma unroll
-        for (int o = 16; o <= 32; o <<= 1) {
-            const float ov = __shfl_xor(bv, o, 64); const int oi = __shfl_xor(bi, o, 64);
-            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-        }
+        auto better = [&](auto sv, auto si) {                       // this lane's candidate or the other's
+            const float v0 = __uint_as_float(sv[0]), v1 = __uint_as_float(sv[1]);
+            const bool first = v0 > v1 || (v0 == v1 && (int)si[0] < (int)si[1]);
+            bv = first ? v0 : v1; bi = (int)(first ? si[0] : si[1]);
+        };
+        better(__builtin_amdgcn_permlane16_swap(__float_as_uint(bv), __float_as_uint(bv), false, false), __builtin_amdgcn_permlane16_swap((uint32_t)bi, (uint32_t)bi, false, false));
+        better(__builtin_amdgcn_permlane32_swap(__float_as_uint(bv), __float_as_uint(bv), false, false), __builtin_amdgcn_permlane32_swap((uint32_t)bi, (uint32_t)bi, false, false));
         // candidates are stored row-major ([16][vocab/16]) so that the reduction over strips reads contiguously
         if (lane < 16) { const size_t o = (size_t)j * (a.vocab >> 4) + strip; a.pmax_val[o] = bv; a.pmax_idx[o] = bi; }
     }

@@ -65,6 +65,33 @@ template <typename T> __device__ inline const T *uniform_ptr(const T *p)
     return (const T *)((uint64_t)hi << 32 | lo);
 }
 
+// The other lane's value combined with the own one, for lanes 16 or 32 apart, or n apart within a row of 16 (a rotation): vector instructions, where a shuffle goes through LDS (some
+// 120 cycles each, and they come in chains).
+template <typename F> __device__ inline float with_lane32(float v, F op)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <typename F> __device__ inline float with_lane16(float v, F op)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <int N, typename F> __device__ inline float with_rotated(float v, F op) { return op(v, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x120 + N, 0xF, 0xF, true))); }
+template <typename F> __device__ inline float over_wave(float v, F op)
+{
+    v = with_rotated<1>(v, op); v = with_rotated<2>(v, op); v = with_rotated<4>(v, op); v = with_rotated<8>(v, op);
+    return with_lane32(with_lane16(v, op), op);
+}
+__device__ inline float op_max(float a, float b) { return fmaxf(a, b); }
+__device__ inline float op_add(float a, float b) { return a + b; }
+// the value of the lane 16 further on (even rows of 16 lanes) or 16 back (odd ones)
+__device__ inline float of_lane16(float v, bool odd)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(odd ? r[0] : r[1]);
+}
+
 // ------------------------------------------------------------------------------------------
 // Operand writers.  Element (row j, K-index k) of an activation lives at
 //   arr[(k/32)*512 + (j%16 + 16*((k%32)/8))*8 + k%8]            (NB == 2: rows in column tiles of 16, tile j/16 has a hi
@@ -110,24 +137,3 @@ __device__ inline void store_operand4(uint16_t *xop, int K, int j, int k0, const
 // row, its neighbours the next rows: 256 bytes for 16 lanes.  With each row's features in one piece every lane had a line of its own, and the address path, which takes a cycle a line and 16
 // lanes, a third of k_attn's time (eight rows, groups of four heads).
 __device__ inline size_t q_at(int h, int j, int e, int hd, int rows) { return (((size_t)h * (hd >> 3) + (e >> 3)) * rows + j) * 8 + (e & 7); }
-
-// The other lane's value combined with the own one, for lanes 16 or 32 apart, or n apart within a row of 16 (a rotation): vector instructions, where a shuffle goes through LDS (some
-// 120 cycles each, and they come in chains).
-template <typename F> __device__ inline float with_lane32(float v, F op)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-template <typename F> __device__ inline float with_lane16(float v, F op)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-template <int N, typename F> __device__ inline float with_rotated(float v, F op) { return op(v, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x120 + N, 0xF, 0xF, true))); }
-template <typename F> __device__ inline float over_wave(float v, F op)
-{
-    v = with_rotated<1>(v, op); v = with_rotated<2>(v, op); v = with_rotated<4>(v, op); v = with_rotated<8>(v, op);
-    return with_lane32(with_lane16(v, op), op);
-}
-__device__ inline float op_max(float a, float b) { return fmaxf(a, b); }
-__device__ inline float op_add(float a, float b) { return a + b; }

@@ -684,13 +684,15 @@ k_gemm_wide(const gemm_args a)
 // ------------------------------------------------------------------------------------------
 template <int NB, int S, int EPI, int NW = 8>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NB == 2 && S == 7) ? 2 : 4, (NB == 2 && S == 7) ? 2 : 4)))
-k_gemm_q4(const gemm_args a)
+k_gemm_q4(const gemm_args a, int bps, float4 *part)
 {
     static_assert(S <= NW, "one epilogue wave per strip");
     constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LMHEAD);
     constexpr bool EARLY = S <= 4;                              // the epilogue's inputs are fetched beside the first batch (more strips: no registers for them)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int KT = a.ktiles, nb4 = KT >> 2, nst = (nb4 + NW - 1) / NW;      // batches of a wave: wave, wave + NW, ... (some waves' last one is past the end)
+    constexpr bool CUT = EPI == EPI_RESID;                      // (may be cut along K: blockIdx.y; the sums then go to part, for k_tile_finish)
+    const int KT = a.ktiles, nb4 = KT >> 2, b0 = CUT ? (int)blockIdx.y * bps : 0, b1 = CUT ? min(nb4, b0 + bps) : nb4;      // this slice's batches (not none: the launch sees to it)
+    const int nst = (b1 - b0 + NW - 1) / NW;                    // batches of a wave: wave, wave + NW, ... (some waves' last one is past the end)
     const int rot = (int)((blockIdx.x * 5u) % (unsigned)nst);   // workgroups start at different ones, or all would stream from addresses a power of two apart
     const int strip0 = blockIdx.x * S, mine = min(S, a.nstrips - strip0);   // (strips past the end re-read the last one; dropped below)
     __shared__ f32x4 red[NW][S][64];
@@ -710,8 +712,8 @@ k_gemm_q4(const gemm_args a)
     struct place { uint32_t off, offx, offs; };
     const uint32_t sl8 = (uint32_t)min(lane >> 3, mine - 1) * qs + 1024 + (lane & 7) * 16;
     auto place_of = [&](int i) {
-        const int k = i + rot, t = (k < nst ? k : k - nst) * NW + wave;
-        const bool in = t < nb4;                                // (past the end: codes, scales and activations of zero, nothing fetched)
+        const int k = i + rot, t = b0 + (k < nst ? k : k - nst) * NW + wave;
+        const bool in = t < b1;                                 // (past the end: codes, scales and activations of zero, nothing fetched)
         return place{in ? (uint32_t)t * PV_Q4_BATCH : BUFFER_END, xl + (in ? (uint32_t)t * 4 * xs : BUFFER_END), in ? (uint32_t)t * PV_Q4_BATCH + sl8 : BUFFER_END};
     };
     auto load_strip = [&](place p, int si) {
@@ -800,6 +802,15 @@ k_gemm_q4(const gemm_args a)
     f32x4 v = red[0][wave][lane];                               // the waves' sums in wave order
 #pragma unroll
     for (int w = 1; w < NW; ++w) v += red[w][wave][lane];
+    if (CUT && part != nullptr) {
+        const size_t at = (size_t)blockIdx.y * a.nstrips + strip0 + wave;
+        if (NB == 1) {                                          // hi and lo columns together: half a KiB a strip
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = with_rotated<8>(v[r], op_add);
+            if (!(lane & 8)) part[at * 32 + (lane >> 4) * 8 + (lane & 7)] = make_float4(v[0], v[1], v[2], v[3]);
+        } else part[at * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+        return;
+    }
     if (!EARLY) epi_prefetch<EPI>(a, strip0 + wave, lane, pre, 0);
     if (NORM) {
         auto col = [&](int w) { return NB == 1 ? ssq_s[w][lane & 7] + ssq_s[w][8 + (lane & 7)] : ssq_s[w][lane & 15]; };   // (two halves of a strip: emit_x)
@@ -1124,7 +1135,7 @@ k_gemm_tile_q4(const gemm_args a, int bps, float4 *part)
 // per (strip, column tile), the four waves of a workgroup take four strips of column tile
 // blockIdx.y.  At most TILE_MAX_SLICES slices: their loads go out together.
 #define TILE_MAX_SLICES 16
-template <int CT, int EPI>
+template <int CT, int EPI, int NB = 2>
 __global__ void __launch_bounds__(256)
 k_tile_finish(const gemm_args a, const float4 *part, int slices)
 {
@@ -1137,8 +1148,16 @@ k_tile_finish(const gemm_args a, const float4 *part, int slices)
     ssq_loads<4> sl;
     if (NORM) ssq_issue(a.ssq + (size_t)ct * a.ssq_parts * 16, a.ssq_parts, threadIdx.x, NW * 64, sl);
     float4 p[TILE_MAX_SLICES];
+    // (packed rows: hi and lo columns have been added up, 32 lanes a strip)
+    const float4 *q = NB == 1 ? part + (size_t)strip * 32 + (lane >> 4) * 8 + (lane & 7) : part + ((size_t)strip * CT + ct) * 64 + lane;
+    const size_t step = (size_t)a.nstrips * (NB == 1 ? 32 : CT * 64);
+    auto fetch = [&](int y0, int y1) {
 #pragma unroll
-    for (int y = 0; y < TILE_MAX_SLICES; ++y) p[y] = part[(((size_t)(y < slices ? y : 0) * a.nstrips + strip) * CT + ct) * 64 + lane];
+        for (int y = 0; y < TILE_MAX_SLICES; ++y) if (y >= y0 && y < y1) p[y] = q[(size_t)(y < slices ? y : 0) * step];
+    };
+    fetch(0, 4);
+    if (slices > 4) fetch(4, 8);
+    if (slices > 8) fetch(8, TILE_MAX_SLICES);
     epi_pre pre;
     epi_prefetch<EPI>(a, strip, lane, pre, ct);
     if (NORM) {
@@ -1154,7 +1173,8 @@ k_tile_finish(const gemm_args a, const float4 *part, int slices)
 #pragma unroll
     for (int y = 1; y < TILE_MAX_SLICES; ++y)
         if (y < slices) { v.x += p[y].x; v.y += p[y].y; v.z += p[y].z; v.w += p[y].w; }
-    if (mine) epi_apply<2, EPI>(a, strip, lane, (f32x4){v.x, v.y, v.z, v.w}, pre, ct);   // (wave-uniform; no barrier inside)
+    if (NB == 1 && (lane & 8)) v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (mine) epi_apply<NB, EPI>(a, strip, lane, (f32x4){v.x, v.y, v.z, v.w}, pre, ct);   // (wave-uniform; no barrier inside)
 }
 
 // ------------------------------- host side ----------------------------------------
@@ -1309,6 +1329,24 @@ static bool q4_unshared(const pv_model *m, int strips, int ktiles, q4_split q)
     return q.S == 7 && 8 * q.S * q.rounds * slices <= 7 * there;
 }
 
+// Output and down projections: K-slices for k_gemm_q4, four strips a workgroup and one workgroup a CU, or 1.  Uncut, a CU reads the whole operand (4 bytes a row and feature, 64 as
+// 16-row tiles) for one or two strips of codes (9 bytes a strip and feature); cut, its share of it for four, and k_tile_finish follows, some 3.5 us in all.  So what counts is the operand that a CU
+// no longer reads, few rows as 18 bytes a feature (their waves have few bytes in flight).  us, uncut / cut, 256 strips: 8 rows, K = 4096 5.8 / 6.9, 8192 8.8 / 8.3, 14336 13.4 / 11.4, 28672
+// 24.0 / 16.0; 13 rows, K = 2048 5.0 / 7.0, 4096 7.4 / 7.2, 8192 12.0 / 9.1, 14336 19.2 / 12.9, 28672 35.4 / 19.4; 1 row, 8192 7.5 / 7.8, 14336 11.0 / 10.9, 28672 19.1 / 14.8; 512 strips: 8 rows,
+// 8192 10.9 / 11.3, 14336 16.9 / 16.2, 28672 30.9 / 26.8; 13 rows, 4096 8.7 / 9.1, 8192 14.8 / 13.2, 28672 44.0 / 33.5; 1 row, 14336 14.5 / 15.0, 28672 26.2 / 24.4.  Where the
+// groups are no multiple of eight, cut ones take 0.6 us more (200 strips, 8 rows, K = 8192 8.7 / 9.0; 65 strips, 13 rows, K = 4096 6.9 / 7.4; 400 strips, 13 rows, K = 8192 14.4 / 12.9).
+// These are chains of one projection; between a step's other kernels the sum takes another us (four 8B-shaped layers, one row, uncut / cut 229 / 233 us a step), hence lines a little further out.
+// Steps of four layers, us: 8B shape, 13 rows 296 -> 290, 8 rows 257 -> 253, 70B shape, 8 rows 514 -> 501.
+static int q4_slices(const pv_model *m, int strips, int ktiles, int rows, const float *part)
+{
+    const int groups = (strips + 3) / 4;
+    if (part == nullptr || !pv_offsets_fit(ktiles) || 2 * groups > m->n_cus) return 1;
+    const int slices = min(min(TILE_MAX_SLICES, m->n_cus / groups), ktiles / 32);       // (a batch for each of eight waves)
+    if (slices < 2) return 1;
+    const double operand = 32.0 * ktiles * (rows <= 8 ? max(4 * rows, 18) : 64);
+    return operand * (slices - 1) / slices >= (groups % 8 == 0 ? 280e3 : 340e3) ? slices : 1;
+}
+
 // Eight waves, two workgroups a CU where there are that many.  Sixteen waves and one or two strips up to 4 rows, whose operand is small (K = 14336, 256 strips 16.4 -> 13.8; 8
 // rows 16.8 and 16.5), but not below K = 2048, where sixteen waves have no batch each: 4 rows, K = 512, 256 strips 7.4 against
 // 6.7, 512 strips 8.2 against 7.3, K = 1024 7.4 and 8.3 against 6.8 and 7.4, K = 2048 7.7 and 8.5 against 7.7 and 8.7.
@@ -1319,17 +1357,17 @@ static int launch_q4(const gemm_args &ga, int strips, q4_split q, hipStream_t s)
     bool done = false;
     if constexpr (NB == 1) {
         if (q.S <= 2 && ga.rows <= 4 && ga.ktiles >= 64) {
-            if (q.S == 1) k_gemm_q4<NB, 1, EPI, 16><<<groups, 1024, 0, s>>>(ga);
-            else k_gemm_q4<NB, 2, EPI, 16><<<groups, 1024, 0, s>>>(ga);
+            if (q.S == 1) k_gemm_q4<NB, 1, EPI, 16><<<groups, 1024, 0, s>>>(ga, ga.ktiles >> 2, nullptr);
+            else k_gemm_q4<NB, 2, EPI, 16><<<groups, 1024, 0, s>>>(ga, ga.ktiles >> 2, nullptr);
             done = true;
         }
     }
     if (done) ;
-    else if (q.S == 1) k_gemm_q4<NB, 1, EPI><<<groups, 512, 0, s>>>(ga);
-    else if (q.S == 2) k_gemm_q4<NB, 2, EPI><<<groups, 512, 0, s>>>(ga);
-    else if (q.S == 3) k_gemm_q4<NB, 3, EPI><<<groups, 512, 0, s>>>(ga);
-    else if (q.S == 4) k_gemm_q4<NB, 4, EPI><<<groups, 512, 0, s>>>(ga);
-    else if constexpr (q4_seven<NB, EPI>()) k_gemm_q4<NB, 7, EPI><<<groups, 512, 0, s>>>(ga);
+    else if (q.S == 1) k_gemm_q4<NB, 1, EPI><<<groups, 512, 0, s>>>(ga, ga.ktiles >> 2, nullptr);
+    else if (q.S == 2) k_gemm_q4<NB, 2, EPI><<<groups, 512, 0, s>>>(ga, ga.ktiles >> 2, nullptr);
+    else if (q.S == 3) k_gemm_q4<NB, 3, EPI><<<groups, 512, 0, s>>>(ga, ga.ktiles >> 2, nullptr);
+    else if (q.S == 4) k_gemm_q4<NB, 4, EPI><<<groups, 512, 0, s>>>(ga, ga.ktiles >> 2, nullptr);
+    else if constexpr (q4_seven<NB, EPI>()) k_gemm_q4<NB, 7, EPI><<<groups, 512, 0, s>>>(ga, ga.ktiles >> 2, nullptr);
     PV_HIP(hipGetLastError());
     return PV_OK;
 }
@@ -1344,6 +1382,18 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
     ga.interleave = g.ktiles > 128 || (NB == 1 && EPI == EPI_LMHEAD && strips >= 2048);
     if (m->wbits == 4) {
         if constexpr (CT == 1) {
+            if constexpr (EPI == EPI_RESID) {
+                const int cut = q4_slices(m, strips, g.ktiles, NB == 1 ? g.rows : 16, g.tile_part);
+                if (cut > 1) {
+                    const int nb4 = g.ktiles >> 2, bps = (nb4 + cut - 1) / cut, slices = (nb4 + bps - 1) / bps;
+                    float4 *part = (float4 *)g.tile_part;
+                    k_gemm_q4<NB, 4, EPI><<<dim3((strips + 3) / 4, slices), 512, 0, s>>>(ga, bps, part);
+                    PV_HIP(hipGetLastError());
+                    k_tile_finish<1, EPI, NB><<<dim3((strips + 3) / 4, 1), 256, 0, s>>>(ga, part, slices);
+                    PV_HIP(hipGetLastError());
+                    return PV_OK;
+                }
+            }
             const q4_split q = q4_strips(m, strips, g.ktiles, NB == 1 ? g.rows : 16, q4_seven<NB, EPI>());
             if (NB == 1 || q4_unshared(m, strips, g.ktiles, q)) return launch_q4<NB, EPI>(ga, strips, q, s);
         }

@@ -169,7 +169,7 @@ int pv_mat_repack_q4(const pv_model *m, const pv_tensor_ref &t, int kind, int64_
 
 // Block set-up on the matrix path: embedding rows -> x, first operand, first sum of squares;
 // rotary table for positions len .. len+rows-1.  The draft ids come straight from the cache's
-// pinned host mailbox; the first workgroup copies them, the row count and the mode into the
+// pinned host mailbox; one workgroup copies them, the row count and the mode into the
 // device state for the kernels that follow.
 template <int NB>
 __global__ void __launch_bounds__(64)
@@ -178,7 +178,11 @@ k_mat_begin(pv_dev_state *st, const int32_t *mailbox, int rows, int mode, const 
 {
     const int lane = threadIdx.x, ct = blockIdx.y, j = ct * 16 + (lane & 15), g = lane >> 4, strip = blockIdx.x;
     const int nseq = st->blk.n_seq;
-    const bool tree = mode == PV_MODE_TREE;
+    const bool tree = mode == PV_MODE_TREE, writes_rows = blockIdx.x == gridDim.x - 1 && ct == 0;
+    // The token ids come over the bus, the longest trip of all: asked for first, the rotary table meanwhile.  (The last workgroup along the strips writes the rows' state, the first ones
+    // the table.  8B shape, 8 rows, inside the kernel 4.5 -> 3.6 us.)
+    const int tok = j < rows ? mailbox[j] : 0, own = writes_rows && lane < rows ? mailbox[lane] : 0;
+    const uint2 gn = *(const uint2 *)(gain + strip * 16 + 4 * g);
     __shared__ int parent[PV_MAX_ROWS];               // draft tree: the parents follow the draft ids in the mailbox; one read each, then walked in LDS
     if (tree) { parent[lane] = lane < rows ? mailbox[PV_MAX_ROWS + lane] : -1; __syncthreads(); }
     // Cache slot of block row r: the cache's length + r, or in a batched step the length of the row's
@@ -187,10 +191,24 @@ k_mat_begin(pv_dev_state *st, const int32_t *mailbox, int rows, int mode, const 
     auto seq_of = [&](int r) { int sidx = 0; for (int k = 1; k < nseq; ++k) if (r >= st->blk.seq[k].row0) sidx = k; return sidx; };
     auto slot_of = [&](int r) { if (nseq <= 1) return st->len + r; const pv_seq_ref &sq = st->blk.seq[seq_of(r)]; return sq.st->len + r - sq.row0; };
     auto depth_of = [&](int r) { int dpt = 0; for (int q = parent[r]; q >= 0 && dpt < PV_MAX_ROWS; q = parent[q]) ++dpt; return dpt; };
-    if (blockIdx.x == 0 && ct == 0) {
-        for (int i = lane; i < rows; i += 64) {
+    if (ct == 0)
+        for (int idx = blockIdx.x * 64 + lane; idx < rows * half; idx += gridDim.x * 64) {
+            const int jj = idx / half, i = idx - jj * half;
+            double sn, cs;
+            sincos((double)(tree ? st->len + depth_of(jj) : slot_of(jj)) * inv_freq[i], &sn, &cs);
+            rope[idx] = make_float2((float)cs, (float)sn);
+        }
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (j < rows) {
+        const uint2 e = *(const uint2 *)(embed + (size_t)tok * d + strip * 16 + 4 * g);
+        v[0] = pv_bf16_to_f32((uint16_t)(e.x & 0xffffu)); v[1] = pv_bf16_to_f32((uint16_t)(e.x >> 16));
+        v[2] = pv_bf16_to_f32((uint16_t)(e.y & 0xffffu)); v[3] = pv_bf16_to_f32((uint16_t)(e.y >> 16));
+    }
+    emit_x<NB>(lane, rows, strip, d, v, gn, x, ssq, xop, ct, rows);
+    if (writes_rows) {
+        if (const int i = lane; i < rows) {           // (at most 64 rows)
             const int pos = slot_of(i);
-            st->draft[i] = mailbox[i]; st->rowpos[i] = pos;
+            st->draft[i] = own; st->rowpos[i] = pos;
             if (nseq <= 1) st->rowphys[i] = page_table[pos >> page_shift];
             else { const int sidx = seq_of(i); st->rowphys[i] = st->blk.seq[sidx].page_table[pos >> page_shift] | (sidx + 1) << PV_SEQ_TAG_SHIFT; }
             uint64_t m;
@@ -199,20 +217,6 @@ k_mat_begin(pv_dev_state *st, const int32_t *mailbox, int rows, int mode, const 
             st->rowmask[i] = m;
         }
         if (lane == 0) { st->gamma = rows; st->mode = mode; if (nseq <= 1) st->blk.seq[0].gamma = rows; }
-    }
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (j < rows) {
-        const uint16_t *e = embed + (size_t)mailbox[j] * d + strip * 16 + 4 * g;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = pv_bf16_to_f32(e[r]);
-    }
-    emit_x<NB>(lane, rows, strip, d, v, *(const uint2 *)(gain + strip * 16 + 4 * g), x, ssq, xop, ct, rows);
-    if (ct != 0) return;
-    for (int idx = blockIdx.x * 64 + lane; idx < rows * half; idx += gridDim.x * 64) {
-        const int jj = idx / half, i = idx - jj * half;
-        double sn, cs;
-        sincos((double)(tree ? st->len + depth_of(jj) : slot_of(jj)) * inv_freq[i], &sn, &cs);
-        rope[idx] = make_float2((float)cs, (float)sn);
     }
 }
 

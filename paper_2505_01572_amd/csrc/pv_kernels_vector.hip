@@ -6,11 +6,49 @@
 #include <type_traits>
 #include "pv_kernels_common.h"
 
-__device__ inline float wave_sum(float v)
+__device__ inline float wave_sum(float v) { return over_wave(v, op_add); }
+
+// The totals over the wave of N values (1, 4, 8 or 16); lane l is left with that of value l / (64 / N).  Two values share a register from the first exchange on, so 16 of them take some 50
+// vector instructions (six shuffles through LDS each before: 96, in chains of some 120 cycles a link).
+template <int N> __device__ inline float fold(const float (&v)[N], int lane)
 {
+    static_assert(N == 1 || N == 4 || N == 8 || N == 16, "");
+    auto both = [](const auto r) { return __uint_as_float(r[0]) + __uint_as_float(r[1]); };
+    auto two32 = [&](float a, float b) { return both(__builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false)); };
+    auto two16 = [&](float a, float b) { return both(__builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false)); };
+    auto select = [](bool c, float x, float y) { asm("" : "+v"(x), "+v"(y)); return c ? x : y; };      // (or the compiler makes an indexed load of it, from LDS)
+#define PV_PLUS_DPP(A, CTRL) ((A) + __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(A), CTRL, 0xF, 0xF, true)))      // row_ror:8 0x128, row_half_mirror 0x141, quad_perm [1,0,3,2] 0xB1 and [2,3,0,1] 0x4E
+    float a[N < 4 ? 1 : N / 2];
+    if constexpr (N == 1) a[0] = two16(two32(v[0], v[0]), two32(v[0], v[0]));
+    else {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+        for (int i = 0; i < N / 2; ++i) a[i] = two32(v[i], v[i + N / 2]);
+#pragma unroll
+        for (int i = 0; i < N / 4; ++i) a[i] = two16(a[i], a[i + N / 4]);
+    }
+#pragma unroll
+    for (int i = 0; i < (N < 4 ? 1 : N / 4); ++i) a[i] = PV_PLUS_DPP(a[i], 0x128);
+    if constexpr (N >= 8) {
+#pragma unroll
+        for (int i = 0; i < N / 8; ++i) a[i] = select(lane & 8, a[i + N / 8], a[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < (N < 8 ? 1 : N / 8); ++i) a[i] = PV_PLUS_DPP(a[i], 0x141);
+    if constexpr (N == 16) a[0] = select(lane & 4, a[1], a[0]);
+    a[0] = PV_PLUS_DPP(a[0], 0xB1);
+    return PV_PLUS_DPP(a[0], 0x4E);
+#undef PV_PLUS_DPP
+}
+// which value that is, and whether the lane is the first one that has it
+template <int N> __device__ inline int fold_row(int lane) { return lane / (64 / N); }
+template <int N> __device__ inline bool fold_first(int lane) { return lane % (64 / N) == 0; }
+
+// four consecutive stored elements
+__device__ inline float4 ld4(const float *p, size_t i) { return *(const float4 *)(p + i); }
+__device__ inline float4 ld4(const uint16_t *p, size_t i)
+{
+    const uint2 v = *(const uint2 *)(p + i);
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xFFFF0000u));
 }
 
 // ---- reductions over a workgroup of four waves, fixed order; red: 4 floats of LDS ----
@@ -26,8 +64,7 @@ __device__ inline float block_sum(float v, float *red)
 
 __device__ inline float block_max(float v, float *red)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+    v = over_wave(v, op_max);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     v = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
@@ -37,65 +74,67 @@ __device__ inline float block_max(float v, float *red)
 
 // The small models of this path are bound by launches and memory round trips, not bytes: a step of the tiny
 // configuration took 158 us in 28 kernels of 2..5 us (attention 27 us), with some 4 us between dependent ones.
-// (now 92 us in 13).  RMSNorm, the rotary embedding and the page writes, SwiGLU and the vocabulary arg-max ride in the
+// (now 70 us in 13, 16 rows 80, 64 rows 96; before the totals stayed on the vector ALU, the loads of a row went out at once and more than 16 rows came in one launch 79, 125 and 375).  RMSNorm, the rotary embedding and the page writes, SwiGLU and the vocabulary arg-max ride in the
 // projections: a wave that multiplies a weight row with the input rows passes over the whole rows
 // anyway and adds up their squares beside it (the norm's scale commutes with the dot product).
 
-// Dot products of G input rows x (times the gain) with M weight rows, and the rows' sums of squares, over one wavefront.
-// On return every lane has the totals.
+// Pieces of 256 features whose loads go out together: one trip to memory for rows of up to 1024 features where the registers hold that (688 features were three)
+template <int G> constexpr int pieces() { return G <= 4 ? 4 : G <= 8 ? 2 : 1; }
+
+// Dot products of G input rows x (times the gain) with M weight rows, and the rows' sums of squares, over one wavefront: of row
+// fold_row<G>(lane) on return.
 template <typename ST, int G, int M>
-__device__ inline void norm_dots(const ST *const (&w)[M], const ST *gain, const float *x, int K, int lane, float (&acc)[M][G], float (&ss)[G])
+__device__ inline void norm_dots(const ST *const (&w)[M], const ST *gain, const float *x, int K, int lane, float (&dot)[M], float &sq)
 {
+    constexpr int U = pieces<G>();
+    float acc[M][G], ss[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         ss[g] = 0.f;
 #pragma unroll
         for (int m = 0; m < M; ++m) acc[m][g] = 0.f;
     }
-    for (int k = lane * 4; k < K; k += 256) {
-        float wv[M][4];
+    for (int k0 = lane * 4; k0 < K; k0 += 256 * U) {
+        float4 wv[U][M], gn[U], v[U][G];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float gn = pv_ld(gain, k + r);
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + 256 * u;
+            if (u == 0 || k < K) {
+                gn[u] = ld4(gain, k);
 #pragma unroll
-            for (int m = 0; m < M; ++m) wv[m][r] = pv_ld(w[m], k + r) * gn;
+                for (int m = 0; m < M; ++m) wv[u][m] = ld4(w[m], k);
+#pragma unroll
+                for (int g = 0; g < G; ++g) v[u][g] = *(const float4 *)(x + (size_t)g * K + k);
+            }
         }
+        asm volatile("" ::: "memory");
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const float4 v = *(const float4 *)(x + (size_t)g * K + k);
-            ss[g] += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+        for (int u = 0; u < U; ++u) {
+            if (u > 0 && k0 + 256 * u >= K) break;
 #pragma unroll
-            for (int m = 0; m < M; ++m) acc[m][g] += v.x * wv[m][0] + v.y * wv[m][1] + v.z * wv[m][2] + v.w * wv[m][3];
+            for (int m = 0; m < M; ++m) wv[u][m] = make_float4(wv[u][m].x * gn[u].x, wv[u][m].y * gn[u].y, wv[u][m].z * gn[u].z, wv[u][m].w * gn[u].w);
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const float4 y = v[u][g];
+                ss[g] += (y.x * y.x + y.y * y.y) + (y.z * y.z + y.w * y.w);
+#pragma unroll
+                for (int m = 0; m < M; ++m) acc[m][g] += y.x * wv[u][m].x + y.y * wv[u][m].y + y.z * wv[u][m].z + y.w * wv[u][m].w;
+            }
         }
     }
+    sq = fold<G>(ss, lane);
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        ss[g] = wave_sum(ss[g]);
-#pragma unroll
-        for (int m = 0; m < M; ++m) acc[m][g] = wave_sum(acc[m][g]);
-    }
+    for (int m = 0; m < M; ++m) dot[m] = fold<G>(acc[m], lane);
 }
 
-// lane g picks its row's entry of an array that every lane holds
-template <int G>
-__device__ inline float pick(const float (&v)[G], int lane)
-{
-    float r = v[0];
-#pragma unroll
-    for (int g = 1; g < G; ++g) {
-        r = lane == g ? v[g] : r;
-        asm volatile("" : "+v"(r));                    // (or the compiler makes an indexed load of it, from scratch memory)
-    }
-    return r;
-}
+struct vec_norm { const void *gain; const float *x; int K, rows; float eps; };       // rows: of the whole block; a workgroup takes G of them, from G * blockIdx.y on (the buffers hold whole groups of 16)
 
-struct vec_norm { const void *gain; const float *x; int K, rows; float eps; };
 
 // RMSNorm + q, k, v projections + rotary embedding + append to the pages.  One wavefront per pair of outputs (i, i + head_dim / 2)
-// of a head; lane g finishes row g.  K page block: [token][head_dim]; V: [head_dim][token].
+// of a head; the first lane that has a row's totals finishes it.  K page block: [token][head_dim]; V: [head_dim][token].
 template <typename ST, int G>
 __global__ void __launch_bounds__(256)
-k_vec_qkv(const vec_norm a, const ST *Wq, const ST *Wk, const ST *Wv, const pv_dev_state *st, int row0, const int32_t *page_table, const float2 *rope,
+k_vec_qkv(const vec_norm a, const ST *Wq, const ST *Wk, const ST *Wv, const pv_dev_state *st, const int32_t *page_table, const float2 *rope,
           float *q, ST *pool, pv_kv_geom g, int layer, int n_q_heads)
 {
     const int lane = threadIdx.x & 63, hd = g.head_dim, half = hd >> 1;
@@ -104,19 +143,20 @@ k_vec_qkv(const vec_norm a, const ST *Wq, const ST *Wk, const ST *Wv, const pv_d
     const int kind = h < n_q_heads ? 0 : h < n_q_heads + g.n_kv_heads ? 1 : 2, hh = kind == 0 ? h : kind == 1 ? h - n_q_heads : h - n_q_heads - g.n_kv_heads;
     const ST *W = (kind == 0 ? Wq : kind == 1 ? Wk : Wv) + ((size_t)hh * hd + i) * a.K;
     const ST *const w[2] = {W, W + (size_t)half * a.K};
-    const int j = row0 + lane;
+    const int row0 = blockIdx.y * G, j = row0 + fold_row<G>(lane);
+    const bool mine = fold_first<G>(lane) && j < a.rows;
     int pos = 0, phys = 0;
     float2 cs = make_float2(1.f, 0.f);
-    if (lane < a.rows) {                               // on their way while the dot products are taken
+    if (mine) {                               // on their way while the dot products are taken
         pos = st->len + j;
         if (kind != 0) phys = page_table[pos >> g.page_shift];
         if (kind != 2) cs = rope[(size_t)j * half + i];
     }
-    float acc[2][G], ss[G];
-    norm_dots<ST, G, 2>(w, (const ST *)a.gain, a.x, a.K, lane, acc, ss);
-    if (lane >= a.rows) return;
-    const float r = 1.0f / sqrtf(pick<G>(ss, lane) / (float)a.K + a.eps);
-    const float u = pick<G>(acc[0], lane) * r, v = pick<G>(acc[1], lane) * r;
+    float dot[2], sq;
+    norm_dots<ST, G, 2>(w, (const ST *)a.gain, a.x + (size_t)row0 * a.K, a.K, lane, dot, sq);
+    if (!mine) return;
+    const float r = 1.0f / sqrtf(sq / (float)a.K + a.eps);
+    const float u = dot[0] * r, v = dot[1] * r;
     const float ru = u * cs.x - v * cs.y, rv = v * cs.x + u * cs.y;
     const int tok = pos & (g.page_tokens - 1);
     if (kind == 0) {
@@ -139,12 +179,12 @@ k_vec_gateup(const vec_norm a, const ST *Wg, const ST *Wu, float *act, int F)
     const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (n >= F) return;
     const ST *const w[2] = {Wg + (size_t)n * a.K, Wu + (size_t)n * a.K};
-    float acc[2][G], ss[G];
-    norm_dots<ST, G, 2>(w, (const ST *)a.gain, a.x, a.K, lane, acc, ss);
-    if (lane >= a.rows) return;
-    const float r = 1.0f / sqrtf(pick<G>(ss, lane) / (float)a.K + a.eps);
-    const float z = pick<G>(acc[0], lane) * r;
-    act[(size_t)lane * F + n] = z / (1.0f + expf(-z)) * (pick<G>(acc[1], lane) * r);
+    float dot[2], sq;
+    const int row0 = blockIdx.y * G, row = row0 + fold_row<G>(lane);
+    norm_dots<ST, G, 2>(w, (const ST *)a.gain, a.x + (size_t)row0 * a.K, a.K, lane, dot, sq);
+    if (!fold_first<G>(lane) || row >= a.rows) return;
+    const float r = 1.0f / sqrtf(sq / (float)a.K + a.eps), z = dot[0] * r;
+    act[(size_t)row * F + n] = z / (1.0f + expf(-z)) * (dot[1] * r);
 }
 
 // Final RMSNorm + vocabulary projection; a workgroup takes the outputs 4 b + wave, 4 (b + gridDim.x) + wave, ... and leaves
@@ -153,30 +193,33 @@ template <typename ST, int G>
 __global__ void __launch_bounds__(256)
 k_vec_head(const vec_norm a, const ST *W, float *logits, int N, float *cand_val, int32_t *cand_idx)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row0 = blockIdx.y * G, in = fold_row<G>(lane), row = row0 + in;
+    const bool mine = fold_first<G>(lane) && row < a.rows;
     float bv = -INFINITY; int bi = 0x7fffffff;
     for (int n = blockIdx.x * 4 + wave; n < N; n += gridDim.x * 4) {
         const ST *const w[1] = {W + (size_t)n * a.K};
-        float acc[1][G], ss[G];
-        norm_dots<ST, G, 1>(w, (const ST *)a.gain, a.x, a.K, lane, acc, ss);
-        if (lane < a.rows) {
-            const float r = 1.0f / sqrtf(pick<G>(ss, lane) / (float)a.K + a.eps);
-            float v = pick<G>(acc[0], lane) * r;
-            logits[(size_t)lane * N + n] = v;
+        float dot[1], sq;
+        norm_dots<ST, G, 1>(w, (const ST *)a.gain, a.x + (size_t)row0 * a.K, a.K, lane, dot, sq);
+        if (mine) {
+            const float r = 1.0f / sqrtf(sq / (float)a.K + a.eps);
+            float v = dot[0] * r;
+            logits[(size_t)row * N + n] = v;
             v = (v == v) ? v : -INFINITY;
             if (v > bv || (v == bv && n < bi)) { bv = v; bi = n; }
         }
     }
     __shared__ float sv[4][16];
     __shared__ int si[4][16];
-    if (lane < 16) { sv[wave][lane] = bv; si[wave][lane] = bi; }
+    if (fold_first<G>(lane)) { sv[wave][in] = bv; si[wave][in] = bi; }
     __syncthreads();
-    if ((int)threadIdx.x < a.rows) {
+    if ((int)threadIdx.x < min(G, a.rows - row0)) {
+        bv = sv[0][threadIdx.x]; bi = si[0][threadIdx.x];
         for (int w = 1; w < 4; ++w) {
             const float v = sv[w][threadIdx.x]; const int i = si[w][threadIdx.x];
             if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
         }
-        cand_val[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = bv; cand_idx[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = bi;
+        const size_t at = (size_t)(row0 + threadIdx.x) * gridDim.x + blockIdx.x;
+        cand_val[at] = bv; cand_idx[at] = bi;
     }
 }
 
@@ -190,31 +233,36 @@ k_linear(const ST *W, const float *x, const float *res, float *y, int N, int K, 
     const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (n >= N) return;
     const ST *w = W + (size_t)n * K;
+    constexpr int U = pieces<G>();
+    const int row0 = blockIdx.y * G, row = row0 + fold_row<G>(lane);
+    x += (size_t)row0 * K;
+    const bool mine = fold_first<G>(lane) && row < rows;
+    float before = 0.f;
+    if (mine) before = res[(size_t)row * N + n];       // (on its way while the dot products are taken)
     float acc[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) acc[g] = 0.f;
-    for (int k = lane * 4; k < K; k += 256) {
-        const float w0 = pv_ld(w, k), w1 = pv_ld(w, k + 1), w2 = pv_ld(w, k + 2), w3 = pv_ld(w, k + 3);
+    for (int k0 = lane * 4; k0 < K; k0 += 256 * U) {
+        float4 wv[U], v[U][G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const float4 xv = *(const float4 *)(x + (size_t)g * K + k);
-            acc[g] += xv.x * w0 + xv.y * w1 + xv.z * w2 + xv.w * w3;
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + 256 * u;
+            if (u == 0 || k < K) {
+                wv[u] = ld4(w, k);
+#pragma unroll
+                for (int g = 0; g < G; ++g) v[u][g] = *(const float4 *)(x + (size_t)g * K + k);
+            }
+        }
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u > 0 && k0 + 256 * u >= K) break;
+#pragma unroll
+            for (int g = 0; g < G; ++g) acc[g] += v[u][g].x * wv[u].x + v[u][g].y * wv[u].y + v[u][g].z * wv[u].z + v[u][g].w * wv[u].w;
         }
     }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        float a = acc[g];
-        for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
-        if (lane == 0 && g < rows) y[(size_t)g * N + n] = res[(size_t)g * N + n] + a;
-    }
-}
-
-// four consecutive stored elements
-__device__ inline float4 ld4(const float *p, size_t i) { return *(const float4 *)(p + i); }
-__device__ inline float4 ld4(const uint16_t *p, size_t i)
-{
-    const uint2 v = *(const uint2 *)(p + i);
-    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xFFFF0000u));
+    const float total = fold<G>(acc, lane);
+    if (mine) y[(size_t)row * N + n] = before + total;
 }
 
 // Causal attention for one (query head, row): keys 0 .. len+j, 128 at a time, streaming softmax.  K/V come from the paged pool.  Bound by latency: so the pages of 1024 keys
@@ -272,8 +320,7 @@ k_attention(const pv_dev_state *st, const int32_t *page_table, const float *q, c
         __syncthreads();
         const float s0 = s[lane], s1 = s[64 + lane];
         float mn = fmaxf(m, fmaxf(s0, s1));
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) mn = fmaxf(mn, __shfl_xor(mn, d, 64));
+        mn = over_wave(mn, op_max);
         const float w0 = expf(s0 - mn), w1 = expf(s1 - mn), resc = expf(m - mn);
         pw[wave][lane] = w0; pw[wave][64 + lane] = w1;               // (the wave's own copy: no barrier)
         l = l * resc + wave_sum(w0 + w1);
@@ -365,39 +412,25 @@ k_attention_any(const pv_dev_state *st, const int32_t *page_table, const float *
 
 // ------------------------------- host side ----------------------------------------
 
+// calls f(G, groups) once: G the smallest of 1, 4, 8, 16 that holds the rows, more than 16 as groups of 16 in one launch (one after the other, 40 rows: 147 -> 92 us a step of the tiny configuration)
+template <typename F>
+static int row_groups(int rows, F f)
+{
+    if (rows <= 1) f(std::integral_constant<int, 1>(), 1u);
+    else if (rows <= 4) f(std::integral_constant<int, 4>(), 1u);
+    else if (rows <= 8) f(std::integral_constant<int, 8>(), 1u);
+    else f(std::integral_constant<int, 16>(), (unsigned)((rows + 15) / 16));
+    PV_HIP(hipGetLastError());
+    return PV_OK;
+}
+
 template <typename ST>
 static int launch_linear(const pv_model *m, const pv_tensor_ref &t, const float *x, const float *res, float *y,
                          int rows, hipStream_t s)
 {
     const ST *W = (const ST *)(m->d_weights + t.off);
     const int N = (int)t.rows, K = (int)t.cols;
-    const unsigned grid = (unsigned)((N + 3) / 4);
-    for (int r0 = 0; r0 < rows; r0 += 16) {
-        const int r = rows - r0 < 16 ? rows - r0 : 16;
-        const float *xr = x + (size_t)r0 * K, *rr = res + (size_t)r0 * N;
-        float *yr = y + (size_t)r0 * N;
-        if (r <= 1) k_linear<ST, 1><<<grid, 256, 0, s>>>(W, xr, rr, yr, N, K, r);
-        else if (r <= 4) k_linear<ST, 4><<<grid, 256, 0, s>>>(W, xr, rr, yr, N, K, r);
-        else if (r <= 8) k_linear<ST, 8><<<grid, 256, 0, s>>>(W, xr, rr, yr, N, K, r);
-        else k_linear<ST, 16><<<grid, 256, 0, s>>>(W, xr, rr, yr, N, K, r);
-        PV_HIP(hipGetLastError());
-    }
-    return PV_OK;
-}
-
-// calls f(G, first row, rows) for every group of at most 16 rows; G: the smallest of 1, 4, 8, 16 that holds them
-template <typename F>
-static int row_groups(int rows, F f)
-{
-    for (int r0 = 0; r0 < rows; r0 += 16) {
-        const int r = rows - r0 < 16 ? rows - r0 : 16;
-        if (r <= 1) f(std::integral_constant<int, 1>(), r0, r);
-        else if (r <= 4) f(std::integral_constant<int, 4>(), r0, r);
-        else if (r <= 8) f(std::integral_constant<int, 8>(), r0, r);
-        else f(std::integral_constant<int, 16>(), r0, r);
-        PV_HIP(hipGetLastError());
-    }
-    return PV_OK;
+    return row_groups(rows, [&](auto G, unsigned groups) { k_linear<ST, G.value><<<dim3((unsigned)((N + 3) / 4), groups), 256, 0, s>>>(W, x, res, y, N, K, rows); });
 }
 
 template <typename ST>
@@ -410,13 +443,13 @@ static int run_block(pv_cache *c, hipStream_t s)
     const pv_kv_geom g = pv_geom(c);
     pv_ws &w = c->ws;
     auto wt = [&](int kind, int l) { return (const ST *)(m->d_weights + pv_tref(m, kind, l).off); };
-    auto normed = [&](const ST *gain, int r0, int r) { return vec_norm{gain, w.x + (size_t)r0 * d, d, r, (float)f.rms_eps}; };
+    auto normed = [&](const ST *gain) { return vec_norm{gain, w.x, d, rows, (float)f.rms_eps}; };
     int rc;
     if ((rc = pv_k_begin(c, rows_pad, s)) != PV_OK) return rc;
     for (int l = 0; l < f.n_layers; ++l) {
         const int units = (f.n_q_heads + 2 * f.n_kv_heads) * (f.head_dim / 2);
-        rc = row_groups(rows, [&](auto G, int r0, int r) {
-            k_vec_qkv<ST, G.value><<<(units + 3) / 4, 256, 0, s>>>(normed(wt(PV_T_ATTN_NORM, l), r0, r), wt(PV_T_WQ, l), wt(PV_T_WK, l), wt(PV_T_WV, l), w.state, r0,
+        rc = row_groups(rows, [&](auto G, unsigned groups) {
+            k_vec_qkv<ST, G.value><<<dim3((units + 3) / 4, groups), 256, 0, s>>>(normed(wt(PV_T_ATTN_NORM, l)), wt(PV_T_WQ, l), wt(PV_T_WK, l), wt(PV_T_WV, l), w.state,
                                                                    w.page_table, w.rope, w.q, (ST *)c->d_pool, g, l, f.n_q_heads);
         });
         if (rc != PV_OK) return rc;
@@ -428,8 +461,8 @@ static int run_block(pv_cache *c, hipStream_t s)
         else attention(k_attention_any<ST>);
         PV_HIP(hipGetLastError());
         if ((rc = launch_linear<ST>(m, pv_tref(m, PV_T_WO, l), w.attn, w.x, w.x, rows, s)) != PV_OK) return rc;
-        rc = row_groups(rows, [&](auto G, int r0, int r) {
-            k_vec_gateup<ST, G.value><<<(F + 3) / 4, 256, 0, s>>>(normed(wt(PV_T_FFN_NORM, l), r0, r), wt(PV_T_WG, l), wt(PV_T_WU, l), w.gate + (size_t)r0 * F, F);
+        rc = row_groups(rows, [&](auto G, unsigned groups) {
+            k_vec_gateup<ST, G.value><<<dim3((F + 3) / 4, groups), 256, 0, s>>>(normed(wt(PV_T_FFN_NORM, l)), wt(PV_T_WG, l), wt(PV_T_WU, l), w.gate, F);
         });
         if (rc != PV_OK) return rc;
         if ((rc = launch_linear<ST>(m, pv_tref(m, PV_T_WD, l), w.gate, w.x, w.x, rows, s)) != PV_OK) return rc;
@@ -437,9 +470,9 @@ static int run_block(pv_cache *c, hipStream_t s)
     if (c->io->hdr[3] == PV_MODE_PREFILL_MID) return pv_k_finish(c, rows, nullptr, nullptr, 0, s);
     // the candidates ([row][strips]) go where gate and up were
     const int strips = std::min((V + 3) / 4, F);
-    rc = row_groups(rows, [&](auto G, int r0, int r) {
-        k_vec_head<ST, G.value><<<strips, 256, 0, s>>>(normed((const ST *)(m->d_weights + m->global[PV_T_FINAL_NORM].off), r0, r), (const ST *)(m->d_weights + m->global[PV_T_LM_HEAD].off),
-                                                       w.logits + (size_t)r0 * V, V, w.gate + (size_t)r0 * strips, (int32_t *)w.up + (size_t)r0 * strips);
+    rc = row_groups(rows, [&](auto G, unsigned groups) {
+        k_vec_head<ST, G.value><<<dim3(strips, groups), 256, 0, s>>>(normed((const ST *)(m->d_weights + m->global[PV_T_FINAL_NORM].off)), (const ST *)(m->d_weights + m->global[PV_T_LM_HEAD].off),
+                                                       w.logits, V, w.gate, (int32_t *)w.up);
     });
     if (rc != PV_OK) return rc;
     return pv_k_finish(c, rows, w.gate, (const int32_t *)w.up, strips, s);

@@ -65,33 +65,6 @@ template <typename T> __device__ inline const T *uniform_ptr(const T *p)
     return (const T *)((uint64_t)hi << 32 | lo);
 }
 
-// The other lane's value combined with the own one, for lanes 16 or 32 apart, or n apart within a row of 16 (a rotation): vector instructions, where a shuffle goes through LDS (some
-// 120 cycles each, and they come in chains).
-template <typename F> __device__ inline float with_lane32(float v, F op)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-template <typename F> __device__ inline float with_lane16(float v, F op)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-template <int N, typename F> __device__ inline float with_rotated(float v, F op) { return op(v, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x120 + N, 0xF, 0xF, true))); }
-template <typename F> __device__ inline float over_wave(float v, F op)
-{
-    v = with_rotated<1>(v, op); v = with_rotated<2>(v, op); v = with_rotated<4>(v, op); v = with_rotated<8>(v, op);
-    return with_lane32(with_lane16(v, op), op);
-}
-__device__ inline float op_max(float a, float b) { return fmaxf(a, b); }
-__device__ inline float op_add(float a, float b) { return a + b; }
-// the value of the lane 16 further on (even rows of 16 lanes) or 16 back (odd ones)
-__device__ inline float of_lane16(float v, bool odd)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(odd ? r[0] : r[1]);
-}
-
 // ------------------------------------------------------------------------------------------
 // Operand writers.  Element (row j, K-index k) of an activation lives at
 //   arr[(k/32)*512 + (j%16 + 16*((k%32)/8))*8 + k%8]            (NB == 2: rows in column tiles of 16, tile j/16 has a hi

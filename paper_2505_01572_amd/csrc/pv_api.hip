@@ -281,7 +281,8 @@ static int model_complete(const pv_model *m)
 }
 
 // ---- workspace layout ----
-static size_t layout_ws(const pv_model *m, int rows_cap, int units_cap, int n_pages, pv_ws *w, char *base)
+// slices: pv_mat_part_floats
+static size_t layout_ws(const pv_model *m, int rows_cap, int units_cap, int n_pages, pv_ws *w, char *base, bool slices = true)
 {
     const pv_model_config &c = m->cfg;
     size_t off = 0;
@@ -297,7 +298,7 @@ static size_t layout_ws(const pv_model *m, int rows_cap, int units_cap, int n_pa
     p = take(4 * R * c.ffn_dim); if (w) w->gate = (float *)p;
     p = take(4 * R * c.ffn_dim); if (w) w->up = (float *)p;
     p = take(4 * R * (size_t)c.vocab); if (w) w->logits = (float *)p;
-    const size_t pf = m->path >= PV_PATH_MATRIX ? pv_mat_part_floats(m, rows_cap, units_cap, n_pages * m->cfg.page_tokens) : 0;
+    const size_t pf = m->path >= PV_PATH_MATRIX ? pv_mat_part_floats(m, rows_cap, units_cap, n_pages * m->cfg.page_tokens, slices) : 0;
     p = take(4 * pf + 256); if (w) { w->part = (float *)p; w->part_floats = pf; }
     return off;
 }
@@ -704,7 +705,9 @@ extern "C" int pv_verify_async_static(pv_cache *c, int32_t prefix_len, const int
     // as a workspace; the cache state and the page table stay where the cache keeps them)
     const int cap = (gamma + PV_ROW_PAD - 1) / PV_ROW_PAD * PV_ROW_PAD;
     const int ucap = m->path >= PV_PATH_MATRIX ? pv_attn_units(m, cap) : 0;          // one sequence: no batch allowance
-    const size_t need = layout_ws(m, cap, ucap, c->n_pages, nullptr, nullptr);
+    size_t need = layout_ws(m, cap, ucap, c->n_pages, nullptr, nullptr);
+    const bool slices = need <= PV_STATIC_SCRATCH_BYTES;         // (no room for K-slices' sums: a step without them, as before there were any)
+    if (!slices) need = layout_ws(m, cap, ucap, c->n_pages, nullptr, nullptr, false);
     if (need > PV_STATIC_SCRATCH_BYTES) {
         pv_set_error("a %d-row step of this model with max_tokens %d needs %zu bytes of per-step buffers, the fixed array holds %zu",
                      gamma, c->max_tokens, need, (size_t)PV_STATIC_SCRATCH_BYTES);
@@ -718,7 +721,7 @@ extern "C" int pv_verify_async_static(pv_cache *c, int32_t prefix_len, const int
     PV_HIP(hipGetLastError());
     const pv_ws own = c->ws;
     const int own_cap = c->rows_cap, own_ucap = c->units_cap;
-    layout_ws(m, cap, ucap, c->n_pages, &c->ws, base);
+    layout_ws(m, cap, ucap, c->n_pages, &c->ws, base, slices);
     c->ws.state = own.state; c->ws.page_table = own.page_table;
     c->rows_cap = cap; c->units_cap = ucap;
     for (int j = 0; j < gamma; ++j)

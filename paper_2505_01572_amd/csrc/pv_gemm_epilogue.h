@@ -4,7 +4,7 @@
 #pragma once
 #include "pv_matrix_common.h"
 
-enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3 };
+enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3, EPI_PART = 4 };      // (EPI_PART: none, the sums of a K-slice)
 
 struct gemm_args {
     const uint4 *W;             // tiled region, strip-major

@@ -192,7 +192,7 @@ static inline bool pv_packs_rows(const pv_model *m, int rows)
 {
     return rows <= 8 && pv_offsets_fit(m->cfg.d_model / 32) && pv_offsets_fit(m->cfg.n_q_heads * m->cfg.head_dim / 32) && pv_offsets_fit(m->cfg.ffn_dim / 32);
 }
-size_t pv_mat_part_floats(const pv_model *m, int rows_cap, int units_cap, int max_tokens);
+size_t pv_mat_part_floats(const pv_model *m, int rows_cap, int units_cap, int max_tokens, bool slices);
 size_t pv_attn_part_floats(const pv_model *m, int units_cap, int max_tokens);
 int pv_attn_units(const pv_model *m, int rows);              // attention row-group units of one sequence with `rows` rows
 int pv_mat_attention_init(int head_dim);

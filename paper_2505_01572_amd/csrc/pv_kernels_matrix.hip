@@ -46,10 +46,13 @@ static inline int col_tiles(int rows) { return rows <= 16 ? 1 : rows <= 32 ? 2 :
 // workgroup; fewer with 8), i.e. 2 Mi floats per column tile; 24 MiB in all, which the launches stay under.
 static const size_t TILE_PART_FLOATS = (size_t)6 << 20;
 static inline size_t tile_part_floats(int col_tiles) { return std::min(TILE_PART_FLOATS, (size_t)col_tiles << 21); }
-// blocks that use those kernels: more than 16 rows, or any block of more than 8 rows with 4-bit weights
+// blocks that use those kernels: more than 16 rows, or any block with 4-bit weights
 static inline bool tile_part_needed(const pv_model *m, int col_tiles) { return col_tiles >= 2 || m->wbits == 4; }
+// 16-bit weights and up to 16 rows, where O and down projections are cut (cut_slices): at most a group of four strips and a slice per CU
+static inline size_t cut_part_floats(const pv_model *m) { return (size_t)m->n_cus * 4 * 256; }
 
-static size_t mat_ws_layout(const pv_model *m, int rows_cap, int units_cap, int max_tokens, float *base, mat_ws *w)
+// slices: with room for the sums of cut projections in a layout of up to 16 rows; without it (have: the floats that there are) these projections stay whole
+static size_t mat_ws_layout(const pv_model *m, int rows_cap, int units_cap, int max_tokens, bool slices, float *base, mat_ws *w, size_t have = 0)
 {
     const pv_model_config &f = m->cfg;
     const int qd = f.n_q_heads * f.head_dim;
@@ -66,12 +69,12 @@ static size_t mat_ws_layout(const pv_model *m, int rows_cap, int units_cap, int 
     p = take(ctc * (size_t)f.vocab); if (w) w->pmax_val = p;
     p = take(ctc * (size_t)f.vocab); if (w) w->pmax_idx = (int32_t *)p;
     p = take(pv_attn_part_floats(m, units_cap, max_tokens)); if (w) w->attn_part = p;
-    const size_t tp = tile_part_needed(m, (int)ctc) ? tile_part_floats((int)ctc) : 0;
-    p = take(tp); if (w) w->tile_part = tp ? p : nullptr;  // (none: the launches then do not slice)
+    const size_t tp = tile_part_needed(m, (int)ctc) ? tile_part_floats((int)ctc) : slices ? cut_part_floats(m) : 0;
+    p = take(tp); if (w) w->tile_part = tp && off <= have ? p : nullptr;  // (none: the launches then do not slice)
     return off;
 }
 
-size_t pv_mat_part_floats(const pv_model *m, int rows_cap, int units_cap, int max_tokens) { return mat_ws_layout(m, rows_cap, units_cap, max_tokens, nullptr, nullptr); }
+size_t pv_mat_part_floats(const pv_model *m, int rows_cap, int units_cap, int max_tokens, bool slices) { return mat_ws_layout(m, rows_cap, units_cap, max_tokens, slices, nullptr, nullptr); }
 
 // ------------------------------------------------------------------------------------------
 // Weight repack: rows [row_begin, row_begin+row_count) of one tensor, row-major in staging,
@@ -550,7 +553,7 @@ k_gemm(const gemm_args a)
 }
 
 // ------------------------------------------------------------------------------------------
-// Projections with three or more strips a CU (gate/up, the vocabulary, the QKV projection without shared heads), 9..64 rows (NB = 2: CT column
+// Projections with three or more strips a CU (gate/up, the vocabulary, the QKV projection without shared heads; others cut along K), 9..64 rows (NB = 2: CT column
 // tiles of 16 rows, a hi and a lo operand each; which of them: wide_strips), and up to 8 (NB = 1) with more than four and up to seven strips a CU (packed_wide): one workgroup per CU owns S strips and its NW waves split K, so
 // that each activation tile enters the CU once, for S strips, and straight into the registers of the one wave
 // that uses it: no LDS and no barrier before the final sum over the waves.
@@ -559,6 +562,7 @@ k_gemm(const gemm_args a)
 // for 1792 strips).  Two K-tiles per wave (one used, one on its way) are enough for that; three or four measured the same.
 // 8B-shaped gate/up, 235 MB, us: 16 rows 45.6 (two strips a workgroup) -> 37.5, 32 rows 43.8 (k_gemm_tile) -> 41.0, 48 rows 52.2 -> 46.8 (three
 // column tiles instead of four; 64 rows 53.2 -> 50.3); 1024-strip vocabulary 26.1 -> 24.0, 34.2 -> 26.5, 39.0 -> 31.1, 39.8 -> 37.8.
+// Output and down projections of up to half as many groups of four strips as CUs are cut along K over blockIdx.y (EPI_PART: the sums go to `part` and k_tile_finish adds them in slice order): cut_slices.
 // Loads go through buffer descriptors: a K-tile past the end of the slice gets an offset past the buffer's end,
 // for which zeros come back and nothing is fetched, so every load of the loop is unconditional.
 // ------------------------------------------------------------------------------------------
@@ -570,14 +574,16 @@ static inline bool wide_fits(int ktiles) { return ktiles <= (1 << 16); }        
 
 template <int NB, int CT, int S, int EPI>
 __global__ void __launch_bounds__(wide_waves(CT, S) * 64) __attribute__((amdgpu_waves_per_eu(wide_waves(CT, S) / 4, wide_waves(CT, S) / 4)))
-k_gemm_wide(const gemm_args a)
+k_gemm_wide(const gemm_args a, int tps, float4 *part)
 {
     static_assert(NB == 2 || CT == 1, "packed rows come in one tile");
+    constexpr bool CUT = (EPI == EPI_PART);                     // blockIdx.y: a slice of tps K-tiles, its sums go to `part`
     constexpr int NW = wide_waves(CT, S), NX = NB == 1 ? 1 : 2 * CT;
     constexpr bool NORM = (EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LMHEAD);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int KT = a.ktiles, nst = (KT + NW - 1) / NW;          // K-tiles of a wave: wave, wave + NW, ... (some waves' last one is past the end)
-    const int rot = (int)((blockIdx.x * 5u) % (unsigned)nst);   // workgroups start at different ones, or all would stream from addresses a power of two apart
+    const int KT = a.ktiles, t0 = CUT ? blockIdx.y * tps : 0, t1 = CUT ? min(KT, t0 + tps) : KT;
+    const int nst = (t1 - t0 + NW - 1) / NW;                    // K-tiles of a wave: wave, wave + NW, ... (some waves' last one is past the end)
+    const int rot = (int)((blockIdx.x * 5u + (CUT ? blockIdx.y * 3u : 0u)) % (unsigned)nst);   // workgroups start at different ones, or all would stream from addresses a power of two apart
     const int strip0 = blockIdx.x * S;
     extern __shared__ f32x4 wide_red[];                         // [NW][S * CT][64]
     __shared__ float ssq_s[NW][CT][16];
@@ -607,8 +613,8 @@ k_gemm_wide(const gemm_args a)
         for (int ct = 0; ct < CT; ++ct) acc[si][ct] = tot[si][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
     struct stage { uint4 w[S], x[NX]; };
     auto issue = [&](stage &q, int i) {
-        const int k = i + rot, t = (k < nst ? k : k - nst) * NW + wave;
-        const bool in = i < nst && t < KT;
+        const int k = i + rot, t = t0 + (k < nst ? k : k - nst) * NW + wave;
+        const bool in = i < nst && t < t1;
         const uint32_t off = lane * 16 + (in ? (uint32_t)t * 1024 : BUFFER_END), offx = xl + (in ? (uint32_t)t * xs : BUFFER_END);
 #pragma unroll
         for (int si = 0; si < S; ++si) q.w[si] = buffer_load16<LOAD_ONCE>(W, off, wo[si]);
@@ -656,6 +662,14 @@ k_gemm_wide(const gemm_args a)
         f32x4 v = wide_red[u * 64 + lane];
 #pragma unroll
         for (int w = 1; w < NW; ++w) v += wide_red[(w * S * CT + u) * 64 + lane];
+        if constexpr (CUT) {
+            const size_t at = ((size_t)blockIdx.y * a.nstrips + strip0 + si) * CT + ct;
+            if (NB == 1) {                                      // hi and lo columns together: half a KiB a strip
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = with_rotated<8>(v[r], op_add);
+                if (!(lane & 8)) part[at * 32 + (lane >> 4) * 8 + (lane & 7)] = make_float4(v[0], v[1], v[2], v[3]);
+            } else part[at * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
         epi_pre pre;
         epi_prefetch<EPI>(a, strip0 + si, lane, pre, ct);
         if (NORM) {
@@ -666,6 +680,7 @@ k_gemm_wide(const gemm_args a)
             pre.rj = 1.0f / sqrtf(s * a.inv_d + a.eps);
         }
         epi_apply<NB, EPI>(a, strip0 + si, lane, v, pre, ct);
+        }
     }
 }
 
@@ -942,7 +957,7 @@ k_gemm_tile(const gemm_args a, int tps, float4 *part)
         for (int si = 0; si < S; ++si)
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
-                if (sw + si < a.nstrips) part[(((size_t)blockIdx.y * a.nstrips + sw + si) * CT + ct) * 64 + lane] = make_float4(tot[si][ct][0], tot[si][ct][1], tot[si][ct][2], tot[si][ct][3]);
+                if (sw + si < a.nstrips) store_through(&part[(((size_t)blockIdx.y * a.nstrips + sw + si) * CT + ct) * 64 + lane], tot[si][ct]);
         return;
     }
     __syncthreads();                                  // (ssq_s of every wave; also covers a slice of a single step)
@@ -1119,7 +1134,7 @@ k_gemm_tile_q4(const gemm_args a, int bps, float4 *part)
         for (int ct = 0; ct < CT; ++ct) {
             const f32x4 v = si == 0 ? acc0[ct] : acc1[ct];
             if (part != nullptr) {
-                part[(((size_t)blockIdx.y * a.nstrips + strip) * CT + ct) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+                store_through(&part[(((size_t)blockIdx.y * a.nstrips + strip) * CT + ct) * 64 + lane], v);
                 continue;
             }
             epi_pre pre;
@@ -1267,7 +1282,7 @@ static int allow_wide_all()
 template <int NB, int CT, int EPI, int S>
 static int launch_wide_s(const gemm_args &ga, int strips, hipStream_t s)
 {
-    k_gemm_wide<NB, CT, S, EPI><<<(strips + S - 1) / S, wide_waves(CT, S) * 64, wide_lds(CT, S), s>>>(ga);
+    k_gemm_wide<NB, CT, S, EPI><<<(strips + S - 1) / S, wide_waves(CT, S) * 64, wide_lds(CT, S), s>>>(ga, ga.ktiles, nullptr);
     PV_HIP(hipGetLastError());
     return PV_OK;
 }
@@ -1293,6 +1308,8 @@ int pv_mat_gemm_init(int wbits)
         if ((rc = allow_tile_q4<1>()) != PV_OK || (rc = allow_tile_q4<2>()) != PV_OK) return rc;
         return allow_tile_q4<4>();
     }
+    if ((rc = allow_wide_lds<1, 1, 4, EPI_PART>()) != PV_OK || (rc = allow_wide_lds<2, 1, 4, EPI_PART>()) != PV_OK || (rc = allow_wide_lds<2, 2, 4, EPI_PART>()) != PV_OK ||
+        (rc = allow_wide_lds<2, 3, 4, EPI_PART>()) != PV_OK || (rc = allow_wide_lds<2, 4, 4, EPI_PART>()) != PV_OK) return rc;
     if ((rc = allow_wide<1, 1>()) != PV_OK || (rc = allow_wide<2, 1>()) != PV_OK || (rc = allow_wide<2, 2>()) != PV_OK || (rc = allow_wide<2, 3>()) != PV_OK) return rc;
     return allow_wide<2, 4>();
 }
@@ -1349,6 +1366,54 @@ static int q4_slices(const pv_model *m, int strips, int ktiles, int rows, const 
     if (slices < 2) return 1;
     const double operand = 32.0 * ktiles * (rows <= 8 ? max(4 * rows, 18) : 64);
     return operand * (slices - 1) / slices >= (groups % 8 == 0 ? 280e3 : 340e3) ? slices : 1;
+}
+
+// Output and down projections, 16-bit weights: K-slices for k_gemm_wide, four strips a workgroup and at most one workgroup a CU, or 1.
+// Up to 16 rows: whole, a CU reads all of the operand for each of its strips, and with 257 strips some CUs go through two; cut, its share of it once for four strips, and k_tile_finish
+// follows.  Both sides of 250 sizes (32 to 516 strips, K = 2048 to 28672, 1, 4, 8 and 13 rows) lie within some 6 % of 2.7 us (cut, with the sum: 5.3) plus the larger of what the busiest CU takes
+// in at 59 GB/s, strips and operand, and the chip's weights at 7.64 TB/s, with a smooth step between them (both).  us, whole / cut: 256 strips, 13 rows, K = 4096 9.7 / 9.8, 8192 16.9 /
+// 14.5, 14336 27.8 / 22.0, 28672 52.9 / 39.9, 8 rows, 14336 21.6 / 21.4, 28672 40.9 / 38.0; 128 strips, 13 rows, 4096 8.7 / 7.3, 8192 15.4 / 9.6, 8 rows, 8192 10.3 / 9.6, 14336 16.2 / 13.2; 320
+// strips, 13 rows, 4096 15.5 / 11.3, 8 rows, 8192 21.8 / 17.4; 512 strips, 13 rows, 14336 41.1 / 41.1, 28672 80.2 / 74.5; one row, 256 strips, 14336 18.9 / 21.6, 64 strips 12.6 / 9.3.
+// These are chains of one projection; between a step's other kernels the sum takes another 1.2 us, and the line leaves as much again.  Steps of four layers, us: 8B shape, 13 rows 472 -> 453,
+// 7B shape 411 -> 401, 70B shape (two layers) 636 -> 628; 1B shape, 12 rows, eight layers 560 -> 525.
+static int cut_slices(const pv_model *m, int strips, int ktiles, int rows, const float *part)
+{
+    const int cus = m->n_cus, groups = (strips + 3) / 4;
+    if (part == nullptr || !wide_fits(ktiles) || 2 * groups > cus) return 1;
+    const int slices = min(TILE_MAX_SLICES, cus / groups);
+    const double K = 32.0 * ktiles, operand = rows > 8 ? 64.0 : rows > 2 ? 4.0 * rows : 10.5;       // bytes a feature (one and two rows: the waves have few bytes in flight)
+    const bool halves = rows <= 8 && ktiles >= 64 && 2 * strips <= cus, two = strips >= 512;
+    const int wgs = halves ? 2 * strips : two ? (strips + 1) / 2 : strips, rounds = (wgs + cus - 1) / cus;
+    const double hbm = strips * 32.0 * K / 7.64e6;
+    auto both = [&](double load) { return pow(pow(load / 59.2e3, 2.73) + pow(hbm, 2.73), 1 / 2.73); };
+    const double whole = both(rounds * ((halves ? 16 : two ? 64 : 32) + operand) * K), cut = both((128 + operand) * K / slices);
+    return whole - cut > 2.6 + 2.1 ? slices : 1;
+}
+
+// 17..64 rows: against k_gemm_tile, whose workgroups take eight strips and half as long slices, so that twice as many sums are written and read (4 MiB with 32 rows and 256 strips), but half
+// as much of the operand: up to 1024 features a slice, a multiple of eight groups.  us, there / here, 32 and 64 rows: 256 strips, K = 2048 10.0 / 8.4, 13.4 / 10.1, 4096 12.0 / 10.9, 15.9 / 14.0, 8192
+// 16.6 / 16.8, 20.1 / 22.2; 128 strips, 8192 12.1 / 10.9, 15.9 / 14.1, 14336 15.9 / 16.0, 20.1 / 21.9; 64 strips, 14336 13.1 / 11.0, 16.0 / 14.7; 512 strips, 2048 14.8 / 12.1, 18.0 / 14.6, 4096
+// 18.0 / 17.8, 21.3 / 22.9; 25 groups, 2048 8.0 / 8.2, 9.8 / 10.8, 33 groups, 4096 9.5 / 10.0, 12.4 / 13.1.  Four layers of the 8B shape, us a step, with stores that go through: 4 x 8 rows 542 -> 533, 48
+// nodes 593 -> 579.
+static int cut_slices_shared(const pv_model *m, int strips, int ktiles, const float *part)
+{
+    const int groups = (strips + 3) / 4;
+    if (part == nullptr || !wide_fits(ktiles) || groups % 8 != 0 || 2 * groups > m->n_cus) return 1;
+    const int slices = min(TILE_MAX_SLICES, m->n_cus / groups);
+    return ktiles <= 32 * slices ? slices : 1;
+}
+
+template <int NB, int CT, int EPI>
+static int launch_cut(const gemm_args &ga, int strips, int slices, hipStream_t s)
+{
+    const int tps = (ga.ktiles + slices - 1) / slices, groups = (strips + 3) / 4;
+    slices = (ga.ktiles + tps - 1) / tps;                        // (none empty)
+    float4 *part = (float4 *)ga.tile_part;
+    k_gemm_wide<NB, CT, 4, EPI_PART><<<dim3(groups, slices), wide_waves(CT, 4) * 64, wide_lds(CT, 4), s>>>(ga, tps, part);
+    PV_HIP(hipGetLastError());
+    k_tile_finish<CT, EPI, NB><<<dim3(groups, CT), 256, 0, s>>>(ga, part, slices);
+    PV_HIP(hipGetLastError());
+    return PV_OK;
 }
 
 // Eight waves, two workgroups a CU where there are that many.  Sixteen waves and one or two strips up to 4 rows, whose operand is small (K = 14336, 256 strips 16.4 -> 13.8; 8
@@ -1430,6 +1495,10 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
         if constexpr (EPI != EPI_RESID) {
             const int ws = wide_strips(m, strips, g.ktiles, CT);
             if (ws) return launch_wide<NB, CT, EPI>(ga, strips, ws, s);
+        }
+        if constexpr (EPI == EPI_RESID) {
+            const int cut = CT == 1 ? cut_slices(m, strips, g.ktiles, 16, g.tile_part) : cut_slices_shared(m, strips, g.ktiles, g.tile_part);
+            if (cut > 1) return launch_cut<NB, CT, EPI>(ga, strips, cut, s);
         }
         if constexpr (CT >= 2) {
             // Activation tiles shared through LDS; few strips: cut along K, into at most 256 workgroups, one a CU: with a few more (288 for the
@@ -1525,6 +1594,8 @@ static int launch_gemm(const pv_model *m, const gemm_args &g, int strips, hipStr
                 PV_HIP(hipGetLastError());
                 return PV_OK;
             }
+            const int cut = cut_slices(m, strips, g.ktiles, g.rows, g.tile_part);
+            if (cut > 1) return launch_cut<NB, CT, EPI>(ga, strips, cut, s);
             if (g.ktiles >= 64 && 2 * strips <= m->n_cus) {
                 ga.half_base = 0;
                 k_gemm<NB, CT, 1, EPI, 8, 3, true><<<2 * strips, 512, 0, s>>>(ga);
@@ -1571,7 +1642,7 @@ static int run_block(pv_cache *c, hipStream_t s)
     const pv_model_config &f = m->cfg;
     const int rows = c->last_rows, d = f.d_model, hd = f.head_dim, qd = f.n_q_heads * hd, kvd = f.n_kv_heads * hd, F = f.ffn_dim;
     mat_ws mw;
-    mat_ws_layout(m, c->rows_cap, c->units_cap, c->n_pages * f.page_tokens, c->ws.part, &mw);
+    mat_ws_layout(m, c->rows_cap, c->units_cap, c->n_pages * f.page_tokens, true, c->ws.part, &mw, c->ws.part_floats);
     const char *Wb = m->d_weights;
     auto gainp = [&](int kind, int l) { return (const uint16_t *)(Wb + pv_tref(m, kind, l).off); };
 
@@ -1650,7 +1721,7 @@ int pv_mat_run_prompt(pv_cache *c, int rows, int keep, hipStream_t s)
     const pv_model *m = c->m;
     const pv_model_config &f = m->cfg;
     mat_ws mw;
-    mat_ws_layout(m, c->rows_cap, c->units_cap, c->n_pages * f.page_tokens, c->ws.part, &mw);
+    mat_ws_layout(m, c->rows_cap, c->units_cap, c->n_pages * f.page_tokens, true, c->ws.part, &mw, c->ws.part_floats);
     pv_pre_out out;
     int rc = pv_pre_block(c, c->d_io->prompt, rows, keep, &out, s);
     if (rc != PV_OK || keep == 0) return rc;

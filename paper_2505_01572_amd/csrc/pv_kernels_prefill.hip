@@ -578,11 +578,44 @@ k_pre_gemm_h4(const gemm_args a, const pre_gemm_args p)
     }
 }
 
-// An operand's rows as scaled f16 pairs, in place.  First the largest |hi| of each row, PRE_MAX_PARTS pieces of K side by side; then the conversion.
+// RMSNorm scales of a row tile from the per-strip sums of squares ([row tile][strips][16]): once per row instead of once per workgroup of the GEMM that follows.  One workgroup of NT threads: thread
+// t adds the strips t / 16, t / 16 + NT / 16, ... of row t % 16, eight loads at a time.  Bound by its chain, so few trips to
+// memory (256 strips 5.5 -> 4.7 us between other kernels, 2.5 of them the start); with 4-bit weights k_pre_rowmax does it beside its own work.  Prompts, three or four layers: 8B shape, 100 tokens 1219 -> 1190
+// us, 4-bit, 349 tokens 2100 -> 2052; 231 tokens of a 2080-wide model 741 -> 723; 2048 tokens 6383 -> 6363.
+template <int NT>
+__device__ inline void pre_rscale(const float *ssq, float *rscale, int ct, int strips, float inv_d, float eps)
+{
+    __shared__ float s[NT / 64][16];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const float *q = ssq + (size_t)ct * strips * 16 + threadIdx.x;
+    float v = 0.f;
+    for (int i0 = threadIdx.x >> 4; i0 < strips; i0 += NT / 2) {
+        float p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) p[u] = q[(size_t)(i0 - (threadIdx.x >> 4) + (i0 + u * (NT / 16) < strips ? u * (NT / 16) : 0)) * 16];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) if (i0 + u * (NT / 16) < strips) v += p[u];
+    }
+    v = with_lane32(with_lane16(v, op_add), op_add);
+    if (lane < 16) s[wave][lane] = v;
+    __syncthreads();
+    if (threadIdx.x < 16) {
+        v = s[0][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < NT / 64; ++w) v += s[w][threadIdx.x];
+        rscale[ct * 16 + threadIdx.x] = 1.0f / sqrtf(v * inv_d + eps);
+    }
+}
+
+__global__ void __launch_bounds__(1024)
+k_pre_rscale(const float *ssq, float *rscale, int strips, float inv_d, float eps) { pre_rscale<1024>(ssq, rscale, blockIdx.x, strips, inv_d, eps); }
+
+// An operand's rows as scaled f16 pairs, in place.  First the largest |hi| of each row, PRE_MAX_PARTS pieces of K side by side (and beside them, where an RMSNorm scales the rows, that); then the conversion.
 #define PRE_MAX_PARTS 16
 __global__ void __launch_bounds__(256)
-k_pre_rowmax(const uint4 *xop, int ktiles, float *part, int part_rows)
+k_pre_rowmax(const uint4 *xop, int ktiles, float *part, int part_rows, const float *ssq, float *rscale, int strips, float inv_d, float eps)
 {
+    if (blockIdx.x == PRE_MAX_PARTS) { pre_rscale<256>(ssq, rscale, blockIdx.y, strips, inv_d, eps); return; }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ct = blockIdx.y;
     const int per = (ktiles + PRE_MAX_PARTS - 1) / PRE_MAX_PARTS, t0 = blockIdx.x * per, t1 = min(ktiles, t0 + per);
     const uint4 *q = xop + (size_t)2 * ct * ktiles * 64 + lane;
@@ -602,6 +635,10 @@ __global__ void __launch_bounds__(256)
 k_pre_to_f16(uint4 *xop, int ktiles, const float *part, int part_rows, float *rinv)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ct = blockIdx.y, row = ct * 16 + (lane & 15);
+    const int t = blockIdx.x * 4 + wave;
+    uint4 *q = xop + ((size_t)2 * ct * ktiles + min(t, ktiles - 1)) * 64 + lane;
+    uint4 *ql = q + (size_t)ktiles * 64;
+    const uint4 hi = *q, lo = *ql;                     // (with the maxima: one trip to memory)
     uint32_t m = 0;
 #pragma unroll
     for (int i = 0; i < PRE_MAX_PARTS; ++i) m = max(m, __float_as_uint(part[(size_t)i * part_rows + row]));
@@ -609,11 +646,7 @@ k_pre_to_f16(uint4 *xop, int ktiles, const float *part, int part_rows, float *ri
     const int e = (int)(m >> 23) - 127, up = m == 0 || e == 128 ? 0 : 14 - max(e, -100);
     const float f = __uint_as_float((uint32_t)(127 + up) << 23), inv = __uint_as_float((uint32_t)(127 - up) << 23);
     if (blockIdx.x == 0 && threadIdx.x < 16) rinv[row] = inv;
-    const int t = blockIdx.x * 4 + wave;
     if (t >= ktiles) return;
-    uint4 *q = xop + ((size_t)2 * ct * ktiles + t) * 64 + lane;
-    uint4 *ql = q + (size_t)ktiles * 64;
-    const uint4 hi = *q, lo = *ql;
     uint4 oh, ol;
     auto conv = [&](uint32_t h, uint32_t l, uint32_t &rh, uint32_t &rl) {
         const float x0 = (__uint_as_float(h << 16) + __uint_as_float(l << 16)) * f, x1 = (__uint_as_float(h & 0xFFFF0000u) + __uint_as_float(l & 0xFFFF0000u)) * f;
@@ -672,23 +705,6 @@ k_pre_embed(int rows, int len, const int32_t *tokens, const uint16_t *embed, con
         double sn, cs;
         sincos((double)(len + jj) * inv_freq[i], &sn, &cs);
         rope[idx] = make_float2((float)cs, (float)sn);
-    }
-}
-
-// RMSNorm scales of the block's rows from the per-strip sums of squares ([row tile][strips][16]): once per row instead
-// of once per workgroup of the GEMM that follows.  One workgroup per row tile: thread t adds the strips t / 16, t / 16 + 16, ... of row t % 16.
-__global__ void __launch_bounds__(256)
-k_pre_rscale(const float *ssq, float *rscale, int strips, float inv_d, float eps)
-{
-    __shared__ float s[256];
-    const float *q = ssq + (size_t)blockIdx.x * strips * 16 + threadIdx.x;
-    float v = 0.f;
-    for (int i = threadIdx.x >> 4; i < strips; i += 16, q += 256) v += *q;
-    s[threadIdx.x] = v;
-    __syncthreads();
-    if (threadIdx.x < 16) {
-        for (int i = 1; i < 16; ++i) v += s[i * 16 + threadIdx.x];
-        rscale[blockIdx.x * 16 + threadIdx.x] = 1.0f / sqrtf(v * inv_d + eps);
     }
 }
 
@@ -1015,7 +1031,7 @@ int pv_pre_init(const pv_model *m)
 }
 
 template <int EPI>
-static int pre_gemm(const pv_model *m, const gemm_args &g, bool wide, int strips, const float *rscale, float *rowsum, int rows, int len, size_t part_floats, hipStream_t s)
+static int pre_gemm(const pv_model *m, const gemm_args &g, bool wide, int strips, float *rscale, float *rowsum, int rows, int len, size_t part_floats, hipStream_t s)
 {
     const int mtiles = (rows + 15) / 16;
     gemm_args ga = g;
@@ -1026,7 +1042,7 @@ static int pre_gemm(const pv_model *m, const gemm_args &g, bool wide, int strips
     if (h4) {
         float *rinv = rowsum, *part = rowsum + (mtiles + 7) / 8 * 128;       // (in the place of the row sums)
         pa.rinv = rinv;
-        k_pre_rowmax<<<dim3(PRE_MAX_PARTS, mtiles), 256, 0, s>>>(g.xop, g.ktiles, part, mtiles * 16);
+        k_pre_rowmax<<<dim3(PRE_MAX_PARTS + (rscale != nullptr), mtiles), 256, 0, s>>>(g.xop, g.ktiles, part, mtiles * 16, g.ssq, rscale, g.ssq_parts, g.inv_d, g.eps);
         PV_HIP(hipGetLastError());
         k_pre_to_f16<<<dim3((g.ktiles + 3) / 4, mtiles), 256, 0, s>>>((uint4 *)g.xop, g.ktiles, part, mtiles * 16, rinv);
         PV_HIP(hipGetLastError());
@@ -1100,12 +1116,18 @@ int pv_pre_block(pv_cache *c, const int32_t *d_host_tokens, int rows, int keep, 
     at.scale2 = 1.44269504088896340736f / sqrtf((float)hd); at.xop_o = w.xop_o;
 
     int rc;
-    for (int l = 0; l < f.n_layers; ++l) {
-        k_pre_rscale<<<mtiles, 256, 0, s>>>(w.ssq, w.rscale, d / 16, g.inv_d, g.eps);
+    auto rscale = [&](bool wide_w) -> int {
+        if (m->wbits == 4 && !wide_w) return PV_OK;         // (k_pre_rowmax does it)
+        k_pre_rscale<<<mtiles, 1024, 0, s>>>(w.ssq, w.rscale, d / 16, g.inv_d, g.eps);
         PV_HIP(hipGetLastError());
+        return PV_OK;
+    };
+    for (int l = 0; l < f.n_layers; ++l) {
+        const bool wide_qkv = wide(PV_T_WQ, l) || wide(PV_T_WK, l) || wide(PV_T_WV, l), wide_gu = wide(PV_T_WG, l) || wide(PV_T_WU, l);
+        if ((rc = rscale(wide_qkv)) != PV_OK) return rc;
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WQ, l).off); g.xop = (const uint4 *)w.xop; g.ktiles = d / 32; g.layer = l;
         if ((rc = pv_prof_mark(c, PV_PROF_QKV, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_QKV>(m, g, wide(PV_T_WQ, l) || wide(PV_T_WK, l) || wide(PV_T_WV, l), (qd + 2 * kvd) / 16, w.rscale, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_QKV>(m, g, wide_qkv, (qd + 2 * kvd) / 16, w.rscale, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_QKV, l, 1, s)) != PV_OK) return rc;
         at.layer = l;
         if ((rc = pv_prof_mark(c, PV_PROF_ATTENTION, l, 0, s)) != PV_OK) return rc;
@@ -1116,11 +1138,10 @@ int pv_pre_block(pv_cache *c, const int32_t *d_host_tokens, int rows, int keep, 
         if ((rc = pv_prof_mark(c, PV_PROF_OPROJ, l, 0, s)) != PV_OK) return rc;
         if ((rc = pre_gemm<EPI_RESID>(m, g, wide(PV_T_WO, l), d / 16, nullptr, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_OPROJ, l, 1, s)) != PV_OK) return rc;
-        k_pre_rscale<<<mtiles, 256, 0, s>>>(w.ssq, w.rscale, d / 16, g.inv_d, g.eps);
-        PV_HIP(hipGetLastError());
+        if ((rc = rscale(wide_gu)) != PV_OK) return rc;
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WG, l).off); g.xop = (const uint4 *)w.xop; g.ktiles = d / 32;
         if ((rc = pv_prof_mark(c, PV_PROF_GATEUP, l, 0, s)) != PV_OK) return rc;
-        if ((rc = pre_gemm<EPI_SWIGLU>(m, g, wide(PV_T_WG, l) || wide(PV_T_WU, l), F / 8, w.rscale, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
+        if ((rc = pre_gemm<EPI_SWIGLU>(m, g, wide_gu, F / 8, w.rscale, w.rowsum, rows, len, w.part_floats, s)) != PV_OK) return rc;
         if ((rc = pv_prof_mark(c, PV_PROF_GATEUP, l, 1, s)) != PV_OK) return rc;
         g.W = (const uint4 *)(Wb + pv_tref(m, PV_T_WD, l).off); g.xop = (const uint4 *)w.xop_d; g.ktiles = F / 32;
         g.gain_next = (l + 1 < f.n_layers) ? gainp(PV_T_ATTN_NORM, l + 1) : (const uint16_t *)(Wb + m->global[PV_T_FINAL_NORM].off);

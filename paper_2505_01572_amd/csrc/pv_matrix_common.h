@@ -31,10 +31,11 @@ __device__ inline uint2 load_once(const uint2 *p)
 // A store that goes through to memory at once (sc1), for the partial sums of K-slices, which workgroups of other XCDs read in the next kernel.  Left dirty in the L2 they are written back
 // when the kernel ends, and the next one waits for that: 4 MiB of sums (256 strips, 32 rows, eight slices), K = 4096, projection and sum 12.6 -> 12.0 us, K = 14336 25.3 -> 24.8; 64 rows 16.6 ->
 // 15.8 and 30.9 -> 30.3.  Four layers of the 8B shape, 4-bit, 32 rows, 472 -> 458 us
-// a step.  One MiB (16 rows, four slices) 10.2 and 10.4: there plain stores.
+// a step.  One MiB (16 rows, four slices) 10.2 and 10.4: there plain stores.  The s_nop: an instruction right behind a store of more than 8 bytes must not write the registers it reads, and the
+// compiler, which sees to that for stores of its own, does not look into assembly.
 __device__ inline void store_through(float4 *p, f32x4 v)
 {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(p), "v"(v) : "memory");
 }
 
 // One 1 KiB operand tile (64 lanes x 16 bytes) from global memory straight into LDS.  Written in assembly (there is

@@ -171,7 +171,7 @@ __device__ inline void attn_chunk(const attn_args &a, int c, int kvh, int z, int
     auto group_at = [&](int grp, int phys) { return uniform_ptr(pool + (size_t)phys * a.page_bytes + (size_t)(grp & sub_mask) * (32 * HD)); };
     // this lane's query row: row lane%16 of the wave's 16-row tile.  A lane past the rows takes row 0 of the first head: its results are not used
     const int m = mp * 32 + rt * 16 + jl;
-    const int al0 = (int)(((float)m + 0.5f) * __builtin_amdgcn_rcpf((float)gamma));     // m / gamma: up to m = 2^20 the rounding errors are under a half of 0.5 / gamma
+    const int al0 = (int)(((float)m + 0.5f) * __builtin_amdgcn_rcpf((float)gamma));     // m / gamma: up to m = 2^21 (the grid's 65536 units) the rounding errors are under 0.5 / gamma
     const bool live = m < nrows;
     const int al = live ? al0 : 0, j = live ? m - al0 * gamma : 0;
     // which keys the row may see: every committed position, and of the block's own slots (len + q) those its
@@ -187,11 +187,13 @@ __device__ inline void attn_chunk(const attn_args &a, int c, int kvh, int z, int
     float (*sh_o)[16][OS] = (float (*)[16][OS])(smem + 2 * 8 * 16);           // [8][16][OS]
     if (p0 < nkeys) {
         uint4 qh[KS], ql[KS];
-        const uint32_t qo = (uint32_t)(q_at(kvh * a.group + al, row0 + j, 8 * g, HD, a.rows) * 2), qs = (uint32_t)a.rows * 64;
+        // (the group's first head from scalars, 64-bit; a lane's place behind it is under 2^29 bytes)
+        const size_t qb = q_at(kvh * a.group, 0, 0, HD, a.rows) * 2;
+        const uint32_t qo = (uint32_t)(q_at(al, row0 + j, 8 * g, HD, a.rows) * 2), qs = (uint32_t)a.rows * 64;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            qh[ks] = *(const uint4 *)((const char *)a.q_hi + ks * qs + qo);
-            ql[ks] = *(const uint4 *)((const char *)a.q_lo + ks * qs + qo);
+            qh[ks] = *(const uint4 *)((const char *)a.q_hi + qb + ks * qs + qo);
+            ql[ks] = *(const uint4 *)((const char *)a.q_lo + qb + ks * qs + qo);
         }
         const char *vs = (const char *)sh_o[wave];     // (V, and then the wave's partial result)
         const char *kb0 = group_at(p0 >> 4, ph0);      // a second group past the end re-reads the first one (it is masked)
@@ -275,7 +277,7 @@ __device__ inline void attn_merge_unit(const attn_args &a, int r, int aq, int n_
     // More than 64 chunks, or 32 (128 features), were a loop of round trips before: 65 chunks 6.4 -> 4.7 us, 94 chunks 7.5 -> 5.8.
     constexpr int SL = 4, FL = 8;
     const int lane = tid & 63;
-    // (a row of a unit: places known to the whole workgroup, its chunks 32-bit offsets behind them)
+    // (a row of a unit: places known to the whole workgroup, its up to 256 chunks 32-bit offsets behind them)
     const char *pm = (const char *)uniform_ptr(a.part_ml + (unit0 * 32 + row) * 2), *po = (const char *)uniform_ptr(a.part_o + (unit0 * 32 + row) * HD);
     float2 ml[SL];
 #pragma unroll

@@ -1394,11 +1394,13 @@ static int cut_slices(const pv_model *m, int strips, int ktiles, int rows, const
 // as much of the operand: up to 1024 features a slice, a multiple of eight groups.  us, there / here, 32 and 64 rows: 256 strips, K = 2048 10.0 / 8.4, 13.4 / 10.1, 4096 12.0 / 10.9, 15.9 / 14.0, 8192
 // 16.6 / 16.8, 20.1 / 22.2; 128 strips, 8192 12.1 / 10.9, 15.9 / 14.1, 14336 15.9 / 16.0, 20.1 / 21.9; 64 strips, 14336 13.1 / 11.0, 16.0 / 14.7; 512 strips, 2048 14.8 / 12.1, 18.0 / 14.6, 4096
 // 18.0 / 17.8, 21.3 / 22.9; 25 groups, 2048 8.0 / 8.2, 9.8 / 10.8, 33 groups, 4096 9.5 / 10.0, 12.4 / 13.1.  Four layers of the 8B shape, us a step, with stores that go through: 4 x 8 rows 542 -> 533, 48
-// nodes 593 -> 579.
+// nodes 593 -> 579.  From K = 512 on: below it k_gemm takes the projection whole, and the sum is a kernel for nothing (steps of eight layers with two such projections each, us, 17 / 64 rows, there / here: 32 strips,
+// K = 256 248 / 283, 298 / 335, 480 270 / 293, 317 / 342, 512 296 / 297, 351 / 351; 256 strips, 256 292 / 326, 360 / 407, 480 317 / 346, 383 / 430, 512 352 / 346, 433 / 432; 48 rows go to
+// k_gemm_tile there, K = 256 306 / 306 and 366 / 372, 384 324 / 317 and 387 / 381).
 static int cut_slices_shared(const pv_model *m, int strips, int ktiles, const float *part)
 {
     const int groups = (strips + 3) / 4;
-    if (part == nullptr || !wide_fits(ktiles) || groups % 8 != 0 || 2 * groups > m->n_cus) return 1;
+    if (part == nullptr || ktiles < 16 || !wide_fits(ktiles) || groups % 8 != 0 || 2 * groups > m->n_cus) return 1;
     const int slices = min(TILE_MAX_SLICES, m->n_cus / groups);
     return ktiles <= 32 * slices ? slices : 1;
 }

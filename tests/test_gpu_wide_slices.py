@@ -29,7 +29,8 @@ def _cut(call):
 
 
 # d_model, K of the down projection -> {rows: cut projections of the layer}.  The output projection (K = 512) is cut from 17 rows on where the groups of four strips are a multiple of eight.
-@pytest.mark.parametrize("d,k,cut", [(512, 3328, {16: 0}), (512, 3520, {16: 1, 9: 1, 8: 0}), (512, 7040, {8: 0}), (512, 8192, {8: 1, 4: 0, 17: 2, 64: 2}), (512, 12800, {4: 0}), (512, 14336, {4: 1}),
+@pytest.mark.parametrize("d,k,cut", [(512, 256, {17: 1, 48: 1, 64: 1}), (512, 480, {17: 1, 33: 1, 64: 1}), (512, 512, {17: 2, 64: 2}),
+                                     (512, 3328, {16: 0}), (512, 3520, {16: 1, 9: 1, 8: 0}), (512, 7040, {8: 0}), (512, 8192, {8: 1, 4: 0, 17: 2, 64: 2}), (512, 12800, {4: 0}), (512, 14336, {4: 1}),
                                      (512, 16384, {32: 2, 48: 2}), (512, 16416, {17: 1, 33: 1, 64: 1}), (640, 2048, {17: 0, 64: 0}), (4096, 8000, {16: 0}), (4096, 8576, {16: 1}), (4096, 4096, {32: 2}),
                                      (4096, 4128, {32: 1})])
 def test_where_projections_are_cut(pvlib, d, k, cut):  # noqa: F811

@@ -695,14 +695,15 @@ k_gemm_wide(const gemm_args a, int tps, float4 *part)
 // behind the first half, a strip's codes behind its last tile, the other two K-tiles at the end.  So there are loads in flight while it multiplies; with a batch loaded, used up and loaded again
 // they drained once a batch (70B-shaped gate/up, 264 MB, 8 rows, inside the kernel 50.0 -> 43.1 us; without the products and the operand 37.0, 7.1 TB/s; 8B shape, 13 rows, 17.4 -> 14.7).
 // The scales of up to eight strips come in one load and go through LDS to the lanes of their features: as a load a strip (8 bytes of 16 lanes) they took 6 of the 50 us.
-// A product is scaled and added while the next one runs.  128 registers hold seven strips of packed rows, two workgroups of eight waves a CU; seven strips of 16-row tiles take 169 and one
-// workgroup a CU (70B shape, 13 rows, a step of two layers: 326 us before and now).  The multiply-adds are pinned behind their products: left alone, the compiler moves all of them to the end
+// A product is scaled and added while the next one runs.  128 registers hold seven strips, two workgroups of eight waves a CU, as 16-row tiles too (all 128 of them).  Where the strips take
+// several rounds that is what covers a workgroup's start and end: 13 rows, 2560 strips, K = 4096, four layers, one workgroup a CU / two 293 / 285 us a step, 3584 strips 320 / 312, 70B shape, two layers 308 / 301; one
+// round (1376 and 1792 strips) 217 / 216 and 233 / 233.  The multiply-adds are pinned behind their products: left alone, the compiler moves all of them to the end
 // of the batch and holds every product.
 // One or two strips (the 70B-shaped down projection, 30.6 us, before 32.0): the L2 -> CU path, 917 KB of operand beside 516 KB of codes per CU at 50 GB/s.
 // Against k_gemm_tile_q4 and the sum of its K-slices, 13 rows, us, before the loads went out early: 8B shape QKV 15.0 -> 9.1, O 11.2 -> 7.2, gate/up 24.6 -> 18.9; 70B shape 23.1 -> 17.5, 18.4 -> 14.4, 65.5 -> 56.4.
 // ------------------------------------------------------------------------------------------
 template <int NB, int S, int EPI, int NW = 8>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NB == 2 && S == 7) ? 2 : 4, (NB == 2 && S == 7) ? 2 : 4)))
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 k_gemm_q4(const gemm_args a, int bps, float4 *part)
 {
     static_assert(S <= NW, "one epilogue wave per strip");

@@ -563,6 +563,8 @@ k_gemm(const gemm_args a)
 // 8B-shaped gate/up, 235 MB, us: 16 rows 45.6 (two strips a workgroup) -> 37.5, 32 rows 43.8 (k_gemm_tile) -> 41.0, 48 rows 52.2 -> 46.8 (three
 // column tiles instead of four; 64 rows 53.2 -> 50.3); 1024-strip vocabulary 26.1 -> 24.0, 34.2 -> 26.5, 39.0 -> 31.1, 39.8 -> 37.8.
 // Output and down projections of up to half as many groups of four strips as CUs are cut along K over blockIdx.y (EPI_PART: the sums go to `part` and k_tile_finish adds them in slice order): cut_slices.
+// Their stores are plain ones: half as many sums as k_gemm_tile's, and through to memory (store_through) they were no faster (us a step, plain / through, 17, 32, 48 and 64 rows: four layers of the 8B
+// shape 453 / 455, 460 / 461, 518 / 518, 571 / 569; eight layers, 256 strips, K = 4096 571 / 571, 585 / 586, 640 / 645, 715 / 720; 64 strips, K = 8192 443 / 446, 464 / 466, 533 / 533, 593 / 591).
 // Loads go through buffer descriptors: a K-tile past the end of the slice gets an offset past the buffer's end,
 // for which zeros come back and nothing is fetched, so every load of the loop is unconditional.
 // ------------------------------------------------------------------------------------------
@@ -699,7 +701,8 @@ k_gemm_wide(const gemm_args a, int tps, float4 *part)
 // several rounds that is what covers a workgroup's start and end: 13 rows, 2560 strips, K = 4096, four layers, one workgroup a CU / two 293 / 285 us a step, 3584 strips 320 / 312, 70B shape, two layers 308 / 301; one
 // round (1376 and 1792 strips) 217 / 216 and 233 / 233.  The multiply-adds are pinned behind their products: left alone, the compiler moves all of them to the end
 // of the batch and holds every product.
-// One or two strips (the 70B-shaped down projection, 30.6 us, before 32.0): the L2 -> CU path, 917 KB of operand beside 516 KB of codes per CU at 50 GB/s.
+// One or two strips (the 70B-shaped output projection, 12.0 us, 4.5 of which a kernel takes in any case): the L2 -> CU path, 262 KB of operand beside 147 KB of codes per CU at 54 GB/s.  Where that
+// is much more operand than codes, K-slices (q4_slices).
 // Against k_gemm_tile_q4 and the sum of its K-slices, 13 rows, us, before the loads went out early: 8B shape QKV 15.0 -> 9.1, O 11.2 -> 7.2, gate/up 24.6 -> 18.9; 70B shape 23.1 -> 17.5, 18.4 -> 14.4, 65.5 -> 56.4.
 // ------------------------------------------------------------------------------------------
 template <int NB, int S, int EPI, int NW = 8>
@@ -1394,7 +1397,7 @@ static int cut_slices(const pv_model *m, int strips, int ktiles, int rows, const
 // 17..64 rows: against k_gemm_tile, whose workgroups take eight strips and half as long slices, so that twice as many sums are written and read (4 MiB with 32 rows and 256 strips), but half
 // as much of the operand: up to 1024 features a slice, a multiple of eight groups.  us, there / here, 32 and 64 rows: 256 strips, K = 2048 10.0 / 8.4, 13.4 / 10.1, 4096 12.0 / 10.9, 15.9 / 14.0, 8192
 // 16.6 / 16.8, 20.1 / 22.2; 128 strips, 8192 12.1 / 10.9, 15.9 / 14.1, 14336 15.9 / 16.0, 20.1 / 21.9; 64 strips, 14336 13.1 / 11.0, 16.0 / 14.7; 512 strips, 2048 14.8 / 12.1, 18.0 / 14.6, 4096
-// 18.0 / 17.8, 21.3 / 22.9; 25 groups, 2048 8.0 / 8.2, 9.8 / 10.8, 33 groups, 4096 9.5 / 10.0, 12.4 / 13.1.  Four layers of the 8B shape, us a step, with stores that go through: 4 x 8 rows 542 -> 533, 48
+// 18.0 / 17.8, 21.3 / 22.9; 25 groups, 2048 8.0 / 8.2, 9.8 / 10.8, 33 groups, 4096 9.5 / 10.0, 12.4 / 13.1.  Four layers of the 8B shape, us a step: 4 x 8 rows 542 -> 533, 48
 // nodes 593 -> 579.  From K = 512 on: below it k_gemm takes the projection whole, and the sum is a kernel for nothing (steps of eight layers with two such projections each, us, 17 / 64 rows, there / here: 32 strips,
 // K = 256 248 / 283, 298 / 335, 480 270 / 293, 317 / 342, 512 296 / 297, 351 / 351; 256 strips, 256 292 / 326, 360 / 407, 480 317 / 346, 383 / 430, 512 352 / 346, 433 / 432; 48 rows go to
 // k_gemm_tile there, K = 256 306 / 306 and 366 / 372, 384 324 / 317 and 387 / 381).

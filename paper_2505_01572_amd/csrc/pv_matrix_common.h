@@ -28,10 +28,10 @@ __device__ inline uint2 load_once(const uint2 *p)
     return make_uint2(v.x, v.y);
 }
 
-// A store that goes through to memory at once (sc1), for the partial sums of K-slices, which workgroups of other XCDs read in the next kernel.  Left dirty in the L2 they are written back
+// A store that goes through to memory at once (sc1), for the partial sums of the shared-tile kernels' K-slices, which workgroups of other XCDs read in the next kernel.  Left dirty in the L2 they are written back
 // when the kernel ends, and the next one waits for that: 4 MiB of sums (256 strips, 32 rows, eight slices), K = 4096, projection and sum 12.6 -> 12.0 us, K = 14336 25.3 -> 24.8; 64 rows 16.6 ->
 // 15.8 and 30.9 -> 30.3.  Four layers of the 8B shape, 4-bit, 32 rows, 472 -> 458 us
-// a step.  One MiB (16 rows, four slices) 10.2 and 10.4: there plain stores.  The s_nop: an instruction right behind a store of more than 8 bytes must not write the registers it reads, and the
+// a step.  One MiB (16 rows, four slices) 10.2 and 10.4: there plain stores, and in k_gemm_wide.  The s_nop: an instruction right behind a store of more than 8 bytes must not write the registers it reads, and the
 // compiler, which sees to that for stores of its own, does not look into assembly.
 __device__ inline void store_through(float4 *p, f32x4 v)
 {
@@ -43,7 +43,8 @@ __device__ inline void store_through(float4 *p, f32x4 v)
 // kernels wait for the copies by count (pre_wait).  src is uniform, voff the lane's byte offset behind it.  m0 is put back:
 // the compiler may hold a value of its own in it, and a clobber list does not tell it otherwise (m0 is a reserved register there: it
 // warns, and reuses the value all the same).  0.3 % of a prompt's time (8B shape, 2048 tokens: 6.68 -> 6.70 ms); 0.9 % with an s_nop behind
-// it, which only an instruction that reads m0 next would need: tests/test_lds_copies.py sees to it that there is none.
+// it, which only an instruction that reads m0 next would need: tests/test_lds_copies.py sees to it that there is none, and that no vector instruction writes the scalar registers of src
+// in the five states before the copy reads them.
 __device__ inline void dma_tile(uint32_t lds, const void *src, uint32_t voff)
 {
     uint32_t m0;

@@ -1375,7 +1375,7 @@ static int q4_slices(const pv_model *m, int strips, int ktiles, int rows, const 
 // Output and down projections, 16-bit weights: K-slices for k_gemm_wide, four strips a workgroup and at most one workgroup a CU, or 1.
 // Up to 16 rows: whole, a CU reads all of the operand for each of its strips, and with 257 strips some CUs go through two; cut, its share of it once for four strips, and k_tile_finish
 // follows.  Both sides of 250 sizes (32 to 516 strips, K = 2048 to 28672, 1, 4, 8 and 13 rows) lie within some 6 % of 2.7 us (cut, with the sum: 5.3) plus the larger of what the busiest CU takes
-// in at 59 GB/s, strips and operand, and the chip's weights at 7.64 TB/s, with a smooth step between them (both).  us, whole / cut: 256 strips, 13 rows, K = 4096 9.7 / 9.8, 8192 16.9 /
+// in at 59 GB/s, strips and operand, and the weights of all 256 CUs at 7.64 TB/s, with a smooth step between them (both).  us, whole / cut: 256 strips, 13 rows, K = 4096 9.7 / 9.8, 8192 16.9 /
 // 14.5, 14336 27.8 / 22.0, 28672 52.9 / 39.9, 8 rows, 14336 21.6 / 21.4, 28672 40.9 / 38.0; 128 strips, 13 rows, 4096 8.7 / 7.3, 8192 15.4 / 9.6, 8 rows, 8192 10.3 / 9.6, 14336 16.2 / 13.2; 320
 // strips, 13 rows, 4096 15.5 / 11.3, 8 rows, 8192 21.8 / 17.4; 512 strips, 13 rows, 14336 41.1 / 41.1, 28672 80.2 / 74.5; one row, 256 strips, 14336 18.9 / 21.6, 64 strips 12.6 / 9.3.
 // These are chains of one projection; between a step's other kernels the sum takes another 1.2 us, and the line leaves as much again.  Steps of four layers, us: 8B shape, 13 rows 472 -> 453,
